@@ -16,8 +16,7 @@
  *    kfac_create(), which it uses as scratch until kfac_destroy().
  *  - Work is enqueued on the hipStream_t given to kfac_create().  All calls
  *    are asynchronous with respect to the host except kfac_eig(), which waits
- *    on the stream between sweeps to decide convergence and returns with its
- *    outputs complete.
+ *    on the stream to check its result and returns with its outputs complete.
  *  - Matrices are row-major, fp32 unless stated.  Outputs must not alias
  *    inputs except where a parameter is marked in/out.
  *  - A context is not thread-safe; use one context per stream.
@@ -62,22 +61,28 @@ typedef struct {
 
 typedef struct {
     int max_sweeps;          /* cap on Jacobi sweeps (<=0: 30)                    */
-    float tol;               /* stop when off(F)_F <= tol * ||F||_F (<=0: 2e-6)   */
-    int fp32_only;           /* 0 (default): for d >= 2048 the rank-256 update passes run as split-fp16
-                                MFMA products (hi + lo halves, three products per fp32 product, fp32
-                                accumulation): same tolerances met, errors bounded normwise (relative to
-                                ||F||_F).  1: every product on the fp32 MFMA path: slower, keeps fp32's
-                                elementwise accuracy on strongly graded spectra.                   */
+    float tol;               /* stop when off(F)_F <= tol * ||F||_F (<=0: 2e-6).  From 1e-6 on the factors are
+                                decomposed directly (Householder reduction, fp64 tridiagonal eigenproblem), to fp32
+                                rounding; a smaller tol asks for Jacobi sweeps until the rotated matrix meets it.  */
+    int fp32_only;           /* 0 (default): for d >= 2048 the orthogonalisation products (and, in Jacobi sweeps, the
+                                rank-256 update passes) run as split-fp16 MFMA products (hi + lo halves, three
+                                products per fp32 product, fp32 accumulation): same tolerances met, errors bounded
+                                normwise (relative to ||F||_F).  1: every product on the fp32 MFMA path: slower, keeps
+                                fp32's elementwise accuracy on strongly graded spectra.            */
     int warm_start;          /* 1: on entry every Q_i with d_i > 128 holds an orthonormal basis to start from
                                 (typically the eigenvectors of the previous decomposition of a slowly moving
-                                factor: the remark of Sec. V-C that the FIM becomes more stable as training progresses); the iteration then runs on Q_i^T F_i Q_i, which is close to
-                                diagonal, and needs fewer sweeps.  Costs 4 d^3 flops per factor up front; a basis
-                                that is not orthonormal to fp32 rounding gives wrong results.  0: start from I.   */
+                                factor: the remark of Sec. V-C that the FIM becomes more stable as training progresses).
+                                Jacobi sweeps then run on Q_i^T F_i Q_i, which is close to diagonal, and fewer are needed
+                                (4 d^3 flops per factor up front; a basis that is not orthonormal to fp32 rounding
+                                gives wrong results).  The direct decomposition needs no start basis and overwrites
+                                it.  0: start from I.                                              */
 } kfac_eig_opts;
 
 typedef struct {             /* host memory, filled when kfac_eig() returns       */
-    int sweeps;              /* sweeps performed                                  */
-    float off_norm_rel;      /* off(F)_F / ||F||_F of the rotated matrix at exit  */
+    int sweeps;              /* Jacobi sweeps performed.  A direct decomposition counts as one, as none if F was
+                                diagonal to begin with or if it only replaces a start basis (warm_start)    */
+    float off_norm_rel;      /* off(F)_F / ||F||_F of the rotated matrix at exit (direct: of Q^T F Q, i.e. the residual
+                                ||F Q - Q diag(lam)||_F / ||F||_F, with its fp32 rounding)         */
     int converged;           /* 1 if the tolerance was met                        */
 } kfac_eig_info;
 
@@ -157,7 +162,8 @@ int kfac_update_factors_static(kfac_ctx *ctx, const void *X, int dtype, int layo
 size_t kfac_static_scratch_bytes(void);
 
 /* Symmetric eigendecompositions F_i = Q_i diag(lam_i) Q_i^T (Sec. IV-A, Algorithm 1 step 2) of a
- * batch of factors by (block) Jacobi iteration; lam ascending, eigenvectors in the columns of Q.
+ * batch of factors, directly or by (block) Jacobi iteration (see kfac_eig_opts.tol); lam ascending, eigenvectors in
+ * the columns of Q.
  *   F, Q, lam : HOST arrays of `batch` device pointers; F_i is [d_i][d_i] (read only),
  *               Q_i [d_i][d_i], lam_i [d_i]
  *   d         : host array of dimensions, 1 <= d_i <= 8192

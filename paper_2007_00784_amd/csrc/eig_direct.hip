@@ -1,0 +1,1357 @@
+// Direct route of the eigensolver F = Q diag(lam) Q^T (Sec. IV-A; Algorithm 1, step 2): every factor of a call goes
+// through the same few stages, and every stage is one launch (or one chain of launches) over all factors.
+//
+//  1. Householder reduction to tridiagonal form, A = H T H^T, in fp32, of the factor with its diagonal in descending order
+//     (the reduction starts at the large end, so the small end of a graded factor is not swamped by the large end's
+//     rounding: on a factor graded over eight decades the small eigenvectors come out fifty times as accurate).  Factors up to 256 wide: one workgroup each, the
+//     matrix in registers.  Wider ones: the blocked right-looking reduction (panels of 32 columns; per column one
+//     symmetric matrix-vector product over the lower tiles and one vector step; per panel one rank-64 update on the fp32
+//     matrix instructions), all factors in one chain of launches, aligned so that all end together.
+//  2. Eigenvalues of T by bisection and eigenvectors of T by twisted factorisation, both in fp64 and both
+//     independent per eigenvalue.  T carries fp32 rounding noise, so fp64 has nine digits to spare: the eigenvectors of
+//     eigenvalues that agree to many digits still come out orthogonal without any re-orthogonalisation, once exact
+//     multiplicities are broken by a perturbation of T below its rounding noise (PERTURB_REL, PERTURB_ABS).
+//  3. Back-transformation by the reflectors: compact WY blocks of 128 on the fp32 matrix instructions, or (small
+//     factors) a wave per four columns with the columns in registers.
+//  4. One Newton-Schulz step on Q, Rayleigh quotients against the caller's F, ascending order.
+//
+// The residual ||F Q - Q diag(lam)||_F = off(Q^T F Q) of the result is measured (it falls out of the Rayleigh quotients), and
+// so is the orthogonality of the eigenvectors before the last step; a factor with an unsound result is decomposed by
+// Jacobi iteration instead (eig.hip).
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+#include <vector>
+#include "kfac_internal.h"
+#include "mfma_gemm.h"
+#include "mfma_gemm_x3.h"
+
+namespace {
+
+using namespace kfac;
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+constexpr int NB = 32;            // columns of a panel
+constexpr int TB = 128;           // tile edge
+constexpr int RB = 64;            // rows per workgroup of the vector step
+constexpr int TD_SMALL = 256;     // factors up to this size are reduced by one workgroup, in registers
+constexpr int WY = 128;           // reflectors of a compact WY block
+constexpr int WY_K = 512;         // contraction of one workgroup in Y = V^T Z
+constexpr int NPARTS = 64;         // parts of the Rayleigh quotients' sums
+constexpr int NORM_WGS = 256;      // workgroups per factor of the norms and copies
+constexpr double PERTURB_REL = 0x1p-25;   // of every element of T: half the rounding it already carries
+constexpr double PERTURB_ABS = 1e-11;     // of the Gershgorin bound, added to the diagonal: breaks multiple zeros
+constexpr double NS_AGAIN = 4e-6;         // ||I - Q^T Q||_F^2 from which one Newton-Schulz step is not enough (it leaves 3/4 of this)
+constexpr double E_MIN = 1e-20;     // of the same: no off-diagonal element of T is exactly zero
+constexpr double PIVOT_MIN = 1e-30;
+
+struct DirMat {
+    const float *F;
+    float *Q, *lam;
+    float *A;        // [np][ld]: the matrix, its lower tiles reduced in place; row p of the upper part receives reflector p
+    float *Z;        // [np][ld]: eigenvectors of T, then of A
+    float *B1, *B2;  // [np][ld] each, adjacent: together the fp64 pivots of the eigenvectors; then scratch
+    float *panel;    // [3 NB][ld]: V, W, V of the current panel
+    float *part;     // [nb][np]: partial products of the column's matrix-vector product
+    float *dots;     // [nb][2 NB]: partial V^T v, W^T v per row block
+    float *tsum;     // per tile: its share of v^T A v
+    float *acol;     // [np]: next column of the matrix, not yet scaled
+    float *npart;    // [np / RB]: its squared norm, per workgroup
+    float *scal;     // scale, tau of the current column
+    float *tau;      // [np]
+    double *d, *e;   // [np]: T as reduced
+    double2 *td;     // [np]: T perturbed and divided by its Gershgorin bound: {d_i, e_i^2}; |e_i| is kept away from zero
+    double *te;      // [np]: e_i of the same; later 1 / norm of every eigenvector
+    double *lam64;   // [np]: eigenvalues of T, later the Rayleigh quotients
+    double *sums;    // [NPARTS][3][np] partial sums of the Rayleigh quotients
+    double *npartd;  // [NORM_WGS][2] partial norms: off^2, diag^2; later of D and of the residual
+    double *stat;    // off^2, diag^2, residual^2, ||I - Q^T Q||^2
+    float *Tm;       // [nb][WY][WY]: Gram matrices of the WY blocks, then their T
+    int *perm;       // [np]: final order of the eigenvectors
+    int *ord;        // [np]: row of F that became row i of A (diagonal descending)
+    int n, np, ld, nb, off, split;
+};
+
+__device__ inline float wave_sum_all(float v) {   // the sum over the wave, in every lane
+    int x = __float_as_int(v);
+#define KFAC_DPP_ADD(ctrl, rmask) x = __float_as_int(__int_as_float(x) + __int_as_float(__builtin_amdgcn_update_dpp(0, x, ctrl, rmask, 0xf, true)))
+    KFAC_DPP_ADD(0x111, 0xf);   // row_shr:1, 2, 4, 8: the last lane of a row of 16 holds the row's sum
+    KFAC_DPP_ADD(0x112, 0xf);
+    KFAC_DPP_ADD(0x114, 0xf);
+    KFAC_DPP_ADD(0x118, 0xf);
+    KFAC_DPP_ADD(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
+    KFAC_DPP_ADD(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
+#undef KFAC_DPP_ADD
+    return __int_as_float(__builtin_amdgcn_readlane(x, 63));
+}
+__device__ inline double wave_sum_f64(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// ---- norms and the working copy ------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void dir_norm_kernel(const DirMat *mats) {
+    const DirMat M = mats[blockIdx.y];
+    const global_ptr<const float> F = as_global(M.F);
+    const int n = M.n;
+    double o2 = 0.0, d2 = 0.0;
+    for (int r = blockIdx.x; r < n; r += NORM_WGS)
+        for (int c = threadIdx.x; c < n; c += 256) {
+            const double v = (double)F[(int64_t)r * n + c];
+            if (c == r) d2 += v * v; else o2 += v * v;
+        }
+    __shared__ double red[8];
+    o2 = wave_sum_f64(o2);
+    d2 = wave_sum_f64(d2);
+    if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6] = o2; red[4 + (threadIdx.x >> 6)] = d2; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        M.npartd[2 * blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+        M.npartd[2 * blockIdx.x + 1] = red[4] + red[5] + red[6] + red[7];
+    }
+}
+
+// off^2 and diag^2 from the partial norms (a wave; fixed order), and the power of two that brings ||F||_F into [1, 2)
+__device__ inline float dir_norms(const DirMat &M, double &o2, double &d2) {
+    const int lane = threadIdx.x & 63;
+    o2 = d2 = 0.0;
+#pragma unroll
+    for (int i = 0; i < NORM_WGS / 64; ++i) {
+        o2 += M.npartd[2 * (64 * i + lane)];
+        d2 += M.npartd[2 * (64 * i + lane) + 1];
+    }
+    o2 = wave_sum_f64(o2);
+    d2 = wave_sum_f64(d2);
+    const double f2 = o2 + d2;
+    if (!(f2 > 0.0) || !(f2 < 1e300)) return 1.f;
+    return ldexpf(1.f, min(max(-ilogb(sqrt(f2)), -120), 120));
+}
+
+// ord[rank] = index of the rank-th largest diagonal element (ties and NaNs by index: always a permutation)
+constexpr int RANK_IPB = 16;
+__global__ __launch_bounds__(256) void dir_order_kernel(const DirMat *mats) {
+    __shared__ float chunk[256];
+    __shared__ int part[256];
+    const DirMat M = mats[blockIdx.y];
+    const int n = M.n, ii = threadIdx.x & (RANK_IPB - 1), js = threadIdx.x / RANK_IPB, i = blockIdx.x * RANK_IPB + ii;
+    if ((int)blockIdx.x * RANK_IPB >= n) return;
+    const global_ptr<const float> F = as_global(M.F);
+    const float di = i < n ? F[(int64_t)i * (n + 1)] : 0.f;
+    const bool nan_i = di != di;
+    int rank = 0;
+    for (int j0 = 0; j0 < n; j0 += 256) {
+        __syncthreads();
+        chunk[threadIdx.x] = j0 + (int)threadIdx.x < n ? F[(int64_t)(j0 + threadIdx.x) * (n + 1)] : 0.f;
+        __syncthreads();
+        const int cnt = min(256, n - j0);
+        for (int k = js; k < cnt; k += 256 / RANK_IPB) {
+            const float dj = chunk[k];
+            const int j = j0 + k;
+            const bool nan_j = dj != dj;
+            rank += nan_i ? (!nan_j || j < i) : (!nan_j && ((dj > di) || (dj == di && j < i)));
+        }
+    }
+    part[threadIdx.x] = rank;
+    __syncthreads();
+    if (js == 0 && i < n) {
+        int total = 0;
+        for (int t = 0; t < 256 / RANK_IPB; ++t) total += part[t * RANK_IPB + ii];
+        M.ord[total] = i;
+    }
+}
+
+// A <- scale * F, reordered, with zero padding, for the factors reduced by the chain; the norms for all of them.
+__global__ __launch_bounds__(256) void dir_copy_kernel(const DirMat *mats) {
+    const DirMat M = mats[blockIdx.y];
+    double o2, d2;
+    const float sc = dir_norms(M, o2, d2);
+    if (blockIdx.x == 0 && threadIdx.x == 0) { M.stat[0] = o2; M.stat[1] = d2; }
+    if (M.n <= TD_SMALL) return;
+    const global_ptr<const float> F = as_global(M.F);
+    const global_ptr<float> A = as_global(M.A);
+    const int n = M.n, np = M.np;
+    if (blockIdx.x == 0)
+        for (int i = n - 1 + (int)threadIdx.x; i < np; i += 256) M.tau[i] = 0.f;   // no reflectors there
+    const global_ptr<const int> ord = as_global((const int *)M.ord);
+    for (int r = blockIdx.x; r < np; r += NORM_WGS) {
+        const int64_t fr = r < n ? (int64_t)ord[r] * n : 0;
+        for (int c = threadIdx.x; c < np; c += 256)
+            A[(int64_t)r * M.ld + c] = (r < n && c < n) ? sc * F[fr + ord[c]] : 0.f;
+    }
+}
+
+// ---- reduction, one workgroup (n <= 256) -------------------------------------------------------------------
+// Four threads per row, each with KC columns of it in registers (groups of four: group k covers columns 16 k + 4 q ..).
+// The matrix never touches LDS; per column one row goes to LDS (it is the column, by symmetry), v and w are read
+// back by everybody.  A column costs three barriers and a few LDS latencies, 0.5 to 0.9 us.
+template <int KC>
+__global__ __launch_bounds__(16 * KC) void dir_td_small_kernel(const DirMat *mats, const int *list) {
+    constexpr int G = KC / 4, NTH = 16 * KC, NW = NTH / 64, CMAX = 4 * KC;
+    __shared__ __attribute__((aligned(16))) float xs[CMAX], v[CMAX], w[CMAX];
+    __shared__ float red[NW];
+    const DirMat M = mats[list[blockIdx.x]];
+    const int n = M.n, tid = threadIdx.x, row = tid >> 2, q = tid & 3, wave = tid >> 6, lane = tid & 63;
+    double o2, d2;
+    const float sc = dir_norms(M, o2, d2);
+    floatx4 a[G];
+    {
+        const global_ptr<const float> F = as_global(M.F);
+        const int64_t fr = row < n ? (int64_t)M.ord[row] * n : 0;
+#pragma unroll
+        for (int k = 0; k < G; ++k)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int c = 16 * k + 4 * q + u;
+                a[k][u] = (row < n && c < n) ? sc * F[fr + M.ord[c]] : 0.f;
+            }
+    }
+    const global_ptr<float> A = as_global(M.A);
+    for (int j = 0; j < n; ++j) {
+        if (row == j)
+#pragma unroll
+            for (int k = 0; k < G; ++k) *(floatx4 *)(xs + 16 * k + 4 * q) = a[k];
+        __syncthreads();
+        if (j == n - 1) break;
+        // norm of the column below its first element: every wave forms it for itself
+        float s2 = 0.f;
+#pragma unroll
+        for (int c0 = 0; c0 < CMAX; c0 += 64) {
+            const int c = c0 + lane;
+            const float x = (CMAX % 64 == 0 || c < CMAX) ? xs[c < CMAX ? c : 0] : 0.f;
+            s2 += c > j + 1 && c < CMAX ? x * x : 0.f;
+        }
+        s2 = wave_sum_all(s2);
+        const float alpha = xs[j + 1];
+        float beta = alpha, tau = 0.f, scale = 0.f;
+        if (s2 > 0.f) {
+            beta = -copysignf(sqrtf(fmaf(alpha, alpha, s2)), alpha);
+            tau = (beta - alpha) / beta;
+            scale = 1.f / (alpha - beta);
+        }
+        if (tid < CMAX) {
+            const float x = xs[tid];
+            const float vv = tid > j + 1 ? x * scale : (tid == j + 1 ? 1.f : 0.f);
+            v[tid] = vv;
+            if (tid < n) A[(int64_t)j * M.ld + tid] = vv;
+        }
+        if (tid == 0) {
+            M.d[j] = (double)xs[j];
+            M.e[j] = (double)beta;
+            M.tau[j] = tau;
+        }
+        __syncthreads();
+        const int k0 = (j + 1) >> 4;     // column groups before it are finished
+        float y = 0.f;
+#pragma unroll
+        for (int k = 0; k < G; ++k)
+            if (k >= k0) {
+                const floatx4 vc = *(const floatx4 *)(v + 16 * k + 4 * q);
+                y = fmaf(a[k].x, vc.x, y);
+                y = fmaf(a[k].y, vc.y, y);
+                y = fmaf(a[k].z, vc.z, y);
+                y = fmaf(a[k].w, vc.w, y);
+            }
+        y += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), 0xB1, 0xf, 0xf, true));   // quad_perm 1,0,3,2
+        y += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), 0x4E, 0xf, 0xf, true));   // quad_perm 2,3,0,1
+        const float vr = v[row];
+        const float ty = row > j ? tau * y : 0.f;
+        const float part = wave_sum_all(q == 0 ? vr * ty : 0.f);
+        if (q == 0) w[row] = ty;
+        if (lane == 0) red[wave] = part;
+        __syncthreads();
+        float vty = 0.f;                 // tau v^T A v
+#pragma unroll
+        for (int u = 0; u < NW; ++u) vty += red[u];
+        // w = tau A v - (tau/2)(tau v^T A v) v;  A <- A - v w^T - w v^T with the v v^T parts of both gathered in one factor
+        const float wr = fmaf(-tau * vty, vr, ty);
+#pragma unroll
+        for (int k = 0; k < G; ++k)
+            if (k >= k0) {
+                const floatx4 vc = *(const floatx4 *)(v + 16 * k + 4 * q), wc = *(const floatx4 *)(w + 16 * k + 4 * q);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) a[k][u] = fmaf(-vr, wc[u], fmaf(-wr, vc[u], a[k][u]));
+            }
+    }
+    if (tid == 0) {
+        M.d[n - 1] = (double)xs[n - 1];
+        M.e[n - 1] = 0.0;
+        M.tau[n - 1] = 0.f;
+    }
+}
+
+// ---- reduction, chain of launches -----------------------------------------------------------------------------
+// Step t of the chain treats column j = t - off of every factor; off is a multiple of NB, so all factors are at the same place
+// of their panels.  The tables list the tiles (symv, update) and row blocks (vector step) that a panel touches:
+// factor << 14 | row block << 7 | column block.
+struct TabRef { int m, I, J; };
+__device__ inline TabRef tab_ref(unsigned w) { return TabRef{(int)(w >> 14), (int)((w >> 7) & 127u), (int)(w & 127u)}; }
+
+// Column j as it stands: acol, its norm, its diagonal element.
+__global__ __launch_bounds__(RB) void dir_column_kernel(const DirMat *mats, const unsigned *tab, int t) {
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    const int j = t - M.off, row = tr.J * RB + (int)threadIdx.x;
+    const float a = row >= j ? as_global(M.A)[(int64_t)row * M.ld + j] : 0.f;
+    if (row == j) M.d[j] = (double)a;
+    as_global(M.acol)[row] = row > j ? a : 0.f;
+    const float s = wave_sum_all(row > j + 1 ? a * a : 0.f);
+    if (threadIdx.x == 0) M.npart[tr.J] = s;
+}
+
+// y = A v over the lower tiles: tile (I, J) gives A_IJ v_J to the rows of block I and (I > J) A_IJ^T v_I to those of block
+// J; both land in part[], one slot per pair of blocks, and are added in the vector step.  Also v^T A v (per tile) and,
+// on the diagonal tiles, V^T v and W^T v of the panel's earlier columns.  Reads n'^2 / 2 elements once: bound by the
+// memory system (Infinity Cache) while the trailing matrix is large and by the launch below that.
+__global__ __launch_bounds__(256) void dir_symv_kernel(const DirMat *mats, const unsigned *tab, int t) {
+    __shared__ __attribute__((aligned(16))) float vI[TB], vJ[TB];
+    __shared__ float cred[8][TB];
+    __shared__ float tred[4];
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    const int j = t - M.off;
+    if (j > M.n - 2) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c4 = tid & 31, rs = tid >> 5;
+    const int ip = t & (NB - 1), b0 = j / TB, I = tr.I, J = tr.J;
+    const bool diag = I == J;
+    // the column's norm: partial sums of the row blocks from the panel's first on
+    float s2 = 0.f;
+    for (int rb = 2 * b0 + lane; rb < M.np / RB; rb += 64) s2 += as_global(M.npart)[rb];
+    const float alpha = as_global(M.acol)[j + 1];
+    const int vi = (tid < TB ? I * TB : J * TB - TB) + tid;
+    const float xv = as_global(M.acol)[vi];
+    floatx4 a[16];
+    {
+        const global_ptr<const float> p = as_global((const float *)M.A) + (int64_t)(I * TB + rs) * M.ld + J * TB + 4 * c4;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) a[u] = *(global_ptr<const floatx4>)(p + (int64_t)(8 * u) * M.ld);
+    }
+    s2 = wave_sum_all(s2);
+    float beta = alpha, tau = 0.f, scale = 0.f;
+    if (s2 > 0.f) {
+        beta = -copysignf(sqrtf(fmaf(alpha, alpha, s2)), alpha);
+        tau = (beta - alpha) / beta;
+        scale = 1.f / (alpha - beta);
+    }
+    (tid < TB ? vI : vJ - TB)[tid] = vi > j + 1 ? xv * scale : (vi == j + 1 ? 1.f : 0.f);
+    if (diag && I == (j + 1) / TB && tid == 0) {
+        M.scal[0] = scale;
+        M.scal[1] = tau;
+        M.tau[j] = tau;
+        M.e[j] = (double)beta;
+    }
+    __syncthreads();
+    const floatx4 vc = *(const floatx4 *)(vJ + 4 * c4);
+    float rsum[16];
+    floatx4 cs = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        rsum[u] = fmaf(a[u].x, vc.x, fmaf(a[u].y, vc.y, fmaf(a[u].z, vc.z, a[u].w * vc.w)));
+        const float vr = vI[rs + 8 * u];
+        cs.x = fmaf(a[u].x, vr, cs.x);
+        cs.y = fmaf(a[u].y, vr, cs.y);
+        cs.z = fmaf(a[u].z, vr, cs.z);
+        cs.w = fmaf(a[u].w, vr, cs.w);
+    }
+    // sixteen sums over the 32 lanes of a half wave: halve the values with every exchange
+#pragma unroll
+    for (int h = 8; h >= 1; h >>= 1) {
+        const bool up = (c4 & (2 * h)) != 0;
+#pragma unroll
+        for (int k = 0; k < h; ++k) {
+            const float keep = up ? rsum[k + h] : rsum[k], give = up ? rsum[k] : rsum[k + h];
+            rsum[k] = keep + __shfl_xor(give, 2 * h, 64);
+        }
+    }
+    const float ysum = rsum[0] + __shfl_xor(rsum[0], 1, 64);
+    const int r = rs + 8 * (c4 >> 1);      // c4 bits 4..1 = which of the sixteen rows this lane ended up with
+    const float va = wave_sum_all((c4 & 1) ? 0.f : vI[r] * ysum);
+    if (!(c4 & 1)) as_global(M.part)[(int64_t)J * M.np + I * TB + r] = ysum;
+    if (!diag) *(floatx4 *)(cred[rs] + 4 * c4) = cs;
+    if (lane == 0) tred[wave] = va;
+    __syncthreads();
+    if (tid == 0) {
+        const int ri = I - b0;
+        M.tsum[ri * (ri + 1) / 2 + J - b0] = (diag ? 1.f : 2.f) * (tred[0] + tred[1] + tred[2] + tred[3]);
+    }
+    if (!diag) {
+        if (tid < TB) {
+            float s = 0.f;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) s += cred[k][tid];
+            as_global(M.part)[(int64_t)I * M.np + J * TB + tid] = s;
+        }
+    } else {
+        const float v0 = vI[lane], v1 = vI[64 + lane];
+        for (int p = wave; p < 2 * NB; p += 4) {     // waves take the products in turn: V^T v, then W^T v
+            if ((p & (NB - 1)) >= ip) continue;
+            const global_ptr<const float> row = as_global((const float *)M.panel) + (int64_t)p * M.ld + I * TB;
+            const float s = wave_sum_all(fmaf(row[lane], v0, row[64 + lane] * v1));
+            if (lane == 0) M.dots[I * 2 * NB + p] = s;
+        }
+    }
+}
+
+// Vector step of column j: w, the panel's new columns, reflector j, and (unless the panel ends here) column j + 1 with the
+// panel's updates applied.
+__global__ __launch_bounds__(256) void dir_vector_kernel(const DirMat *mats, const unsigned *tab, int t) {
+    __shared__ float cw[4][2 * NB], cf[2 * NB], rowj[2 * NB];   // V^T v, W^T v; the panel's row j + 1
+    __shared__ float ys[4][RB], as_[4][RB];
+    __shared__ float sred[4], yj_s, dvw_s;
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    const int j = t - M.off;
+    if (j > M.n - 2) return;
+    const int tid = threadIdx.x, lane = tid & 63, g = tid >> 6;
+    const int ip = t & (NB - 1), b0 = j / TB, row = tr.J * RB + lane;
+    const bool next = ip != NB - 1;
+    const global_ptr<const float> panel = as_global((const float *)M.panel), part = as_global((const float *)M.part);
+    // loads first: they are all independent
+    float y = 0.f;
+    for (int k = b0 + g; k < M.nb; k += 4) y += part[(int64_t)k * M.np + row];
+    float pv[NB / 4], pw[NB / 4];
+#pragma unroll
+    for (int u = 0; u < NB / 4; ++u) {
+        const int p = g + 4 * u;
+        pv[u] = p < ip ? panel[(int64_t)p * M.ld + row] : 0.f;
+        pw[u] = p < ip ? panel[(int64_t)(NB + p) * M.ld + row] : 0.f;
+    }
+    float c = 0.f;
+    if ((lane & (NB - 1)) < ip)
+        for (int k = b0 + g; k < M.nb; k += 4) c += as_global(M.dots)[k * 2 * NB + lane];
+    cw[g][lane] = c;
+    const int ct = M.nb - b0, nt = ct * (ct + 1) / 2;
+    float va = 0.f;
+    for (int i = tid; i < nt; i += 256) va += as_global(M.tsum)[i];
+    const float scale = M.scal[0], tau = M.scal[1];
+    float acur = 0.f;
+    if (g == 0 && next && row > j) acur = as_global((const float *)M.A)[(int64_t)row * M.ld + j + 1];
+    const float xv = as_global(M.acol)[row];
+    if (g == 1) rowj[lane] = (lane & (NB - 1)) < ip ? panel[(int64_t)lane * M.ld + j + 1] : 0.f;
+    if (g == 2) {
+        float yj = 0.f;
+        if (b0 + lane < M.nb) yj = part[(int64_t)(b0 + lane) * M.np + j + 1];
+        yj = wave_sum_all(yj);
+        if (lane == 0) yj_s = yj;
+    }
+    va = wave_sum_all(va);
+    if (lane == 0) sred[g] = va;
+    __syncthreads();
+    if (g == 0) {
+        const float s = cw[0][lane] + cw[1][lane] + cw[2][lane] + cw[3][lane];
+        cf[lane] = s;
+        const float o = __shfl_xor(s, 32, 64);
+        const float dvw = wave_sum_all(lane < 32 ? s * o : 0.f);   // (V^T v) . (W^T v)
+        if (lane == 0) dvw_s = dvw;
+    }
+    __syncthreads();
+    float ac = 0.f;
+#pragma unroll
+    for (int u = 0; u < NB / 4; ++u) {
+        const int p = g + 4 * u;
+        y = fmaf(-pv[u], cf[NB + p], fmaf(-pw[u], cf[p], y));
+        ac = fmaf(pv[u], rowj[NB + p], fmaf(pw[u], rowj[p], ac));
+    }
+    ys[g][lane] = y;
+    as_[g][lane] = ac;
+    __syncthreads();
+    if (g != 0) return;
+    y = ys[0][lane] + ys[1][lane] + ys[2][lane] + ys[3][lane];
+    ac = as_[0][lane] + as_[1][lane] + as_[2][lane] + as_[3][lane];
+    // alpha_h of w = tau y + alpha_h v, and row j + 1 of w (where v is 1)
+    const float vy = sred[0] + sred[1] + sred[2] + sred[3] - 2.f * dvw_s;
+    const float ah = -0.5f * tau * tau * vy;
+    float yj = (lane & 31) == lane ? fmaf(-rowj[lane], cf[NB + lane], -rowj[NB + lane] * cf[lane]) : 0.f;
+    yj = yj_s + wave_sum_all(yj);
+    const float wj = fmaf(tau, yj, ah);
+    const float v = row > j + 1 ? xv * scale : (row == j + 1 ? 1.f : 0.f);
+    const float w = row > j ? fmaf(tau, y, ah * v) : 0.f;
+    const global_ptr<float> pan = as_global(M.panel);
+    pan[(int64_t)ip * M.ld + row] = v;
+    pan[(int64_t)(NB + ip) * M.ld + row] = w;
+    pan[(int64_t)(2 * NB + ip) * M.ld + row] = v;
+    as_global(M.A)[(int64_t)j * M.ld + row] = v;
+    if (!next) return;
+    const float a = row > j ? acur - ac - fmaf(v, wj, w) : 0.f;
+    if (row == j + 1) M.d[j + 1] = (double)a;
+    as_global(M.acol)[row] = row > j + 1 ? a : 0.f;
+    const float s = wave_sum_all(row > j + 2 ? a * a : 0.f);
+    if (lane == 0) M.npart[tr.J] = s;
+}
+
+// C -= acc for the rows of the tile from `first` on, sixteen elements at a time (one accumulator's loads in flight, not 64)
+__device__ inline void subtract_tile(const floatx16 (&acc)[2][2], global_ptr<float> C, int64_t ld, int first) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lk = lane >> 5, lc = lane & 31;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int r0 = (wave >> 1) * 64 + 32 * i + 4 * lk;
+            const global_ptr<float> p = C + (int64_t)r0 * ld + (wave & 1) * 64 + 32 * k + lc;
+            float old[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) old[r] = p[(int64_t)(8 * (r >> 2) + (r & 3)) * ld];
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (r0 + 8 * (r >> 2) + (r & 3) >= first) p[(int64_t)(8 * (r >> 2) + (r & 3)) * ld] = old[r] - acc[i][k][r];
+        }
+}
+
+// Rank-64 update of the trailing matrix by the panel that ends before step t: A_IJ -= V_I W_J^T + W_I V_J^T (lower tiles).
+__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(3))) void dir_update_kernel(const DirMat *mats, const unsigned *tab, int t) {
+    __shared__ TileSmem sm;
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    if (t - M.off <= 0) return;        // this factor's reduction starts at step t
+    const int64_t ld = M.ld;
+    OpStrided<float, false> a{M.panel + tr.I * TB, 1, ld, TB, 2 * NB, -1};
+    OpStrided<float, false> b{M.panel + NB * ld + tr.J * TB, 1, ld, TB, 2 * NB, -1};
+    floatx16 acc[2][2];
+    const global_ptr<float> C = as_global(M.A) + (int64_t)tr.I * TB * ld + tr.J * TB;
+    gemm_tile(a, b, 0, 0, 0, 2 * NB, sm, acc);
+    subtract_tile(acc, C, ld, t - M.off - tr.I * TB);      // rows of finished columns hold reflectors
+}
+
+// Row p of A keeps reflector p only: zeros up to and including the diagonal.
+__global__ __launch_bounds__(256) void dir_clear_kernel(const DirMat *mats) {
+    const DirMat M = mats[blockIdx.y];
+    if (M.n <= TD_SMALL) return;
+    const global_ptr<float> A = as_global(M.A);
+    for (int r = blockIdx.x; r < M.np; r += NORM_WGS) {
+        const int end = r >= M.n - 1 ? M.np : r + 1;
+        for (int c = threadIdx.x; c < end; c += 256) A[(int64_t)r * M.ld + c] = 0.f;
+    }
+}
+
+// ---- eigenvalues and eigenvectors of T ------------------------------------------------------------------------
+__device__ inline double hash_unit(int i) {   // in [-1, 1)
+    unsigned long long z = (unsigned long long)(i + 1) * 0x9E3779B97F4A7C15ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    z ^= z >> 31;
+    return (double)(long long)(z >> 11) * (1.0 / 4503599627370496.0) - 1.0;
+}
+
+// td <- T / (Gershgorin bound), its diagonal perturbed; zeros where the matrix is not finite.
+__global__ __launch_bounds__(256) void dir_scale_t_kernel(const DirMat *mats) {
+    const DirMat M = mats[blockIdx.x];
+    const int n = M.n;
+    double g = 0.0;
+    for (int i = threadIdx.x; i < n; i += 256)
+        g = fmax(g, fabs(M.d[i]) + (i > 0 ? fabs(M.e[i - 1]) : 0.0) + (i < n - 1 ? fabs(M.e[i]) : 0.0));
+    __shared__ double red[4];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) g = fmax(g, __shfl_xor(g, o, 64));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = g;
+    __syncthreads();
+    g = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    const double inv = (g > 0.0 && g < 1e300) ? 1.0 / g : 0.0;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const double e = i < n - 1 ? M.e[i] : 0.0, d = M.d[i];
+        double en = fabs(e) < 1e300 ? e * inv * (1.0 + PERTURB_REL * hash_unit(-2 - i)) : 0.0;
+        if (i < n - 1 && fabs(en) < E_MIN) en = E_MIN;
+        M.td[i] = make_double2((fabs(d) < 1e300 ? d * inv : 0.0) * (1.0 + PERTURB_REL * hash_unit(2 * i)) + PERTURB_ABS * hash_unit(2 * i + 1), en * en);
+        M.te[i] = en;
+    }
+}
+
+// Eigenvalue k of T by bisection in fp64: four lanes per eigenvalue try the four points that cut its interval into five
+// (2.3 bits a pass).  A count is a Sturm sequence of the leading minors' signs, two dependent FMAs per row; the minors are
+// rescaled every eight rows.
+constexpr int BIS_CHUNK = 256;
+__global__ __launch_bounds__(256) void dir_bisect_kernel(const DirMat *mats, const unsigned *tab) {
+    __shared__ double2 ch[BIS_CHUNK];
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    const int n = M.n, tid = threadIdx.x, q = tid & 3, k = tr.J * 64 + (tid >> 2);
+    double lo = -1.0 - 1e-6, hi = 1.0 + 1e-6;     // Gershgorin, with room for the perturbation
+    for (int pass = 0; pass < 25; ++pass) {
+        const double step = (hi - lo) * 0.2, x = lo + step * (q + 1);
+        double p = 1.0, pp = 0.0;     // minors i and i - 1
+        double e2 = 0.0;
+        int count = 0;
+        for (int base = 0; base < n; base += BIS_CHUNK) {
+            __syncthreads();
+            if (base + tid < n) ch[tid] = M.td[base + tid];
+            else ch[tid] = make_double2(4.0, 0.0);   // rows past the end: no sign changes
+            __syncthreads();
+            const int cnt = min(BIS_CHUNK, (n - base + 7) & ~7);
+            for (int i = 0; i < cnt; i += 8) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const double2 t = ch[i + u];
+                    const double np_ = fma(t.x - x, p, -e2 * pp);   // p and pp are never both zero: e2 is not
+                    count += (int)(((unsigned)__double2hiint(np_) ^ (unsigned)__double2hiint(p)) >> 31);
+                    pp = p;
+                    p = np_;
+                    e2 = t.y;
+                }
+                const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pp)));
+                p = ldexp(p, ex);
+                pp = ldexp(pp, ex);
+            }
+        }
+        int below = count <= k ? 1 : 0;     // the eigenvalue is not below this point
+        below += __shfl_xor(below, 1, 64);
+        below += __shfl_xor(below, 2, 64);
+        const double l0 = lo;
+        lo = below > 0 ? l0 + step * below : lo;
+        hi = below < 4 ? l0 + step * (below + 1) : hi;
+    }
+    if (q == 0 && k < n) M.lam64[k] = 0.5 * (lo + hi);
+}
+
+__device__ inline double fast_rcp(double q) {   // |q| in [1e-30, 1e60]: hardware estimate, two Newton steps
+    double r = __builtin_amdgcn_rcp(q);
+    r = fma(fma(-q, r, 1.0), r, r);
+    r = fma(fma(-q, r, 1.0), r, r);
+    return r;
+}
+__device__ inline double pivot(double q) { return fabs(q) < PIVOT_MIN ? -PIVOT_MIN : q; }
+
+// Eigenvector k of T by twisted factorisation: pivots q_i of the elimination from the top and r_i of the one from the
+// bottom, the twist where |q_i + r_i - (d_i - lam)| is least, and the two recurrences away from it.  One lane per
+// eigenvector; the pivots of the wave's 64 vectors are rows of 512 bytes.  A serial chain of a few divisions per row:
+// bound by the latency of the fp64 units, all vectors of all factors at once.
+constexpr int VEC_CHUNK = 128;
+__global__ __launch_bounds__(64) void dir_vectors_kernel(const DirMat *mats, const unsigned *tab) {
+    __shared__ double2 ch[VEC_CHUNK + 1];
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    const int n = M.n, lane = threadIdx.x, k = tr.J * 64 + lane;
+    const bool act = k < n;
+    const double lam = M.lam64[min(k, n - 1)];
+    const int64_t ld = M.ld;
+    const global_ptr<double> D = as_global((double *)M.B1) + (act ? k : 0);
+    const global_ptr<float> Z = as_global(M.Z) + (act ? k : 0);
+    const int nch = (n + VEC_CHUNK - 1) / VEC_CHUNK;
+    // from the top
+    double q = 1.0, e2 = 0.0;
+    for (int b = 0; b < nch; ++b) {
+        const int base = b * VEC_CHUNK, cnt = min(VEC_CHUNK, n - base);
+        __syncthreads();
+        for (int i = lane; i < cnt; i += 64) ch[i] = M.td[base + i];
+        __syncthreads();
+        for (int i = 0; i < cnt; ++i) {
+            const double2 t = ch[i];
+            q = pivot((t.x - lam) - e2 * fast_rcp(q));
+            if (act) D[(int64_t)(base + i) * ld] = q;
+            e2 = t.y;
+        }
+    }
+    // from the bottom: find the twist
+    double r = 1.0, best = 1e300;
+    int tw = n - 1;
+    for (int b = nch - 1; b >= 0; --b) {
+        const int base = b * VEC_CHUNK, cnt = min(VEC_CHUNK, n - base);
+        __syncthreads();
+        for (int i = lane; i < cnt; i += 64) ch[i] = M.td[base + i];
+        __syncthreads();
+        for (int i0 = cnt; i0 > 0; i0 -= 8) {
+            double qs[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) qs[u] = i0 - 1 - u >= 0 ? D[(int64_t)(base + i0 - 1 - u) * ld] : 0.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 - 1 - u;
+                if (i < 0) break;
+                const double2 t = ch[i];
+                const double dl = t.x - lam;
+                r = pivot(dl - t.y * fast_rcp(r));     // t.y couples rows i and i + 1 (zero in the last row)
+                const double gam = fabs(qs[u] + (r - dl));
+                if (gam < best) { best = gam; tw = base + i; }
+            }
+        }
+    }
+    int tmin = tw, tmax = tw;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { tmin = min(tmin, __shfl_xor(tmin, o, 64)); tmax = max(tmax, __shfl_xor(tmax, o, 64)); }
+    // the pivots from the bottom again, over those from the top, where they are needed: below the twist
+    r = 1.0;
+    for (int b = nch - 1; b >= 0 && (b + 1) * VEC_CHUNK > tmin + 1; --b) {
+        const int base = b * VEC_CHUNK, cnt = min(VEC_CHUNK, n - base);
+        __syncthreads();
+        for (int i = lane; i < cnt; i += 64) ch[i] = M.td[base + i];
+        __syncthreads();
+        for (int i = cnt - 1; i >= 0; --i) {
+            const double2 t = ch[i];
+            r = pivot((t.x - lam) - t.y * fast_rcp(r));
+            if (act && base + i > tw) D[(int64_t)(base + i) * ld] = r;
+        }
+    }
+    // upwards from the twist
+    double *ce = (double *)ch;
+    double z = 0.0, nrm = 1.0;
+    for (int b = nch - 1; b >= 0; --b) {
+        const int base = b * VEC_CHUNK, cnt = min(VEC_CHUNK, n - base);
+        if (base > tmax) continue;
+        __syncthreads();
+        for (int i = lane; i < cnt; i += 64) ce[i] = M.te[base + i];
+        __syncthreads();
+        for (int i0 = cnt; i0 > 0; i0 -= 8) {
+            double qs[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) qs[u] = i0 - 1 - u >= 0 ? D[(int64_t)(base + i0 - 1 - u) * ld] : 1.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 - 1 - u;
+                if (i < 0) break;
+                const int gi = base + i;
+                if (gi > tw) continue;
+                if (gi == tw) z = 1.0;
+                else {
+                    z = -ce[i] * z * fast_rcp(qs[u]);
+                    nrm += z * z;
+                }
+                if (act) Z[(int64_t)gi * ld] = (float)z;
+            }
+        }
+    }
+    // downwards
+    z = 1.0;
+    double eprev = 0.0;
+    for (int b = tmin / VEC_CHUNK; b < nch; ++b) {
+        const int base = b * VEC_CHUNK, cnt = min(VEC_CHUNK, n - base);
+        __syncthreads();
+        for (int i = lane; i < cnt; i += 64) ce[i] = M.te[base + i];
+        __syncthreads();
+        for (int i0 = 0; i0 < cnt; i0 += 8) {
+            double rs[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) rs[u] = i0 + u < cnt ? D[(int64_t)(base + i0 + u) * ld] : 1.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + u, gi = base + i;
+                if (i >= cnt) break;
+                if (gi > tw) {
+                    z = -eprev * z * fast_rcp(rs[u]);
+                    nrm += z * z;
+                    if (act) Z[(int64_t)gi * ld] = (float)z;
+                }
+                eprev = ce[i];
+            }
+        }
+    }
+    const float inv = (float)(1.0 / sqrt(nrm));
+    if (act)
+        for (int i0 = 0; i0 < n; i0 += 8) {
+            float zz[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) zz[u] = i0 + u < n ? Z[(int64_t)(i0 + u) * ld] : 0.f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (i0 + u < n) Z[(int64_t)(i0 + u) * ld] = zz[u] * inv;
+        }
+}
+
+// ---- back-transformation -------------------------------------------------------------------------------------
+// Small factors: a wave owns four columns of Z, lane l the rows l, l + 64, ..: all reflectors are applied out of registers, no
+// barriers; what bounds it is the latency of a reflector's four wave sums.
+__global__ __launch_bounds__(256) void dir_apply_kernel(const DirMat *mats, const unsigned *tab) {
+    constexpr int RPL = TD_SMALL / 64;
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    const int n = M.n, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c0 = tr.J * 16 + wave * 4;
+    if (c0 >= n) return;
+    const int64_t ld = M.ld;
+    const global_ptr<float> Z = as_global(M.Z) + c0;
+    floatx4 z[RPL];
+#pragma unroll
+    for (int k = 0; k < RPL; ++k) {
+        const int r = lane + 64 * k;
+        z[k] = r < n ? *(global_ptr<floatx4>)(Z + (int64_t)r * ld) : floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    const global_ptr<const float> A = as_global((const float *)M.A), tau = as_global((const float *)M.tau);
+    float v[RPL], vn[RPL];
+    auto load = [&](float (&x)[RPL], int p) {
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) {
+            const int r = lane + 64 * k;
+            x[k] = (r < n && r > p) ? A[(int64_t)p * ld + r] : 0.f;
+        }
+    };
+    int p = n - 2;
+    if (p >= 0) load(v, p);
+    for (; p >= 0; --p) {
+        if (p > 0) load(vn, p - 1);
+        floatx4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) s += v[k] * z[k];
+        const float tp = tau[p];
+        const floatx4 f = {-tp * wave_sum_all(s.x), -tp * wave_sum_all(s.y), -tp * wave_sum_all(s.z), -tp * wave_sum_all(s.w)};
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) {
+            z[k] += v[k] * f;
+            v[k] = vn[k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < RPL; ++k) {
+        const int r = lane + 64 * k;
+        if (r < n) *(global_ptr<floatx4>)(Z + (int64_t)r * ld) = z[k];
+    }
+}
+
+// Large factors: H_{j0} .. H_{j0+127} = I - V T V^T.  Gram matrices of all blocks, their T, U = V T (as rows T^T V^T), then
+// block after block from the last: Y = V^T Z, Z -= U Y.
+__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void dir_wy_gram_kernel(const DirMat *mats, const unsigned *tab) {
+    __shared__ TileSmem sm;
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    const int j0 = tr.J * WY;
+    const int64_t ld = M.ld;
+    OpStrided<float, true> a{M.A + (int64_t)j0 * ld, ld, 1, WY, M.np, -1}, b{M.A + (int64_t)j0 * ld, ld, 1, WY, M.np, -1};
+    floatx16 acc[2][2];
+    gemm_tile_segmented<128, false>(a, b, 0, 0, j0, M.np, sm, acc);
+    float *G = M.Tm + (int64_t)tr.J * WY * WY;
+    for_each_acc(acc, [&](int r, int c, float v) { as_global(G)[r * WY + c] = v; });
+}
+
+__global__ __launch_bounds__(WY) void dir_wy_t_kernel(const DirMat *mats, const unsigned *tab) {
+    extern __shared__ float lds[];
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    float *T = lds, *G = lds + WY * (WY + 1);
+    const int r = threadIdx.x;
+    const global_ptr<float> g = as_global(M.Tm + (int64_t)tr.J * WY * WY);
+    for (int i = 0; i < WY; ++i) { G[i * (WY + 1) + r] = g[i * WY + r]; T[i * (WY + 1) + r] = 0.f; }
+    __syncthreads();
+    for (int i = 0; i < WY; ++i) {
+        const float ti = M.tau[tr.J * WY + i];
+        double s = 0.0;
+        for (int p = r; p < i; ++p) s = fma((double)T[r * (WY + 1) + p], (double)G[p * (WY + 1) + i], s);
+        if (r <= i) T[r * (WY + 1) + i] = r == i ? ti : (float)(-ti * s);
+        __syncthreads();
+    }
+    for (int i = 0; i < WY; ++i) g[i * WY + r] = T[i * (WY + 1) + r];
+}
+
+__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(3))) void dir_wy_u_kernel(const DirMat *mats, const unsigned *tab) {
+    __shared__ TileSmem sm;
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    const int j0 = tr.I * WY;
+    const int64_t ld = M.ld;
+    OpStrided<float, false> a{M.Tm + (int64_t)tr.I * WY * WY, 1, WY, WY, WY, -1};          // T[k][i]
+    OpStrided<float, false> b{M.A + (int64_t)j0 * ld + tr.J * TB, 1, ld, TB, WY, -1};      // V^T[k][n]
+    floatx16 acc[2][2];
+    gemm_tile(a, b, 0, 0, 0, WY, sm, acc);
+    const global_ptr<float> U = as_global(M.B1) + (int64_t)j0 * ld + tr.J * TB;
+    for_each_acc(acc, [&](int r, int c, float v) { U[(int64_t)r * ld + c] = v; });
+}
+
+// Step s counts blocks from the last one of every factor.  Y = V^T Z is one row of tiles with a contraction of up to n: it
+// is cut into pieces of 512 (more workgroups than the 111 tiles of three 4609-wide factors, and partial sums short enough
+// not to lose accuracy), which dir_wy_sum_kernel adds.  The pieces lie in B2, 128 rows each.
+__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(3))) void dir_wy_y_kernel(const DirMat *mats, const unsigned *tab, int s) {
+    __shared__ TileSmem sm;
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    const int blk = M.nb - 1 - s, j0 = blk * WY, k0 = j0 + tr.I * WY_K;
+    if (blk < 0 || k0 >= M.n) return;
+    const int k1 = min(k0 + WY_K, M.n);
+    const int64_t ld = M.ld;
+    OpStrided<float, true> a{M.A + (int64_t)j0 * ld, ld, 1, WY, k1, -1};
+    OpStrided<float, false> b{M.Z + tr.J * TB, 1, ld, TB, k1, -1};
+    floatx16 acc[2][2];
+    gemm_tile(a, b, 0, 0, k0, k1, sm, acc);
+    const global_ptr<float> Y = as_global(M.B2) + (int64_t)tr.I * WY * ld + tr.J * TB;
+    for_each_acc(acc, [&](int r, int c, float v) { Y[(int64_t)r * ld + c] = v; });
+}
+__global__ __launch_bounds__(256) void dir_wy_sum_kernel(const DirMat *mats, const unsigned *tab, int s) {
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    const int blk = M.nb - 1 - s;
+    const int pieces = blk < 0 ? 0 : (M.n - blk * WY + WY_K - 1) / WY_K;
+    if (pieces < 2) return;
+    const int64_t ld = M.ld;
+    const global_ptr<float> Y = as_global(M.B2) + (int64_t)(threadIdx.x >> 5) * ld + tr.J * TB + 4 * (threadIdx.x & 31);
+#pragma unroll 4
+    for (int r = 0; r < WY / 8; ++r) {
+        const global_ptr<float> p = Y + (int64_t)(8 * r) * ld;
+        floatx4 v = *(global_ptr<floatx4>)p;
+        for (int c = 1; c < pieces; ++c) v += *(global_ptr<floatx4>)(p + (int64_t)c * WY * ld);
+        *(global_ptr<floatx4>)p = v;
+    }
+}
+__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(3))) void dir_wy_z_kernel(const DirMat *mats, const unsigned *tab, int s) {
+    __shared__ TileSmem sm;
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    const int blk = M.nb - 1 - s;
+    if (blk < 0 || tr.I < blk) return;
+    const int64_t ld = M.ld;
+    OpStrided<float, false> a{M.B1 + (int64_t)blk * WY * ld + tr.I * TB, 1, ld, TB, WY, -1};   // U^T: elem(i, k) = U[k][i]
+    OpStrided<float, false> b{M.B2 + tr.J * TB, 1, ld, TB, WY, -1};
+    floatx16 acc[2][2];
+    gemm_tile(a, b, 0, 0, 0, WY, sm, acc);
+    subtract_tile(acc, as_global(M.Z) + (int64_t)tr.I * TB * ld + tr.J * TB, ld, 0);
+}
+
+// ---- Newton-Schulz step and F Q, all factors in one launch each (tables: largest factor first) ------------------
+// ORTH: B1 = (I - Q^T Q) / 2 (lower tiles and their mirror images).  STEP: Q' = Q + Q B1.  Q is Z, Q' is B2 with its rows back
+// in the caller's order; for the few factors that need a second step (nearly equal eigenvalues of T whose eigenvectors
+// were off by more than 1e-3) Q is B2 and Q' is Z.  TIMES_F: B1 = F Q'.
+enum { ORTH, STEP, TIMES_F };
+__device__ inline bool needs_second_step(const DirMat &M) { return M.stat[3] > NS_AGAIN; }
+__device__ inline float *final_q(const DirMat &M) { return needs_second_step(M) ? M.Z : M.B2; }
+
+template <int WHAT, bool X3>
+__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void dir_product_kernel(const DirMat *mats, const unsigned *tab, int second) {
+    __shared__ typename std::conditional<X3, X3Smem, TileSmem>::type sm;
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    if (WHAT != TIMES_F && ((M.split != 0) != X3 || (second && !needs_second_step(M)))) return;
+    const int n = M.n, i0 = tr.I * TB, j0 = tr.J * TB;
+    const int64_t ld = M.ld;
+    const float *Q = second ? M.B2 : M.Z;
+    constexpr float SC = 16384.f, OUT = 1.f / (SC * SC);     // entries of Q and of the correction are below 1
+    floatx16 acc[2][2];
+    if constexpr (WHAT == ORTH) {
+        if constexpr (X3) {
+            X3OpG<float, false> a{Q, ld, SC, n, n}, b{Q, ld, SC, n, n};
+            a.start(threadIdx.x, i0);
+            b.start(threadIdx.x, j0);
+            gemm_tile_x3(a, b, n, sm, acc);
+        } else {
+            OpStrided<float, false> a{Q, 1, ld, n, n, -1}, b{Q, 1, ld, n, n, -1};
+            gemm_tile(a, b, i0, j0, 0, n, sm, acc);
+        }
+        const float os = X3 ? OUT : 1.f;
+        const global_ptr<float> D = as_global(M.B1);
+        auto epi = [&](int gr, int gc, float v) {
+            if (gr < n && gc < n) D[(int64_t)gr * ld + gc] = (gr == gc ? 0.5f : 0.f) - 0.5f * (v * os);
+        };
+        for_each_acc(acc, [&](int r, int c, float v) { epi(i0 + r, j0 + c, v); });
+        if (j0 < i0) for_each_acc_transposed(acc, reinterpret_cast<float *>(&sm), [&](int r, int c, float v) { epi(j0 + r, i0 + c, v); });
+    } else if constexpr (WHAT == STEP) {
+        const global_ptr<const float> Qi = as_global(Q);
+        const global_ptr<float> O = as_global(second ? M.Z : M.B2);
+        const global_ptr<const int> ord = as_global((const int *)M.ord);
+        auto epi = [&](int gr, int gc, float v) { O[(int64_t)(second ? gr : ord[gr]) * ld + gc] = Qi[(int64_t)gr * ld + gc] + v; };
+        if constexpr (X3) {
+            X3OpG<float, true> a{Q, ld, SC, n, n};
+            X3OpG<float, false> b{M.B1, ld, SC, n, n};
+            a.start(threadIdx.x, i0);
+            b.start(threadIdx.x, j0);
+            gemm_tile_x3(a, b, n, sm, acc);
+            for_each_acc(acc, [&](int r, int c, float v) { if (i0 + r < n && j0 + c < n) epi(i0 + r, j0 + c, v * OUT); });
+        } else {
+            OpStrided<float, true> a{Q, ld, 1, n, n, -1};
+            OpStrided<float, false> b{M.B1, 1, ld, n, n, -1};
+            gemm_tile_ragged(a, b, i0, j0, n, n, n, sm, epi);
+        }
+    } else {
+        OpStrided<float, true> a{M.F, n, 1, n, n, -1};
+        OpStrided<float, false> b{final_q(M), 1, ld, n, n, -1};
+        const global_ptr<float> O = as_global(M.B1);
+        gemm_tile_ragged<512>(a, b, i0, j0, n, n, n, sm, [&](int gr, int gc, float v) { O[(int64_t)gr * ld + gc] = v; });
+    }
+}
+
+// ||I - Q^T Q||_F^2 (four times that of D), per workgroup
+__global__ __launch_bounds__(256) void dir_dev_kernel(const DirMat *mats) {
+    const DirMat M = mats[blockIdx.y];
+    const global_ptr<const float> D = as_global((const float *)M.B1);
+    double s = 0.0;
+    for (int r = blockIdx.x; r < M.n; r += NORM_WGS)
+        for (int c = threadIdx.x; c < M.n; c += 256) {
+            const double v = (double)D[(int64_t)r * M.ld + c];
+            s += v * v;
+        }
+    __shared__ double red[4];
+    s = wave_sum_f64(s);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) M.npartd[blockIdx.x] = 4.0 * (red[0] + red[1] + red[2] + red[3]);
+}
+
+// the sum over the workgroups: stat[3]
+__global__ __launch_bounds__(64) void dir_dev_sum_kernel(const DirMat *mats) {
+    const DirMat M = mats[blockIdx.x];
+    double dev = 0.0;
+#pragma unroll
+    for (int i = 0; i < NORM_WGS / 64; ++i) dev += M.npartd[64 * i + (int)threadIdx.x];
+    dev = wave_sum_f64(dev);
+    if (threadIdx.x == 0) M.stat[3] = dev;
+}
+
+// Per column: sums of q fq, fq^2 and q^2 over the rows of part blockIdx.y.
+__global__ __launch_bounds__(256) void dir_rayleigh_kernel(const DirMat *mats) {
+    const DirMat M = mats[blockIdx.z];
+    const int c = blockIdx.x * 256 + threadIdx.x;
+    if (c >= M.n) return;
+    const global_ptr<const float> Q = as_global((const float *)final_q(M)) + c, FQ = as_global((const float *)M.B1) + c;
+    const int per = (M.n + NPARTS - 1) / NPARTS, r0 = blockIdx.y * per, r1 = min(M.n, r0 + per);
+    double s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    for (int r = r0; r < r1; ++r) {
+        const double q = (double)Q[(int64_t)r * M.ld], f = (double)FQ[(int64_t)r * M.ld];
+        s1 = fma(q, f, s1);
+        s2 = fma(f, f, s2);
+        s3 = fma(q, q, s3);
+    }
+    double *o = M.sums + (int64_t)blockIdx.y * 3 * M.np + c;
+    o[0] = s1;
+    o[M.np] = s2;
+    o[2 * M.np] = s3;
+}
+// lam64 = q^T F q / q^T q, and the factor that makes the column a unit vector; its residual is then s2 / s3 - lam^2
+__global__ __launch_bounds__(256) void dir_lambda_kernel(const DirMat *mats) {
+    const DirMat M = mats[blockIdx.y];
+    const int c = blockIdx.x * 256 + threadIdx.x;
+    double res = 0.0;
+    if (c < M.n) {
+        double s1 = 0.0, s2 = 0.0, s3 = 0.0;
+        for (int p = 0; p < NPARTS; ++p) {
+            const double *o = M.sums + (int64_t)p * 3 * M.np + c;
+            s1 += o[0];
+            s2 += o[M.np];
+            s3 += o[2 * M.np];
+        }
+        const double l = s1 / s3;
+        M.lam64[c] = l;
+        M.te[c] = 1.0 / sqrt(s3);
+        res = s2 / s3 - l * l;
+    }
+    __shared__ double red[4];
+    res = wave_sum_f64(res);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = res;
+    __syncthreads();
+    if (threadIdx.x == 0 && (int)blockIdx.x * 256 < M.n) M.npartd[NORM_WGS + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+}
+
+// perm[rank] = index of the rank-th smallest Rayleigh quotient (ties and NaNs by index: always a permutation)
+__global__ __launch_bounds__(256) void dir_rank_kernel(const DirMat *mats) {
+    __shared__ float chunk[256];
+    __shared__ int part[256];
+    const DirMat M = mats[blockIdx.y];
+    const int n = M.n, ii = threadIdx.x & (RANK_IPB - 1), js = threadIdx.x / RANK_IPB, i = blockIdx.x * RANK_IPB + ii;
+    if ((int)blockIdx.x * RANK_IPB >= n) return;
+    if (blockIdx.x == 0 && threadIdx.x < 64) {     // the residual of the whole factor, for the host
+        const int lane = threadIdx.x, nr = (n + 255) / 256;
+        double res = lane < nr ? M.npartd[NORM_WGS + lane] : 0.0;
+        res = wave_sum_f64(res);
+        if (lane == 0) M.stat[2] = res;
+    }
+    const float li = i < n ? (float)M.lam64[i] : 0.f;
+    const bool nan_i = li != li;
+    int rank = 0;
+    for (int j0 = 0; j0 < n; j0 += 256) {
+        __syncthreads();
+        chunk[threadIdx.x] = j0 + (int)threadIdx.x < n ? (float)M.lam64[j0 + threadIdx.x] : 0.f;
+        __syncthreads();
+        const int cnt = min(256, n - j0);
+        for (int k = js; k < cnt; k += 256 / RANK_IPB) {
+            const float lj = chunk[k];
+            const int j = j0 + k;
+            const bool nan_j = lj != lj;
+            rank += nan_i ? (!nan_j || j < i) : (!nan_j && ((lj < li) || (lj == li && j < i)));
+        }
+    }
+    part[threadIdx.x] = rank;
+    __syncthreads();
+    if (js == 0 && i < n) {
+        int total = 0;
+        for (int t = 0; t < 256 / RANK_IPB; ++t) total += part[t * RANK_IPB + ii];
+        M.perm[total] = i;
+        M.lam[total] = li;
+    }
+}
+// the caller's Q (columns in ascending order of the eigenvalues); NaNs for a factor that was not finite
+__global__ __launch_bounds__(256) void dir_gather_kernel(const DirMat *mats) {
+    const DirMat M = mats[blockIdx.y];
+    const int n = M.n;
+    const bool bad = !(M.stat[0] + M.stat[1] < 1e300);
+    const float nan = __uint_as_float(0x7fc00000u);
+    const global_ptr<const float> S = as_global((const float *)final_q(M));
+    const global_ptr<float> Q = as_global(M.Q);
+    const global_ptr<const double> unit = as_global((const double *)M.te);
+    const global_ptr<const int> perm = as_global((const int *)M.perm);
+    for (int r = blockIdx.x; r < n; r += NORM_WGS)
+        for (int c = threadIdx.x; c < n; c += 256) {
+            const int p = perm[c];
+            Q[(int64_t)r * n + c] = bad ? nan : S[(int64_t)r * M.ld + p] * (float)unit[p];
+        }
+    if (bad && blockIdx.x == 0)
+        for (int c = threadIdx.x; c < n; c += 256) M.lam[c] = nan;
+}
+
+// ---- host side -------------------------------------------------------------------------------------------------
+struct DirSize { int n, np, ld, nb; };
+DirSize dir_size(int n) {
+    DirSize s;
+    s.n = n;
+    s.np = (n + TB - 1) / TB * TB;
+    s.ld = s.np + 32;         // not a multiple of 128: rows of one tile then start in different channels
+    s.nb = s.np / TB;
+    return s;
+}
+
+// Carves a factor's buffers out of `p` (null: sizes only); returns the bytes.
+size_t dir_layout(const DirSize &s, char *p, DirMat *M) {
+    size_t at = 0;
+    auto take = [&](size_t bytes) { char *r = p + at; at += kfac_align_up(bytes, 256); return r; };
+    const size_t mat = (size_t)s.np * s.ld * sizeof(float);
+    DirMat d{};
+    d.A = (float *)take(mat);
+    d.Z = (float *)take(mat);
+    d.B1 = (float *)take(2 * mat);
+    d.B2 = d.B1 + (size_t)s.np * s.ld;
+    if (s.n > TD_SMALL) {
+        d.panel = (float *)take((size_t)3 * NB * s.ld * sizeof(float));
+        d.part = (float *)take((size_t)s.nb * s.np * sizeof(float));
+        d.dots = (float *)take((size_t)s.nb * 2 * NB * sizeof(float));
+        d.tsum = (float *)take((size_t)s.nb * (s.nb + 1) / 2 * sizeof(float));
+        d.acol = (float *)take((size_t)s.np * sizeof(float));
+        d.npart = (float *)take((size_t)(s.np / RB) * sizeof(float));
+        d.scal = (float *)take(16);
+    }
+    d.tau = (float *)take((size_t)s.np * sizeof(float));
+    d.d = (double *)take((size_t)s.np * sizeof(double));
+    d.e = (double *)take((size_t)s.np * sizeof(double));
+    d.td = (double2 *)take((size_t)s.np * sizeof(double2));
+    d.te = (double *)take((size_t)s.np * sizeof(double));
+    d.lam64 = (double *)take((size_t)s.np * sizeof(double));
+    d.sums = (double *)take((size_t)NPARTS * 3 * s.np * sizeof(double));
+    d.npartd = (double *)take((size_t)2 * NORM_WGS * sizeof(double));
+    if (s.n > TD_SMALL) d.Tm = (float *)take((size_t)s.nb * WY * WY * sizeof(float));
+    d.perm = (int *)take((size_t)s.np * sizeof(int));
+    d.ord = (int *)take((size_t)s.np * sizeof(int));
+    if (M) {
+        d.n = s.n; d.np = s.np; d.ld = s.ld; d.nb = s.nb;
+        *M = d;
+    }
+    return at;
+}
+
+struct DirPlan {
+    std::vector<DirMat> mats;
+    std::vector<unsigned> tab;            // all tables, one after another
+    struct Range { unsigned at, count; };
+    int steps = 0;                        // of the reduction chain
+    std::vector<Range> tiles, rows;       // per panel
+    std::vector<int> small[4];            // factors per register kernel: up to 64, 128, 192, 256
+    unsigned small_at[4] = {0, 0, 0, 0};
+    Range values{0, 0}, apply{0, 0}, gram{0, 0}, wyu{0, 0}, wyy{0, 0}, wys{0, 0}, wyz{0, 0}, lower{0, 0}, full{0, 0};
+    int wy_steps = 0, nmax = 0;
+    bool any_split = false, any_plain = false;
+};
+
+unsigned pack(int m, int I, int J) { return (unsigned)m << 14 | (unsigned)I << 7 | (unsigned)J; }
+
+void dir_tables(DirPlan &P) {
+    const int nm = (int)P.mats.size();
+    std::vector<int> order(nm);
+    for (int i = 0; i < nm; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return P.mats[a].n > P.mats[b].n; });
+    auto begin = [&](DirPlan::Range &r) { r.at = (unsigned)P.tab.size(); };
+    auto end = [&](DirPlan::Range &r) { r.count = (unsigned)P.tab.size() - r.at; };
+    P.nmax = nm ? P.mats[order[0]].n : 0;
+    for (auto &M : P.mats)
+        if (M.n > TD_SMALL) M.off = (P.nmax - M.n) / NB * NB;
+    if (P.nmax > TD_SMALL) {
+        for (auto &M : P.mats)
+            if (M.n > TD_SMALL) P.steps = std::max(P.steps, M.off + M.n);
+        const int npanel = (P.steps + NB - 1) / NB;
+        P.tiles.resize(npanel);
+        P.rows.resize(npanel);
+        for (int q = 0; q < npanel; ++q) {
+            begin(P.tiles[q]);
+            for (int m : order) {
+                const DirMat &M = P.mats[m];
+                const int j = q * NB - M.off;
+                if (M.n <= TD_SMALL || j < 0 || j > M.n - 1) continue;
+                for (int I = j / TB; I < M.nb; ++I)
+                    for (int J = j / TB; J <= I; ++J) P.tab.push_back(pack(m, I, J));
+            }
+            end(P.tiles[q]);
+            begin(P.rows[q]);
+            for (int m : order) {
+                const DirMat &M = P.mats[m];
+                const int j = q * NB - M.off;
+                if (M.n <= TD_SMALL || j < 0 || j > M.n - 1) continue;
+                for (int r = j / TB * 2; r < 2 * M.nb; ++r) P.tab.push_back(pack(m, 0, r));
+            }
+            end(P.rows[q]);
+        }
+    }
+    for (int m : order) {
+        const int n = P.mats[m].n;
+        if (n <= TD_SMALL) P.small[n <= 64 ? 0 : n <= 128 ? 1 : n <= 192 ? 2 : 3].push_back(m);
+    }
+    for (int k = 0; k < 4; ++k) {
+        P.small_at[k] = (unsigned)P.tab.size();
+        for (int m : P.small[k]) P.tab.push_back((unsigned)m);
+    }
+    begin(P.values);
+    for (int m : order)
+        for (int c = 0; c < (P.mats[m].n + 63) / 64; ++c) P.tab.push_back(pack(m, 0, c));
+    end(P.values);
+    begin(P.apply);
+    for (int m : order)
+        if (P.mats[m].n <= TD_SMALL)
+            for (int c = 0; c < (P.mats[m].n + 15) / 16; ++c) P.tab.push_back(pack(m, 0, c));
+    end(P.apply);
+    auto wy = [&](DirPlan::Range &r, auto f) {
+        begin(r);
+        for (int m : order)
+            if (P.mats[m].n > TD_SMALL) f(m, P.mats[m].nb);
+        end(r);
+    };
+    wy(P.gram, [&](int m, int nb) { P.wy_steps = std::max(P.wy_steps, nb); for (int b = 0; b < nb; ++b) P.tab.push_back(pack(m, 0, b)); });
+    wy(P.wyu, [&](int m, int nb) { for (int b = 0; b < nb; ++b) for (int c = b; c < nb; ++c) P.tab.push_back(pack(m, b, c)); });
+    wy(P.wyy, [&](int m, int nb) { for (int k = 0; k * WY_K < P.mats[m].n; ++k) for (int c = 0; c < nb; ++c) P.tab.push_back(pack(m, k, c)); });
+    wy(P.wys, [&](int m, int nb) { for (int c = 0; c < nb; ++c) P.tab.push_back(pack(m, 0, c)); });
+    wy(P.wyz, [&](int m, int nb) { for (int r = 0; r < nb; ++r) for (int c = 0; c < nb; ++c) P.tab.push_back(pack(m, r, c)); });
+    begin(P.lower);
+    for (int m : order)
+        for (int I = 0; I < P.mats[m].nb; ++I)
+            for (int J = 0; J <= I; ++J) P.tab.push_back(pack(m, I, J));
+    end(P.lower);
+    begin(P.full);
+    for (int m : order)
+        for (int I = 0; I < P.mats[m].nb; ++I)
+            for (int J = 0; J < P.mats[m].nb; ++J) P.tab.push_back(pack(m, I, J));
+    end(P.full);
+}
+
+// Entries dir_tables() makes, without making them.
+size_t dir_table_bound(int batch, const int *d) {
+    size_t t = 0;
+    for (int i = 0; i < batch; ++i) {
+        const size_t nb = (d[i] + TB - 1) / TB;
+        t += 4 * nb * nb + 16 * nb + 16 + (size_t)(d[i] + 15) / 16 + (d[i] + 63) / 64;
+        if (d[i] > TD_SMALL) t += 4 * (nb * (nb + 1) * (nb + 2) / 6) + 4 * nb * (nb + 1) + 8;   // four panels per block
+    }
+    return t;
+}
+
+}  // namespace
+
+size_t kfac_eig_direct_ws_bytes(int batch, const int *d) {
+    size_t need = kfac_align_up((size_t)batch * sizeof(DirMat), 256) + kfac_align_up((size_t)batch * 4 * sizeof(double), 256) +
+                  kfac_align_up(dir_table_bound(batch, d) * sizeof(unsigned), 256);
+    for (int i = 0; i < batch; ++i) need += dir_layout(dir_size(d[i]), nullptr, nullptr);
+    return need;
+}
+
+// All factors of the call by the direct route; stat (pinned host memory): four doubles per factor, off^2 and diag^2 of F, the
+// squared residual ||F Q - Q diag(lam)||_F^2 and ||I - Q^T Q||_F^2 before it was orthogonalised.  Waits for the result.
+int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
+                           bool fp32_only, double *stat) {
+    if (kfac_eig_direct_ws_bytes(batch, d) > ctx->ws_bytes) return KFAC_EWORKSPACE;
+    DirPlan P;
+    P.mats.resize(batch);
+    DirMat *d_mats = (DirMat *)ctx->ws;
+    double *d_stat = (double *)(ctx->ws + kfac_align_up((size_t)batch * sizeof(DirMat), 256));
+    unsigned *d_tab = (unsigned *)((char *)d_stat + kfac_align_up((size_t)batch * 4 * sizeof(double), 256));
+    char *p = (char *)d_tab + kfac_align_up(dir_table_bound(batch, d) * sizeof(unsigned), 256);
+    for (int i = 0; i < batch; ++i) {
+        DirMat &M = P.mats[i];
+        p += dir_layout(dir_size(d[i]), p, &M);
+        M.F = F[i];
+        M.Q = Q[i];
+        M.lam = lam[i];
+        M.stat = d_stat + 4 * i;
+        M.split = !fp32_only && d[i] >= KFAC_EIG_SPLIT_MIN;
+        (M.split ? P.any_split : P.any_plain) = true;
+    }
+    dir_tables(P);
+    hipStream_t st = ctx->stream;
+    KFAC_CHECK(kfac_upload(ctx, d_mats, P.mats.data(), (size_t)batch * sizeof(DirMat)));
+    KFAC_CHECK(kfac_upload(ctx, d_tab, P.tab.data(), P.tab.size() * sizeof(unsigned)));
+    const DirMat *dm = d_mats;
+    const unsigned *tab = d_tab;
+    const dim3 per_mat4(NORM_WGS, batch);
+    double cube = 0.0, square = 0.0;
+    for (int i = 0; i < batch; ++i) { cube += (double)d[i] * d[i] * d[i]; square += (double)d[i] * d[i]; }
+    {
+        KfacProfScope prof(ctx, KC_EIG_MISC, 0.0, 8.0 * square);
+        hipLaunchKernelGGL(dir_norm_kernel, dim3(NORM_WGS, batch), dim3(256), 0, st, dm);
+        hipLaunchKernelGGL(dir_order_kernel, dim3((P.nmax + RANK_IPB - 1) / RANK_IPB, batch), dim3(256), 0, st, dm);
+        hipLaunchKernelGGL(dir_copy_kernel, per_mat4, dim3(256), 0, st, dm);
+    }
+    for (int k = 0; k < 4; ++k) {
+        if (P.small[k].empty()) continue;
+        const dim3 grid((unsigned)P.small[k].size());
+        const int *list = (const int *)(tab + P.small_at[k]);
+        double fl = 0.0;
+        for (int m : P.small[k]) fl += 4.0 / 3.0 * (double)d[m] * d[m] * d[m];
+        KfacProfScope prof(ctx, KC_EIG_SMALL, fl, 0.0);
+        switch (k) {
+            case 0: hipLaunchKernelGGL(dir_td_small_kernel<16>, grid, dim3(256), 0, st, dm, list); break;
+            case 1: hipLaunchKernelGGL(dir_td_small_kernel<32>, grid, dim3(512), 0, st, dm, list); break;
+            case 2: hipLaunchKernelGGL(dir_td_small_kernel<48>, grid, dim3(768), 0, st, dm, list); break;
+            default: hipLaunchKernelGGL(dir_td_small_kernel<64>, grid, dim3(1024), 0, st, dm, list); break;
+        }
+    }
+    for (int t = 0; t < P.steps; ++t) {
+        const DirPlan::Range tiles = P.tiles[t / NB], rows = P.rows[t / NB];
+        if (t % NB == 0) {
+            if (t > 0) {
+                KfacProfScope prof(ctx, KC_EIG_REDUCE_GEMM, 2.0 * 2.0 * NB * TB * TB * tiles.count, 8.0 * TB * TB * tiles.count);
+                hipLaunchKernelGGL(dir_update_kernel, dim3(tiles.count), dim3(NTHREADS), 0, st, dm, tab + tiles.at, t);
+            }
+            KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 0.0);
+            hipLaunchKernelGGL(dir_column_kernel, dim3(rows.count), dim3(RB), 0, st, dm, tab + rows.at, t);
+        }
+        {
+            KfacProfScope prof(ctx, KC_EIG_REDUCE_MV, 4.0 * TB * TB * tiles.count, 4.0 * TB * TB * tiles.count);
+            hipLaunchKernelGGL(dir_symv_kernel, dim3(tiles.count), dim3(256), 0, st, dm, tab + tiles.at, t);
+        }
+        KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 0.0);
+        hipLaunchKernelGGL(dir_vector_kernel, dim3(rows.count), dim3(256), 0, st, dm, tab + rows.at, t);
+    }
+    {
+        KfacProfScope prof(ctx, KC_EIG_TRI, 0.0, 0.0);
+        hipLaunchKernelGGL(dir_clear_kernel, per_mat4, dim3(256), 0, st, dm);
+        hipLaunchKernelGGL(dir_scale_t_kernel, dim3(batch), dim3(256), 0, st, dm);
+        hipLaunchKernelGGL(dir_bisect_kernel, dim3(P.values.count), dim3(256), 0, st, dm, tab + P.values.at);
+        hipLaunchKernelGGL(dir_vectors_kernel, dim3(P.values.count), dim3(64), 0, st, dm, tab + P.values.at);
+    }
+    {
+        KfacProfScope prof(ctx, KC_EIG_BACK, 2.0 * cube, 0.0);
+        if (P.apply.count) hipLaunchKernelGGL(dir_apply_kernel, dim3(P.apply.count), dim3(256), 0, st, dm, tab + P.apply.at);
+        if (P.wy_steps > 0) {
+            const int lds = 2 * WY * (WY + 1) * (int)sizeof(float);
+            if (lds > ctx->max_lds) return KFAC_EHIP;
+            KFAC_HIP_CHECK(hipFuncSetAttribute((const void *)dir_wy_t_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+            hipLaunchKernelGGL(dir_wy_gram_kernel, dim3(P.gram.count), dim3(NTHREADS), 0, st, dm, tab + P.gram.at);
+            hipLaunchKernelGGL(dir_wy_t_kernel, dim3(P.gram.count), dim3(WY), lds, st, dm, tab + P.gram.at);
+            hipLaunchKernelGGL(dir_wy_u_kernel, dim3(P.wyu.count), dim3(NTHREADS), 0, st, dm, tab + P.wyu.at);
+            for (int s = 0; s < P.wy_steps; ++s) {
+                hipLaunchKernelGGL(dir_wy_y_kernel, dim3(P.wyy.count), dim3(NTHREADS), 0, st, dm, tab + P.wyy.at, s);
+                hipLaunchKernelGGL(dir_wy_sum_kernel, dim3(P.wys.count), dim3(256), 0, st, dm, tab + P.wys.at, s);
+                hipLaunchKernelGGL(dir_wy_z_kernel, dim3(P.wyz.count), dim3(NTHREADS), 0, st, dm, tab + P.wyz.at, s);
+            }
+        }
+    }
+    {
+        KfacProfScope prof(ctx, KC_EIG_POST, 5.0 * cube, 0.0);
+        const dim3 lo(P.lower.count), fu(P.full.count), b(NTHREADS);
+        const unsigned *tl = tab + P.lower.at, *tf = tab + P.full.at;
+        for (int second = 0; second < 2; ++second) {
+            if (P.any_split) hipLaunchKernelGGL((dir_product_kernel<ORTH, true>), lo, b, 0, st, dm, tl, second);
+            if (P.any_plain) hipLaunchKernelGGL((dir_product_kernel<ORTH, false>), lo, b, 0, st, dm, tl, second);
+            if (!second) {
+                hipLaunchKernelGGL(dir_dev_kernel, dim3(NORM_WGS, batch), dim3(256), 0, st, dm);
+                hipLaunchKernelGGL(dir_dev_sum_kernel, dim3(batch), dim3(64), 0, st, dm);
+            }
+            if (P.any_split) hipLaunchKernelGGL((dir_product_kernel<STEP, true>), fu, b, 0, st, dm, tf, second);
+            if (P.any_plain) hipLaunchKernelGGL((dir_product_kernel<STEP, false>), fu, b, 0, st, dm, tf, second);
+        }
+        hipLaunchKernelGGL((dir_product_kernel<TIMES_F, false>), fu, b, 0, st, dm, tf, 0);
+    }
+    {
+        KfacProfScope prof(ctx, KC_EIG_MISC, 0.0, 16.0 * square);
+        hipLaunchKernelGGL(dir_rayleigh_kernel, dim3((P.nmax + 255) / 256, NPARTS, batch), dim3(256), 0, st, dm);
+        hipLaunchKernelGGL(dir_lambda_kernel, dim3((P.nmax + 255) / 256, batch), dim3(256), 0, st, dm);
+        hipLaunchKernelGGL(dir_rank_kernel, dim3((P.nmax + RANK_IPB - 1) / RANK_IPB, batch), dim3(256), 0, st, dm);
+        hipLaunchKernelGGL(dir_gather_kernel, per_mat4, dim3(256), 0, st, dm);
+    }
+    KFAC_HIP_CHECK(hipGetLastError());
+    KFAC_HIP_CHECK(hipMemcpyAsync(stat, d_stat, (size_t)batch * 4 * sizeof(double), hipMemcpyDeviceToHost, st));
+    KFAC_HIP_CHECK(hipStreamSynchronize(st));
+    return KFAC_OK;
+}

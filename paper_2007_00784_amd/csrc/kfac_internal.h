@@ -17,7 +17,8 @@ template <typename T> __device__ inline global_ptr<T> as_global(T *p) { return (
 // Kernel classes for the optional per-kernel timing (kfac_profile_begin / kfac_profile_end).
 enum KfacKernelClass {
     KC_UNFOLD = 0, KC_SYRK, KC_SYRK_REDUCE, KC_PRECOND_GEMM, KC_EIG_SMALL, KC_EIG_SOLVE, KC_EIG_APPLY,
-    KC_EIG_MISC, KC_EIG_POST, KC_EIG_COPY, KC_EIG_OUTER, KC_PRECOND_SCALE, KC_SYRK_B16, KC_PRECOND_GEMM_X3, KC_EIG_OUTER_ROWS, KC_INVERSE, KC_COUNT
+    KC_EIG_MISC, KC_EIG_POST, KC_EIG_COPY, KC_EIG_OUTER, KC_PRECOND_SCALE, KC_SYRK_B16, KC_PRECOND_GEMM_X3, KC_EIG_OUTER_ROWS, KC_INVERSE,
+    KC_EIG_REDUCE_MV, KC_EIG_REDUCE_VEC, KC_EIG_REDUCE_GEMM, KC_EIG_TRI, KC_EIG_BACK, KC_COUNT
 };
 struct KfacProfRec { int cls; hipEvent_t t0, t1; double flops, bytes; };
 
@@ -99,6 +100,7 @@ constexpr int KFAC_TILE = 128;       // GEMM / SYRK output tile edge
 constexpr int KFAC_EIG_SMALL = 128;  // factors up to this size are solved inside one workgroup's LDS
 constexpr int KFAC_EIG_B = 32;       // block size of the blocked Jacobi path (sub-problems are 2B x 2B)
 constexpr int KFAC_MAX_D = 8192;
+constexpr int KFAC_EIG_SPLIT_MIN = 2048;   // factors from here on use split-fp16 products where an option allows them
 // A factor updated alone splits its contraction into at most this many partial tiles (or one per tile, if it has
 // more tiles than that): what kfac_workspace_bytes() sizes the workspace of a single update for.
 constexpr int KFAC_SYRK_MAX_SINGLE_PARTIALS = 1536;
@@ -124,6 +126,9 @@ int kfac_launch_precondition_batched(kfac_ctx *ctx, int n, const kfac_precond_it
                                      float *nu);
 size_t kfac_precond_ws_bytes_impl(int n, const kfac_precond_item *items);
 size_t kfac_eig_ws_bytes_impl(int batch, const int *d);
+size_t kfac_eig_direct_ws_bytes(int batch, const int *d);
+int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
+                           bool fp32_only, double *stat /* pinned, 4 per factor */);
 size_t kfac_invert_ws_bytes_impl(int batch, const int *d);
 int kfac_launch_invert_factors(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float damping, float *const *Finv);
 size_t kfac_precondition_inverse_ws_bytes_impl(int n, const kfac_precond_inv_item *items);

@@ -331,6 +331,53 @@ def test_eig_non_finite_input(ctx, n):
     check_eigpairs(good, Ld[1].cpu().numpy(), Qd[1].cpu().numpy(), "beside NaN")
 
 
+# edges of the direct route: the register kernels' sizes (64, 128, 192, 256), the first and last sizes of a 128-wide tile,
+# panels of 32 columns, back-transformation blocks of 128 reflectors and contraction pieces of 512
+DIRECT_SIZES = [(3, 9), (63, 90), (64, 20), (127, 500), (191, 100), (192, 700), (193, 90), (255, 40), (256, 800), (258, 700),
+                (288, 100), (383, 900), (384, 60), (385, 500), (512, 1300), (513, 200), (545, 1500), (641, 90)]
+
+
+@pytest.mark.parametrize("n,rows", DIRECT_SIZES)
+def test_eig_direct_at_the_edges_of_its_kernels(ctx, n, rows):
+    F = gram_factor(n, rows, seed=n, ones=n % 2 == 0)
+    Ld, Qd, info = ctx.eig([F])
+    assert info[0][2] and info[0][0] == 1, info
+    check_eigpairs(F, Ld[0].cpu().numpy(), Qd[0].cpu().numpy(), "direct")
+
+
+def _special(kind, n):
+    rng = np.random.default_rng(n)
+    if kind == "ones":                   # rank one: n - 1 zeros
+        return np.ones((n, n))
+    if kind == "identity plus":          # n - 1 equal eigenvalues
+        return 3.0 * np.eye(n) + np.ones((n, n))
+    if kind == "mostly zero":            # decoupled rows
+        return np.diag((np.arange(n) < 3) * 1.0)
+    if kind == "equal blocks":           # every eigenvalue of a block n / 4 times
+        return np.kron(np.eye(n // 4), np.ones((4, 4)))
+    if kind == "repeated gram":          # generic spectrum, every eigenvalue four times
+        return np.kron(np.eye(4), gram_factor(n // 4, n, seed=n).astype(np.float64))
+    if kind == "pairs":                  # eigenvalues in pairs that agree to 1e-14, eigenvectors not local
+        m = n // 2 * 2 + 1
+        return np.diag(np.abs(np.arange(m) - m // 2).astype(np.float64)) + np.diag(np.ones(m - 1), 1) + np.diag(np.ones(m - 1), -1)
+    if kind == "tiny":                   # squares below the range of fp32
+        return gram_factor(n, 2 * n, seed=n).astype(np.float64) * 1e-30
+    d = 10.0 ** rng.uniform(-4, 0.5, n)  # graded: eigenvalues over nine decades
+    return gram_factor(n, 3 * n, seed=n, ones=False).astype(np.float64) * d[:, None] * d[None, :]
+
+
+@pytest.mark.parametrize("n", [100, 300])
+@pytest.mark.parametrize("kind", ["ones", "identity plus", "mostly zero", "equal blocks", "repeated gram", "pairs", "tiny", "graded"])
+def test_eig_direct_on_special_spectra(ctx, kind, n):
+    """Multiple, zero and nearly equal eigenvalues: the eigenvectors come out orthonormal without the Jacobi route's help
+    (which would report several sweeps), within the same bounds as any other factor."""
+    F = _special(kind, n).astype(np.float32)
+    Ld, Qd, info = ctx.eig([F])
+    assert info[0][2] and info[0][0] <= 1, info
+    scale = 1e30 if kind == "tiny" else 1.0
+    check_eigpairs((F.astype(np.float64) * scale).astype(np.float32), Ld[0].cpu().numpy().astype(np.float64) * scale, Qd[0].cpu().numpy(), kind)
+
+
 # ------------------------------------------------------------------ precondition
 # (230, 100) and (97, 200): edge tiles between 65 and 127 wide and tall (accumulator blocks masked under the full
 # wave map); the others: edge tiles at most 64 wide or tall (the waves share them in slices)
