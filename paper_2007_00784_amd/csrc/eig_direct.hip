@@ -41,8 +41,10 @@ constexpr int WY_K = 512;         // contraction of one workgroup in Y = V^T Z
 constexpr int NPARTS = 64;         // parts of the Rayleigh quotients' sums
 constexpr int NORM_WGS = 256;      // workgroups per factor of the norms and copies
 constexpr double PERTURB_REL = 0x1p-25;   // of every element of T: half the rounding it already carries
-constexpr double PERTURB_ABS = 1e-11;     // of the Gershgorin bound, added to the diagonal: breaks multiple zeros
+constexpr double PERTURB_ABS = 1e-10;     // of the Gershgorin bound, added to the diagonal: breaks multiple zeros
 constexpr double NS_AGAIN = 4e-6;         // ||I - Q^T Q||_F^2 from which one Newton-Schulz step is not enough (it leaves 3/4 of this)
+constexpr double BIS_REL = 0x1p-51, BIS_ABS = 1e-25;   // width at which an eigenvalue's interval is done, of its size and of the bound
+constexpr int BIS_WIDE_MAX = 160;         // up to this many groups of 64 eigenvalues, sixteen lanes each
 constexpr double E_MIN = 1e-20;     // of the same: no off-diagonal element of T is exactly zero
 constexpr double PIVOT_MIN = 1e-30;
 
@@ -84,6 +86,11 @@ __device__ inline float wave_sum_all(float v) {   // the sum over the wave, in e
     KFAC_DPP_ADD(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
 #undef KFAC_DPP_ADD
     return __int_as_float(__builtin_amdgcn_readlane(x, 63));
+}
+__device__ inline float quad_sum(float v) {       // the sum over four neighbouring lanes, in each of them
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));   // quad_perm 1,0,3,2
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));   // quad_perm 2,3,0,1
+    return v;
 }
 __device__ inline double wave_sum_f64(double v) {
 #pragma unroll
@@ -253,8 +260,7 @@ __global__ __launch_bounds__(16 * KC) void dir_td_small_kernel(const DirMat *mat
                 y = fmaf(a[k].z, vc.z, y);
                 y = fmaf(a[k].w, vc.w, y);
             }
-        y += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), 0xB1, 0xf, 0xf, true));   // quad_perm 1,0,3,2
-        y += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), 0x4E, 0xf, 0xf, true));   // quad_perm 2,3,0,1
+        y = quad_sum(y);
         const float vr = v[row];
         const float ty = row > j ? tau * y : 0.f;
         const float part = wave_sum_all(q == 0 ? vr * ty : 0.f);
@@ -315,9 +321,11 @@ __global__ __launch_bounds__(256) void dir_symv_kernel(const DirMat *mats, const
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c4 = tid & 31, rs = tid >> 5;
     const int ip = t & (NB - 1), b0 = j / TB, I = tr.I, J = tr.J;
     const bool diag = I == J;
+    // all loads first, without a loop or a wait between them: what a launch costs beside its bytes is memory latency
     // the column's norm: partial sums of the row blocks from the panel's first on
-    float s2 = 0.f;
-    for (int rb = 2 * b0 + lane; rb < M.np / RB; rb += 64) s2 += as_global(M.npart)[rb];
+    const int nrb = M.np / RB, rb = 2 * b0 + lane;
+    const float n0 = as_global(M.npart)[min(rb, nrb - 1)], n1 = as_global(M.npart)[min(rb + 64, nrb - 1)];
+    float s2 = (rb < nrb ? n0 : 0.f) + (rb + 64 < nrb ? n1 : 0.f);
     const float alpha = as_global(M.acol)[j + 1];
     const int vi = (tid < TB ? I * TB : J * TB - TB) + tid;
     const float xv = as_global(M.acol)[vi];
@@ -326,6 +334,15 @@ __global__ __launch_bounds__(256) void dir_symv_kernel(const DirMat *mats, const
         const global_ptr<const float> p = as_global((const float *)M.A) + (int64_t)(I * TB + rs) * M.ld + J * TB + 4 * c4;
 #pragma unroll
         for (int u = 0; u < 16; ++u) a[u] = *(global_ptr<const floatx4>)(p + (int64_t)(8 * u) * M.ld);
+    }
+    // diagonal tiles: four lanes per earlier column of the panel, V then W, for V^T v and W^T v
+    const int pc = tid >> 2, pq = 4 * (tid & 3);
+    const bool dot = diag && (pc & (NB - 1)) < ip;
+    floatx4 pr[TB / 16];
+    if (dot) {
+        const global_ptr<const float> p = as_global((const float *)M.panel) + (int64_t)pc * M.ld + I * TB + pq;
+#pragma unroll
+        for (int u = 0; u < TB / 16; ++u) pr[u] = *(global_ptr<const floatx4>)(p + 16 * u);
     }
     s2 = wave_sum_all(s2);
     float beta = alpha, tau = 0.f, scale = 0.f;
@@ -383,13 +400,16 @@ __global__ __launch_bounds__(256) void dir_symv_kernel(const DirMat *mats, const
             as_global(M.part)[(int64_t)I * M.np + J * TB + tid] = s;
         }
     } else {
-        const float v0 = vI[lane], v1 = vI[64 + lane];
-        for (int p = wave; p < 2 * NB; p += 4) {     // waves take the products in turn: V^T v, then W^T v
-            if ((p & (NB - 1)) >= ip) continue;
-            const global_ptr<const float> row = as_global((const float *)M.panel) + (int64_t)p * M.ld + I * TB;
-            const float s = wave_sum_all(fmaf(row[lane], v0, row[64 + lane] * v1));
-            if (lane == 0) M.dots[I * 2 * NB + p] = s;
+        float d = 0.f;
+        if (dot) {
+#pragma unroll
+            for (int u = 0; u < TB / 16; ++u) {
+                const floatx4 x = *(const floatx4 *)(vI + 16 * u + pq);
+                d = fmaf(pr[u].x, x.x, fmaf(pr[u].y, x.y, fmaf(pr[u].z, x.z, fmaf(pr[u].w, x.w, d))));
+            }
         }
+        d = quad_sum(d);
+        if (dot && pq == 0) as_global(M.dots)[I * 2 * NB + pc] = d;
     }
 }
 
@@ -407,23 +427,22 @@ __global__ __launch_bounds__(256) void dir_vector_kernel(const DirMat *mats, con
     const int ip = t & (NB - 1), b0 = j / TB, row = tr.J * RB + lane;
     const bool next = ip != NB - 1;
     const global_ptr<const float> panel = as_global((const float *)M.panel), part = as_global((const float *)M.part);
-    // loads first: they are all independent
-    float y = 0.f;
-    for (int k = b0 + g; k < M.nb; k += 4) y += part[(int64_t)k * M.np + row];
+    // loads first, without a loop or a wait between them: they are all independent (loops for what is beyond 32 row blocks)
+    const int ct = M.nb - b0, nt = ct * (ct + 1) / 2, last = M.nb - 1;
+    float yk[8], ck[8], tk[3];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) yk[u] = part[(int64_t)min(b0 + g + 4 * u, last) * M.np + row];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) ck[u] = as_global((const float *)M.dots)[min(b0 + g + 4 * u, last) * 2 * NB + lane];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) tk[u] = as_global((const float *)M.tsum)[min(tid + 256 * u, nt - 1)];
     float pv[NB / 4], pw[NB / 4];
 #pragma unroll
     for (int u = 0; u < NB / 4; ++u) {
         const int p = g + 4 * u;
-        pv[u] = p < ip ? panel[(int64_t)p * M.ld + row] : 0.f;
-        pw[u] = p < ip ? panel[(int64_t)(NB + p) * M.ld + row] : 0.f;
+        pv[u] = panel[(int64_t)p * M.ld + row];
+        pw[u] = panel[(int64_t)(NB + p) * M.ld + row];
     }
-    float c = 0.f;
-    if ((lane & (NB - 1)) < ip)
-        for (int k = b0 + g; k < M.nb; k += 4) c += as_global(M.dots)[k * 2 * NB + lane];
-    cw[g][lane] = c;
-    const int ct = M.nb - b0, nt = ct * (ct + 1) / 2;
-    float va = 0.f;
-    for (int i = tid; i < nt; i += 256) va += as_global(M.tsum)[i];
     const float scale = M.scal[0], tau = M.scal[1];
     float acur = 0.f;
     if (g == 0 && next && row > j) acur = as_global((const float *)M.A)[(int64_t)row * M.ld + j + 1];
@@ -435,6 +454,22 @@ __global__ __launch_bounds__(256) void dir_vector_kernel(const DirMat *mats, con
         yj = wave_sum_all(yj);
         if (lane == 0) yj_s = yj;
     }
+    float y = 0.f, c = 0.f, va = 0.f;
+#pragma unroll
+    for (int u = 0; u < NB / 4; ++u)
+        if (g + 4 * u >= ip) pv[u] = pw[u] = 0.f;       // not this panel's
+#pragma unroll
+    for (int u = 0; u < 8; ++u) y += g + 4 * u < ct ? yk[u] : 0.f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) c += g + 4 * u < ct ? ck[u] : 0.f;
+#pragma unroll
+    for (int u = 0; u < 3; ++u) va += tid + 256 * u < nt ? tk[u] : 0.f;
+    for (int k = b0 + g + 32; k < M.nb; k += 4) {
+        y += part[(int64_t)k * M.np + row];
+        c += as_global((const float *)M.dots)[k * 2 * NB + lane];
+    }
+    for (int i = tid + 768; i < nt; i += 256) va += as_global((const float *)M.tsum)[i];
+    cw[g][lane] = (lane & (NB - 1)) < ip ? c : 0.f;     // (the others' dots are an earlier panel's)
     va = wave_sum_all(va);
     if (lane == 0) sred[g] = va;
     __syncthreads();
@@ -556,18 +591,23 @@ __global__ __launch_bounds__(256) void dir_scale_t_kernel(const DirMat *mats) {
     }
 }
 
-// Eigenvalue k of T by bisection in fp64: four lanes per eigenvalue try the four points that cut its interval into five
-// (2.3 bits a pass).  A count is a Sturm sequence of the leading minors' signs, two dependent FMAs per row; the minors are
-// rescaled every eight rows.
+// Eigenvalue k of T by multisection in fp64: LPE lanes per eigenvalue try the points that cut its interval into LPE + 1 (2.3 bits
+// a pass with four lanes, 4.1 with sixteen).  A count is a Sturm sequence of the leading minors' signs, two dependent
+// FMAs per row; the minors are rescaled every eight rows.  The passes go on until the interval is at the last bits of the
+// eigenvalue itself, not of the largest one: the thousands of tiny eigenvalues of a graded rank-deficient factor have localised
+// eigenvectors and do not repel each other, so two of them can agree to 1e-17 of the largest, and where the passes
+// stopped there both got the same eigenvector.
 constexpr int BIS_CHUNK = 256;
+template <int LPE>
 __global__ __launch_bounds__(256) void dir_bisect_kernel(const DirMat *mats, const unsigned *tab) {
+    constexpr int PER_WG = 256 / LPE, PARTS = 64 / PER_WG;      // a table entry stands for 64 eigenvalues
     __shared__ double2 ch[BIS_CHUNK];
-    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const TabRef tr = tab_ref(tab[blockIdx.x / PARTS]);
     const DirMat M = mats[tr.m];
-    const int n = M.n, tid = threadIdx.x, q = tid & 3, k = tr.J * 64 + (tid >> 2);
+    const int n = M.n, tid = threadIdx.x, q = tid & (LPE - 1), k = tr.J * 64 + (int)(blockIdx.x % PARTS) * PER_WG + tid / LPE;
     double lo = -1.0 - 1e-6, hi = 1.0 + 1e-6;     // Gershgorin, with room for the perturbation
-    for (int pass = 0; pass < 25; ++pass) {
-        const double step = (hi - lo) * 0.2, x = lo + step * (q + 1);
+    for (int pass = 0; pass < 40; ++pass) {
+        const double step = (hi - lo) * (1.0 / (LPE + 1)), x = lo + step * (q + 1);
         double p = 1.0, pp = 0.0;     // minors i and i - 1
         double e2 = 0.0;
         int count = 0;
@@ -593,11 +633,13 @@ __global__ __launch_bounds__(256) void dir_bisect_kernel(const DirMat *mats, con
             }
         }
         int below = count <= k ? 1 : 0;     // the eigenvalue is not below this point
-        below += __shfl_xor(below, 1, 64);
-        below += __shfl_xor(below, 2, 64);
+#pragma unroll
+        for (int o = 1; o < LPE; o <<= 1) below += __shfl_xor(below, o, 64);
         const double l0 = lo;
         lo = below > 0 ? l0 + step * below : lo;
-        hi = below < 4 ? l0 + step * (below + 1) : hi;
+        hi = below < LPE ? l0 + step * (below + 1) : hi;
+        const bool open = k < n && hi - lo > BIS_REL * fmax(fabs(lo), fabs(hi)) + BIS_ABS;
+        if (!__syncthreads_or(open)) break;
     }
     if (q == 0 && k < n) M.lam64[k] = 0.5 * (lo + hi);
 }
@@ -1307,7 +1349,11 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
         KfacProfScope prof(ctx, KC_EIG_TRI, 0.0, 0.0);
         hipLaunchKernelGGL(dir_clear_kernel, per_mat4, dim3(256), 0, st, dm);
         hipLaunchKernelGGL(dir_scale_t_kernel, dim3(batch), dim3(256), 0, st, dm);
-        hipLaunchKernelGGL(dir_bisect_kernel, dim3(P.values.count), dim3(256), 0, st, dm, tab + P.values.at);
+        // sixteen lanes per eigenvalue do 9/4 of the work of four in 4/7 of the passes: right where four leave the chip idle
+        if (P.values.count <= BIS_WIDE_MAX)
+            hipLaunchKernelGGL(dir_bisect_kernel<16>, dim3(4 * P.values.count), dim3(256), 0, st, dm, tab + P.values.at);
+        else
+            hipLaunchKernelGGL(dir_bisect_kernel<4>, dim3(P.values.count), dim3(256), 0, st, dm, tab + P.values.at);
         hipLaunchKernelGGL(dir_vectors_kernel, dim3(P.values.count), dim3(64), 0, st, dm, tab + P.values.at);
     }
     {

@@ -378,6 +378,29 @@ def test_eig_direct_on_special_spectra(ctx, kind, n):
     check_eigpairs((F.astype(np.float64) * scale).astype(np.float32), Ld[0].cpu().numpy().astype(np.float64) * scale, Qd[0].cpu().numpy(), kind)
 
 
+@pytest.mark.parametrize("n,rows,seed", [(4609, 3136, 0), (4609, 3136, 1), (4609, 3136, 2), (4609, 3136, 3), (8192, 2000, 0)])
+def test_eig_direct_large_graded_and_rank_deficient(n, rows, seed):
+    """Features scaled over four decades, fewer rows than columns: thousands of eigenvalues around 1e-11 of the largest with
+    localised eigenvectors, some of which agree to more digits than fp64 has at the largest one.  The direct route has to tell
+    them apart (one sweep reported: Jacobi iteration was not needed).  8192: the largest size, past 32 row blocks."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    X = torch.randn((rows, n), generator=gen, device="cuda").relu_() * 10.0 ** (torch.rand(n, generator=gen, device="cuda") * 4.0 - 3.0)
+    X[:, -1] = 1.0
+    F = (X.double().T.contiguous() @ X.double() / rows).float()
+    F = ((F + F.T) * 0.5).contiguous()
+    c = Ctx(K.kfac_eig_workspace_bytes([n]) + 4096)
+    Q, lam = torch.empty_like(F), torch.empty(n, device="cuda")
+    info = K.kfac_eig(c.h, [F], [Q], [lam])
+    torch.cuda.synchronize()
+    c.close()
+    assert info[0][2] and info[0][0] == 1, info
+    assert bool((lam[1:] >= lam[:-1]).all())
+    Fd, Qd = F.double(), Q.double()
+    assert float((Fd @ Qd - Qd * lam.double()).norm() / Fd.norm()) <= TOL_RES
+    # n^2 inner products of unit vectors that are rounded to fp32: 2^-24 apiece
+    assert float((Qd.T.contiguous() @ Qd - torch.eye(n, device="cuda", dtype=torch.float64)).norm()) <= n * 2.0 ** -24
+
+
 # ------------------------------------------------------------------ precondition
 # (230, 100) and (97, 200): edge tiles between 65 and 127 wide and tall (accumulator blocks masked under the full
 # wave map); the others: edge tiles at most 64 wide or tall (the waves share them in slices)
