@@ -5,8 +5,8 @@
 //     (the reduction starts at the large end, so the small end of a graded factor is not swamped by the large end's
 //     rounding: on a factor graded over eight decades the small eigenvectors come out fifty times as accurate).  Factors up to 256 wide: one workgroup each, the
 //     matrix in registers.  Wider ones: the blocked right-looking reduction (panels of 32 columns; per column one
-//     symmetric matrix-vector product over the lower tiles and one vector step; per panel one rank-64 update on the fp32
-//     matrix instructions), all factors in one chain of launches, aligned so that all end together.
+//     symmetric matrix-vector product over the lower tiles and one vector step, in one launch where the tiles are few;
+//     per panel one rank-64 update on the fp32 matrix instructions), all factors in one chain of launches, aligned so that all end together.
 //  2. Eigenvalues of T by bisection and eigenvectors of T by twisted factorisation, both in fp64 and both
 //     independent per eigenvalue.  T carries fp32 rounding noise, so fp64 has nine digits to spare: the eigenvectors of
 //     eigenvalues that agree to many digits still come out orthogonal without any re-orthogonalisation, once exact
@@ -36,6 +36,10 @@ constexpr int NB = 32;            // columns of a panel
 constexpr int TB = 128;           // tile edge
 constexpr int RB = 64;            // rows per workgroup of the vector step
 constexpr int TD_SMALL = 256;     // factors up to this size are reduced by one workgroup, in registers
+// Tiles of a launch up to which the vector step and the next column's products share it.  Measured with everything unfused, fused
+// up to 300 tiles, and up to 800: one 4609-wide factor (703 tiles and fewer as it shrinks) 61.5, 58.6, 61.1 ms; ResNet-32's factors
+// (135 tiles at the most) 9.81, 9.12, 9.14 ms; beyond 800 tiles fusing costs as much again as it saves (ResNet-50: 155 and 177 ms).
+constexpr int FUSE_MAX = 300;
 constexpr int WY = 128;           // reflectors of a compact WY block
 constexpr int WY_K = 512;         // contraction of one workgroup in Y = V^T Z
 constexpr int NPARTS = 64;         // parts of the Rayleigh quotients' sums
@@ -55,12 +59,13 @@ struct DirMat {
     float *Z;        // [np][ld]: eigenvectors of T, then of A
     float *B1, *B2;  // [np][ld] each, adjacent: together the fp64 pivots of the eigenvectors; then scratch
     float *panel;    // [3 NB][ld]: V, W, V of the current panel
-    float *part;     // [nb][np]: partial products of the column's matrix-vector product
-    float *dots;     // [nb][2 NB]: partial V^T v, W^T v per row block
-    float *tsum;     // per tile: its share of v^T A v
-    float *acol;     // [np]: next column of the matrix, not yet scaled
-    float *npart;    // [np / RB]: its squared norm, per workgroup
-    float *scal;     // scale, tau of the current column
+    float *apan;     // [NB + 1][np]: the panel's columns, and the one after it, as they stood when the panel began
+    // what a column's launch leaves for the next, twice:
+    float *part;     // [2][nb][np]: partial products of the column's matrix-vector product
+    float *dots;     // [2][nb][2 NB]: partial V^T x, W^T x per row block
+    double *tsum;    // [2] per tile: its share of x^T A x
+    float *acol;     // [2][np]: the column x, not yet scaled
+    float *npart;    // [2][np / RB]: its squared norm, per workgroup
     float *tau;      // [np]
     double *d, *e;   // [np]: T as reduced
     double2 *td;     // [np]: T perturbed and divided by its Gershgorin bound: {d_i, e_i^2}; |e_i| is kept away from zero
@@ -92,10 +97,22 @@ __device__ inline float quad_sum(float v) {       // the sum over four neighbour
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));   // quad_perm 2,3,0,1
     return v;
 }
-__device__ inline double wave_sum_f64(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+template <int CTRL, int ROWS> __device__ inline double dpp_add_f64(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, true);
+    return v + __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ inline double wave_sum_f64(double v) {   // the same steps as wave_sum_all
+    v = dpp_add_f64<0x111, 0xf>(v);
+    v = dpp_add_f64<0x112, 0xf>(v);
+    v = dpp_add_f64<0x114, 0xf>(v);
+    v = dpp_add_f64<0x118, 0xf>(v);
+    v = dpp_add_f64<0x142, 0xa>(v);
+    v = dpp_add_f64<0x143, 0xc>(v);
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, 63), hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
 // ---- norms and the working copy ------------------------------------------------------------------------
@@ -294,82 +311,76 @@ __global__ __launch_bounds__(16 * KC) void dir_td_small_kernel(const DirMat *mat
 struct TabRef { int m, I, J; };
 __device__ inline TabRef tab_ref(unsigned w) { return TabRef{(int)(w >> 14), (int)((w >> 7) & 127u), (int)(w & 127u)}; }
 
-// Column j as it stands: acol, its norm, its diagonal element.
+// What one launch leaves for the next lies in buffers that alternate with t (no launch reads what it writes):
+// launch t multiplies column j of the reduced matrix, not yet scaled to a reflector, with the trailing matrix (x = acol, so the
+// norm of x need not be known), and the vector step turns the products into those of the reflector v = scale (x - beta e):
+//   A v = scale (A x - beta A e),  V^T v = scale (V^T x - beta V^T e),  v^T A v = scale^2 (x^T A x - 2 beta e^T A x + beta^2 e^T A e)
+// with e the unit vector of row j + 1; column j + 1 of the trailing matrix, A e, is in apan.
+struct StepBufs { global_ptr<float> part, dots, acol, npart; global_ptr<double> tsum; };
+__device__ inline StepBufs step_bufs(const DirMat &M, int t) {
+    const int h = t & 1;
+    return StepBufs{as_global(M.part) + (int64_t)h * M.nb * M.np, as_global(M.dots) + h * M.nb * 2 * NB, as_global(M.acol) + h * M.np,
+                    as_global(M.npart) + h * (M.np / RB), as_global(M.tsum) + h * (M.nb * (M.nb + 1) / 2)};
+}
+
+// The panel's columns (and the one after it) row by row, and its first column: acol, its norm, its diagonal element.
 __global__ __launch_bounds__(RB) void dir_column_kernel(const DirMat *mats, const unsigned *tab, int t) {
     const TabRef tr = tab_ref(tab[blockIdx.x]);
     const DirMat M = mats[tr.m];
     const int j = t - M.off, row = tr.J * RB + (int)threadIdx.x;
-    const float a = row >= j ? as_global(M.A)[(int64_t)row * M.ld + j] : 0.f;
+    const StepBufs B = step_bufs(M, t);
+    const global_ptr<const float> p = as_global((const float *)M.A) + (int64_t)row * M.ld + j;
+    const global_ptr<float> o = as_global(M.apan) + row;
+    floatx4 c[NB / 4];
+#pragma unroll
+    for (int u = 0; u < NB / 4; ++u) c[u] = *(global_ptr<const floatx4>)(p + 4 * u);
+    const float c32 = j + NB < M.np ? p[NB] : 0.f;
+#pragma unroll
+    for (int u = 0; u < NB; ++u) o[(int64_t)u * M.np] = c[u >> 2][u & 3];
+    o[(int64_t)NB * M.np] = c32;
+    const float a = row >= j ? c[0].x : 0.f;
     if (row == j) M.d[j] = (double)a;
-    as_global(M.acol)[row] = row > j ? a : 0.f;
+    B.acol[row] = row > j ? a : 0.f;
     const float s = wave_sum_all(row > j + 1 ? a * a : 0.f);
-    if (threadIdx.x == 0) M.npart[tr.J] = s;
+    if (threadIdx.x == 0) B.npart[tr.J] = s;
 }
 
-// y = A v over the lower tiles: tile (I, J) gives A_IJ v_J to the rows of block I and (I > J) A_IJ^T v_I to those of block
-// J; both land in part[], one slot per pair of blocks, and are added in the vector step.  Also v^T A v (per tile) and,
-// on the diagonal tiles, V^T v and W^T v of the panel's earlier columns.  Reads n'^2 / 2 elements once: bound by the
-// memory system (Infinity Cache) while the trailing matrix is large and by the launch below that.
-__global__ __launch_bounds__(256) void dir_symv_kernel(const DirMat *mats, const unsigned *tab, int t) {
-    __shared__ __attribute__((aligned(16))) float vI[TB], vJ[TB];
-    __shared__ float cred[8][TB];
-    __shared__ float tred[4];
-    const TabRef tr = tab_ref(tab[blockIdx.x]);
-    const DirMat M = mats[tr.m];
-    const int j = t - M.off;
-    if (j > M.n - 2) return;
+// y = A x over one lower tile: tile (I, J) gives A_IJ x_J to the rows of block I and (I > J) A_IJ^T x_I to those of block
+// J; both land in part[], one slot per pair of blocks.  Also x^T A x (per tile, fp64: the squares of a column of 1e-19 of
+// the matrix are below fp32's range) and, on the diagonal tiles, V^T x and W^T x of the panel's `ncols` earlier columns.
+struct SymvSmem {
+    __attribute__((aligned(16))) float xI[TB], xJ[TB];
+    float cred[8][TB];
+    double tred[4];
+};
+struct TileLoads { floatx4 a[16], pr[TB / 16]; };
+__device__ inline void tile_load(const DirMat &M, int I, int J, int ncols, TileLoads &L) {
+    const int tid = threadIdx.x, c4 = tid & 31, rs = tid >> 5, pc = tid >> 2, pq = 4 * (tid & 3);
+    const global_ptr<const float> p = as_global((const float *)M.A) + (int64_t)(I * TB + rs) * M.ld + J * TB + 4 * c4;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) L.a[u] = *(global_ptr<const floatx4>)(p + (int64_t)(8 * u) * M.ld);
+    // diagonal tiles: four lanes per earlier column of the panel, V then W
+    if (I == J && (pc & (NB - 1)) < ncols) {
+        const global_ptr<const float> q = as_global((const float *)M.panel) + (int64_t)pc * M.ld + I * TB + pq;
+#pragma unroll
+        for (int u = 0; u < TB / 16; ++u) L.pr[u] = *(global_ptr<const floatx4>)(q + 16 * u);
+    }
+}
+__device__ inline void tile_product(const DirMat &M, int I, int J, int b0, int ncols, const StepBufs &B, const TileLoads &L, SymvSmem &sm) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c4 = tid & 31, rs = tid >> 5;
-    const int ip = t & (NB - 1), b0 = j / TB, I = tr.I, J = tr.J;
     const bool diag = I == J;
-    // all loads first, without a loop or a wait between them: what a launch costs beside its bytes is memory latency
-    // the column's norm: partial sums of the row blocks from the panel's first on
-    const int nrb = M.np / RB, rb = 2 * b0 + lane;
-    const float n0 = as_global(M.npart)[min(rb, nrb - 1)], n1 = as_global(M.npart)[min(rb + 64, nrb - 1)];
-    float s2 = (rb < nrb ? n0 : 0.f) + (rb + 64 < nrb ? n1 : 0.f);
-    const float alpha = as_global(M.acol)[j + 1];
-    const int vi = (tid < TB ? I * TB : J * TB - TB) + tid;
-    const float xv = as_global(M.acol)[vi];
-    floatx4 a[16];
-    {
-        const global_ptr<const float> p = as_global((const float *)M.A) + (int64_t)(I * TB + rs) * M.ld + J * TB + 4 * c4;
-#pragma unroll
-        for (int u = 0; u < 16; ++u) a[u] = *(global_ptr<const floatx4>)(p + (int64_t)(8 * u) * M.ld);
-    }
-    // diagonal tiles: four lanes per earlier column of the panel, V then W, for V^T v and W^T v
-    const int pc = tid >> 2, pq = 4 * (tid & 3);
-    const bool dot = diag && (pc & (NB - 1)) < ip;
-    floatx4 pr[TB / 16];
-    if (dot) {
-        const global_ptr<const float> p = as_global((const float *)M.panel) + (int64_t)pc * M.ld + I * TB + pq;
-#pragma unroll
-        for (int u = 0; u < TB / 16; ++u) pr[u] = *(global_ptr<const floatx4>)(p + 16 * u);
-    }
-    s2 = wave_sum_all(s2);
-    float beta = alpha, tau = 0.f, scale = 0.f;
-    if (s2 > 0.f) {
-        beta = -copysignf(sqrtf(fmaf(alpha, alpha, s2)), alpha);
-        tau = (beta - alpha) / beta;
-        scale = 1.f / (alpha - beta);
-    }
-    (tid < TB ? vI : vJ - TB)[tid] = vi > j + 1 ? xv * scale : (vi == j + 1 ? 1.f : 0.f);
-    if (diag && I == (j + 1) / TB && tid == 0) {
-        M.scal[0] = scale;
-        M.scal[1] = tau;
-        M.tau[j] = tau;
-        M.e[j] = (double)beta;
-    }
-    __syncthreads();
-    const floatx4 vc = *(const floatx4 *)(vJ + 4 * c4);
+    const floatx4 vc = *(const floatx4 *)(sm.xJ + 4 * c4);
     float rsum[16];
     floatx4 cs = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
-        rsum[u] = fmaf(a[u].x, vc.x, fmaf(a[u].y, vc.y, fmaf(a[u].z, vc.z, a[u].w * vc.w)));
-        const float vr = vI[rs + 8 * u];
-        cs.x = fmaf(a[u].x, vr, cs.x);
-        cs.y = fmaf(a[u].y, vr, cs.y);
-        cs.z = fmaf(a[u].z, vr, cs.z);
-        cs.w = fmaf(a[u].w, vr, cs.w);
+        const floatx4 a = L.a[u];
+        rsum[u] = fmaf(a.x, vc.x, fmaf(a.y, vc.y, fmaf(a.z, vc.z, a.w * vc.w)));
+        const float vr = sm.xI[rs + 8 * u];
+        cs.x = fmaf(a.x, vr, cs.x);
+        cs.y = fmaf(a.y, vr, cs.y);
+        cs.z = fmaf(a.z, vr, cs.z);
+        cs.w = fmaf(a.w, vr, cs.w);
     }
     // sixteen sums over the 32 lanes of a half wave: halve the values with every exchange
 #pragma unroll
@@ -383,136 +394,262 @@ __global__ __launch_bounds__(256) void dir_symv_kernel(const DirMat *mats, const
     }
     const float ysum = rsum[0] + __shfl_xor(rsum[0], 1, 64);
     const int r = rs + 8 * (c4 >> 1);      // c4 bits 4..1 = which of the sixteen rows this lane ended up with
-    const float va = wave_sum_all((c4 & 1) ? 0.f : vI[r] * ysum);
-    if (!(c4 & 1)) as_global(M.part)[(int64_t)J * M.np + I * TB + r] = ysum;
-    if (!diag) *(floatx4 *)(cred[rs] + 4 * c4) = cs;
-    if (lane == 0) tred[wave] = va;
+    const double va = wave_sum_f64((c4 & 1) ? 0.0 : (double)sm.xI[r] * (double)ysum);
+    if (!(c4 & 1)) B.part[(int64_t)J * M.np + I * TB + r] = ysum;
+    if (!diag) *(floatx4 *)(sm.cred[rs] + 4 * c4) = cs;
+    if (lane == 0) sm.tred[wave] = va;
     __syncthreads();
     if (tid == 0) {
         const int ri = I - b0;
-        M.tsum[ri * (ri + 1) / 2 + J - b0] = (diag ? 1.f : 2.f) * (tred[0] + tred[1] + tred[2] + tred[3]);
+        B.tsum[ri * (ri + 1) / 2 + J - b0] = (diag ? 1.0 : 2.0) * (sm.tred[0] + sm.tred[1] + sm.tred[2] + sm.tred[3]);
     }
     if (!diag) {
         if (tid < TB) {
             float s = 0.f;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) s += cred[k][tid];
-            as_global(M.part)[(int64_t)I * M.np + J * TB + tid] = s;
+            for (int k = 0; k < 8; ++k) s += sm.cred[k][tid];
+            B.part[(int64_t)I * M.np + J * TB + tid] = s;
         }
     } else {
+        const int pc = tid >> 2, pq = 4 * (tid & 3);
+        const bool dot = (pc & (NB - 1)) < ncols;
         float d = 0.f;
         if (dot) {
 #pragma unroll
             for (int u = 0; u < TB / 16; ++u) {
-                const floatx4 x = *(const floatx4 *)(vI + 16 * u + pq);
-                d = fmaf(pr[u].x, x.x, fmaf(pr[u].y, x.y, fmaf(pr[u].z, x.z, fmaf(pr[u].w, x.w, d))));
+                const floatx4 x = *(const floatx4 *)(sm.xI + 16 * u + pq);
+                d = fmaf(L.pr[u].x, x.x, fmaf(L.pr[u].y, x.y, fmaf(L.pr[u].z, x.z, fmaf(L.pr[u].w, x.w, d))));
             }
         }
         d = quad_sum(d);
-        if (dot && pq == 0) as_global(M.dots)[I * 2 * NB + pc] = d;
+        if (dot && pq == 0) B.dots[I * 2 * NB + pc] = d;
     }
 }
 
-// Vector step of column j: w, the panel's new columns, reflector j, and (unless the panel ends here) column j + 1 with the
-// panel's updates applied.
-__global__ __launch_bounds__(256) void dir_vector_kernel(const DirMat *mats, const unsigned *tab, int t) {
-    __shared__ float cw[4][2 * NB], cf[2 * NB], rowj[2 * NB];   // V^T v, W^T v; the panel's row j + 1
-    __shared__ float ys[4][RB], as_[4][RB];
-    __shared__ float sred[4], yj_s, dvw_s;
+// Products of column j.  Reads n'^2 / 2 elements once: 5 TB/s where many large factors share a launch, memory latency (6 us)
+// where few do; all loads are issued before anything is waited for.
+__global__ __launch_bounds__(256) void dir_symv_kernel(const DirMat *mats, const unsigned *tab, int t) {
+    __shared__ SymvSmem sm;
     const TabRef tr = tab_ref(tab[blockIdx.x]);
     const DirMat M = mats[tr.m];
     const int j = t - M.off;
     if (j > M.n - 2) return;
+    const int tid = threadIdx.x, ip = t & (NB - 1);
+    const StepBufs B = step_bufs(M, t);
+    const float x = B.acol[(tid < TB ? tr.I * TB : tr.J * TB - TB) + tid];
+    TileLoads L;
+    tile_load(M, tr.I, tr.J, ip, L);
+    (tid < TB ? sm.xI : sm.xJ - TB)[tid] = x;
+    __syncthreads();
+    tile_product(M, tr.I, tr.J, j / TB, ip, B, L, sm);
+}
+
+// The vector step's sums over row blocks and what follows from them, for one wave: column j's products are in P.  Every wave
+// of a workgroup forms the scalars for itself; partial sums over four waves go through LDS.
+struct VecSmem { float cw[4][2 * NB]; double tred[4]; };
+struct VecLoads {
+    float n0, n1, alpha, rowj, yj, ajj, ck[8];
+    double tk[3];
+};
+struct VecScalars { float scale, beta, tau, cf, ah, wj; };
+__device__ inline void vec_load(const DirMat &M, const StepBufs &P, int j, int ip, int b0, VecLoads &L) {
     const int tid = threadIdx.x, lane = tid & 63, g = tid >> 6;
-    const int ip = t & (NB - 1), b0 = j / TB, row = tr.J * RB + lane;
-    const bool next = ip != NB - 1;
-    const global_ptr<const float> panel = as_global((const float *)M.panel), part = as_global((const float *)M.part);
-    // loads first, without a loop or a wait between them: they are all independent (loops for what is beyond 32 row blocks)
-    const int ct = M.nb - b0, nt = ct * (ct + 1) / 2, last = M.nb - 1;
-    float yk[8], ck[8], tk[3];
+    const int ct = M.nb - b0, nt = ct * (ct + 1) / 2, last = M.nb - 1, nrb = M.np / RB, rb = 2 * b0 + lane;
+    L.n0 = P.npart[min(rb, nrb - 1)];
+    L.n1 = P.npart[min(rb + 64, nrb - 1)];
+    L.alpha = P.acol[j + 1];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) yk[u] = part[(int64_t)min(b0 + g + 4 * u, last) * M.np + row];
+    for (int u = 0; u < 8; ++u) L.ck[u] = P.dots[min(b0 + g + 4 * u, last) * 2 * NB + lane];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) ck[u] = as_global((const float *)M.dots)[min(b0 + g + 4 * u, last) * 2 * NB + lane];
+    for (int u = 0; u < 3; ++u) L.tk[u] = P.tsum[min(tid + 256 * u, nt - 1)];
+    L.rowj = as_global((const float *)M.panel)[(int64_t)lane * M.ld + j + 1];
+    L.yj = P.part[(int64_t)min(b0 + lane, last) * M.np + j + 1];
+    L.ajj = as_global((const float *)M.apan)[(int64_t)(ip + 1) * M.np + j + 1];
+}
+__device__ inline void vec_partial(const DirMat &M, const StepBufs &P, int ip, int b0, const VecLoads &L, VecSmem &sm) {
+    const int tid = threadIdx.x, lane = tid & 63, g = tid >> 6;
+    const int ct = M.nb - b0, nt = ct * (ct + 1) / 2;
+    float c = 0.f;
+    double xax = 0.0;
 #pragma unroll
-    for (int u = 0; u < 3; ++u) tk[u] = as_global((const float *)M.tsum)[min(tid + 256 * u, nt - 1)];
-    float pv[NB / 4], pw[NB / 4];
+    for (int u = 0; u < 8; ++u) c += g + 4 * u < ct ? L.ck[u] : 0.f;
 #pragma unroll
-    for (int u = 0; u < NB / 4; ++u) {
-        const int p = g + 4 * u;
-        pv[u] = panel[(int64_t)p * M.ld + row];
-        pw[u] = panel[(int64_t)(NB + p) * M.ld + row];
+    for (int u = 0; u < 3; ++u) xax += tid + 256 * u < nt ? L.tk[u] : 0.0;
+    for (int k = b0 + g + 32; k < M.nb; k += 4) c += P.dots[k * 2 * NB + lane];
+    for (int i = tid + 768; i < nt; i += 256) xax += P.tsum[i];
+    sm.cw[g][lane] = (lane & (NB - 1)) < ip ? c : 0.f;     // (the others' dots are an earlier panel's)
+    xax = wave_sum_f64(xax);
+    if (lane == 0) sm.tred[g] = xax;
+}
+// after the barrier behind vec_partial(); rowj: V and W of row j + 1, zero beyond the panel's columns
+__device__ inline VecScalars vec_scalars(const DirMat &M, int ip, int b0, const VecLoads &L, float rowj, const VecSmem &sm) {
+    const int lane = threadIdx.x & 63, nrb = M.np / RB, rb = 2 * b0 + lane;
+    VecScalars S;
+    const float s2 = wave_sum_all((rb < nrb ? L.n0 : 0.f) + (rb + 64 < nrb ? L.n1 : 0.f));
+    const float alpha = L.alpha;
+    S.beta = alpha;
+    S.tau = S.scale = 0.f;
+    if (s2 > 0.f) {
+        S.beta = -copysignf(sqrtf(fmaf(alpha, alpha, s2)), alpha);
+        S.tau = (S.beta - alpha) / S.beta;
+        S.scale = 1.f / (alpha - S.beta);
     }
-    const float scale = M.scal[0], tau = M.scal[1];
-    float acur = 0.f;
-    if (g == 0 && next && row > j) acur = as_global((const float *)M.A)[(int64_t)row * M.ld + j + 1];
-    const float xv = as_global(M.acol)[row];
-    if (g == 1) rowj[lane] = (lane & (NB - 1)) < ip ? panel[(int64_t)lane * M.ld + j + 1] : 0.f;
-    if (g == 2) {
-        float yj = 0.f;
-        if (b0 + lane < M.nb) yj = part[(int64_t)(b0 + lane) * M.np + j + 1];
-        yj = wave_sum_all(yj);
-        if (lane == 0) yj_s = yj;
-    }
-    float y = 0.f, c = 0.f, va = 0.f;
-#pragma unroll
-    for (int u = 0; u < NB / 4; ++u)
-        if (g + 4 * u >= ip) pv[u] = pw[u] = 0.f;       // not this panel's
-#pragma unroll
-    for (int u = 0; u < 8; ++u) y += g + 4 * u < ct ? yk[u] : 0.f;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) c += g + 4 * u < ct ? ck[u] : 0.f;
-#pragma unroll
-    for (int u = 0; u < 3; ++u) va += tid + 256 * u < nt ? tk[u] : 0.f;
-    for (int k = b0 + g + 32; k < M.nb; k += 4) {
-        y += part[(int64_t)k * M.np + row];
-        c += as_global((const float *)M.dots)[k * 2 * NB + lane];
-    }
-    for (int i = tid + 768; i < nt; i += 256) va += as_global((const float *)M.tsum)[i];
-    cw[g][lane] = (lane & (NB - 1)) < ip ? c : 0.f;     // (the others' dots are an earlier panel's)
-    va = wave_sum_all(va);
-    if (lane == 0) sred[g] = va;
-    __syncthreads();
-    if (g == 0) {
-        const float s = cw[0][lane] + cw[1][lane] + cw[2][lane] + cw[3][lane];
-        cf[lane] = s;
-        const float o = __shfl_xor(s, 32, 64);
-        const float dvw = wave_sum_all(lane < 32 ? s * o : 0.f);   // (V^T v) . (W^T v)
-        if (lane == 0) dvw_s = dvw;
-    }
-    __syncthreads();
-    float ac = 0.f;
-#pragma unroll
-    for (int u = 0; u < NB / 4; ++u) {
-        const int p = g + 4 * u;
-        y = fmaf(-pv[u], cf[NB + p], fmaf(-pw[u], cf[p], y));
-        ac = fmaf(pv[u], rowj[NB + p], fmaf(pw[u], rowj[p], ac));
-    }
-    ys[g][lane] = y;
-    as_[g][lane] = ac;
-    __syncthreads();
-    if (g != 0) return;
-    y = ys[0][lane] + ys[1][lane] + ys[2][lane] + ys[3][lane];
-    ac = as_[0][lane] + as_[1][lane] + as_[2][lane] + as_[3][lane];
+    const float yj = wave_sum_all(b0 + lane < M.nb ? L.yj : 0.f);
+    const double xax = sm.tred[0] + sm.tred[1] + sm.tred[2] + sm.tred[3];
+    S.cf = S.scale * fmaf(-S.beta, rowj, sm.cw[0][lane] + sm.cw[1][lane] + sm.cw[2][lane] + sm.cw[3][lane]);   // V^T v, W^T v
+    const float o = __shfl_xor(S.cf, 32, 64);
+    const float dvw = wave_sum_all(lane < 32 ? S.cf * o : 0.f);                       // (V^T v) . (W^T v)
+    const float rc = wave_sum_all(rowj * o);                                         // row j + 1 of V (W^T v) + W (V^T v)
+    const double b = S.beta, sc = S.scale;
+    const float vav = (float)(sc * (sc * (xax - 2.0 * b * yj + b * b * L.ajj)));
     // alpha_h of w = tau y + alpha_h v, and row j + 1 of w (where v is 1)
-    const float vy = sred[0] + sred[1] + sred[2] + sred[3] - 2.f * dvw_s;
-    const float ah = -0.5f * tau * tau * vy;
-    float yj = (lane & 31) == lane ? fmaf(-rowj[lane], cf[NB + lane], -rowj[NB + lane] * cf[lane]) : 0.f;
-    yj = yj_s + wave_sum_all(yj);
-    const float wj = fmaf(tau, yj, ah);
-    const float v = row > j + 1 ? xv * scale : (row == j + 1 ? 1.f : 0.f);
-    const float w = row > j ? fmaf(tau, y, ah * v) : 0.f;
+    S.ah = -0.5f * S.tau * S.tau * (vav - 2.f * dvw);
+    S.wj = fmaf(S.tau, fmaf(S.scale, fmaf(-S.beta, L.ajj, yj), -rc), S.ah);
+    return S;
+}
+// element `row` of the reflector and of w, stored where the panel's update and the back-transformation read them
+__device__ inline void vec_store(const DirMat &M, int j, int ip, int row, float v, float w, const VecScalars &S) {
     const global_ptr<float> pan = as_global(M.panel);
     pan[(int64_t)ip * M.ld + row] = v;
     pan[(int64_t)(NB + ip) * M.ld + row] = w;
     pan[(int64_t)(2 * NB + ip) * M.ld + row] = v;
     as_global(M.A)[(int64_t)j * M.ld + row] = v;
+    if (row == j + 1) {
+        M.tau[j] = S.tau;
+        M.e[j] = (double)S.beta;
+    }
+}
+__device__ inline float lane_value(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+
+// Vector step of column j: w, the panel's new columns, reflector j, and (unless the panel ends here) column j + 1 with the
+// panel's updates applied.
+__global__ __launch_bounds__(256) void dir_vector_kernel(const DirMat *mats, const unsigned *tab, int t) {
+    __shared__ VecSmem vs;
+    __shared__ float ys[4][RB], as_[4][RB];
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    const int j = t - M.off;
+    if (j > M.n - 2) return;
+    const int tid = threadIdx.x, lane = tid & 63, g = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ip = t & (NB - 1), b0 = j / TB, row = tr.J * RB + lane, ct = M.nb - b0, last = M.nb - 1;
+    const bool next = ip != NB - 1;
+    const StepBufs P = step_bufs(M, t), B = step_bufs(M, t + 1);
+    const global_ptr<const float> panel = as_global((const float *)M.panel);
+    VecLoads L;
+    vec_load(M, P, j, ip, b0, L);
+    float yk[8], pv[NB / 4], pw[NB / 4];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) yk[u] = P.part[(int64_t)min(b0 + g + 4 * u, last) * M.np + row];
+#pragma unroll
+    for (int u = 0; u < NB / 4; ++u) {
+        pv[u] = panel[(int64_t)(g + 4 * u) * M.ld + row];
+        pw[u] = panel[(int64_t)(NB + g + 4 * u) * M.ld + row];
+    }
+    const float acur = as_global((const float *)M.apan)[(int64_t)(ip + 1) * M.np + row], xv = P.acol[row];
+    float y = 0.f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) y += g + 4 * u < ct ? yk[u] : 0.f;
+    for (int k = b0 + g + 32; k < M.nb; k += 4) y += P.part[(int64_t)k * M.np + row];
+    vec_partial(M, P, ip, b0, L, vs);
+    __syncthreads();
+    const float rowj = (lane & (NB - 1)) < ip ? L.rowj : 0.f;
+    const VecScalars S = vec_scalars(M, ip, b0, L, rowj, vs);
+    float yc = 0.f, ac = 0.f;
+#pragma unroll
+    for (int u = 0; u < NB / 4; ++u) {
+        const int p = g + 4 * u;
+        if (p >= ip) pv[u] = pw[u] = 0.f;       // not this panel's
+        yc = fmaf(pv[u], lane_value(S.cf, NB + p), fmaf(pw[u], lane_value(S.cf, p), yc));
+        ac = fmaf(pv[u], lane_value(rowj, NB + p), fmaf(pw[u], lane_value(rowj, p), ac));
+    }
+    ys[g][lane] = fmaf(S.scale, y, -yc);
+    as_[g][lane] = ac;
+    __syncthreads();
+    if (g != 0) return;
+    y = ys[0][lane] + ys[1][lane] + ys[2][lane] + ys[3][lane] - S.scale * S.beta * acur;
+    ac = as_[0][lane] + as_[1][lane] + as_[2][lane] + as_[3][lane];
+    const float v = row > j + 1 ? xv * S.scale : (row == j + 1 ? 1.f : 0.f);
+    const float w = row > j ? fmaf(S.tau, y, S.ah * v) : 0.f;
+    vec_store(M, j, ip, row, v, w, S);
     if (!next) return;
-    const float a = row > j ? acur - ac - fmaf(v, wj, w) : 0.f;
+    const float a = row > j ? acur - ac - fmaf(v, S.wj, w) : 0.f;
     if (row == j + 1) M.d[j + 1] = (double)a;
-    as_global(M.acol)[row] = row > j + 1 ? a : 0.f;
+    B.acol[row] = row > j + 1 ? a : 0.f;
     const float s = wave_sum_all(row > j + 2 ? a * a : 0.f);
-    if (lane == 0) M.npart[tr.J] = s;
+    if (lane == 0) B.npart[tr.J] = s;
+}
+
+// Both in one launch: the vector step of column j - 1, by every tile's workgroup for the rows of its own two blocks, then the
+// products of column j.  A tile reads up to 100 KB of panel and partial sums from L2 beside its own 64 KB: worth the launch
+// it saves (4 us) while the tiles of a launch are few (FUSE_MAX).
+__global__ __launch_bounds__(256, 2) void dir_fused_kernel(const DirMat *mats, const unsigned *tab, int t) {
+    __shared__ SymvSmem sm;
+    __shared__ VecSmem vs;
+    __shared__ __attribute__((aligned(16))) float ys[4][2 * TB], as_[4][2 * TB];
+    __shared__ float nd[2][2];
+    const TabRef tr = tab_ref(tab[blockIdx.x]);
+    const DirMat M = mats[tr.m];
+    const int j = t - M.off;            // the new column; j >= 1: a panel's first column is not fused
+    if (j > M.n - 1) return;
+    const int tid = threadIdx.x, lane = tid & 63, g = __builtin_amdgcn_readfirstlane(tid >> 6), I = tr.I, J = tr.J;
+    const int ip = (t & (NB - 1)) - 1, b0 = j / TB, ct = M.nb - b0, last = M.nb - 1;     // ip: column j - 1 in the panel
+    const bool diag = I == J, more = j < M.n - 1;
+    const StepBufs P = step_bufs(M, t - 1), B = step_bufs(M, t);
+    const global_ptr<const float> panel = as_global((const float *)M.panel);
+    const int row4 = (lane < 32 ? I : J) * TB + 4 * (lane & 31), row = (tid < TB ? I * TB : J * TB - TB) + tid;
+    VecLoads L;
+    vec_load(M, P, j - 1, ip, b0, L);
+    floatx4 yk[8], pv[NB / 4], pw[NB / 4];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) yk[u] = *(global_ptr<const floatx4>)(P.part + (int64_t)min(b0 + g + 4 * u, last) * M.np + row4);
+#pragma unroll
+    for (int u = 0; u < NB / 4; ++u) {
+        pv[u] = *(global_ptr<const floatx4>)(panel + (int64_t)(g + 4 * u) * M.ld + row4);
+        pw[u] = *(global_ptr<const floatx4>)(panel + (int64_t)(NB + g + 4 * u) * M.ld + row4);
+    }
+    const float acur = as_global((const float *)M.apan)[(int64_t)(ip + 1) * M.np + row], xv = P.acol[row];
+    TileLoads T;
+    tile_load(M, I, J, ip, T);
+    floatx4 y = {0.f, 0.f, 0.f, 0.f}, ac = y, yc = y;
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+        if (g + 4 * u < ct) y += yk[u];
+    for (int k = b0 + g + 32; k < M.nb; k += 4) y += *(global_ptr<const floatx4>)(P.part + (int64_t)k * M.np + row4);
+    vec_partial(M, P, ip, b0, L, vs);
+    __syncthreads();
+    const float rowj = (lane & (NB - 1)) < ip ? L.rowj : 0.f;
+    const VecScalars S = vec_scalars(M, ip, b0, L, rowj, vs);
+#pragma unroll
+    for (int u = 0; u < NB / 4; ++u) {
+        const int p = g + 4 * u;
+        if (p < ip) {
+            yc += pv[u] * lane_value(S.cf, NB + p) + pw[u] * lane_value(S.cf, p);
+            ac += pv[u] * lane_value(rowj, NB + p) + pw[u] * lane_value(rowj, p);
+        }
+    }
+    *(floatx4 *)(ys[g] + 4 * lane) = y * S.scale - yc;
+    *(floatx4 *)(as_[g] + 4 * lane) = ac;
+    __syncthreads();
+    const float yr = ys[0][tid] + ys[1][tid] + ys[2][tid] + ys[3][tid] - S.scale * S.beta * acur;
+    const float ar = as_[0][tid] + as_[1][tid] + as_[2][tid] + as_[3][tid];
+    const float v = row > j ? xv * S.scale : (row == j ? 1.f : 0.f);
+    const float w = row >= j ? fmaf(S.tau, yr, S.ah * v) : 0.f;
+    const float a = row >= j ? acur - ar - fmaf(v, S.wj, w) : 0.f;
+    const float x = row > j ? a : 0.f;
+    if (diag && tid < TB) {
+        vec_store(M, j - 1, ip, row, v, w, S);
+        if (row == j) M.d[j] = (double)a;
+        B.acol[row] = x;
+        const float s = wave_sum_all(row > j + 1 ? x * x : 0.f);
+        if (lane == 0) B.npart[2 * I + g] = s;
+        const float dv = wave_sum_all(v * x), dw = wave_sum_all(w * x);
+        if (lane == 0) { nd[g][0] = dv; nd[g][1] = dw; }
+    }
+    if (!more) return;
+    (tid < TB ? sm.xI : sm.xJ - TB)[tid] = x;
+    __syncthreads();
+    if (diag && tid < 2) B.dots[I * 2 * NB + NB * tid + ip] = nd[0][tid] + nd[1][tid];
+    tile_product(M, I, J, b0, ip, B, T, sm);
 }
 
 // C -= acc for the rows of the tile from `first` on, sixteen elements at a time (one accumulator's loads in flight, not 64)
@@ -850,23 +987,32 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     for_each_acc(acc, [&](int r, int c, float v) { as_global(G)[r * WY + c] = v; });
 }
 
-__global__ __launch_bounds__(WY) void dir_wy_t_kernel(const DirMat *mats, const unsigned *tab) {
+// T column by column: T(r, i) = -tau_i sum_p T(r, p) G(p, i).  WT lanes share a row's sum: the chain of columns is serial, and
+// with one lane per row its LDS latencies made 1.2 ms of the ResNet-50 step (410 us for a single block).
+constexpr int WT = 8;
+__global__ __launch_bounds__(WY * WT) void dir_wy_t_kernel(const DirMat *mats, const unsigned *tab) {
     extern __shared__ float lds[];
+    __shared__ float taus[WY];
     const TabRef tr = tab_ref(tab[blockIdx.x]);
     const DirMat M = mats[tr.m];
     float *T = lds, *G = lds + WY * (WY + 1);
-    const int r = threadIdx.x;
+    if (threadIdx.x < WY) taus[threadIdx.x] = M.tau[tr.J * WY + threadIdx.x];
+    const int r = threadIdx.x / WT, l = threadIdx.x & (WT - 1), c0 = threadIdx.x & (WY - 1), r0 = threadIdx.x / WY;
     const global_ptr<float> g = as_global(M.Tm + (int64_t)tr.J * WY * WY);
-    for (int i = 0; i < WY; ++i) { G[i * (WY + 1) + r] = g[i * WY + r]; T[i * (WY + 1) + r] = 0.f; }
+    for (int i = r0; i < WY; i += WT) { G[i * (WY + 1) + c0] = g[i * WY + c0]; T[i * (WY + 1) + c0] = 0.f; }
     __syncthreads();
     for (int i = 0; i < WY; ++i) {
-        const float ti = M.tau[tr.J * WY + i];
+        const float ti = taus[i];
         double s = 0.0;
-        for (int p = r; p < i; ++p) s = fma((double)T[r * (WY + 1) + p], (double)G[p * (WY + 1) + i], s);
-        if (r <= i) T[r * (WY + 1) + i] = r == i ? ti : (float)(-ti * s);
+        if (r < i)
+#pragma unroll 4
+            for (int p = r + l; p < i; p += WT) s = fma((double)T[r * (WY + 1) + p], (double)G[p * (WY + 1) + i], s);
+#pragma unroll
+        for (int o = 1; o < WT; o <<= 1) s += __shfl_xor(s, o, 64);
+        if (l == 0 && r <= i) T[r * (WY + 1) + i] = r == i ? ti : (float)(-ti * s);
         __syncthreads();
     }
-    for (int i = 0; i < WY; ++i) g[i * WY + r] = T[i * (WY + 1) + r];
+    for (int i = r0; i < WY; i += WT) g[i * WY + c0] = T[i * (WY + 1) + c0];
 }
 
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(3))) void dir_wy_u_kernel(const DirMat *mats, const unsigned *tab) {
@@ -1142,12 +1288,12 @@ size_t dir_layout(const DirSize &s, char *p, DirMat *M) {
     d.B2 = d.B1 + (size_t)s.np * s.ld;
     if (s.n > TD_SMALL) {
         d.panel = (float *)take((size_t)3 * NB * s.ld * sizeof(float));
-        d.part = (float *)take((size_t)s.nb * s.np * sizeof(float));
-        d.dots = (float *)take((size_t)s.nb * 2 * NB * sizeof(float));
-        d.tsum = (float *)take((size_t)s.nb * (s.nb + 1) / 2 * sizeof(float));
-        d.acol = (float *)take((size_t)s.np * sizeof(float));
-        d.npart = (float *)take((size_t)(s.np / RB) * sizeof(float));
-        d.scal = (float *)take(16);
+        d.apan = (float *)take((size_t)(NB + 1) * s.np * sizeof(float));
+        d.part = (float *)take((size_t)2 * s.nb * s.np * sizeof(float));
+        d.dots = (float *)take((size_t)2 * s.nb * 2 * NB * sizeof(float));
+        d.tsum = (double *)take((size_t)s.nb * (s.nb + 1) * sizeof(double));
+        d.acol = (float *)take((size_t)2 * s.np * sizeof(float));
+        d.npart = (float *)take((size_t)2 * (s.np / RB) * sizeof(float));
     }
     d.tau = (float *)take((size_t)s.np * sizeof(float));
     d.d = (double *)take((size_t)s.np * sizeof(double));
@@ -1269,85 +1415,77 @@ size_t dir_table_bound(int batch, const int *d) {
     return t;
 }
 
-}  // namespace
-
-size_t kfac_eig_direct_ws_bytes(int batch, const int *d) {
-    size_t need = kfac_align_up((size_t)batch * sizeof(DirMat), 256) + kfac_align_up((size_t)batch * 4 * sizeof(double), 256) +
-                  kfac_align_up(dir_table_bound(batch, d) * sizeof(unsigned), 256);
-    for (int i = 0; i < batch; ++i) need += dir_layout(dir_size(d[i]), nullptr, nullptr);
-    return need;
-}
-
-// All factors of the call by the direct route; stat (pinned host memory): four doubles per factor, off^2 and diag^2 of F, the
-// squared residual ||F Q - Q diag(lam)||_F^2 and ||I - Q^T Q||_F^2 before it was orthogonalised.  Waits for the result.
-int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
-                           bool fp32_only, double *stat) {
-    if (kfac_eig_direct_ws_bytes(batch, d) > ctx->ws_bytes) return KFAC_EWORKSPACE;
+// One group of factors on its stream.
+struct DirRun {
     DirPlan P;
-    P.mats.resize(batch);
-    DirMat *d_mats = (DirMat *)ctx->ws;
-    double *d_stat = (double *)(ctx->ws + kfac_align_up((size_t)batch * sizeof(DirMat), 256));
-    unsigned *d_tab = (unsigned *)((char *)d_stat + kfac_align_up((size_t)batch * 4 * sizeof(double), 256));
-    char *p = (char *)d_tab + kfac_align_up(dir_table_bound(batch, d) * sizeof(unsigned), 256);
-    for (int i = 0; i < batch; ++i) {
-        DirMat &M = P.mats[i];
-        p += dir_layout(dir_size(d[i]), p, &M);
-        M.F = F[i];
-        M.Q = Q[i];
-        M.lam = lam[i];
-        M.stat = d_stat + 4 * i;
-        M.split = !fp32_only && d[i] >= KFAC_EIG_SPLIT_MIN;
-        (M.split ? P.any_split : P.any_plain) = true;
-    }
-    dir_tables(P);
-    hipStream_t st = ctx->stream;
-    KFAC_CHECK(kfac_upload(ctx, d_mats, P.mats.data(), (size_t)batch * sizeof(DirMat)));
-    KFAC_CHECK(kfac_upload(ctx, d_tab, P.tab.data(), P.tab.size() * sizeof(unsigned)));
-    const DirMat *dm = d_mats;
-    const unsigned *tab = d_tab;
-    const dim3 per_mat4(NORM_WGS, batch);
+    std::vector<int> members;      // indices of the call
+    hipStream_t st;
+    const DirMat *dm;
+    const unsigned *tab;
     double cube = 0.0, square = 0.0;
-    for (int i = 0; i < batch; ++i) { cube += (double)d[i] * d[i] * d[i]; square += (double)d[i] * d[i]; }
+};
+
+void enqueue_begin(kfac_ctx *ctx, const DirRun &R) {
+    const DirPlan &P = R.P;
+    const hipStream_t st = R.st;
+    const unsigned batch = (unsigned)P.mats.size();
     {
-        KfacProfScope prof(ctx, KC_EIG_MISC, 0.0, 8.0 * square);
-        hipLaunchKernelGGL(dir_norm_kernel, dim3(NORM_WGS, batch), dim3(256), 0, st, dm);
-        hipLaunchKernelGGL(dir_order_kernel, dim3((P.nmax + RANK_IPB - 1) / RANK_IPB, batch), dim3(256), 0, st, dm);
-        hipLaunchKernelGGL(dir_copy_kernel, per_mat4, dim3(256), 0, st, dm);
+        KfacProfScope prof(ctx, KC_EIG_MISC, 0.0, 8.0 * R.square, st);
+        hipLaunchKernelGGL(dir_norm_kernel, dim3(NORM_WGS, batch), dim3(256), 0, st, R.dm);
+        hipLaunchKernelGGL(dir_order_kernel, dim3((P.nmax + RANK_IPB - 1) / RANK_IPB, batch), dim3(256), 0, st, R.dm);
+        hipLaunchKernelGGL(dir_copy_kernel, dim3(NORM_WGS, batch), dim3(256), 0, st, R.dm);
     }
     for (int k = 0; k < 4; ++k) {
         if (P.small[k].empty()) continue;
         const dim3 grid((unsigned)P.small[k].size());
-        const int *list = (const int *)(tab + P.small_at[k]);
+        const int *list = (const int *)(R.tab + P.small_at[k]);
         double fl = 0.0;
-        for (int m : P.small[k]) fl += 4.0 / 3.0 * (double)d[m] * d[m] * d[m];
-        KfacProfScope prof(ctx, KC_EIG_SMALL, fl, 0.0);
+        for (int m : P.small[k]) fl += 4.0 / 3.0 * std::pow((double)P.mats[m].n, 3);
+        KfacProfScope prof(ctx, KC_EIG_SMALL, fl, 0.0, st);
         switch (k) {
-            case 0: hipLaunchKernelGGL(dir_td_small_kernel<16>, grid, dim3(256), 0, st, dm, list); break;
-            case 1: hipLaunchKernelGGL(dir_td_small_kernel<32>, grid, dim3(512), 0, st, dm, list); break;
-            case 2: hipLaunchKernelGGL(dir_td_small_kernel<48>, grid, dim3(768), 0, st, dm, list); break;
-            default: hipLaunchKernelGGL(dir_td_small_kernel<64>, grid, dim3(1024), 0, st, dm, list); break;
+            case 0: hipLaunchKernelGGL(dir_td_small_kernel<16>, grid, dim3(256), 0, st, R.dm, list); break;
+            case 1: hipLaunchKernelGGL(dir_td_small_kernel<32>, grid, dim3(512), 0, st, R.dm, list); break;
+            case 2: hipLaunchKernelGGL(dir_td_small_kernel<48>, grid, dim3(768), 0, st, R.dm, list); break;
+            default: hipLaunchKernelGGL(dir_td_small_kernel<64>, grid, dim3(1024), 0, st, R.dm, list); break;
         }
     }
-    for (int t = 0; t < P.steps; ++t) {
-        const DirPlan::Range tiles = P.tiles[t / NB], rows = P.rows[t / NB];
-        if (t % NB == 0) {
-            if (t > 0) {
-                KfacProfScope prof(ctx, KC_EIG_REDUCE_GEMM, 2.0 * 2.0 * NB * TB * TB * tiles.count, 8.0 * TB * TB * tiles.count);
-                hipLaunchKernelGGL(dir_update_kernel, dim3(tiles.count), dim3(NTHREADS), 0, st, dm, tab + tiles.at, t);
-            }
-            KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 0.0);
-            hipLaunchKernelGGL(dir_column_kernel, dim3(rows.count), dim3(RB), 0, st, dm, tab + rows.at, t);
+}
+
+void enqueue_step(kfac_ctx *ctx, const DirRun &R, int t) {
+    const hipStream_t st = R.st;
+    const DirPlan::Range tiles = R.P.tiles[t / NB], rows = R.P.rows[t / NB];
+    if (t % NB == 0) {
+        if (t > 0) {
+            KfacProfScope prof(ctx, KC_EIG_REDUCE_GEMM, 2.0 * 2.0 * NB * TB * TB * tiles.count, 8.0 * TB * TB * tiles.count, st);
+            hipLaunchKernelGGL(dir_update_kernel, dim3(tiles.count), dim3(NTHREADS), 0, st, R.dm, R.tab + tiles.at, t);
         }
-        {
-            KfacProfScope prof(ctx, KC_EIG_REDUCE_MV, 4.0 * TB * TB * tiles.count, 4.0 * TB * TB * tiles.count);
-            hipLaunchKernelGGL(dir_symv_kernel, dim3(tiles.count), dim3(256), 0, st, dm, tab + tiles.at, t);
-        }
-        KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 0.0);
-        hipLaunchKernelGGL(dir_vector_kernel, dim3(rows.count), dim3(256), 0, st, dm, tab + rows.at, t);
+        KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 0.0, st);
+        hipLaunchKernelGGL(dir_column_kernel, dim3(rows.count), dim3(RB), 0, st, R.dm, R.tab + rows.at, t);
     }
+    const double fl = 4.0 * TB * TB * tiles.count;
+    if ((int)tiles.count <= FUSE_MAX && t % NB != 0) {
+        KfacProfScope prof(ctx, KC_EIG_REDUCE_MV, fl, fl, st);
+        hipLaunchKernelGGL(dir_fused_kernel, dim3(tiles.count), dim3(256), 0, st, R.dm, R.tab + tiles.at, t);
+    } else {
+        KfacProfScope prof(ctx, KC_EIG_REDUCE_MV, fl, fl, st);
+        hipLaunchKernelGGL(dir_symv_kernel, dim3(tiles.count), dim3(256), 0, st, R.dm, R.tab + tiles.at, t);
+    }
+    if ((int)tiles.count > FUSE_MAX || t % NB == NB - 1) {
+        KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 0.0, st);
+        hipLaunchKernelGGL(dir_vector_kernel, dim3(rows.count), dim3(256), 0, st, R.dm, R.tab + rows.at, t);
+    }
+}
+
+int enqueue_finish(kfac_ctx *ctx, const DirRun &R) {
+    const DirPlan &P = R.P;
+    const hipStream_t st = R.st;
+    const unsigned batch = (unsigned)P.mats.size();
+    const dim3 per_mat(NORM_WGS, batch);
+    const DirMat *dm = R.dm;
+    const unsigned *tab = R.tab;
     {
-        KfacProfScope prof(ctx, KC_EIG_TRI, 0.0, 0.0);
-        hipLaunchKernelGGL(dir_clear_kernel, per_mat4, dim3(256), 0, st, dm);
+        KfacProfScope prof(ctx, KC_EIG_TRI, 0.0, 0.0, st);
+        hipLaunchKernelGGL(dir_clear_kernel, per_mat, dim3(256), 0, st, dm);
         hipLaunchKernelGGL(dir_scale_t_kernel, dim3(batch), dim3(256), 0, st, dm);
         // sixteen lanes per eigenvalue do 9/4 of the work of four in 4/7 of the passes: right where four leave the chip idle
         if (P.values.count <= BIS_WIDE_MAX)
@@ -1357,14 +1495,14 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
         hipLaunchKernelGGL(dir_vectors_kernel, dim3(P.values.count), dim3(64), 0, st, dm, tab + P.values.at);
     }
     {
-        KfacProfScope prof(ctx, KC_EIG_BACK, 2.0 * cube, 0.0);
+        KfacProfScope prof(ctx, KC_EIG_BACK, 2.0 * R.cube, 0.0, st);
         if (P.apply.count) hipLaunchKernelGGL(dir_apply_kernel, dim3(P.apply.count), dim3(256), 0, st, dm, tab + P.apply.at);
         if (P.wy_steps > 0) {
             const int lds = 2 * WY * (WY + 1) * (int)sizeof(float);
             if (lds > ctx->max_lds) return KFAC_EHIP;
             KFAC_HIP_CHECK(hipFuncSetAttribute((const void *)dir_wy_t_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
             hipLaunchKernelGGL(dir_wy_gram_kernel, dim3(P.gram.count), dim3(NTHREADS), 0, st, dm, tab + P.gram.at);
-            hipLaunchKernelGGL(dir_wy_t_kernel, dim3(P.gram.count), dim3(WY), lds, st, dm, tab + P.gram.at);
+            hipLaunchKernelGGL(dir_wy_t_kernel, dim3(P.gram.count), dim3(WY * WT), lds, st, dm, tab + P.gram.at);
             hipLaunchKernelGGL(dir_wy_u_kernel, dim3(P.wyu.count), dim3(NTHREADS), 0, st, dm, tab + P.wyu.at);
             for (int s = 0; s < P.wy_steps; ++s) {
                 hipLaunchKernelGGL(dir_wy_y_kernel, dim3(P.wyy.count), dim3(NTHREADS), 0, st, dm, tab + P.wyy.at, s);
@@ -1374,7 +1512,7 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
         }
     }
     {
-        KfacProfScope prof(ctx, KC_EIG_POST, 5.0 * cube, 0.0);
+        KfacProfScope prof(ctx, KC_EIG_POST, 5.0 * R.cube, 0.0, st);
         const dim3 lo(P.lower.count), fu(P.full.count), b(NTHREADS);
         const unsigned *tl = tab + P.lower.at, *tf = tab + P.full.at;
         for (int second = 0; second < 2; ++second) {
@@ -1390,14 +1528,96 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
         hipLaunchKernelGGL((dir_product_kernel<TIMES_F, false>), fu, b, 0, st, dm, tf, 0);
     }
     {
-        KfacProfScope prof(ctx, KC_EIG_MISC, 0.0, 16.0 * square);
+        KfacProfScope prof(ctx, KC_EIG_MISC, 0.0, 16.0 * R.square, st);
         hipLaunchKernelGGL(dir_rayleigh_kernel, dim3((P.nmax + 255) / 256, NPARTS, batch), dim3(256), 0, st, dm);
         hipLaunchKernelGGL(dir_lambda_kernel, dim3((P.nmax + 255) / 256, batch), dim3(256), 0, st, dm);
         hipLaunchKernelGGL(dir_rank_kernel, dim3((P.nmax + RANK_IPB - 1) / RANK_IPB, batch), dim3(256), 0, st, dm);
-        hipLaunchKernelGGL(dir_gather_kernel, per_mat4, dim3(256), 0, st, dm);
+        hipLaunchKernelGGL(dir_gather_kernel, per_mat, dim3(256), 0, st, dm);
     }
     KFAC_HIP_CHECK(hipGetLastError());
-    KFAC_HIP_CHECK(hipMemcpyAsync(stat, d_stat, (size_t)batch * 4 * sizeof(double), hipMemcpyDeviceToHost, st));
-    KFAC_HIP_CHECK(hipStreamSynchronize(st));
     return KFAC_OK;
+}
+
+int run_groups(kfac_ctx *ctx, std::vector<DirRun> &runs) {
+    int steps = 0;
+    for (DirRun &R : runs) {
+        enqueue_begin(ctx, R);
+        steps = std::max(steps, R.P.steps);
+    }
+    // the chains are fed in turn, step by step: the host is not much faster than the device
+    for (int t = 0; t <= steps; ++t)
+        for (DirRun &R : runs) {
+            if (t < R.P.steps) enqueue_step(ctx, R, t);
+            else if (t == R.P.steps) KFAC_CHECK(enqueue_finish(ctx, R));
+        }
+    return KFAC_OK;
+}
+
+}  // namespace
+
+size_t kfac_eig_direct_ws_bytes(int batch, const int *d) {
+    size_t need = kfac_align_up((size_t)batch * sizeof(DirMat), 256) + kfac_align_up((size_t)batch * 4 * sizeof(double), 256) +
+                  kfac_align_up(dir_table_bound(batch, d) * sizeof(unsigned), 256);
+    for (int i = 0; i < batch; ++i) need += dir_layout(dir_size(d[i]), nullptr, nullptr);
+    return need;
+}
+
+// All factors of the call by the direct route; stat (pinned host memory): four doubles per factor, off^2 and diag^2 of F, the
+// squared residual ||F Q - Q diag(lam)||_F^2 and ||I - Q^T Q||_F^2 before it was orthogonalised.  Waits for the result.
+int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
+                           bool fp32_only, double *stat) {
+    if (kfac_eig_direct_ws_bytes(batch, d) > ctx->ws_bytes) return KFAC_EWORKSPACE;
+    DirMat *d_mats = (DirMat *)ctx->ws;
+    double *d_stat = (double *)(ctx->ws + kfac_align_up((size_t)batch * sizeof(DirMat), 256));
+    unsigned *d_tab = (unsigned *)((char *)d_stat + kfac_align_up((size_t)batch * 4 * sizeof(double), 256));
+    char *p = (char *)d_tab + kfac_align_up(dir_table_bound(batch, d) * sizeof(unsigned), 256);
+    std::vector<std::vector<int>> groups;
+    groups.emplace_back(batch);
+    for (int i = 0; i < batch; ++i) groups[0][i] = i;
+    std::vector<DirRun> runs(groups.size());
+    std::vector<DirMat> mats;
+    std::vector<unsigned> tab;
+    for (size_t g = 0; g < groups.size(); ++g) {
+        DirRun &R = runs[g];
+        R.members = groups[g];
+        R.st = groups.size() > 1 ? ctx->aux[g] : ctx->stream;
+        R.dm = d_mats + mats.size();
+        R.tab = d_tab + tab.size();
+        for (int i : R.members) {
+            DirMat M;
+            p += dir_layout(dir_size(d[i]), p, &M);
+            M.F = F[i];
+            M.Q = Q[i];
+            M.lam = lam[i];
+            M.stat = d_stat + 4 * i;
+            M.split = !fp32_only && d[i] >= KFAC_EIG_SPLIT_MIN;
+            (M.split ? R.P.any_split : R.P.any_plain) = true;
+            R.P.mats.push_back(M);
+            R.cube += (double)d[i] * d[i] * d[i];
+            R.square += (double)d[i] * d[i];
+        }
+        dir_tables(R.P);
+        mats.insert(mats.end(), R.P.mats.begin(), R.P.mats.end());
+        tab.insert(tab.end(), R.P.tab.begin(), R.P.tab.end());
+    }
+    KFAC_CHECK(kfac_upload(ctx, d_mats, mats.data(), mats.size() * sizeof(DirMat)));
+    KFAC_CHECK(kfac_upload(ctx, d_tab, tab.data(), tab.size() * sizeof(unsigned)));
+    // the groups' streams start after what is queued on the caller's stream, which goes on after all of them: on an error,
+    // too, so that no kernel of this call is in flight after the return
+    if (groups.size() > 1) {
+        KFAC_HIP_CHECK(hipEventRecord(ctx->ev_fork, ctx->stream));
+        for (DirRun &R : runs) KFAC_HIP_CHECK(hipStreamWaitEvent(R.st, ctx->ev_fork, 0));
+    }
+    int rc = run_groups(ctx, runs);
+    if (groups.size() > 1)
+        for (size_t g = 0; g < groups.size(); ++g)
+            if (hipEventRecord(ctx->ev_join[g], runs[g].st) != hipSuccess ||
+                hipStreamWaitEvent(ctx->stream, ctx->ev_join[g], 0) != hipSuccess) {
+                (void)hipStreamSynchronize(runs[g].st);
+                rc = KFAC_EHIP;
+            }
+    if (rc == KFAC_OK && hipMemcpyAsync(stat, d_stat, (size_t)batch * 4 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess)
+        rc = KFAC_EHIP;
+    if (hipStreamSynchronize(ctx->stream) != hipSuccess) rc = KFAC_EHIP;
+    return rc;
 }
