@@ -3,8 +3,9 @@
 // compare the eigendecomposition with).  The inverse of a symmetric positive definite matrix is formed the
 // classical way, in fp32: blocked Cholesky factorisation F + gamma I = L L^T (128-wide block columns: the diagonal
 // block is factored, and inverted, by one workgroup in LDS; the panel below it is multiplied by that inverse and the
-// trailing matrix gets its rank-128 update on the fp32 MFMA tile engine), then the triangular inverse L^-1 block
-// row by block row, then L^-T L^-1 as one symmetric product.  n^3 flops in all, 5 n/128 + 1 launches per factor.
+// trailing matrix gets its rank-128 update on the fp32 MFMA tile engine), then the triangular inverse L^-1 by
+// doubling (two products per level), then L^-T L^-1 as one symmetric product.  n^3 flops in all, 3 n/128 + 2 log2(n/128) + 1
+// launches per factor.
 #include <algorithm>
 #include <cmath>
 #include "kfac_internal.h"
@@ -15,32 +16,29 @@ using namespace kfac;
 namespace {
 
 constexpr int NB = BM;            // block size of the factorisation = tile edge of the engine
-constexpr int DLD = NB + 1;       // LDS pitch of a diagonal block
 
 struct InvPtr { const float *F; float *out; };   // one factor: the caller's matrix and where its inverse goes
 
 // One group of factors of the same size, advanced together (blockIdx.y: factor).  Per factor the workspace holds
 //   L  [npad][npad]  F + gamma I on entry to the factorisation (both triangles), the Cholesky factor after
-//   Li [npad][npad]  L^-1 (lower triangular)
+//   Li [npad][npad]  L^-1 (lower triangular); the blocks above the diagonal are scratch of the triangular inversion
 //   D  [nt][NB][NB]  inverses of the diagonal blocks of L
-//   R  [NB][npad]    one block row of L * Li during the triangular inversion
 struct InvArgs {
     float *base;          // first factor's buffers; the next factor's are fstride floats further
     int64_t fstride;
     const InvPtr *tab;    // device table of the group's factors
     int64_t ld;           // npad
-    int n, nt, k;         // k: block column (factorisation) or block row (triangular inversion) of this launch
+    int n, nt, k;         // k: block column (factorisation) or blocks of a pair's first half (triangular inversion) of this launch
     __device__ float *L(int f) const { return base + f * fstride; }
     __device__ float *Li(int f) const { return L(f) + ld * ld; }
     __device__ float *D(int f) const { return Li(f) + ld * ld; }
-    __device__ float *R(int f) const { return D(f) + (int64_t)nt * NB * NB; }
 };
 
-// L = F + gamma I inside n x n, the identity on the padded part of the diagonal, zero elsewhere; Li = 0.
+// L = F + gamma I inside n x n, the identity on the padded part of the diagonal, zero elsewhere.
 __global__ __launch_bounds__(256) void inv_init_kernel(float gamma, InvArgs a) {
     const int f = blockIdx.y, n = a.n;
     const float *F = a.tab[f].F;
-    float *L = a.L(f), *Li = a.Li(f);
+    float *L = a.L(f);
     const int64_t total = a.ld * a.ld;
     for (int64_t e = blockIdx.x * 256ll + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
         const int r = (int)(e / a.ld), c = (int)(e - (int64_t)r * a.ld);
@@ -48,59 +46,81 @@ __global__ __launch_bounds__(256) void inv_init_kernel(float gamma, InvArgs a) {
         if (r < n && c < n) v = F[(int64_t)r * n + c] + (r == c ? gamma : 0.f);
         else if (r == c) v = 1.f;
         L[e] = v;
-        Li[e] = 0.f;
     }
 }
 
 // Diagonal block k: Cholesky factor in place (lower triangle; the upper is cleared) and its inverse, written to D[k]
-// and to the diagonal block of Li.  One workgroup per factor; both matrices live in LDS.  A pivot that is not positive (the
-// input was not positive definite, or not finite) yields NaNs from there on.
+// and to the diagonal block of Li.  One workgroup per factor.  A pivot that is not positive (the input was not positive definite,
+// or not finite) yields NaNs from there on.
+// A chain of 128 pivots: latency is all there is.  Thread (ty, tx) keeps elements (ty + 16 a, tx + 16 b) of the block and of its
+// inverse in registers; per pivot one column and one row of the inverse so far go through LDS (two buffers, one barrier), and both get
+// their rank-1 update, the inverse by the same row operations.  (With both matrices in LDS, three barriers per pivot and the
+// inverse by substitution afterwards, a launch took 312 us, nearly half of the inverse method on the ResNet-50 set; now about 100 us.  With 512 threads: 104 us.)
+constexpr int DT = NB / 16;
+// x / d with r = 1 / d at hand: the product alone carries r's rounding into a whole column of L and a whole row of L^-1, which
+// doubled the error of the inverse of a 129-wide factor
+__device__ inline float quotient(float x, float d, float r) {
+    const float q = x * r;
+    return fmaf(fmaf(-q, d, x), r, q);
+}
 __global__ __launch_bounds__(256) void inv_diag_kernel(InvArgs a) {
-    extern __shared__ float lds[];
-    float *S = lds, *X = lds + NB * DLD;
-    const int tid = threadIdx.x, f = blockIdx.x;
+    __shared__ float col[2][NB], xrow[2][NB];
+    const int tid = threadIdx.x, f = blockIdx.x, ty = tid >> 4, tx = tid & 15;
     float *blk = a.L(f) + ((int64_t)a.k * NB) * a.ld + (int64_t)a.k * NB;
-    for (int e = tid; e < NB * NB; e += 256) {
-        const int r = e / NB, c = e % NB;
-        S[r * DLD + c] = r >= c ? blk[(int64_t)r * a.ld + c] : blk[(int64_t)c * a.ld + r];   // the lower triangle is the valid one
-        X[r * DLD + c] = 0.f;
-    }
-    const int ty = tid >> 4, tx = tid & 15;
-    for (int j = 0; j < NB; ++j) {
-        __syncthreads();
-        const float piv = S[j * DLD + j];
-        const float sq = sqrtf(piv), rs = 1.f / sq;
-        __syncthreads();
-        if (tid < NB - 1 - j) S[(j + 1 + tid) * DLD + j] *= rs;
-        if (tid == 255) S[j * DLD + j] = sq;
-        __syncthreads();
-        // trailing update of the lower triangle: S[i][c] -= S[i][j] S[c][j], j < c <= i
-        for (int i = j + 1 + ty; i < NB; i += 16) {
-            const float lij = S[i * DLD + j];
-            for (int c = j + 1 + tx; c <= i; c += 16) S[i * DLD + c] -= lij * S[c * DLD + j];
+    float S[DT][DT], X[DT][DT];
+#pragma unroll
+    for (int p = 0; p < DT; ++p)
+#pragma unroll
+        for (int q = 0; q < DT; ++q) {
+            const int r = ty + 16 * p, c = tx + 16 * q;
+            X[p][q] = r == c ? 1.f : 0.f;
+            S[p][q] = q > p ? 0.f : (r >= c ? blk[(int64_t)r * a.ld + c] : blk[(int64_t)c * a.ld + r]);   // the lower triangle is the valid one
         }
-    }
-    __syncthreads();
-    // X = S^-1 by forward substitution, one column per thread; every thread walks the same (i, k) so the reads of S
-    // are broadcasts (entries of X above the column's diagonal are zero and add nothing)
-    if (tid < NB) {
-        const int c = tid;
-        for (int i = 0; i < NB; ++i) {
-            float s = i == c ? 1.f : 0.f;
-            for (int k = 0; k < i; ++k) s -= S[i * DLD + k] * X[k * DLD + c];
-            if (i >= c) X[i * DLD + c] = s / S[i * DLD + i];
+#pragma unroll
+    for (int jb = 0; jb < DT; ++jb)
+        for (int jj = 0; jj < 16; ++jj) {
+            const int j = 16 * jb + jj, h = jj & 1;
+            if (tx == jj)
+#pragma unroll
+                for (int p = jb; p < DT; ++p) col[h][ty + 16 * p] = S[p][jb];
+            if (ty == jj)
+#pragma unroll
+                for (int q = 0; q <= jb; ++q) xrow[h][tx + 16 * q] = X[jb][q];
+            __syncthreads();
+            const float sq = sqrtf(col[h][j]), rs = 1.f / sq;
+            float lr[DT], lc[DT], xs[DT];
+#pragma unroll
+            for (int p = jb; p < DT; ++p) {
+                const float vr = quotient(col[h][ty + 16 * p], sq, rs), vc = quotient(col[h][tx + 16 * p], sq, rs);
+                lr[p] = p > jb || ty > jj ? vr : 0.f;
+                lc[p] = p > jb || tx > jj ? vc : 0.f;
+            }
+#pragma unroll
+            for (int q = 0; q <= jb; ++q) xs[q] = quotient(xrow[h][tx + 16 * q], sq, rs);
+#pragma unroll
+            for (int p = jb; p < DT; ++p) {
+#pragma unroll
+                for (int q = jb; q <= p; ++q) S[p][q] = fmaf(-lr[p], lc[q], S[p][q]);
+                if (tx == jj) S[p][jb] = p == jb && ty == jj ? sq : (p > jb || ty > jj ? lr[p] : S[p][jb]);
+#pragma unroll
+                for (int q = 0; q <= jb; ++q) X[p][q] = fmaf(-lr[p], xs[q], X[p][q]);
+            }
+            if (ty == jj)
+#pragma unroll
+                for (int q = 0; q <= jb; ++q) X[jb][q] = xs[q];
         }
-    }
-    __syncthreads();
     float *Dk = a.D(f) + (int64_t)a.k * NB * NB;
     float *Lik = a.Li(f) + ((int64_t)a.k * NB) * a.ld + (int64_t)a.k * NB;
-    for (int e = tid; e < NB * NB; e += 256) {
-        const int r = e / NB, c = e % NB;
-        blk[(int64_t)r * a.ld + c] = r >= c ? S[r * DLD + c] : 0.f;
-        const float x = r >= c ? X[r * DLD + c] : 0.f;
-        Dk[e] = x;
-        Lik[(int64_t)r * a.ld + c] = x;
-    }
+#pragma unroll
+    for (int p = 0; p < DT; ++p)
+#pragma unroll
+        for (int q = 0; q < DT; ++q) {
+            const int r = ty + 16 * p, c = tx + 16 * q;
+            const float x = r >= c ? X[p][q] : 0.f;
+            blk[(int64_t)r * a.ld + c] = r >= c ? S[p][q] : 0.f;
+            Dk[r * NB + c] = x;
+            Lik[(int64_t)r * a.ld + c] = x;
+        }
 }
 
 __device__ inline void inv_tri_decode(int idx, int &ti, int &tj) {   // idx = ti (ti + 1) / 2 + tj, tj <= ti
@@ -114,17 +134,19 @@ __device__ inline void inv_tri_decode(int idx, int &ti, int &tj) {   // idx = ti
 // The five products, one 128 x 128 output tile per workgroup (all operands are padded to whole tiles):
 //   PANEL   L[i,k] <- L[i,k] D_k^T                                      i > k              (grid: nt-k-1)
 //   UPDATE  L[i,j] <- L[i,j] - L[i,k] L[j,k]^T                          i >= j > k         (grid: lower tiles)
-//   ROW     R[:, j] <- sum_{c = j}^{i-1} L[i,c] Li[c,j]                 j < i = a.k        (grid: i)
-//   SCALE   Li[i,j] <- -D_i R[:, j]                                     j < i = a.k        (grid: i)
+//   HALF    Li[j,i] <- sum_{c = j}^{m-1} L[i,c] Li[c,j]    scratch: block (i, j) of L21 Li11, kept above the diagonal
+//   JOIN    Li[i,j] <- -sum_{c = m}^{i} Li[i,c] Li[j,c]    (block (c, j) of the scratch is at (j, c))
+//           for every pair of neighbouring index ranges [m - s, m), [m, m + s) of s = a.k blocks whose inverses are there:
+//           j in the first, i in the second                                               (grid: pairs * s^2)
 //   GRAM    out[i,j] <- sum_{c >= i} Li[c,i]^T Li[c,j], and its mirror  i >= j             (grid: lower tiles)
-enum { INV_PANEL = 0, INV_UPDATE, INV_ROW, INV_SCALE, INV_GRAM };
+enum { INV_PANEL = 0, INV_UPDATE, INV_HALF, INV_JOIN, INV_GRAM };
 template <int MODE>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void inv_gemm_kernel(InvArgs a) {
     __shared__ TileSmem sm;
     floatx16 acc[2][2];
     const int64_t ld = a.ld;
     const int npad = a.nt * NB, f = blockIdx.y;
-    float *const L = a.L(f), *const Li = a.Li(f), *const D = a.D(f), *const R = a.R(f);
+    float *const L = a.L(f), *const Li = a.Li(f), *const D = a.D(f);
     if (MODE == INV_PANEL) {
         const int i = a.k + 1 + blockIdx.x;
         float *Lik = L + ((int64_t)i * NB) * ld + (int64_t)a.k * NB;
@@ -141,20 +163,24 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         gemm_tile(A, B, 0, 0, 0, NB, sm, acc);
         float *Lij = L + ((int64_t)i * NB) * ld + (int64_t)j * NB;
         for_each_acc(acc, [&](int r, int c, float v) { Lij[(int64_t)r * ld + c] -= v; });
-    } else if (MODE == INV_ROW) {
-        const int i = a.k, j = blockIdx.x;
-        OpStrided<float, true> A{L + ((int64_t)i * NB) * ld, ld, 1, NB, i * NB, -1};           // elem(m,c) = L[i*NB+m][c]
-        OpStrided<float, false> B{Li + (int64_t)j * NB, 1, ld, NB, i * NB, -1};                // elem(n,c) = Li[c][j*NB+n]
-        gemm_tile(A, B, 0, 0, j * NB, i * NB, sm, acc);
-        float *Rj = R + (int64_t)j * NB;
-        for_each_acc(acc, [&](int r, int c, float v) { Rj[(int64_t)r * ld + c] = v; });
-    } else if (MODE == INV_SCALE) {
-        const int i = a.k, j = blockIdx.x;
-        OpStrided<float, true> A{D + (int64_t)i * NB * NB, NB, 1, NB, NB, -1};                 // elem(m,c) = D_i[m][c]
-        OpStrided<float, false> B{R + (int64_t)j * NB, 1, ld, NB, NB, -1};                     // elem(n,c) = R[c][j*NB+n]
-        gemm_tile(A, B, 0, 0, 0, NB, sm, acc);
-        float *Lij = Li + ((int64_t)i * NB) * ld + (int64_t)j * NB;
-        for_each_acc(acc, [&](int r, int c, float v) { Lij[(int64_t)r * ld + c] = -v; });
+    } else if (MODE == INV_HALF || MODE == INV_JOIN) {
+        const int s = a.k, idx = blockIdx.x, pair = idx / (s * s), m = (2 * pair + 1) * s;
+        const int i = m + (idx / s) % s, j = m - s + idx % s;
+        if (i >= a.nt) return;
+        if (MODE == INV_HALF) {
+            OpStrided<float, true> A{L + ((int64_t)i * NB) * ld, ld, 1, NB, m * NB, -1};           // elem(r,c) = L[i*NB+r][c]
+            OpStrided<float, false> B{Li + (int64_t)j * NB, 1, ld, NB, m * NB, -1};                // elem(n,c) = Li[c][j*NB+n]
+            gemm_tile(A, B, 0, 0, j * NB, m * NB, sm, acc);
+            float *H = Li + ((int64_t)j * NB) * ld + (int64_t)i * NB;
+            for_each_acc_transposed(acc, reinterpret_cast<float *>(&sm), [&](int r, int c, float v) { H[(int64_t)r * ld + c] = v; });
+        } else {
+            // the scratch is the block's transpose, so that the blocks of one column j are one row of the matrix: elem(n,c) = H[j*NB+n][c]
+            OpStrided<float, true> A{Li + ((int64_t)i * NB) * ld, ld, 1, NB, (i + 1) * NB, -1};     // elem(r,c) = Li[i*NB+r][c]
+            OpStrided<float, true> B{Li + ((int64_t)j * NB) * ld, ld, 1, NB, (i + 1) * NB, -1};
+            gemm_tile(A, B, 0, 0, m * NB, (i + 1) * NB, sm, acc);
+            float *Lij = Li + ((int64_t)i * NB) * ld + (int64_t)j * NB;
+            for_each_acc(acc, [&](int r, int c, float v) { Lij[(int64_t)r * ld + c] = -v; });
+        }
     } else {
         int i, j;
         inv_tri_decode(blockIdx.x, i, j);
@@ -178,7 +204,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 inline int inv_npad(int n) { return (n + NB - 1) / NB * NB; }
 inline size_t inv_bytes_one(int n) {
     const size_t np = inv_npad(n), nt = np / NB;
-    return kfac_align_up((2 * np * np + nt * NB * NB + (size_t)NB * np) * sizeof(float), 256);
+    return kfac_align_up((2 * np * np + nt * NB * NB) * sizeof(float), 256);
 }
 
 // grad <- Ginv grad Ainv: T = grad Ainv into the workspace, then grad = Ginv T.
@@ -208,7 +234,7 @@ namespace {
 struct InvGroup { int n, first, count; };   // `count` factors of size n, entries first.. of the sorted table
 
 // The whole chain of one group on one stream.
-int inv_enqueue_group(kfac_ctx *ctx, hipStream_t st, const InvGroup &g, const InvPtr *tab_dev, float *slot, float damping, size_t lds) {
+int inv_enqueue_group(kfac_ctx *ctx, hipStream_t st, const InvGroup &g, const InvPtr *tab_dev, float *slot, float damping) {
     const int n = g.n, np = inv_npad(n), nt = np / NB, nm = g.count;
     InvArgs a;
     a.base = slot;
@@ -222,7 +248,7 @@ int inv_enqueue_group(kfac_ctx *ctx, hipStream_t st, const InvGroup &g, const In
                            damping, a);
         for (int k = 0; k < nt; ++k) {
             a.k = k;
-            hipLaunchKernelGGL(inv_diag_kernel, dim3(nm), dim3(256), lds, st, a);
+            hipLaunchKernelGGL(inv_diag_kernel, dim3(nm), dim3(256), 0, st, a);
             const int rest = nt - k - 1;
             if (rest > 0) {
                 hipLaunchKernelGGL(inv_gemm_kernel<INV_PANEL>, dim3(rest, nm), dim3(NTHREADS), 0, st, a);
@@ -232,10 +258,13 @@ int inv_enqueue_group(kfac_ctx *ctx, hipStream_t st, const InvGroup &g, const In
     }
     {
         KfacProfScope prof(ctx, KC_INVERSE, n3 / 3.0, 0.0, st);
-        for (int i = 1; i < nt; ++i) {
-            a.k = i;
-            hipLaunchKernelGGL(inv_gemm_kernel<INV_ROW>, dim3(i, nm), dim3(NTHREADS), 0, st, a);
-            hipLaunchKernelGGL(inv_gemm_kernel<INV_SCALE>, dim3(i, nm), dim3(NTHREADS), 0, st, a);
+        // by doubling: a block row after the other is nt - 1 dependent pairs of launches of at most nt tiles each (119 + 17 us per
+        // pair on the ResNet-50 set)
+        for (int s = 1; s < nt; s *= 2) {
+            a.k = s;
+            const int pairs = (nt - s + 2 * s - 1) / (2 * s);      // with a second half that is not empty
+            hipLaunchKernelGGL(inv_gemm_kernel<INV_HALF>, dim3(pairs * s * s, nm), dim3(NTHREADS), 0, st, a);
+            hipLaunchKernelGGL(inv_gemm_kernel<INV_JOIN>, dim3(pairs * s * s, nm), dim3(NTHREADS), 0, st, a);
         }
     }
     KfacProfScope prof(ctx, KC_INVERSE, n3 / 3.0, 0.0, st);
@@ -247,9 +276,6 @@ int inv_enqueue_group(kfac_ctx *ctx, hipStream_t st, const InvGroup &g, const In
 
 int kfac_launch_invert_factors(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float damping, float *const *Finv) {
     if (kfac_invert_ws_bytes_impl(batch, d) > ctx->ws_bytes) return KFAC_EWORKSPACE;
-    const size_t lds = (size_t)2 * NB * DLD * sizeof(float);
-    if ((int)lds > ctx->max_lds) return KFAC_EHIP;
-    KFAC_HIP_CHECK(hipFuncSetAttribute((const void *)inv_diag_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     // factors sorted by size (largest first); equal sizes form groups
     std::vector<int> order(batch);
     for (int b = 0; b < batch; ++b) order[b] = b;
@@ -284,7 +310,7 @@ int kfac_launch_invert_factors(kfac_ctx *ctx, int batch, const float *const *F, 
         for (int i = 1; i < nstreams; ++i) if (load[i] < load[best]) best = i;
         const double nt = inv_npad(g.n) / NB;
         load[best] += nt * 250e-6 + (double)g.count * g.n * (double)g.n * g.n / 60e12;   // launch-latency floor + products
-        rc = inv_enqueue_group(ctx, ctx->aux[best], g, tab_dev, (float *)(pool + (size_t)best * region), damping, lds);
+        rc = inv_enqueue_group(ctx, ctx->aux[best], g, tab_dev, (float *)(pool + (size_t)best * region), damping);
         if (rc != KFAC_OK) break;
     }
     // ... and the caller's stream continues after all of them

@@ -578,6 +578,22 @@ def test_invert_factors_matches_cholesky_oracle(ctx, n, rows):
         assert res <= max(2e-6, 2e-7 * cond), (n, gamma, res, cond)
 
 
+@pytest.mark.parametrize("n", [129, 257, 385, 513, 641, 897, 1100])
+def test_invert_factors_every_shape_of_the_doubling(ctx, n):
+    """2 to 9 blocks of 128: whole pairs, a short second half, none.  Well conditioned, so the bound is fp32's."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randn((4 * n, n), generator=gen, device="cuda", dtype=torch.float64)
+    F = (X.T.contiguous() @ X / (4 * n)).float()
+    F = ((F + F.T) * 0.5).contiguous()
+    out = torch.full_like(F, float("nan"))
+    K.kfac_invert_factors(ctx.h, [F], 0.1, [out])
+    torch.cuda.synchronize()
+    A = F.cpu().double() + 0.1 * torch.eye(n, dtype=torch.float64)
+    ref = torch.linalg.inv(A)
+    cond = float(torch.linalg.matrix_norm(A, 2) * torch.linalg.matrix_norm(ref, 2))
+    assert float((out.cpu().double() - ref).norm() / ref.norm()) <= max(2e-6, 2e-7 * cond)
+
+
 def test_invert_factors_batch_of_mixed_sizes(ctx):
     """Several factors in one call share the workspace one after another; every inverse is checked."""
     rng = np.random.default_rng(77)
