@@ -401,6 +401,27 @@ def test_eig_direct_large_graded_and_rank_deficient(n, rows, seed):
     assert float((Qd.T.contiguous() @ Qd - torch.eye(n, device="cuda", dtype=torch.float64)).norm()) <= n * 2.0 ** -24
 
 
+def test_eig_direct_in_several_chains(ctx):
+    """Enough large factors in one call that they are decomposed as several chains on streams of their own: every result as good as
+    one chain's, and the caller's stream goes on after all of them."""
+    dims = [2900, 1300, 2900, 100, 2900, 20, 2900, 2900, 300, 2900]
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    F = []
+    for n in dims:
+        X = torch.randn((2 * n, n), generator=gen, device="cuda")
+        G = X.T.contiguous() @ X / (2 * n)
+        F.append(((G + G.T) * 0.5).contiguous())
+    c = Ctx(K.kfac_eig_workspace_bytes(dims) + 4096)
+    Q, lam = [torch.empty_like(f) for f in F], [torch.empty(n, device="cuda") for n in dims]
+    info = K.kfac_eig(c.h, F, Q, lam)
+    for f, q, l, n, i in zip(F, Q, lam, dims, info):     # on the caller's stream, without a synchronisation in between
+        assert i[2] and i[0] == 1, (n, i)
+        fd, qd = f.double(), q.double()
+        assert float((fd @ qd - qd * l.double()).norm() / fd.norm()) <= TOL_RES, n
+        assert float((qd.T.contiguous() @ qd - torch.eye(n, device="cuda", dtype=torch.float64)).norm()) <= max(n, 16) * 2.0 ** -22, n
+    c.close()
+
+
 # ------------------------------------------------------------------ precondition
 # (230, 100) and (97, 200): edge tiles between 65 and 127 wide and tall (accumulator blocks masked under the full
 # wave map); the others: edge tiles at most 64 wide or tall (the waves share them in slices)
