@@ -284,27 +284,43 @@ int form_of(const kfac_factor_item &it) {
     return !ndt ? 3 : (it.T >= 8 ? 4 : 1);
 }
 
-void plan_item(int n, const kfac_factor_item &it, int &ntri, int &nsplit, int &kchunk) {
+void plan_item(int n, const kfac_factor_item &it, int shift, int &ntri, int &nsplit, int &kchunk) {
     const int form = form_of(it);
     if (form >= 4) {   // contraction units are groups of 16 bytes
         const int epg = form == 4 ? 8 : 4;
         const int64_t Q = (int64_t)it.N * ((it.T + epg - 1) / epg);
         if (n == 1) plan_single(it.d, Q, GRP_GROUPS, form == 4 ? 30.0 : 6.0, ntri, nsplit, kchunk);
-        else plan_batched(it.d, Q, GRP_GROUPS, form == 4 ? JOB_SLABS_GRP_B16 : JOB_SLABS_GRP_F32, ntri, nsplit, kchunk);
+        else plan_batched(it.d, Q, GRP_GROUPS, (form == 4 ? JOB_SLABS_GRP_B16 : JOB_SLABS_GRP_F32) >> shift, ntri, nsplit, kchunk);
         return;
     }
     const int64_t R = (int64_t)it.N * it.T;
     if (n == 1) plan_single(it.d, R, BK, 12.0, ntri, nsplit, kchunk);
-    else plan_batched(it.d, R, BK, JOB_SLABS, ntri, nsplit, kchunk);
+    else plan_batched(it.d, R, BK, JOB_SLABS >> shift, ntri, nsplit, kchunk);
+}
+
+// A batch with fewer jobs than compute units: half the slabs per job, and again, down to a sixteenth.  (One conv layer, factors 145
+// and 16 wide from 2048 samples: 4 jobs of 64 slabs took 131 us, 16 of 16 slabs and the reducer 38.)
+constexpr int MIN_JOBS = 256, MAX_SHIFT = 4;
+int plan_shift(int n, const kfac_factor_item *items) {
+    for (int shift = 0; shift < MAX_SHIFT && n > 1; ++shift) {
+        int64_t jobs = 0;
+        for (int i = 0; i < n; ++i) {
+            int ntri, nsplit, kchunk;
+            plan_item(n, items[i], shift, ntri, nsplit, kchunk);
+            jobs += (int64_t)ntri * nsplit;
+        }
+        if (jobs >= MIN_JOBS) return shift;
+    }
+    return n > 1 ? MAX_SHIFT : 0;
 }
 
 // Workspace layout: SyrkArgs[n], the job table, the reducer's job table, then every factor's partials.
-size_t layout(int n, const kfac_factor_item *items, size_t &off_jobs, size_t &off_rjobs, size_t &off_part, size_t &njobs, size_t &nrjobs) {
+size_t layout(int n, const kfac_factor_item *items, int shift, size_t &off_jobs, size_t &off_rjobs, size_t &off_part, size_t &njobs, size_t &nrjobs) {
     njobs = nrjobs = 0;
     size_t part = 0;
     for (int i = 0; i < n; ++i) {
         int ntri, nsplit, kchunk;
-        plan_item(n, items[i], ntri, nsplit, kchunk);
+        plan_item(n, items[i], shift, ntri, nsplit, kchunk);
         njobs += (size_t)ntri * nsplit;
         if (nsplit > 1) {
             nrjobs += ntri;
@@ -374,7 +390,7 @@ void launch_class(kfac_ctx *ctx, const SyrkArgs *d_items, const SyrkJob *d_jobs,
 
 size_t kfac_syrk_ws_bytes_impl(int n, const kfac_factor_item *items) {
     size_t a, b, c, d, e;
-    return layout(n, items, a, b, c, d, e);
+    return layout(n, items, plan_shift(n, items), a, b, c, d, e);
 }
 
 size_t kfac_syrk_workspace_bytes(int D, int64_t R) {
@@ -391,8 +407,9 @@ int kfac_launch_update_factors_batched(kfac_ctx *ctx, int n, const kfac_factor_i
 
 int kfac_launch_update_factors_ws(kfac_ctx *ctx, int n, const kfac_factor_item *items, char *ws, size_t ws_bytes) {
     size_t off_jobs, off_rjobs, off_part, njobs, nrjobs;
-    const size_t need = layout(n, items, off_jobs, off_rjobs, off_part, njobs, nrjobs);
-    if (need > ws_bytes) return KFAC_EWORKSPACE;
+    int shift = plan_shift(n, items);
+    while (layout(n, items, shift, off_jobs, off_rjobs, off_part, njobs, nrjobs) > ws_bytes)    // fewer partials where they don't fit
+        if (--shift < 0) return KFAC_EWORKSPACE;
     std::vector<SyrkArgs> args(n);
     // jobs grouped by operand form, inside a form the longest contraction first
     std::vector<SyrkJob> jobs[NFORM], rjobs;
@@ -402,7 +419,7 @@ int kfac_launch_update_factors_ws(kfac_ctx *ctx, int n, const kfac_factor_item *
         const kfac_factor_item &it = items[i];
         SyrkArgs &g = args[i];
         const int64_t R = (int64_t)it.N * it.T;
-        plan_item(n, it, g.ntri, g.nsplit, g.kchunk);
+        plan_item(n, it, shift, g.ntri, g.nsplit, g.kchunk);
         g.X = it.X;
         g.d = it.d;
         g.D = it.d + (it.append_ones ? 1 : 0);

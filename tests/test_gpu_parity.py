@@ -422,6 +422,26 @@ def test_eig_direct_in_several_chains(ctx):
     c.close()
 
 
+@pytest.mark.parametrize("N,d,T,bf16,layout", [(32, 144, 64, False, K.KFAC_LAYOUT_NDT), (9, 130, 49, False, K.KFAC_LAYOUT_NDT), (40, 257, 64, True, K.KFAC_LAYOUT_NDT),
+                                                (1111, 70, 1, False, K.KFAC_LAYOUT_RD), (3, 17, 3, False, K.KFAC_LAYOUT_NDT)])
+def test_update_factors_batch_too_small_for_the_machine(N, d, T, bf16, layout):
+    """A batch of two factors is cut into shorter jobs than a large one, if its workspace holds their partial sums, and into
+    the usual ones if it does not: the same factors either way."""
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    shapes = [(N, d, T), (N, 16, T)] if layout == K.KFAC_LAYOUT_NDT else [(N, d), (N, 16)]
+    X = [torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16 if bf16 else torch.float32) for s in shapes]
+    for ws in (64 << 20, 1 << 16):
+        c = Ctx(ws)
+        F = [torch.zeros((x.shape[1] + 1, x.shape[1] + 1), device="cuda") for x in X]
+        K.kfac_update_factors_batched(c.h, [dict(X=x, dtype=K.KFAC_BF16 if bf16 else K.KFAC_F32, layout=layout, N=N, d=x.shape[1], T=T, append_ones=1,
+                                                 scale=1.0 / (N * T), decay=0.0, F=f) for x, f in zip(X, F)])
+        torch.cuda.synchronize()
+        c.close()
+        for x, f in zip(X, F):
+            rows = (x.double().permute(0, 2, 1).reshape(N * T, -1) if x.dim() == 3 else x.double()).cpu().numpy()
+            assert relfro(f.cpu().numpy(), oracle.gram(rows, 1, 1.0 / (N * T))) <= 1e-6, (ws, x.shape)
+
+
 # ------------------------------------------------------------------ precondition
 # (230, 100) and (97, 200): edge tiles between 65 and 127 wide and tall (accumulator blocks masked under the full
 # wave map); the others: edge tiles at most 64 wide or tall (the waves share them in slices)
