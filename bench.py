@@ -273,8 +273,8 @@ def main():
     if args.no_extras:
         warm_ms, warm_sweeps = [0.0], None
 
-    # the eigendecomposition with every product on the fp32 matrix instructions (the default runs the rank-256 passes of
-    # factors with d >= 2048 on split-fp16 products until it recomputes W = Q^T F Q in fp32): not part of `value`
+    # the eigendecomposition with every product on the fp32 matrix instructions (the default runs the orthogonalisation
+    # of factors with d >= 2048 on split-fp16 products): not part of `value`
     fp32_ms, fp32_sweeps = None, None
     if not args.no_extras:
         run.update_factors(1, wl.decay)
@@ -385,11 +385,10 @@ def main():
         "config": {"workload": "%s: %d layers, batch %d, %s; factor update + eig of %d factors + precondition"
                                % (wl.name, len(wl.layers), wl.batch, "bf16 in / fp32 factors" if wl.bf16 else "fp32",
                                   2 * len(wl.layers)),
-                   "arithmetic": "factors, pivot solves, round applications, W = Q^T F Q, eigenvalues, preconditioner: fp32 "
-                                 "(fp32 MFMA); rank-256 update passes of the eigensolver for factors with d >= 2048: "
-                                 "split-fp16 MFMA (hi + lo halves, 3 products, fp32 accumulation), followed by a recomputation "
-                                 "of W = Q^T F Q in fp32; derived.eig_fp32_only_ms is the same step's eigensolve with "
-                                 "every product in fp32"},
+                   "arithmetic": "factors, reduction to tridiagonal form, back-transformation, F Q, preconditioner: fp32 (fp32 "
+                                 "MFMA); eigenpairs of the tridiagonal matrix, Rayleigh quotients: fp64; orthogonalisation step "
+                                 "of factors with d >= 2048: split-fp16 MFMA (hi + lo halves, 3 products, fp32 accumulation); "
+                                 "derived.eig_fp32_only_ms is the same step's eigensolve with every product in fp32"},
         "phases_ms": {k: round(v, 3) for k, v in phases.items()},
         "step_ms_median": round(step_ms[len(step_ms) // 2], 3), "step_ms_min": round(step_ms[0], 3),
         "derived": derived,
