@@ -40,10 +40,6 @@ constexpr int TD_SMALL = 256;     // factors up to this size are reduced by one 
 // up to 300 tiles, and up to 800: one 4609-wide factor (703 tiles and fewer as it shrinks) 61.5, 58.6, 61.1 ms; ResNet-32's factors
 // (135 tiles at the most) 9.81, 9.12, 9.14 ms; beyond 800 tiles fusing costs as much again as it saves (ResNet-50: 155 and 177 ms).
 constexpr int FUSE_MAX = 300;
-// Tiles of a call's first launch from which on its factors are several chains.  One chain and four, ms per decomposition: 5410 tiles
-// (ResNet-50) 145 and 135, 4383: 122 and 114, 2716: 98.7 and 94.9, 1968 (four factors of 2901): 68.8 and 67.5, 1734 (2049): 47.7 and
-// 45.4; 1480 (2305 at the most): 37.3 and 37.5, 1071 (seven factors of 2049): 29.8 and 32: several queues slow each launch down.
-constexpr int64_t SPLIT_TILES = 1700;
 constexpr int WY = 128;           // reflectors of a compact WY block
 constexpr int WY_K = 512;         // contraction of one workgroup in Y = V^T Z
 constexpr int NPARTS = 64;         // parts of the Rayleigh quotients' sums
@@ -1542,28 +1538,6 @@ int enqueue_finish(kfac_ctx *ctx, const DirRun &R) {
     return KFAC_OK;
 }
 
-// The factors of a call are one chain of launches on the caller's stream, unless its launches are bound by memory traffic
-// (SPLIT_TILES); then the largest ones (of more than two thirds of the largest size) are dealt to three chains on streams of their own and
-// the rest are a fourth: one chain's vector steps and products of the tridiagonal stage run under another's matrix traffic.
-void dir_groups(const int *d, int batch, bool serial, std::vector<std::vector<int>> &groups) {
-    std::vector<int> order(batch);
-    int64_t tiles = 0;
-    for (int i = 0; i < batch; ++i) {
-        order[i] = i;
-        const int64_t nb = (d[i] + TB - 1) / TB;
-        if (d[i] > TD_SMALL) tiles += nb * (nb + 1) / 2;
-    }
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return d[a] > d[b]; });
-    const bool split = !serial && tiles >= SPLIT_TILES;
-    groups.assign(split ? 4 : 1, {});
-    int large = 0;
-    for (int i : order) {
-        const bool is_large = (int64_t)3 * d[i] > (int64_t)2 * d[order[0]];
-        groups[!split ? 0 : is_large ? large++ % 3 : 3].push_back(i);
-    }
-    groups.erase(std::remove_if(groups.begin(), groups.end(), [](const std::vector<int> &g) { return g.empty(); }), groups.end());
-}
-
 int run_groups(kfac_ctx *ctx, std::vector<DirRun> &runs) {
     int steps = 0;
     for (DirRun &R : runs) {
@@ -1598,7 +1572,8 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
     unsigned *d_tab = (unsigned *)((char *)d_stat + kfac_align_up((size_t)batch * 4 * sizeof(double), 256));
     char *p = (char *)d_tab + kfac_align_up(dir_table_bound(batch, d) * sizeof(unsigned), 256);
     std::vector<std::vector<int>> groups;
-    dir_groups(d, batch, ctx->prof_on, groups);
+    groups.emplace_back(batch);
+    for (int i = 0; i < batch; ++i) groups[0][i] = i;
     std::vector<DirRun> runs(groups.size());
     std::vector<DirMat> mats;
     std::vector<unsigned> tab;

@@ -401,9 +401,9 @@ def test_eig_direct_large_graded_and_rank_deficient(n, rows, seed):
     assert float((Qd.T.contiguous() @ Qd - torch.eye(n, device="cuda", dtype=torch.float64)).norm()) <= n * 2.0 ** -24
 
 
-def test_eig_direct_in_several_chains(ctx):
-    """Enough large factors in one call that they are decomposed as several chains on streams of their own: every result as good as
-    one chain's, and the caller's stream goes on after all of them."""
+def test_eig_direct_many_large_factors(ctx):
+    """Large and small factors in one call, launches beyond and below the tiles of a fused one: every result as good as
+    a single factor's, and complete when the call returns."""
     dims = [2900, 1300, 2900, 100, 2900, 20, 2900, 2900, 300, 2900]
     gen = torch.Generator(device="cuda").manual_seed(5)
     F = []
