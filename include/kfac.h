@@ -63,7 +63,8 @@ typedef struct {
     int max_sweeps;          /* cap on Jacobi sweeps (<=0: 30)                    */
     float tol;               /* stop when off(F)_F <= tol * ||F||_F (<=0: 2e-6).  From 1e-6 on the factors are
                                 decomposed directly (Householder reduction, fp64 tridiagonal eigenproblem), to fp32
-                                rounding; a smaller tol asks for Jacobi sweeps until the rotated matrix meets it.  */
+                                rounding; a smaller tol, or a factor whose direct result misses tol, asks for Jacobi
+                                sweeps until the rotated matrix meets it.                          */
     int fp32_only;           /* 0 (default): for d >= 2048 the orthogonalisation products (and, in Jacobi sweeps, the
                                 rank-256 update passes) run as split-fp16 MFMA products (hi + lo halves, three
                                 products per fp32 product, fp32 accumulation): same tolerances met, errors bounded

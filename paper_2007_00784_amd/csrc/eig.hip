@@ -1993,9 +1993,11 @@ static int launch_jacobi(kfac_ctx *ctx, int batch, const float *const *F, const 
     return (rc != KFAC_OK && rc != KFAC_ENOCONV) ? rc : (jrc != KFAC_OK ? jrc : rc);
 }
 
-// The direct route diagonalises by construction; what is left is the fp32 rounding of the reduction, 3e-7 ||F|| at 129 to
-// 1.6e-6 ||F|| at 4609 as measured through F Q (about half of that is F Q's own rounding).  It serves stopping rules down to
-// DIRECT_TOL_MIN; tighter ones are Jacobi's, whose sweeps go on until the rotated matrix itself is that close to diagonal.
+// The direct route diagonalises by construction; what is left is the fp32 rounding of the reduction.  Measured through F Q: 3e-7 ||F||
+// at 129 to 7e-7 at 8192 for Gram matrices, 4.5e-7 at 64 to 1.2e-6 at 8192 for dense ones with random entries.  It serves stopping
+// rules down to DIRECT_TOL_MIN, and a factor that comes out further off than the caller's tol is left to Jacobi like one whose
+// result is not sound; tighter rules are Jacobi's from the start, whose sweeps go on until the rotated matrix itself is that close to
+// diagonal.
 constexpr float DIRECT_TOL_MIN = 1e-6f;
 constexpr double DIRECT_MAX_RES = 5e-6;    // measured residual / ||F||_F of a sound result
 constexpr double DIRECT_MAX_DEV2 = 1e-3;   // ||I - Q^T Q||_F^2 that two Newton-Schulz steps bring below fp32 rounding
@@ -2007,11 +2009,12 @@ int kfac_launch_eig(kfac_ctx *ctx, int batch, const float *const *F, const int *
     if ((size_t)batch * 4 * sizeof(double) > ctx->pinned_bytes) return KFAC_EINVAL;
     double *stat = ctx->pinned;
     KFAC_CHECK(kfac_launch_eig_direct(ctx, batch, F, d, Q, lam, opts && opts->fp32_only != 0, stat));
-    std::vector<int> left;         // factors whose result is not sound
+    std::vector<int> left;         // factors whose result is not sound, or not as close as the caller asks
     bool bad = false;
     for (int i = 0; i < batch; ++i) {
         const double off2 = stat[4 * i], f2 = off2 + stat[4 * i + 1], res2 = std::max(stat[4 * i + 2], 0.0), dev2 = stat[4 * i + 3];
-        const double tol2 = (double)tol * tol * f2, max_res2 = DIRECT_MAX_RES * DIRECT_MAX_RES * f2;
+        const double max_res = std::min((double)tol, DIRECT_MAX_RES);
+        const double tol2 = (double)tol * tol * f2, max_res2 = max_res * max_res * f2;
         const bool finite = f2 < 1e300;
         const bool ok = finite && res2 <= max_res2 && dev2 <= DIRECT_MAX_DEV2;
         if (finite && !ok) left.push_back(i);

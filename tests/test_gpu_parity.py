@@ -401,6 +401,24 @@ def test_eig_direct_large_graded_and_rank_deficient(n, rows, seed):
     assert float((Qd.T.contiguous() @ Qd - torch.eye(n, device="cuda", dtype=torch.float64)).norm()) <= n * 2.0 ** -24
 
 
+def dense_symmetric(n, seed):
+    """Random entries, eigenvalues of both signs: the direct route's residual is larger than for a Gram matrix."""
+    a = np.random.default_rng(seed).standard_normal((n, n))
+    return ((a + a.T) * 0.5).astype(np.float32)
+
+
+@pytest.mark.parametrize("tol", [1e-6, 0.0])
+def test_eig_converged_means_within_the_callers_tolerance(ctx, tol):
+    """A dense matrix of 1100 comes out of the direct route about 1.04e-6 ||F|| off: within the default tolerance of 2e-6, not
+    within 1e-6.  There it is decomposed by Jacobi sweeps, between two factors of the same call that are not."""
+    mats = [gram_factor(300, 900, seed=1), dense_symmetric(1100, 2), gram_factor(100, 300, seed=3)]
+    Ld, Qd, info = ctx.eig(mats, tol=tol)
+    for i, F in enumerate(mats):
+        assert info[i][2] and info[i][1] <= (tol or 2e-6), info
+        check_eigpairs(F, Ld[i].cpu().numpy(), Qd[i].cpu().numpy(), "tol[%d]" % i)
+    assert info[0][0] == 1 and info[2][0] == 1 and (info[1][0] > 1) == (tol == 1e-6), info
+
+
 def test_eig_direct_many_large_factors(ctx):
     """Large and small factors in one call, launches beyond and below the tiles of a fused one: every result as good as
     a single factor's, and complete when the call returns."""
