@@ -96,8 +96,9 @@ int kfac_create(kfac_ctx **ctx, int device, void *hip_stream, void *workspace_de
 int kfac_destroy(kfac_ctx *ctx);
 
 /* Pure host functions: bytes of workspace that suffice for any call with factor dimension <= max_d,
- * at most max_batch_factors factors per kfac_eig() call and at most max_R sample rows; and the exact
- * requirement of one kfac_eig() call on the given host array of dimensions.  */
+ * at most max_batch_factors factors per kfac_eig() call and at most max_R sample rows; and what one kfac_eig() call on
+ * the given host array of dimensions makes use of.  (kfac_eig() iterates by Jacobi sweeps where the workspace holds
+ * these but not the direct decomposition, and returns KFAC_EWORKSPACE where it holds neither.)  */
 size_t kfac_workspace_bytes(int max_d, int max_batch_factors, int64_t max_R);
 size_t kfac_eig_workspace_bytes(int batch, const int *d /* host */);
 

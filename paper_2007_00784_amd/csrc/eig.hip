@@ -1643,13 +1643,17 @@ int enqueue_post(kfac_ctx *ctx, GroupRun &r) {
 
 // All groups are in flight at once, each on one of the context's internal streams, so the workspace
 // holds every group's buffers side by side.
+static size_t jacobi_ws_bytes(const std::vector<int> &small, const std::vector<GroupPlan> &groups) {
+    size_t need = small_bytes(small.size());
+    for (auto &g : groups) need += g.bytes();
+    return need;
+}
+
 size_t kfac_eig_ws_bytes_impl(int batch, const int *d) {
     std::vector<int> small;
     std::vector<GroupPlan> groups;
     make_plan(batch, d, small, groups);
-    size_t need = small_bytes(small.size());
-    for (auto &g : groups) need += g.bytes();
-    return std::max(need, kfac_eig_direct_ws_bytes(batch, d));   // the two routes run one after the other
+    return std::max(jacobi_ws_bytes(small, groups), kfac_eig_direct_ws_bytes(batch, d));   // the two routes run one after the other
 }
 
 // Everything between the fork onto the internal streams and the join back: may return early with an error, the
@@ -1969,7 +1973,7 @@ static int launch_jacobi(kfac_ctx *ctx, int batch, const float *const *F, const 
     std::vector<int> small;
     std::vector<GroupPlan> groups;
     make_plan(batch, d, small, groups);
-    if (kfac_eig_ws_bytes_impl(batch, d) > ctx->ws_bytes) return KFAC_EWORKSPACE;
+    if (jacobi_ws_bytes(small, groups) > ctx->ws_bytes) return KFAC_EWORKSPACE;
     if (groups.size() > (size_t)KFAC_MAX_GROUPS) return KFAC_EINVAL;
     size_t norms_need = 0, tables_need = kfac_align_up(small.size() * sizeof(SmallItem), 64) + kfac_align_up(small.size() * sizeof(EigStat), 64);
     for (auto &gp : groups) {
@@ -2005,7 +2009,10 @@ constexpr double DIRECT_MAX_DEV2 = 1e-3;   // ||I - Q^T Q||_F^2 that two Newton-
 int kfac_launch_eig(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q,
                     float *const *lam, const kfac_eig_opts *opts, kfac_eig_info *info) {
     const float tol = (opts && opts->tol > 0.f) ? opts->tol : 2e-6f;
-    if (tol < DIRECT_TOL_MIN) return launch_jacobi(ctx, batch, F, d, Q, lam, opts, info);
+    // (small factors are solved in LDS by Jacobi iteration, with no workspace to speak of: 1000 factors of 128 in 48 KB, where the
+    // direct route takes hundreds of MB; a workspace sized for that is served as well)
+    if (tol < DIRECT_TOL_MIN || kfac_eig_direct_ws_bytes(batch, d) > ctx->ws_bytes)
+        return launch_jacobi(ctx, batch, F, d, Q, lam, opts, info);
     if ((size_t)batch * 4 * sizeof(double) > ctx->pinned_bytes) return KFAC_EINVAL;
     double *stat = ctx->pinned;
     KFAC_CHECK(kfac_launch_eig_direct(ctx, batch, F, d, Q, lam, opts && opts->fp32_only != 0, stat));

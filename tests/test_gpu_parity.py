@@ -419,6 +419,19 @@ def test_eig_converged_means_within_the_callers_tolerance(ctx, tol):
     assert info[0][0] == 1 and info[2][0] == 1 and (info[1][0] > 1) == (tol == 1e-6), info
 
 
+@pytest.mark.parametrize("sizes,ws", [([64] * 12 + [17, 100, 128], 1 << 16), ([145, 16], 320 << 10), ([300, 577, 129], 6 << 20)])
+def test_eig_in_a_workspace_that_holds_jacobi_sweeps_only(sizes, ws):
+    """Less than the direct decomposition takes: iterated instead, not refused."""
+    assert K.kfac_eig_workspace_bytes(sizes) > ws
+    c = Ctx(ws)
+    mats = [gram_factor(n, 2 * n, seed=n + i) for i, n in enumerate(sizes)]
+    Ld, Qd, info = c.eig(mats)
+    c.close()
+    for i, F in enumerate(mats):
+        assert info[i][2] and info[i][0] > 1, info
+        check_eigpairs(F, Ld[i].cpu().numpy(), Qd[i].cpu().numpy(), "little workspace[%d]" % i)
+
+
 def test_eig_direct_many_large_factors(ctx):
     """Large and small factors in one call, launches beyond and below the tiles of a fused one: every result as good as
     a single factor's, and complete when the call returns."""
