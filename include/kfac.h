@@ -81,7 +81,7 @@ typedef struct {
 
 typedef struct {             /* host memory, filled when kfac_eig() returns       */
     int sweeps;              /* Jacobi sweeps performed.  A direct decomposition counts as one, as none if F was
-                                diagonal to begin with or if it only replaces a start basis (warm_start)    */
+                                diagonal to begin with                                             */
     float off_norm_rel;      /* off(F)_F / ||F||_F of the rotated matrix at exit (direct: of Q^T F Q, i.e. the residual
                                 ||F Q - Q diag(lam)||_F / ||F||_F, with its fp32 rounding)         */
     int converged;           /* 1 if the tolerance was met                        */

@@ -2026,10 +2026,8 @@ int kfac_launch_eig(kfac_ctx *ctx, int batch, const float *const *F, const int *
         const bool ok = finite && res2 <= max_res2 && dev2 <= DIRECT_MAX_DEV2;
         if (finite && !ok) left.push_back(i);
         bad |= !finite;
-        // a matrix that was diagonal to begin with needed no sweep; with a start basis the reduction takes the basis' place
-        // and is not counted as a sweep either
-        const bool warm = opts && opts->warm_start != 0;
-        if (info) info[i] = kfac_eig_info{!ok || off2 <= tol2 || warm ? 0 : 1, finite ? (f2 > 0.0 ? (float)std::sqrt(res2 / f2) : 0.f) : NAN, ok ? 1 : 0};
+        // a matrix that was diagonal to begin with needed no sweep
+        if (info) info[i] = kfac_eig_info{!ok || off2 <= tol2 ? 0 : 1, finite ? (f2 > 0.0 ? (float)std::sqrt(res2 / f2) : 0.f) : NAN, ok ? 1 : 0};
     }
     int rc = bad ? KFAC_ENOCONV : KFAC_OK;
     if (!left.empty()) {
