@@ -75,8 +75,9 @@ typedef struct {
                                 factor: the remark of Sec. V-C that the FIM becomes more stable as training progresses).
                                 Jacobi sweeps then run on Q_i^T F_i Q_i, which is close to diagonal, and fewer are needed
                                 (4 d^3 flops per factor up front; a basis that is not orthonormal to fp32 rounding
-                                gives wrong results).  The direct decomposition needs no start basis and overwrites
-                                it.  0: start from I.                                              */
+                                gives wrong results).  How close it is, is estimated first: factors that sweeps
+                                from there finish sooner than a direct decomposition are iterated, the others
+                                decomposed directly.  0: start from I.                             */
 } kfac_eig_opts;
 
 typedef struct {             /* host memory, filled when kfac_eig() returns       */

@@ -1,7 +1,6 @@
-// Batched symmetric eigensolver F = Q diag(lam) Q^T (Sec. IV-A; Algorithm 1, step 2): the entry point, and two-sided
-// Jacobi iteration in fp32.  The entry point sends every factor through the direct route (eig_direct.hip), which is
-// three times as fast; the Jacobi iteration serves stopping rules tighter than that route's rounding and any
-// factor whose result there is not sound.
+// Batched symmetric eigensolver F = Q diag(lam) Q^T (Sec. IV-A; Algorithm 1, step 2) by two-sided Jacobi iteration in fp32.
+// It serves stopping rules tighter than the rounding of the direct route (eig_direct.hip), factors that few sweeps finish, and
+// any factor whose result there is not sound (eig_route.hip has the rule).
 //
 //  * d <= 128: one workgroup per factor.  The rotated matrix and the accumulated eigenvectors both
 //    stay in LDS for the whole solve; every round applies d/2 disjoint plane rotations (round-robin
@@ -1649,13 +1648,6 @@ static size_t jacobi_ws_bytes(const std::vector<int> &small, const std::vector<G
     return need;
 }
 
-size_t kfac_eig_ws_bytes_impl(int batch, const int *d) {
-    std::vector<int> small;
-    std::vector<GroupPlan> groups;
-    make_plan(batch, d, small, groups);
-    return std::max(jacobi_ws_bytes(small, groups), kfac_eig_direct_ws_bytes(batch, d));   // the two routes run one after the other
-}
-
 // Everything between the fork onto the internal streams and the join back: may return early with an error, the
 // caller joins in every case.
 static int eig_run(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
@@ -1967,9 +1959,44 @@ static int eig_run(kfac_ctx *ctx, int batch, const float *const *F, const int *d
     return all_conv ? KFAC_OK : KFAC_ENOCONV;
 }
 
+size_t kfac_eig_jacobi_ws_bytes(int batch, const int *d) {
+    std::vector<int> small;
+    std::vector<GroupPlan> groups;
+    make_plan(batch, d, small, groups);
+    return jacobi_ws_bytes(small, groups);
+}
+
+// What the sweeps of a call take, in seconds, if factor i (wider than KFAC_EIG_SMALL) needs sweeps[i] of them.  A round is bound by
+// launch latency until its products fill the machine; the groups share four streams and, where they overlap, the machine.  Fitted
+// to 40 calls of 1 to 53 factors from 150 to 4609 wide, 0.4 to 190 ms, with the sweeps they took: within 10 % of most.
+double kfac_eig_jacobi_seconds(int batch, const int *d, const int *sweeps) {
+    std::vector<int> small;
+    std::vector<GroupPlan> groups;
+    make_plan(batch, d, small, groups);
+    std::vector<double> cost;
+    double sum = 0.0;
+    for (auto &gp : groups) {
+        double n2 = 0.0, n3 = 0.0;
+        int s = 0;
+        for (int b : gp.members) {
+            n2 += (double)d[b] * d[b];
+            n3 += (double)d[b] * d[b] * d[b];
+            s = std::max(s, sweeps[b]);
+        }
+        const double sweep = gp.two_level ? gp.splayers * (172e-6 + 4.0 * n2 * LDI / 160e12) : (gp.players - 1) * (40e-6 + 8.0 * n2 * EB / 70e12);
+        cost.push_back(s * sweep + 8.0 * n3 / 100e12 + 250e-6 + 30e-6 * gp.members.size());
+        sum += cost.back();
+    }
+    std::sort(cost.begin(), cost.end(), [](double a, double b) { return a > b; });
+    double load[KFAC_NUM_AUX_STREAMS] = {0};
+    for (double c : cost) *std::min_element(load, load + KFAC_NUM_AUX_STREAMS) += c;
+    const double longest = *std::max_element(load, load + KFAC_NUM_AUX_STREAMS);
+    return longest + 0.2 * (sum - longest) + 100e-6;
+}
+
 // Jacobi iteration for all factors of the call.
-static int launch_jacobi(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q,
-                         float *const *lam, const kfac_eig_opts *opts, kfac_eig_info *info) {
+int kfac_launch_eig_jacobi(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q,
+                           float *const *lam, const kfac_eig_opts *opts, kfac_eig_info *info) {
     std::vector<int> small;
     std::vector<GroupPlan> groups;
     make_plan(batch, d, small, groups);
@@ -1995,55 +2022,4 @@ static int launch_jacobi(kfac_ctx *ctx, int batch, const float *const *F, const 
     for (int i = 0; i < KFAC_NUM_AUX_STREAMS; ++i)
         if (hipStreamSynchronize(ctx->aux[i]) != hipSuccess) jrc = KFAC_EHIP;
     return (rc != KFAC_OK && rc != KFAC_ENOCONV) ? rc : (jrc != KFAC_OK ? jrc : rc);
-}
-
-// The direct route diagonalises by construction; what is left is the fp32 rounding of the reduction.  Measured through F Q: 3e-7 ||F||
-// at 129 to 7e-7 at 8192 for Gram matrices, 4.5e-7 at 64 to 1.2e-6 at 8192 for dense ones with random entries.  It serves stopping
-// rules down to DIRECT_TOL_MIN, and a factor that comes out further off than the caller's tol is left to Jacobi like one whose
-// result is not sound; tighter rules are Jacobi's from the start, whose sweeps go on until the rotated matrix itself is that close to
-// diagonal.
-constexpr float DIRECT_TOL_MIN = 1e-6f;
-constexpr double DIRECT_MAX_RES = 5e-6;    // measured residual / ||F||_F of a sound result
-constexpr double DIRECT_MAX_DEV2 = 1e-3;   // ||I - Q^T Q||_F^2 that two Newton-Schulz steps bring below fp32 rounding
-
-int kfac_launch_eig(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q,
-                    float *const *lam, const kfac_eig_opts *opts, kfac_eig_info *info) {
-    const float tol = (opts && opts->tol > 0.f) ? opts->tol : 2e-6f;
-    // (small factors are solved in LDS by Jacobi iteration, with no workspace to speak of: 1000 factors of 128 in 48 KB, where the
-    // direct route takes hundreds of MB; a workspace sized for that is served as well)
-    if (tol < DIRECT_TOL_MIN || kfac_eig_direct_ws_bytes(batch, d) > ctx->ws_bytes)
-        return launch_jacobi(ctx, batch, F, d, Q, lam, opts, info);
-    if ((size_t)batch * 4 * sizeof(double) > ctx->pinned_bytes) return KFAC_EINVAL;
-    double *stat = ctx->pinned;
-    KFAC_CHECK(kfac_launch_eig_direct(ctx, batch, F, d, Q, lam, opts && opts->fp32_only != 0, stat));
-    std::vector<int> left;         // factors whose result is not sound, or not as close as the caller asks
-    bool bad = false;
-    for (int i = 0; i < batch; ++i) {
-        const double off2 = stat[4 * i], f2 = off2 + stat[4 * i + 1], res2 = std::max(stat[4 * i + 2], 0.0), dev2 = stat[4 * i + 3];
-        const double max_res = std::min((double)tol, DIRECT_MAX_RES);
-        const double tol2 = (double)tol * tol * f2, max_res2 = max_res * max_res * f2;
-        const bool finite = f2 < 1e300;
-        const bool ok = finite && res2 <= max_res2 && dev2 <= DIRECT_MAX_DEV2;
-        if (finite && !ok) left.push_back(i);
-        bad |= !finite;
-        // a matrix that was diagonal to begin with needed no sweep
-        if (info) info[i] = kfac_eig_info{!ok || off2 <= tol2 ? 0 : 1, finite ? (f2 > 0.0 ? (float)std::sqrt(res2 / f2) : 0.f) : NAN, ok ? 1 : 0};
-    }
-    int rc = bad ? KFAC_ENOCONV : KFAC_OK;
-    if (!left.empty()) {
-        const size_t m = left.size();
-        std::vector<const float *> F2(m);
-        std::vector<float *> Q2(m), lam2(m);
-        std::vector<int> d2(m);
-        std::vector<kfac_eig_info> info2(m);
-        for (size_t k = 0; k < m; ++k) { F2[k] = F[left[k]]; Q2[k] = Q[left[k]]; lam2[k] = lam[left[k]]; d2[k] = d[left[k]]; }
-        kfac_eig_opts o{};
-        if (opts) o = *opts;
-        o.warm_start = 0;
-        const int jrc = launch_jacobi(ctx, (int)m, F2.data(), d2.data(), Q2.data(), lam2.data(), &o, info2.data());
-        if (jrc != KFAC_OK && jrc != KFAC_ENOCONV) return jrc;
-        if (jrc == KFAC_ENOCONV) rc = jrc;
-        for (size_t k = 0; info && k < m; ++k) info[left[k]] = info2[k];
-    }
-    return rc;
 }

@@ -1562,6 +1562,19 @@ size_t kfac_eig_direct_ws_bytes(int batch, const int *d) {
     return need;
 }
 
+// What a call takes, in seconds: the chain of the widest factor's columns, and the traffic of all of them.  Fitted to 40 calls of 1
+// to 53 factors, 0.5 to 90 ms: within 5 % of most.
+double kfac_eig_direct_seconds(int batch, const int *d) {
+    int nmax = 0;
+    double n3 = 0.0;
+    for (int i = 0; i < batch; ++i) {
+        nmax = std::max(nmax, d[i]);
+        n3 += (double)d[i] * d[i] * d[i];
+    }
+    if (nmax == 0) return 0.0;
+    return (nmax > TD_SMALL ? 300e-6 + 9e-6 * nmax : 60e-6 + 4.6e-6 * nmax) + 2e-13 * n3;
+}
+
 // All factors of the call by the direct route; stat (pinned host memory): four doubles per factor, off^2 and diag^2 of F, the
 // squared residual ||F Q - Q diag(lam)||_F^2 and ||I - Q^T Q||_F^2 before it was orthogonalised.  Waits for the result.
 int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,

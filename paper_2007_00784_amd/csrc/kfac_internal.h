@@ -127,6 +127,11 @@ int kfac_launch_precondition_batched(kfac_ctx *ctx, int n, const kfac_precond_it
 size_t kfac_precond_ws_bytes_impl(int n, const kfac_precond_item *items);
 size_t kfac_eig_ws_bytes_impl(int batch, const int *d);
 size_t kfac_eig_direct_ws_bytes(int batch, const int *d);
+size_t kfac_eig_jacobi_ws_bytes(int batch, const int *d);
+double kfac_eig_jacobi_seconds(int batch, const int *d, const int *sweeps);
+int kfac_launch_eig_jacobi(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
+                           const kfac_eig_opts *opts, kfac_eig_info *info);
+double kfac_eig_direct_seconds(int batch, const int *d);
 int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
                            bool fp32_only, double *stat /* pinned, 4 per factor */);
 size_t kfac_invert_ws_bytes_impl(int batch, const int *d);

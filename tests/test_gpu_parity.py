@@ -285,6 +285,40 @@ def test_eig_warm_start(ctx):
     assert 1 <= swept[0][0] < cold[0][0] and 1 <= swept[1][0] < cold[1][0]
 
 
+def test_eig_warm_start_from_eigenvectors_that_still_hold(ctx):
+    """Factors that have not moved, or hardly, since their eigenvectors were formed need no sweep or one; a factor of the same
+    call that is another matrix altogether is decomposed anew, and so is one whose basis is of no use.  Every result is as good
+    as without a start."""
+    sizes = [130, 256, 257, 577, 2100, 577, 64, 300, 300]
+    F0 = [gram_factor(n, 3 * n, seed=60 + i) for i, n in enumerate(sizes)]
+    Fd = [ctx.to_dev(f) for f in F0]
+    Q, lam = [torch.zeros_like(f) for f in Fd], [torch.zeros(f.shape[0], device=ctx.dev) for f in Fd]
+    K.kfac_eig(ctx.h, Fd, Q, lam)
+    same = K.kfac_eig(ctx.h, Fd[:5], Q[:5], lam[:5], warm_start=True)
+    torch.cuda.synchronize()
+    assert all(c and s == 0 for (s, _, c) in same), same
+    for i in range(5):
+        check_eigpairs(F0[i], lam[i].cpu().numpy(), Q[i].cpu().numpy(), "unmoved[%d]" % i)
+    F1 = list(F0)
+    F1[3] = (0.9999 * F0[3].astype(np.float64) + 1e-4 * gram_factor(577, 1731, seed=80)).astype(np.float32)
+    F1[5] = gram_factor(577, 1200, seed=81)
+    F1[7] = np.zeros((300, 300), np.float32)
+    Q[8].fill_(float("nan"))
+    for i in (3, 5, 7):
+        Fd[i].copy_(torch.from_numpy(F1[i]))
+    info = K.kfac_eig(ctx.h, Fd, Q, lam, warm_start=True)
+    torch.cuda.synchronize()
+    print("sweeps", [s for (s, _, _) in info])
+    assert all(c for (_, _, c) in info) and all(info[i][0] == 0 for i in range(3)), info
+    assert info[8][0] == 1, info
+    for i, F in enumerate(F1):
+        if i != 7:
+            check_eigpairs(F, lam[i].cpu().numpy(), Q[i].cpu().numpy(), "moved or not[%d]" % i)
+    assert torch.equal(lam[7], torch.zeros_like(lam[7]))
+    q = Q[7].double()
+    assert float((q.T.contiguous() @ q - torch.eye(300, device=ctx.dev, dtype=torch.float64)).norm()) <= 300 * 2.0 ** -22
+
+
 def test_eig_max_sweeps_reports_noconv(ctx):
     F = gram_factor(300, 500, seed=7)
     with pytest.raises(K.KfacError) as e:
