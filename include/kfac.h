@@ -60,11 +60,12 @@ typedef struct {
 } kfac_conv_desc;
 
 typedef struct {
-    int max_sweeps;          /* cap on Jacobi sweeps (<=0: 30)                    */
+    int max_sweeps;          /* cap on Jacobi sweeps (<=0: 30); a direct decomposition has none */
     float tol;               /* stop when off(F)_F <= tol * ||F||_F (<=0: 2e-6).  From 1e-6 on the factors are
                                 decomposed directly (Householder reduction, fp64 tridiagonal eigenproblem), to fp32
-                                rounding; a smaller tol, or a factor whose direct result misses tol, asks for Jacobi
-                                sweeps until the rotated matrix meets it.                          */
+                                rounding, except where a few Jacobi sweeps meet tol sooner (a factor that is diagonal
+                                or nearly so, a loose tol); a smaller tol, or a factor whose direct result misses tol,
+                                asks for Jacobi sweeps until the rotated matrix meets it.          */
     int fp32_only;           /* 0 (default): for d >= 2048 the orthogonalisation products (and, in Jacobi sweeps, the
                                 rank-256 update passes) run as split-fp16 MFMA products (hi + lo halves, three
                                 products per fp32 product, fp32 accumulation): same tolerances met, errors bounded

@@ -35,7 +35,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int NB = 32;            // columns of a panel
 constexpr int TB = 128;           // tile edge
 constexpr int RB = 64;            // rows per workgroup of the vector step
-constexpr int TD_SMALL = 256;     // factors up to this size are reduced by one workgroup, in registers
+constexpr int TD_SMALL = KFAC_EIG_REG;
 // Tiles of a launch up to which the vector step and the next column's products share it.  Measured with everything unfused, fused
 // up to 300 tiles, and up to 800: one 4609-wide factor (703 tiles and fewer as it shrinks) 61.5, 58.6, 61.1 ms; ResNet-32's factors
 // (135 tiles at the most) 9.81, 9.12, 9.14 ms; beyond 800 tiles fusing costs as much again as it saves (ResNet-50: 155 and 177 ms).
@@ -77,8 +77,14 @@ struct DirMat {
     float *Tm;       // [nb][WY][WY]: Gram matrices of the WY blocks, then their T
     int *perm;       // [np]: final order of the eigenvectors
     int *ord;        // [np]: row of F that became row i of A (diagonal descending)
+    double diag_tol2;   // a factor up to TD_SMALL wide with off^2 <= this ||F||^2 is diagonal as it stands (wider ones: see go_on)
     int n, np, ld, nb, off, split;
 };
+
+// Nothing to reduce: the eigenvectors are unit vectors.  (An identity or another diagonal factor, 64 to 256 wide: 100 to 130 us in place
+// of 270 to 1200.)
+__device__ inline bool is_diagonal(const DirMat &M, double o2, double d2) { return M.n <= TD_SMALL && o2 <= M.diag_tol2 * (o2 + d2); }
+__device__ inline bool is_diagonal(const DirMat &M) { return is_diagonal(M, M.stat[0], M.stat[1]); }
 
 __device__ inline float wave_sum_all(float v) {   // the sum over the wave, in every lane
     int x = __float_as_int(v);
@@ -219,6 +225,14 @@ __global__ __launch_bounds__(16 * KC) void dir_td_small_kernel(const DirMat *mat
     const int n = M.n, tid = threadIdx.x, row = tid >> 2, q = tid & 3, wave = tid >> 6, lane = tid & 63;
     double o2, d2;
     const float sc = dir_norms(M, o2, d2);
+    if (is_diagonal(M, o2, d2)) {
+        for (int i = tid; i < n; i += NTH) {
+            M.d[i] = (double)(sc * as_global(M.F)[(int64_t)M.ord[i] * (n + 1)]);
+            M.e[i] = 0.0;
+            M.tau[i] = 0.f;
+        }
+        return;
+    }
     floatx4 a[G];
     {
         const global_ptr<const float> F = as_global(M.F);
@@ -741,6 +755,7 @@ __global__ __launch_bounds__(256) void dir_bisect_kernel(const DirMat *mats, con
     __shared__ double2 ch[BIS_CHUNK];
     const TabRef tr = tab_ref(tab[blockIdx.x / PARTS]);
     const DirMat M = mats[tr.m];
+    if (is_diagonal(M)) return;
     const int n = M.n, tid = threadIdx.x, q = tid & (LPE - 1), k = tr.J * 64 + (int)(blockIdx.x % PARTS) * PER_WG + tid / LPE;
     double lo = -1.0 - 1e-6, hi = 1.0 + 1e-6;     // Gershgorin, with room for the perturbation
     for (int pass = 0; pass < 40; ++pass) {
@@ -800,8 +815,13 @@ __global__ __launch_bounds__(64) void dir_vectors_kernel(const DirMat *mats, con
     const DirMat M = mats[tr.m];
     const int n = M.n, lane = threadIdx.x, k = tr.J * 64 + lane;
     const bool act = k < n;
-    const double lam = M.lam64[min(k, n - 1)];
     const int64_t ld = M.ld;
+    if (is_diagonal(M)) {
+        if (act)
+            for (int i = 0; i < n; ++i) as_global(M.Z)[(int64_t)i * ld + k] = i == k ? 1.f : 0.f;
+        return;
+    }
+    const double lam = M.lam64[min(k, n - 1)];
     const global_ptr<double> D = as_global((double *)M.B1) + (act ? k : 0);
     const global_ptr<float> Z = as_global(M.Z) + (act ? k : 0);
     const int nch = (n + VEC_CHUNK - 1) / VEC_CHUNK;
@@ -932,7 +952,7 @@ __global__ __launch_bounds__(256) void dir_apply_kernel(const DirMat *mats, cons
     const TabRef tr = tab_ref(tab[blockIdx.x]);
     const DirMat M = mats[tr.m];
     const int n = M.n, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c0 = tr.J * 16 + wave * 4;
-    if (c0 >= n) return;
+    if (c0 >= n || is_diagonal(M)) return;
     const int64_t ld = M.ld;
     const global_ptr<float> Z = as_global(M.Z) + c0;
     floatx4 z[RPL];
@@ -1425,16 +1445,19 @@ struct DirRun {
     double cube = 0.0, square = 0.0;
 };
 
-void enqueue_begin(kfac_ctx *ctx, const DirRun &R) {
+void enqueue_copy(kfac_ctx *ctx, const DirRun &R) {
     const DirPlan &P = R.P;
     const hipStream_t st = R.st;
     const unsigned batch = (unsigned)P.mats.size();
-    {
-        KfacProfScope prof(ctx, KC_EIG_MISC, 0.0, 8.0 * R.square, st);
-        hipLaunchKernelGGL(dir_norm_kernel, dim3(NORM_WGS, batch), dim3(256), 0, st, R.dm);
-        hipLaunchKernelGGL(dir_order_kernel, dim3((P.nmax + RANK_IPB - 1) / RANK_IPB, batch), dim3(256), 0, st, R.dm);
-        hipLaunchKernelGGL(dir_copy_kernel, dim3(NORM_WGS, batch), dim3(256), 0, st, R.dm);
-    }
+    KfacProfScope prof(ctx, KC_EIG_MISC, 0.0, 8.0 * R.square, st);
+    hipLaunchKernelGGL(dir_norm_kernel, dim3(NORM_WGS, batch), dim3(256), 0, st, R.dm);
+    hipLaunchKernelGGL(dir_order_kernel, dim3((P.nmax + RANK_IPB - 1) / RANK_IPB, batch), dim3(256), 0, st, R.dm);
+    hipLaunchKernelGGL(dir_copy_kernel, dim3(NORM_WGS, batch), dim3(256), 0, st, R.dm);
+}
+
+void enqueue_small(kfac_ctx *ctx, const DirRun &R) {
+    const DirPlan &P = R.P;
+    const hipStream_t st = R.st;
     for (int k = 0; k < 4; ++k) {
         if (P.small[k].empty()) continue;
         const dim3 grid((unsigned)P.small[k].size());
@@ -1540,10 +1563,7 @@ int enqueue_finish(kfac_ctx *ctx, const DirRun &R) {
 
 int run_groups(kfac_ctx *ctx, std::vector<DirRun> &runs) {
     int steps = 0;
-    for (DirRun &R : runs) {
-        enqueue_begin(ctx, R);
-        steps = std::max(steps, R.P.steps);
-    }
+    for (DirRun &R : runs) steps = std::max(steps, R.P.steps);
     // the chains are fed in turn, step by step: the host is not much faster than the device
     for (int t = 0; t <= steps; ++t)
         for (DirRun &R : runs) {
@@ -1577,8 +1597,10 @@ double kfac_eig_direct_seconds(int batch, const int *d) {
 
 // All factors of the call by the direct route; stat (pinned host memory): four doubles per factor, off^2 and diag^2 of F, the
 // squared residual ||F Q - Q diag(lam)||_F^2 and ||I - Q^T Q||_F^2 before it was orthogonalised.  Waits for the result.
+// diag_tol: off(F)_F / ||F||_F up to which a factor counts as diagonal.  go_on (may be null): called, if a factor is wider than
+// KFAC_EIG_REG, once off^2 and diag^2 of all factors are in stat; if it returns false, nothing more is done (KFAC_EIG_STOPPED).
 int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
-                           bool fp32_only, double *stat) {
+                           bool fp32_only, double diag_tol, double *stat, const std::function<bool()> *go_on) {
     if (kfac_eig_direct_ws_bytes(batch, d) > ctx->ws_bytes) return KFAC_EWORKSPACE;
     DirMat *d_mats = (DirMat *)ctx->ws;
     double *d_stat = (double *)(ctx->ws + kfac_align_up((size_t)batch * sizeof(DirMat), 256));
@@ -1603,6 +1625,7 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
             M.Q = Q[i];
             M.lam = lam[i];
             M.stat = d_stat + 4 * i;
+            M.diag_tol2 = diag_tol * diag_tol;
             M.split = !fp32_only && d[i] >= KFAC_EIG_SPLIT_MIN;
             (M.split ? R.P.any_split : R.P.any_plain) = true;
             R.P.mats.push_back(M);
@@ -1620,6 +1643,20 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
     if (groups.size() > 1) {
         KFAC_HIP_CHECK(hipEventRecord(ctx->ev_fork, ctx->stream));
         for (DirRun &R : runs) KFAC_HIP_CHECK(hipStreamWaitEvent(R.st, ctx->ev_fork, 0));
+    }
+    for (DirRun &R : runs) enqueue_copy(ctx, R);
+    const bool ask = go_on && runs[0].P.nmax > TD_SMALL;
+    if (ask) {   // the register kernels run while the host decides
+        KFAC_HIP_CHECK(hipMemcpyAsync(stat, d_stat, (size_t)batch * 4 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+        KFAC_HIP_CHECK(hipEventRecord(ctx->ev_group[0], ctx->stream));
+    }
+    for (DirRun &R : runs) enqueue_small(ctx, R);
+    if (ask) {
+        const bool waited = hipEventSynchronize(ctx->ev_group[0]) == hipSuccess;
+        if (!waited || !(*go_on)()) {
+            if (hipStreamSynchronize(ctx->stream) != hipSuccess || !waited) return KFAC_EHIP;
+            return KFAC_EIG_STOPPED;
+        }
     }
     int rc = run_groups(ctx, runs);
     if (groups.size() > 1)

@@ -4,10 +4,13 @@
 // The direct decomposition costs the same for every factor of a size.  Jacobi sweeps cost by how far the factor is from diagonal in
 // the basis they start from: none from the eigenvectors of a factor that has not moved since (7 ms at 4609, where the direct
 // decomposition takes 58), four and more after a running average moved by 5 % (88 ms).  So with a start basis, that distance is
-// estimated first (probe kernels below: 20 to 100 us), and the sweeps take the factors with which the call is cheaper.
+// estimated first (probe kernels below: 20 to 100 us), and the sweeps take the factors with which the call is cheaper.  Without one, it
+// is off(F)_F, which the direct route forms anyway: running averages that are still diagonal need no sweep (0.4 ms at 577, 1.2 at
+// 2100, in place of 5.3 and 19), and a loose tol needs few.
 #include <algorithm>
 #include <climits>
 #include <cmath>
+#include <functional>
 #include <vector>
 #include "kfac_internal.h"
 
@@ -178,7 +181,8 @@ constexpr double DIRECT_MAX_DEV2 = 1e-3;   // ||I - Q^T Q||_F^2 that two Newton-
 
 // Sweeps down to tol.  A sweep gains a factor of 8 as long as the columns of the basis still are what they were (2.5e-3 at 1261 took 4,
 // 5e-3 at 577 took 4, 1e-2 at 240 took 3), 3.5 where many of them are not: the null space of a rank-deficient factor, which any
-// movement makes a dense block (5e-3 at 4609 took 8, 2e-2 at 1624 took 7, 8e-3 at 964 took 8).
+// movement makes a dense block (5e-3 at 4609 took 8, 2e-2 at 1624 took 7, 8e-3 at 964 took 8), or no basis at all (0.2 at
+// 577 took 1 to 0.1, 4 to 0.01, 6 to 1e-3 and 9 to 2e-6).
 int sweeps_needed(const StartBasis &b, double tol) {
     if (b.rel <= tol) return 0;
     const double l = std::log(b.rel / tol);
@@ -203,13 +207,15 @@ struct EigPart {
 // The factors (wider than KFAC_EIG_SMALL: the others gain nothing from a start) to iterate rather than to decompose directly, given
 // the bases they would start from.  Those that need the fewest sweeps first, as many as make the call
 // cheapest, if that is clearly cheaper than all of them directly: a chain of launches is shared by all factors of its kind.
-std::vector<int> choose_sweeps(kfac_ctx *ctx, int batch, const int *d, const std::vector<StartBasis> &start, double tol) {
+std::vector<int> choose_sweeps(kfac_ctx *ctx, int batch, const int *d, const std::vector<StartBasis> &start, double tol, int max_sweeps) {
     std::vector<int> need(batch, INT_MAX), levels, best;
-    for (int i = 0; i < batch; ++i)
-        if (d[i] > KFAC_EIG_SMALL && start[i].rel >= 0.0) {
-            need[i] = sweeps_needed(start[i], tol);
-            levels.push_back(need[i]);
-        }
+    for (int i = 0; i < batch; ++i) {
+        if (d[i] <= KFAC_EIG_SMALL || !(start[i].rel >= 0.0)) continue;
+        const int s = sweeps_needed(start[i], tol);
+        if (max_sweeps > 0 && s > max_sweeps) continue;
+        need[i] = s;
+        levels.push_back(s);
+    }
     std::sort(levels.begin(), levels.end());
     levels.erase(std::unique(levels.begin(), levels.end()), levels.end());
     double least = 0.85 * kfac_eig_direct_seconds(batch, d);
@@ -229,23 +235,25 @@ std::vector<int> choose_sweeps(kfac_ctx *ctx, int batch, const int *d, const std
 }
 
 // Direct decomposition of a part of a call; what is not sound, or not as close as the caller asks, goes on to Jacobi sweeps.
-int run_direct(kfac_ctx *ctx, EigPart &P, const kfac_eig_opts *opts, double tol) {
+int run_direct(kfac_ctx *ctx, EigPart &P, const kfac_eig_opts *opts, double tol, const std::function<bool()> *go_on) {
     const int batch = P.size();
     if ((size_t)batch * 4 * sizeof(double) > ctx->pinned_bytes) return KFAC_EINVAL;
-    double *stat = ctx->pinned;
-    KFAC_CHECK(kfac_launch_eig_direct(ctx, batch, P.F.data(), P.d.data(), P.Q.data(), P.lam.data(), opts && opts->fp32_only != 0, stat));
+    const double *stat = ctx->pinned;
+    const double max_res = std::min(tol, DIRECT_MAX_RES);
+    const int drc = kfac_launch_eig_direct(ctx, batch, P.F.data(), P.d.data(), P.Q.data(), P.lam.data(), opts && opts->fp32_only != 0, max_res,
+                                           ctx->pinned, go_on);
+    if (drc != KFAC_OK) return drc;
     std::vector<int> left;
     bool bad = false;
     for (int i = 0; i < batch; ++i) {
         const double off2 = stat[4 * i], f2 = off2 + stat[4 * i + 1], res2 = std::max(stat[4 * i + 2], 0.0), dev2 = stat[4 * i + 3];
-        const double max_res = std::min(tol, DIRECT_MAX_RES);
-        const double tol2 = tol * tol * f2, max_res2 = max_res * max_res * f2;
+        const double max_res2 = max_res * max_res * f2;
         const bool finite = f2 < 1e300;
         const bool ok = finite && res2 <= max_res2 && dev2 <= DIRECT_MAX_DEV2;
         if (finite && !ok) left.push_back(i);
         bad |= !finite;
-        // a matrix that was diagonal to begin with needed no sweep
-        P.info[i] = kfac_eig_info{!ok || off2 <= tol2 ? 0 : 1, finite ? (f2 > 0.0 ? (float)std::sqrt(res2 / f2) : 0.f) : NAN, ok ? 1 : 0};
+        const bool untouched = P.d[i] <= KFAC_EIG_REG && off2 <= max_res2;     // diagonal as it stood
+        P.info[i] = kfac_eig_info{!ok || untouched ? 0 : 1, finite ? (f2 > 0.0 ? (float)std::sqrt(res2 / f2) : 0.f) : NAN, ok ? 1 : 0};
     }
     if (left.empty()) return bad ? KFAC_ENOCONV : KFAC_OK;
     EigPart L(left, P.F.data(), P.d.data(), P.Q.data(), P.lam.data());
@@ -270,14 +278,34 @@ int kfac_launch_eig(kfac_ctx *ctx, int batch, const float *const *F, const int *
     // direct route takes hundreds of MB; a workspace sized for that is served as well)
     if (tol < DIRECT_TOL_MIN || kfac_eig_direct_ws_bytes(batch, d) > ctx->ws_bytes)
         return kfac_launch_eig_jacobi(ctx, batch, F, d, Q, lam, opts, info);
-    std::vector<int> sweep;
+    const int max_sweeps = opts ? opts->max_sweeps : 0;
+    std::vector<StartBasis> start(batch);
+    std::vector<int> sweep, rest(batch);
+    for (int i = 0; i < batch; ++i) rest[i] = i;
+    bool decided = false;
     if (opts && opts->warm_start != 0) {
         std::vector<int> which;
-        std::vector<StartBasis> start(batch);
         for (int i = 0; i < batch; ++i)
             if (d[i] > KFAC_EIG_SMALL) which.push_back(i);
         if (!which.empty()) KFAC_CHECK(probe_start_bases(ctx, which, F, d, Q, start));
-        sweep = choose_sweeps(ctx, batch, d, start, tol);
+        sweep = choose_sweeps(ctx, batch, d, start, tol, max_sweeps);
+        decided = true;
+    }
+    // from the identity: by the norms that the direct route forms at its beginning
+    const std::function<bool()> few_sweeps = [&]() {
+        for (int i = 0; i < batch; ++i) {
+            const double off2 = ctx->pinned[4 * i], f2 = off2 + ctx->pinned[4 * i + 1];
+            start[i].rel = f2 > 0.0 && f2 < 1e300 ? std::sqrt(off2 / f2) : (f2 == 0.0 ? 0.0 : -1.0);
+            start[i].lost = start[i].rel > 1e-2 ? 1.0 : 0.0;
+        }
+        sweep = choose_sweeps(ctx, batch, d, start, tol, max_sweeps);
+        return sweep.empty();
+    };
+    if (!decided) {
+        EigPart D(rest, F, d, Q, lam);
+        const int rc = run_direct(ctx, D, opts, tol, &few_sweeps);
+        if (rc == KFAC_OK || rc == KFAC_ENOCONV) D.report(info);
+        if (rc != KFAC_EIG_STOPPED) return rc;
     }
     std::vector<char> done(batch, 0);
     if (!sweep.empty()) {
@@ -287,12 +315,12 @@ int kfac_launch_eig(kfac_ctx *ctx, int batch, const float *const *F, const int *
         J.report(info);
         for (int k = 0; k < J.size(); ++k) done[J.idx[k]] = J.info[k].converged != 0;    // (max_sweeps may be less than it took)
     }
-    std::vector<int> rest;
+    rest.clear();
     for (int i = 0; i < batch; ++i)
         if (!done[i]) rest.push_back(i);
     if (rest.empty()) return KFAC_OK;
     EigPart D(rest, F, d, Q, lam);
-    const int rc = run_direct(ctx, D, opts, tol);
+    const int rc = run_direct(ctx, D, opts, tol, nullptr);
     if (rc == KFAC_OK || rc == KFAC_ENOCONV) D.report(info);
     return rc;
 }

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <functional>
 #include <vector>
 #include "../../include/kfac.h"
 
@@ -98,6 +99,7 @@ int kfac_upload(kfac_ctx *ctx, void *dst_dev, const void *src_host, size_t bytes
 // Tiling constants shared between host-side sizing and kernels.
 constexpr int KFAC_TILE = 128;       // GEMM / SYRK output tile edge
 constexpr int KFAC_EIG_SMALL = 128;  // factors up to this size are solved inside one workgroup's LDS
+constexpr int KFAC_EIG_REG = 256;    // factors up to this size are reduced to tridiagonal form inside one workgroup's registers
 constexpr int KFAC_EIG_B = 32;       // block size of the blocked Jacobi path (sub-problems are 2B x 2B)
 constexpr int KFAC_MAX_D = 8192;
 constexpr int KFAC_EIG_SPLIT_MIN = 2048;   // factors from here on use split-fp16 products where an option allows them
@@ -133,7 +135,8 @@ int kfac_launch_eig_jacobi(kfac_ctx *ctx, int batch, const float *const *F, cons
                            const kfac_eig_opts *opts, kfac_eig_info *info);
 double kfac_eig_direct_seconds(int batch, const int *d);
 int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
-                           bool fp32_only, double *stat /* pinned, 4 per factor */);
+                           bool fp32_only, double diag_tol, double *stat /* pinned, 4 per factor */, const std::function<bool()> *go_on);
+constexpr int KFAC_EIG_STOPPED = 1;  // its result if go_on() said no
 size_t kfac_invert_ws_bytes_impl(int batch, const int *d);
 int kfac_launch_invert_factors(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float damping, float *const *Finv);
 size_t kfac_precondition_inverse_ws_bytes_impl(int n, const kfac_precond_inv_item *items);

@@ -4,6 +4,8 @@ Tolerances (the benchmark spec): factors and preconditioned gradients rela
 <= 1e-4 in fp32 (<= 2e-2 with bf16 inputs); eigenpairs: ||F - Q diag(lam) Q^T||_F <= 1e-5 ||F||_F and
 eigenvalues within 1e-5 * lam_max of the oracle's; unfold is bit-exact (data movement only).
 """
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -317,6 +319,60 @@ def test_eig_warm_start_from_eigenvectors_that_still_hold(ctx):
     assert torch.equal(lam[7], torch.zeros_like(lam[7]))
     q = Q[7].double()
     assert float((q.T.contiguous() @ q - torch.eye(300, device=ctx.dev, dtype=torch.float64)).norm()) <= 300 * 2.0 ** -22
+
+
+def _eig_seconds(ctx, mats, **kw):
+    Fd = [ctx.to_dev(f) for f in mats]
+    Q, lam = [torch.empty_like(f) for f in Fd], [torch.empty(f.shape[0], device=ctx.dev) for f in Fd]
+    best = 1e9
+    for _ in range(6):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        info = K.kfac_eig(ctx.h, Fd, Q, lam, **kw)
+        best = min(best, time.perf_counter() - t)
+    return best, info, Q, lam
+
+
+@pytest.mark.parametrize("n", [64, 129, 256, 257, 577, 2100])
+@pytest.mark.parametrize("off", [0.0, 1e-7])
+def test_eig_diagonal_factor_costs_no_decomposition(ctx, n, off):
+    """A factor that is diagonal as it stands (to the tolerance): no sweep, sorted, and a fraction of the time that a dense one of
+    that size takes (an eighth to a half)."""
+    rng = np.random.default_rng(n)
+    dg = rng.permutation(np.linspace(0.1, 2.0, n))
+    E = rng.standard_normal((n, n))
+    F = (np.diag(dg) + off * np.linalg.norm(dg) / np.linalg.norm(E) * (E + E.T) / 2.0).astype(np.float32)
+    t, info, Q, lam = _eig_seconds(ctx, [F])
+    assert info[0][2] and info[0][0] == 0, info
+    check_eigpairs(F, lam[0].cpu().numpy(), Q[0].cpu().numpy(), "diagonal")
+    if off == 0.0:
+        assert np.array_equal(lam[0].cpu().numpy(), np.sort(np.diag(F)))
+    dense, _, _, _ = _eig_seconds(ctx, [gram_factor(n, 2 * n, seed=1)])
+    print("diagonal %.0f us, dense %.0f us" % (t * 1e6, dense * 1e6))
+    assert t < 0.65 * dense, (t, dense)
+
+
+def test_eig_diagonal_beside_dense_factors(ctx):
+    mats = [np.eye(n, dtype=np.float32) * 0.5 if i % 2 == 0 else gram_factor(n, 2 * n, seed=i) for i, n in enumerate([577, 300, 64, 64, 200, 200, 1, 130])]
+    Ld, Qd, info = ctx.eig(mats)
+    assert all(c for (_, _, c) in info), info
+    for i, F in enumerate(mats):
+        check_eigpairs(F, Ld[i].cpu().numpy(), Qd[i].cpu().numpy(), "beside[%d]" % i)
+
+
+@pytest.mark.parametrize("n", [577, 1153])
+def test_eig_loose_tolerance_takes_few_sweeps(ctx, n):
+    """To 1e-2 a few sweeps are cheaper than a decomposition; a cap on them that is too low for that does not stand in its way."""
+    F = gram_factor(n, 2 * n, seed=n)
+    Ld, Qd, info = ctx.eig([F], tol=1e-2)
+    lam, Q = Ld[0].cpu().numpy().astype(np.float64), Qd[0].cpu().numpy().astype(np.float64)
+    assert info[0][2] and 1 < info[0][0] < 7 and info[0][1] <= 1e-2, info
+    F64 = F.astype(np.float64)
+    assert np.linalg.norm(F64 - (Q * lam) @ Q.T) <= 1.1e-2 * np.linalg.norm(F64)
+    assert np.linalg.norm(Q.T @ Q - np.eye(n), 2) <= 1e-4
+    Ld, Qd, info = ctx.eig([F], tol=1e-2, max_sweeps=1)
+    assert info[0][2] and info[0][0] == 1, info
+    check_eigpairs(F, Ld[0].cpu().numpy(), Qd[0].cpu().numpy(), "capped")
 
 
 def test_eig_max_sweeps_reports_noconv(ctx):
