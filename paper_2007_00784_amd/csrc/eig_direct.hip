@@ -43,7 +43,7 @@ constexpr int FUSE_MAX = 300;
 constexpr int WY = 128;           // reflectors of a compact WY block
 constexpr int WY_K = 512;         // contraction of one workgroup in Y = V^T Z
 constexpr int NPARTS = 64;         // parts of the Rayleigh quotients' sums
-constexpr int NORM_WGS = 256;      // workgroups per factor of the norms and copies
+constexpr int NORM_WGS = 256;      // workgroups per factor of the norms and copies: workgroup b has rows b, b + gridDim.x, ..; never more than rows
 constexpr double PERTURB_REL = 0x1p-25;   // of every element of T: half the rounding it already carries
 constexpr double PERTURB_ABS = 1e-10;     // of the Gershgorin bound, added to the diagonal: breaks multiple zeros
 constexpr double NS_AGAIN = 4e-6;         // ||I - Q^T Q||_F^2 from which one Newton-Schulz step is not enough (it leaves 3/4 of this)
@@ -71,8 +71,8 @@ struct DirMat {
     double2 *td;     // [np]: T perturbed and divided by its Gershgorin bound: {d_i, e_i^2}; |e_i| is kept away from zero
     double *te;      // [np]: e_i of the same; later 1 / norm of every eigenvector
     double *lam64;   // [np]: eigenvalues of T, later the Rayleigh quotients
-    double *sums;    // [NPARTS][3][np] partial sums of the Rayleigh quotients
-    double *npartd;  // [NORM_WGS][2] partial norms: off^2, diag^2; later of D and of the residual
+    double *sums;    // [min(NPARTS, n)][3][np] partial sums of the Rayleigh quotients
+    double *npartd;  // [NORM_WGS][2] partial norms: off^2, diag^2 of the first min(NORM_WGS, n); later of D and of the residual
     double *stat;    // off^2, diag^2, residual^2, ||I - Q^T Q||^2
     float *Tm;       // [nb][WY][WY]: Gram matrices of the WY blocks, then their T
     int *perm;       // [np]: final order of the eigenvectors
@@ -126,8 +126,9 @@ __global__ __launch_bounds__(256) void dir_norm_kernel(const DirMat *mats) {
     const DirMat M = mats[blockIdx.y];
     const global_ptr<const float> F = as_global(M.F);
     const int n = M.n;
+    if ((int)blockIdx.x >= n) return;
     double o2 = 0.0, d2 = 0.0;
-    for (int r = blockIdx.x; r < n; r += NORM_WGS)
+    for (int r = blockIdx.x; r < n; r += gridDim.x)
         for (int c = threadIdx.x; c < n; c += 256) {
             const double v = (double)F[(int64_t)r * n + c];
             if (c == r) d2 += v * v; else o2 += v * v;
@@ -149,8 +150,9 @@ __device__ inline float dir_norms(const DirMat &M, double &o2, double &d2) {
     o2 = d2 = 0.0;
 #pragma unroll
     for (int i = 0; i < NORM_WGS / 64; ++i) {
-        o2 += M.npartd[2 * (64 * i + lane)];
-        d2 += M.npartd[2 * (64 * i + lane) + 1];
+        const int w = 64 * i + lane;
+        o2 += w < M.n ? M.npartd[2 * w] : 0.0;
+        d2 += w < M.n ? M.npartd[2 * w + 1] : 0.0;
     }
     o2 = wave_sum_f64(o2);
     d2 = wave_sum_f64(d2);
@@ -205,7 +207,7 @@ __global__ __launch_bounds__(256) void dir_copy_kernel(const DirMat *mats) {
     if (blockIdx.x == 0)
         for (int i = n - 1 + (int)threadIdx.x; i < np; i += 256) M.tau[i] = 0.f;   // no reflectors there
     const global_ptr<const int> ord = as_global((const int *)M.ord);
-    for (int r = blockIdx.x; r < np; r += NORM_WGS) {
+    for (int r = blockIdx.x; r < np; r += gridDim.x) {
         const int64_t fr = r < n ? (int64_t)ord[r] * n : 0;
         for (int c = threadIdx.x; c < np; c += 256)
             A[(int64_t)r * M.ld + c] = (r < n && c < n) ? sc * F[fr + ord[c]] : 0.f;
@@ -704,7 +706,7 @@ __global__ __launch_bounds__(256) void dir_clear_kernel(const DirMat *mats) {
     const DirMat M = mats[blockIdx.y];
     if (M.n <= TD_SMALL) return;
     const global_ptr<float> A = as_global(M.A);
-    for (int r = blockIdx.x; r < M.np; r += NORM_WGS) {
+    for (int r = blockIdx.x; r < M.np; r += gridDim.x) {
         const int end = r >= M.n - 1 ? M.np : r + 1;
         for (int c = threadIdx.x; c < end; c += 256) A[(int64_t)r * M.ld + c] = 0.f;
     }
@@ -1161,9 +1163,10 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 // ||I - Q^T Q||_F^2 (four times that of D), per workgroup
 __global__ __launch_bounds__(256) void dir_dev_kernel(const DirMat *mats) {
     const DirMat M = mats[blockIdx.y];
+    if ((int)blockIdx.x >= M.n) return;
     const global_ptr<const float> D = as_global((const float *)M.B1);
     double s = 0.0;
-    for (int r = blockIdx.x; r < M.n; r += NORM_WGS)
+    for (int r = blockIdx.x; r < M.n; r += gridDim.x)
         for (int c = threadIdx.x; c < M.n; c += 256) {
             const double v = (double)D[(int64_t)r * M.ld + c];
             s += v * v;
@@ -1180,7 +1183,7 @@ __global__ __launch_bounds__(64) void dir_dev_sum_kernel(const DirMat *mats) {
     const DirMat M = mats[blockIdx.x];
     double dev = 0.0;
 #pragma unroll
-    for (int i = 0; i < NORM_WGS / 64; ++i) dev += M.npartd[64 * i + (int)threadIdx.x];
+    for (int i = 0; i < NORM_WGS / 64; ++i) dev += 64 * i + (int)threadIdx.x < M.n ? M.npartd[64 * i + (int)threadIdx.x] : 0.0;
     dev = wave_sum_f64(dev);
     if (threadIdx.x == 0) M.stat[3] = dev;
 }
@@ -1189,7 +1192,7 @@ __global__ __launch_bounds__(64) void dir_dev_sum_kernel(const DirMat *mats) {
 __global__ __launch_bounds__(256) void dir_rayleigh_kernel(const DirMat *mats) {
     const DirMat M = mats[blockIdx.z];
     const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= M.n) return;
+    if (c >= M.n || (int)blockIdx.y >= M.n) return;
     const global_ptr<const float> Q = as_global((const float *)final_q(M)) + c, FQ = as_global((const float *)M.B1) + c;
     const int per = (M.n + NPARTS - 1) / NPARTS, r0 = blockIdx.y * per, r1 = min(M.n, r0 + per);
     double s1 = 0.0, s2 = 0.0, s3 = 0.0;
@@ -1211,7 +1214,7 @@ __global__ __launch_bounds__(256) void dir_lambda_kernel(const DirMat *mats) {
     double res = 0.0;
     if (c < M.n) {
         double s1 = 0.0, s2 = 0.0, s3 = 0.0;
-        for (int p = 0; p < NPARTS; ++p) {
+        for (int p = 0; p < min(NPARTS, M.n); ++p) {
             const double *o = M.sums + (int64_t)p * 3 * M.np + c;
             s1 += o[0];
             s2 += o[M.np];
@@ -1276,7 +1279,7 @@ __global__ __launch_bounds__(256) void dir_gather_kernel(const DirMat *mats) {
     const global_ptr<float> Q = as_global(M.Q);
     const global_ptr<const double> unit = as_global((const double *)M.te);
     const global_ptr<const int> perm = as_global((const int *)M.perm);
-    for (int r = blockIdx.x; r < n; r += NORM_WGS)
+    for (int r = blockIdx.x; r < n; r += gridDim.x)
         for (int c = threadIdx.x; c < n; c += 256) {
             const int p = perm[c];
             Q[(int64_t)r * n + c] = bad ? nan : S[(int64_t)r * M.ld + p] * (float)unit[p];
@@ -1290,9 +1293,10 @@ struct DirSize { int n, np, ld, nb; };
 DirSize dir_size(int n) {
     DirSize s;
     s.n = n;
-    s.np = (n + TB - 1) / TB * TB;
-    s.ld = s.np + 32;         // not a multiple of 128: rows of one tile then start in different channels
-    s.nb = s.np / TB;
+    s.nb = (n + TB - 1) / TB;
+    // the chain's kernels take whole tiles; the register kernels and the products look at n alone
+    s.np = n > TD_SMALL ? s.nb * TB : (n + 15) / 16 * 16;
+    s.ld = s.np > 64 ? s.np + 32 : s.np;         // not a multiple of 128: rows of one tile then start in different channels
     return s;
 }
 
@@ -1321,7 +1325,7 @@ size_t dir_layout(const DirSize &s, char *p, DirMat *M) {
     d.td = (double2 *)take((size_t)s.np * sizeof(double2));
     d.te = (double *)take((size_t)s.np * sizeof(double));
     d.lam64 = (double *)take((size_t)s.np * sizeof(double));
-    d.sums = (double *)take((size_t)NPARTS * 3 * s.np * sizeof(double));
+    d.sums = (double *)take((size_t)std::min(NPARTS, s.n) * 3 * s.np * sizeof(double));
     d.npartd = (double *)take((size_t)2 * NORM_WGS * sizeof(double));
     if (s.n > TD_SMALL) d.Tm = (float *)take((size_t)s.nb * WY * WY * sizeof(float));
     d.perm = (int *)take((size_t)s.np * sizeof(int));
@@ -1450,9 +1454,10 @@ void enqueue_copy(kfac_ctx *ctx, const DirRun &R) {
     const hipStream_t st = R.st;
     const unsigned batch = (unsigned)P.mats.size();
     KfacProfScope prof(ctx, KC_EIG_MISC, 0.0, 8.0 * R.square, st);
-    hipLaunchKernelGGL(dir_norm_kernel, dim3(NORM_WGS, batch), dim3(256), 0, st, R.dm);
+    const unsigned wgs = (unsigned)std::min(NORM_WGS, P.nmax);
+    hipLaunchKernelGGL(dir_norm_kernel, dim3(wgs, batch), dim3(256), 0, st, R.dm);
     hipLaunchKernelGGL(dir_order_kernel, dim3((P.nmax + RANK_IPB - 1) / RANK_IPB, batch), dim3(256), 0, st, R.dm);
-    hipLaunchKernelGGL(dir_copy_kernel, dim3(NORM_WGS, batch), dim3(256), 0, st, R.dm);
+    hipLaunchKernelGGL(dir_copy_kernel, dim3(P.nmax > TD_SMALL ? wgs : 1, batch), dim3(256), 0, st, R.dm);
 }
 
 void enqueue_small(kfac_ctx *ctx, const DirRun &R) {
@@ -1503,12 +1508,12 @@ int enqueue_finish(kfac_ctx *ctx, const DirRun &R) {
     const DirPlan &P = R.P;
     const hipStream_t st = R.st;
     const unsigned batch = (unsigned)P.mats.size();
-    const dim3 per_mat(NORM_WGS, batch);
+    const dim3 per_mat((unsigned)std::min(NORM_WGS, P.nmax), batch);
     const DirMat *dm = R.dm;
     const unsigned *tab = R.tab;
     {
         KfacProfScope prof(ctx, KC_EIG_TRI, 0.0, 0.0, st);
-        hipLaunchKernelGGL(dir_clear_kernel, per_mat, dim3(256), 0, st, dm);
+        if (P.nmax > TD_SMALL) hipLaunchKernelGGL(dir_clear_kernel, per_mat, dim3(256), 0, st, dm);
         hipLaunchKernelGGL(dir_scale_t_kernel, dim3(batch), dim3(256), 0, st, dm);
         // sixteen lanes per eigenvalue do 9/4 of the work of four in 4/7 of the passes: right where four leave the chip idle
         if (P.values.count <= BIS_WIDE_MAX)
@@ -1542,7 +1547,7 @@ int enqueue_finish(kfac_ctx *ctx, const DirRun &R) {
             if (P.any_split) hipLaunchKernelGGL((dir_product_kernel<ORTH, true>), lo, b, 0, st, dm, tl, second);
             if (P.any_plain) hipLaunchKernelGGL((dir_product_kernel<ORTH, false>), lo, b, 0, st, dm, tl, second);
             if (!second) {
-                hipLaunchKernelGGL(dir_dev_kernel, dim3(NORM_WGS, batch), dim3(256), 0, st, dm);
+                hipLaunchKernelGGL(dir_dev_kernel, per_mat, dim3(256), 0, st, dm);
                 hipLaunchKernelGGL(dir_dev_sum_kernel, dim3(batch), dim3(64), 0, st, dm);
             }
             if (P.any_split) hipLaunchKernelGGL((dir_product_kernel<STEP, true>), fu, b, 0, st, dm, tf, second);
@@ -1552,7 +1557,7 @@ int enqueue_finish(kfac_ctx *ctx, const DirRun &R) {
     }
     {
         KfacProfScope prof(ctx, KC_EIG_MISC, 0.0, 16.0 * R.square, st);
-        hipLaunchKernelGGL(dir_rayleigh_kernel, dim3((P.nmax + 255) / 256, NPARTS, batch), dim3(256), 0, st, dm);
+        hipLaunchKernelGGL(dir_rayleigh_kernel, dim3((P.nmax + 255) / 256, std::min(NPARTS, P.nmax), batch), dim3(256), 0, st, dm);
         hipLaunchKernelGGL(dir_lambda_kernel, dim3((P.nmax + 255) / 256, batch), dim3(256), 0, st, dm);
         hipLaunchKernelGGL(dir_rank_kernel, dim3((P.nmax + RANK_IPB - 1) / RANK_IPB, batch), dim3(256), 0, st, dm);
         hipLaunchKernelGGL(dir_gather_kernel, per_mat, dim3(256), 0, st, dm);

@@ -64,3 +64,12 @@ def test_workspace_query_covers_every_operand_form():
                         it = dict(X=None, dtype=dtype, layout=layout, N=N, d=d - 1, T=T, append_ones=1, scale=1.0, decay=0.0, F=None)
                         need = K.kfac_update_factors_workspace_bytes([it])
                         assert 0 < need <= cap, (d, R, dtype, T, layout, need, cap)
+
+
+def test_eig_workspace_of_many_small_factors():
+    """What small factors take in the workspace follows their size: about 16 n^2 bytes of matrices and some vectors, not
+    the tiles that the wide ones are cut into (which was half a megabyte for a factor of 8 as for one of 128)."""
+    for n in (1, 8, 16, 33, 64):
+        one = K.kfac_eig_workspace_bytes([n])
+        assert one <= 16 * (n + 16) ** 2 + 1700 * n + 8192, (n, one)
+        assert K.kfac_eig_workspace_bytes([n] * 1000) <= 1000 * one
