@@ -1439,11 +1439,9 @@ size_t dir_table_bound(int batch, const int *d) {
     return t;
 }
 
-// One group of factors on its stream.
+// The factors of a call, on the context's stream.
 struct DirRun {
     DirPlan P;
-    std::vector<int> members;      // indices of the call
-    hipStream_t st;
     const DirMat *dm;
     const unsigned *tab;
     double cube = 0.0, square = 0.0;
@@ -1451,7 +1449,7 @@ struct DirRun {
 
 void enqueue_copy(kfac_ctx *ctx, const DirRun &R) {
     const DirPlan &P = R.P;
-    const hipStream_t st = R.st;
+    const hipStream_t st = ctx->stream;
     const unsigned batch = (unsigned)P.mats.size();
     KfacProfScope prof(ctx, KC_EIG_MISC, 0.0, 8.0 * R.square, st);
     const unsigned wgs = (unsigned)std::min(NORM_WGS, P.nmax);
@@ -1462,7 +1460,7 @@ void enqueue_copy(kfac_ctx *ctx, const DirRun &R) {
 
 void enqueue_small(kfac_ctx *ctx, const DirRun &R) {
     const DirPlan &P = R.P;
-    const hipStream_t st = R.st;
+    const hipStream_t st = ctx->stream;
     for (int k = 0; k < 4; ++k) {
         if (P.small[k].empty()) continue;
         const dim3 grid((unsigned)P.small[k].size());
@@ -1480,7 +1478,7 @@ void enqueue_small(kfac_ctx *ctx, const DirRun &R) {
 }
 
 void enqueue_step(kfac_ctx *ctx, const DirRun &R, int t) {
-    const hipStream_t st = R.st;
+    const hipStream_t st = ctx->stream;
     const DirPlan::Range tiles = R.P.tiles[t / NB], rows = R.P.rows[t / NB];
     if (t % NB == 0) {
         if (t > 0) {
@@ -1506,7 +1504,7 @@ void enqueue_step(kfac_ctx *ctx, const DirRun &R, int t) {
 
 int enqueue_finish(kfac_ctx *ctx, const DirRun &R) {
     const DirPlan &P = R.P;
-    const hipStream_t st = R.st;
+    const hipStream_t st = ctx->stream;
     const unsigned batch = (unsigned)P.mats.size();
     const dim3 per_mat((unsigned)std::min(NORM_WGS, P.nmax), batch);
     const DirMat *dm = R.dm;
@@ -1566,18 +1564,6 @@ int enqueue_finish(kfac_ctx *ctx, const DirRun &R) {
     return KFAC_OK;
 }
 
-int run_groups(kfac_ctx *ctx, std::vector<DirRun> &runs) {
-    int steps = 0;
-    for (DirRun &R : runs) steps = std::max(steps, R.P.steps);
-    // the chains are fed in turn, step by step: the host is not much faster than the device
-    for (int t = 0; t <= steps; ++t)
-        for (DirRun &R : runs) {
-            if (t < R.P.steps) enqueue_step(ctx, R, t);
-            else if (t == R.P.steps) KFAC_CHECK(enqueue_finish(ctx, R));
-        }
-    return KFAC_OK;
-}
-
 }  // namespace
 
 size_t kfac_eig_direct_ws_bytes(int batch, const int *d) {
@@ -1611,51 +1597,34 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
     double *d_stat = (double *)(ctx->ws + kfac_align_up((size_t)batch * sizeof(DirMat), 256));
     unsigned *d_tab = (unsigned *)((char *)d_stat + kfac_align_up((size_t)batch * 4 * sizeof(double), 256));
     char *p = (char *)d_tab + kfac_align_up(dir_table_bound(batch, d) * sizeof(unsigned), 256);
-    std::vector<std::vector<int>> groups;
-    groups.emplace_back(batch);
-    for (int i = 0; i < batch; ++i) groups[0][i] = i;
-    std::vector<DirRun> runs(groups.size());
-    std::vector<DirMat> mats;
-    std::vector<unsigned> tab;
-    for (size_t g = 0; g < groups.size(); ++g) {
-        DirRun &R = runs[g];
-        R.members = groups[g];
-        R.st = groups.size() > 1 ? ctx->aux[g] : ctx->stream;
-        R.dm = d_mats + mats.size();
-        R.tab = d_tab + tab.size();
-        for (int i : R.members) {
-            DirMat M;
-            p += dir_layout(dir_size(d[i]), p, &M);
-            M.F = F[i];
-            M.Q = Q[i];
-            M.lam = lam[i];
-            M.stat = d_stat + 4 * i;
-            M.diag_tol2 = diag_tol * diag_tol;
-            M.split = !fp32_only && d[i] >= KFAC_EIG_SPLIT_MIN;
-            (M.split ? R.P.any_split : R.P.any_plain) = true;
-            R.P.mats.push_back(M);
-            R.cube += (double)d[i] * d[i] * d[i];
-            R.square += (double)d[i] * d[i];
-        }
-        dir_tables(R.P);
-        mats.insert(mats.end(), R.P.mats.begin(), R.P.mats.end());
-        tab.insert(tab.end(), R.P.tab.begin(), R.P.tab.end());
+    DirRun R;
+    R.dm = d_mats;
+    R.tab = d_tab;
+    R.P.mats.resize(batch);
+    for (int i = 0; i < batch; ++i) {
+        DirMat &M = R.P.mats[i];
+        p += dir_layout(dir_size(d[i]), p, &M);
+        M.F = F[i];
+        M.Q = Q[i];
+        M.lam = lam[i];
+        M.stat = d_stat + 4 * i;
+        M.diag_tol2 = diag_tol * diag_tol;
+        M.split = !fp32_only && d[i] >= KFAC_EIG_SPLIT_MIN;
+        (M.split ? R.P.any_split : R.P.any_plain) = true;
+        R.cube += (double)d[i] * d[i] * d[i];
+        R.square += (double)d[i] * d[i];
     }
-    KFAC_CHECK(kfac_upload(ctx, d_mats, mats.data(), mats.size() * sizeof(DirMat)));
-    KFAC_CHECK(kfac_upload(ctx, d_tab, tab.data(), tab.size() * sizeof(unsigned)));
-    // the groups' streams start after what is queued on the caller's stream, which goes on after all of them: on an error,
-    // too, so that no kernel of this call is in flight after the return
-    if (groups.size() > 1) {
-        KFAC_HIP_CHECK(hipEventRecord(ctx->ev_fork, ctx->stream));
-        for (DirRun &R : runs) KFAC_HIP_CHECK(hipStreamWaitEvent(R.st, ctx->ev_fork, 0));
-    }
-    for (DirRun &R : runs) enqueue_copy(ctx, R);
-    const bool ask = go_on && runs[0].P.nmax > TD_SMALL;
+    R.P.tab.reserve(dir_table_bound(batch, d));
+    dir_tables(R.P);
+    KFAC_CHECK(kfac_upload(ctx, d_mats, R.P.mats.data(), R.P.mats.size() * sizeof(DirMat)));
+    KFAC_CHECK(kfac_upload(ctx, d_tab, R.P.tab.data(), R.P.tab.size() * sizeof(unsigned)));
+    enqueue_copy(ctx, R);
+    const bool ask = go_on && R.P.nmax > TD_SMALL;
     if (ask) {   // the register kernels run while the host decides
         KFAC_HIP_CHECK(hipMemcpyAsync(stat, d_stat, (size_t)batch * 4 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
         KFAC_HIP_CHECK(hipEventRecord(ctx->ev_group[0], ctx->stream));
     }
-    for (DirRun &R : runs) enqueue_small(ctx, R);
+    enqueue_small(ctx, R);
     if (ask) {
         const bool waited = hipEventSynchronize(ctx->ev_group[0]) == hipSuccess;
         if (!waited || !(*go_on)()) {
@@ -1663,16 +1632,10 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
             return KFAC_EIG_STOPPED;
         }
     }
-    int rc = run_groups(ctx, runs);
-    if (groups.size() > 1)
-        for (size_t g = 0; g < groups.size(); ++g)
-            if (hipEventRecord(ctx->ev_join[g], runs[g].st) != hipSuccess ||
-                hipStreamWaitEvent(ctx->stream, ctx->ev_join[g], 0) != hipSuccess) {
-                (void)hipStreamSynchronize(runs[g].st);
-                rc = KFAC_EHIP;
-            }
+    for (int t = 0; t < R.P.steps; ++t) enqueue_step(ctx, R, t);
+    int rc = enqueue_finish(ctx, R);
     if (rc == KFAC_OK && hipMemcpyAsync(stat, d_stat, (size_t)batch * 4 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess)
         rc = KFAC_EHIP;
-    if (hipStreamSynchronize(ctx->stream) != hipSuccess) rc = KFAC_EHIP;
+    if (hipStreamSynchronize(ctx->stream) != hipSuccess) rc = KFAC_EHIP;    // on an error, too: no kernel of this call is in flight after the return
     return rc;
 }
