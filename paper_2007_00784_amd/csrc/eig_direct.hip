@@ -1214,11 +1214,23 @@ __global__ __launch_bounds__(256) void dir_lambda_kernel(const DirMat *mats) {
     double res = 0.0;
     if (c < M.n) {
         double s1 = 0.0, s2 = 0.0, s3 = 0.0;
-        for (int p = 0; p < min(NPARTS, M.n); ++p) {
-            const double *o = M.sums + (int64_t)p * 3 * M.np + c;
-            s1 += o[0];
-            s2 += o[M.np];
-            s3 += o[2 * M.np];
+        const int parts = min(NPARTS, M.n);
+        for (int p0 = 0; p0 < parts; p0 += 16) {     // sixteen parts' loads at a time
+            double v[16][3];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const double *o = M.sums + (int64_t)min(p0 + u, parts - 1) * 3 * M.np + c;
+                v[u][0] = o[0];
+                v[u][1] = o[M.np];
+                v[u][2] = o[2 * M.np];
+            }
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const bool in = p0 + u < parts;
+                s1 += in ? v[u][0] : 0.0;
+                s2 += in ? v[u][1] : 0.0;
+                s3 += in ? v[u][2] : 0.0;
+            }
         }
         const double l = s1 / s3;
         M.lam64[c] = l;
