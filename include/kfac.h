@@ -66,11 +66,11 @@ typedef struct {
                                 rounding, except where a few Jacobi sweeps meet tol sooner (a factor that is diagonal
                                 or nearly so, a loose tol); a smaller tol, or a factor whose direct result misses tol,
                                 asks for Jacobi sweeps until the rotated matrix meets it.          */
-    int fp32_only;           /* 0 (default): for d >= 2048 the orthogonalisation products (and, in Jacobi sweeps, the
-                                rank-256 update passes) run as split-fp16 MFMA products (hi + lo halves, three
-                                products per fp32 product, fp32 accumulation): same tolerances met, errors bounded
-                                normwise (relative to ||F||_F).  1: every product on the fp32 MFMA path: slower, keeps
-                                fp32's elementwise accuracy on strongly graded spectra.            */
+    int fp32_only;           /* 0 (default): errors bounded normwise (relative to ||F||_F); for d >= 2048 the
+                                orthogonalisation products (and, in Jacobi sweeps, the rank-256 update passes) run as
+                                split-fp16 MFMA products (hi + lo halves, three products per fp32 product, fp32
+                                accumulation): same tolerances met.  1: Jacobi sweeps with every product on the fp32
+                                MFMA path: slower, keeps fp32's elementwise accuracy on strongly graded spectra.  */
     int warm_start;          /* 1: on entry every Q_i with d_i > 128 holds an orthonormal basis to start from
                                 (typically the eigenvectors of the previous decomposition of a slowly moving
                                 factor: the remark of Sec. V-C that the FIM becomes more stable as training progresses).

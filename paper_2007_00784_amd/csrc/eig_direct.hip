@@ -1603,7 +1603,7 @@ double kfac_eig_direct_seconds(int batch, const int *d) {
 // diag_tol: off(F)_F / ||F||_F up to which a factor counts as diagonal.  go_on (may be null): called, if a factor is wider than
 // KFAC_EIG_REG, once off^2 and diag^2 of all factors are in stat; if it returns false, nothing more is done (KFAC_EIG_STOPPED).
 int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
-                           bool fp32_only, double diag_tol, double *stat, const std::function<bool()> *go_on) {
+                           double diag_tol, double *stat, const std::function<bool()> *go_on) {
     if (kfac_eig_direct_ws_bytes(batch, d) > ctx->ws_bytes) return KFAC_EWORKSPACE;
     DirMat *d_mats = (DirMat *)ctx->ws;
     double *d_stat = (double *)(ctx->ws + kfac_align_up((size_t)batch * sizeof(DirMat), 256));
@@ -1621,7 +1621,7 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
         M.lam = lam[i];
         M.stat = d_stat + 4 * i;
         M.diag_tol2 = diag_tol * diag_tol;
-        M.split = !fp32_only && d[i] >= KFAC_EIG_SPLIT_MIN;
+        M.split = d[i] >= KFAC_EIG_SPLIT_MIN;
         (M.split ? R.P.any_split : R.P.any_plain) = true;
         R.cube += (double)d[i] * d[i] * d[i];
         R.square += (double)d[i] * d[i];

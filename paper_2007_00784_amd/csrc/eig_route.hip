@@ -240,8 +240,7 @@ int run_direct(kfac_ctx *ctx, EigPart &P, const kfac_eig_opts *opts, double tol,
     if ((size_t)batch * 4 * sizeof(double) > ctx->pinned_bytes) return KFAC_EINVAL;
     const double *stat = ctx->pinned;
     const double max_res = std::min(tol, DIRECT_MAX_RES);
-    const int drc = kfac_launch_eig_direct(ctx, batch, P.F.data(), P.d.data(), P.Q.data(), P.lam.data(), opts && opts->fp32_only != 0, max_res,
-                                           ctx->pinned, go_on);
+    const int drc = kfac_launch_eig_direct(ctx, batch, P.F.data(), P.d.data(), P.Q.data(), P.lam.data(), max_res, ctx->pinned, go_on);
     if (drc != KFAC_OK) return drc;
     std::vector<int> left;
     bool bad = false;
@@ -274,9 +273,12 @@ size_t kfac_eig_ws_bytes_impl(int batch, const int *d) {
 int kfac_launch_eig(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q,
                     float *const *lam, const kfac_eig_opts *opts, kfac_eig_info *info) {
     const float tol = (opts && opts->tol > 0.f) ? opts->tol : 2e-6f;
-    // (small factors are solved in LDS by Jacobi iteration, with no workspace to speak of: 1000 factors of 128 in 48 KB, where the
-    // direct route takes hundreds of MB; a workspace sized for that is served as well)
-    if (tol < DIRECT_TOL_MIN || kfac_eig_direct_ws_bytes(batch, d) > ctx->ws_bytes)
+    // fp32_only asks for small eigenvalues to be accurate on their own scale.  Jacobi rotations keep that on a graded matrix, a
+    // Householder reduction rounds at the scale of ||F||: eigenvalues down to 1e-9 of the largest of a 300-wide factor whose features
+    // span four decades, 3e-6 off at most after sweeps, 7e-3 after a reduction.
+    // (Small factors are solved in LDS by Jacobi iteration, with no workspace to speak of: 1000 factors of 128 in 48 KB, where the
+    // direct route takes hundreds of MB; a workspace sized for that is served as well.)
+    if (tol < DIRECT_TOL_MIN || (opts && opts->fp32_only != 0) || kfac_eig_direct_ws_bytes(batch, d) > ctx->ws_bytes)
         return kfac_launch_eig_jacobi(ctx, batch, F, d, Q, lam, opts, info);
     const int max_sweeps = opts ? opts->max_sweeps : 0;
     std::vector<StartBasis> start(batch);

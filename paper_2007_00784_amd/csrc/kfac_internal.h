@@ -135,7 +135,7 @@ int kfac_launch_eig_jacobi(kfac_ctx *ctx, int batch, const float *const *F, cons
                            const kfac_eig_opts *opts, kfac_eig_info *info);
 double kfac_eig_direct_seconds(int batch, const int *d);
 int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
-                           bool fp32_only, double diag_tol, double *stat /* pinned, 4 per factor */, const std::function<bool()> *go_on);
+                           double diag_tol, double *stat /* pinned, 4 per factor */, const std::function<bool()> *go_on);
 constexpr int KFAC_EIG_STOPPED = 1;  // its result if go_on() said no
 size_t kfac_invert_ws_bytes_impl(int batch, const int *d);
 int kfac_launch_invert_factors(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float damping, float *const *Finv);

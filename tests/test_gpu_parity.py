@@ -529,6 +529,26 @@ def test_eig_in_a_workspace_that_holds_jacobi_sweeps_only(sizes, ws):
         check_eigpairs(F, Ld[i].cpu().numpy(), Qd[i].cpu().numpy(), "little workspace[%d]" % i)
 
 
+@pytest.mark.parametrize("n", [300, 577])
+def test_eig_fp32_only_keeps_small_eigenvalues_of_a_graded_factor(ctx, n):
+    """Features scaled over four decades: with fp32_only, eigenvalues down to 1e-9 of the largest are accurate on their own
+    scale (a reduction to tridiagonal form leaves some of them 1e-2 and more off).  Rotations keep that scale; what is left is
+    the off-diagonal norm at which the sweeps stop, 2e-6 ||F||: all of it in one entry beside the largest eigenvalue would move one
+    of 1e-9 by (2e-6)^2 / 1e-9 of itself.  (Measured: 1.4e-4 at 300.)  An fp64 solver resolves them to 1e-6."""
+    rng = np.random.default_rng(n)
+    d = 10.0 ** rng.uniform(-4, 0, n)
+    F = (gram_factor(n, 3 * n, seed=n, ones=False).astype(np.float64) * d[:, None] * d[None, :]).astype(np.float32)
+    Ld, Qd, info = ctx.eig([F], fp32_only=True)
+    lam = Ld[0].cpu().numpy().astype(np.float64)
+    assert info[0][2], info
+    check_eigpairs(F, lam, Qd[0].cpu().numpy(), "graded fp32")
+    ref = np.linalg.eigvalsh(F.astype(np.float64))
+    sel = ref > 1e-9 * ref.max()
+    err = np.abs(lam - ref)[sel] / ref[sel]
+    print("%d eigenvalues, largest relative error %.1e" % (sel.sum(), err.max()))
+    assert err.max() <= 4e-3
+
+
 def test_eig_direct_many_large_factors(ctx):
     """Large and small factors in one call, launches beyond and below the tiles of a fused one: every result as good as
     a single factor's, and complete when the call returns."""
