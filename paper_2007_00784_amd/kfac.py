@@ -373,8 +373,8 @@ def kfac_profile_begin(ctx):
 
 def kfac_profile_end(ctx):
     """Returns {kernel class: dict(launches, ms, flops, bytes)} for the launches since kfac_profile_begin."""
-    out = (kfac_kernel_stat * 16)()
+    out = (kfac_kernel_stat * 64)()     # more than there are kernel classes
     n = ctypes.c_int(0)
-    _check(lib().kfac_profile_end(ctx, out, 16, ctypes.byref(n)), "kfac_profile_end")
+    _check(lib().kfac_profile_end(ctx, out, len(out), ctypes.byref(n)), "kfac_profile_end")
     return {out[i].name.decode(): dict(launches=out[i].launches, ms=out[i].ms, flops=out[i].flops, bytes=out[i].bytes)
             for i in range(n.value)}

@@ -946,3 +946,32 @@ def test_invalid_arguments_are_rejected(ctx):
         K.kfac_eig(small.h, [big], [torch.empty_like(big)], [torch.empty(300, device=ctx.dev)])
     assert e.value.code == K.KFAC_EWORKSPACE
     small.close()
+
+
+# ------------------------------------------------------------------ per-kernel timing
+def test_profile_reports_every_kernel_class(ctx):
+    """One stretch of calls that launches more kernel classes than sixteen: all of them come back."""
+    F = [ctx.to_dev(gram_factor(n, 2 * n, seed=n)) for n in (2100, 577, 100)]
+    Q, lam = [torch.empty_like(f) for f in F], [torch.empty(f.shape[0], device=ctx.dev) for f in F]
+    X = torch.randn((8, 20, 6, 6), device=ctx.dev)
+    P = torch.empty((8, 180, 36), device=ctx.dev)
+    grads = [torch.randn((100, 577), device=ctx.dev) for _ in range(2)]
+    inv = torch.empty_like(F[2])
+    K.kfac_profile_begin(ctx.h)
+    K.kfac_unfold(ctx.h, X, 3, 3, 1, 1, P)
+    for dt in (torch.float32, torch.bfloat16):
+        A = torch.empty((180, 180), device=ctx.dev)
+        K.kfac_update_factors(ctx.h, P.to(dt), K.KFAC_LAYOUT_NDT, 8, 180, 36, 0, 1.0 / 288, 0.0, A)
+    K.kfac_eig(ctx.h, F, Q, lam)
+    K.kfac_eig(ctx.h, F, Q, lam, tol=5e-7)
+    args = ([Q[1]] * 2, [lam[1]] * 2, [Q[2]] * 2, [lam[2]] * 2, 1e-2, grads)
+    K.kfac_precondition_batched_scaled(ctx.h, *args, kappa=1e-3, lr=0.1, nu=torch.empty(1, device=ctx.dev))
+    K.kfac_precondition_batched(ctx.h, *args, split_f16=True)
+    K.kfac_invert_factors(ctx.h, [F[2]], 0.1, [inv])
+    stats = K.kfac_profile_end(ctx.h)
+    want = {"unfold", "syrk", "syrk_bf16", "precond_gemm", "precond_gemm_split", "precond_scale", "factor_inverse", "eig_small", "eig_pivot_solve",
+            "eig_apply", "eig_outer_cols", "eig_outer_rows", "eig_post_gemm", "eig_misc", "eig_reduce_mv", "eig_reduce_vec", "eig_reduce_update",
+            "eig_tridiag_solve", "eig_back"}
+    assert want <= set(stats), want - set(stats)
+    for name, st in stats.items():
+        assert st["launches"] > 0 and st["ms"] > 0.0, (name, st)
