@@ -1903,8 +1903,8 @@ static int eig_run(kfac_ctx *ctx, int batch, const float *const *F, const int *d
             for (int i = 0; i < r.nm; ++i) {
                 const double o2 = hn[2 * i], n2 = o2 + hn[2 * i + 1];
                 r.offrel[i] = n2 > 0 ? (float)std::sqrt(o2 / n2) : 0.f;
-                const bool c = o2 <= (double)tol * tol * n2;   // false for NaN
                 r.bad[i] = !std::isfinite(n2);
+                const bool c = !r.bad[i] && o2 <= (double)tol * tol * n2;
                 all &= c || r.bad[i];
                 if (!r.bad[i]) worst = std::max(worst, r.offrel[i]);
                 if (R.final_ok) {   // no factor of a split-engine group counts as converged before the refresh

@@ -549,6 +549,47 @@ def test_eig_fp32_only_keeps_small_eigenvalues_of_a_graded_factor(ctx, n):
     assert err.max() <= 4e-3
 
 
+# Jacobi sweeps: what tolerances below 1e-6 and fp32_only ask for.  In LDS (64, 128), flat (129 to 640), two-level (2100).
+SWEEPS = [dict(tol=5e-7), dict(fp32_only=True)]
+
+
+@pytest.mark.parametrize("n,rows", [(2, 5), (64, 20), (128, 300), (129, 100), (145, 2048), (577, 300), (640, 900), (2100, 2500)])
+@pytest.mark.parametrize("kw", SWEEPS, ids=["tol", "fp32_only"])
+def test_eig_by_sweeps(ctx, n, rows, kw):
+    F = gram_factor(n, rows, seed=n + 5)
+    Ld, Qd, info = ctx.eig([F], **kw)
+    assert info[0][2] and info[0][0] >= min(n - 1, 3) and info[0][1] <= kw.get("tol", 2e-6), info
+    check_eigpairs(F, Ld[0].cpu().numpy(), Qd[0].cpu().numpy(), "sweeps")
+
+
+def test_eig_by_sweeps_mixed_sizes_repeatable_and_beside_nan(ctx):
+    """A batch over all three forms: every member's eigenpairs, the same bits again, and a factor with a NaN or an infinity only
+    spoils its own outputs, and says so."""
+    sizes = [(16, 50), (145, 500), (2100, 2600), (10, 3), (289, 100), (128, 64), (2300, 900), (289, 900), (577, 1500)]
+    mats = [gram_factor(n, r, seed=300 + i, ones=(i % 2 == 0)) for i, (n, r) in enumerate(sizes)]
+    L1, Q1, i1 = ctx.eig(mats, tol=5e-7)
+    L2, Q2, i2 = ctx.eig(mats, tol=5e-7)
+    assert i1 == i2 and all(c and s > 1 for (s, _, c) in i1), i1
+    for i, F in enumerate(mats):
+        assert torch.equal(L1[i], L2[i]) and torch.equal(Q1[i], Q2[i]), i
+        check_eigpairs(F, L1[i].cpu().numpy(), Q1[i].cpu().numpy(), "sweeps[%d]" % i)
+    bad = {0: np.nan, 1: np.nan, 2: np.inf, 4: np.inf, 5: np.inf, 6: np.nan}
+    for b, x in bad.items():
+        mats[b] = mats[b].copy()
+        mats[b][3, 5] = mats[b][5, 3] = x
+    for kw in (dict(tol=5e-7), dict()):        # by sweeps; directly
+        with pytest.raises(K.KfacError) as e:
+            ctx.eig(mats, **kw)
+        assert e.value.code == K.KFAC_ENOCONV
+        L3, Q3, i3 = ctx.eig(mats, raise_on_noconv=False, **kw)
+        for i in range(len(mats)):
+            if i in bad:
+                assert not i3[i][2] and not torch.isfinite(L3[i]).any() and not torch.isfinite(Q3[i]).any(), i
+            else:
+                assert i3[i][2] and float((L3[i] - L1[i]).abs().max()) <= TOL_LAM * float(L1[i].max()), i
+                check_eigpairs(mats[i], L3[i].cpu().numpy(), Q3[i].cpu().numpy(), "beside nan[%d]" % i)
+
+
 def test_eig_direct_many_large_factors(ctx):
     """Large and small factors in one call, launches beyond and below the tiles of a fused one: every result as good as
     a single factor's, and complete when the call returns."""
