@@ -217,7 +217,7 @@ __global__ __launch_bounds__(256) void dir_copy_kernel(const DirMat *mats) {
 // ---- reduction, one workgroup (n <= 256) -------------------------------------------------------------------
 // Four threads per row, each with KC columns of it in registers (groups of four: group k covers columns 16 k + 4 q ..).
 // The matrix never touches LDS; per column one row goes to LDS (it is the column, by symmetry), v and w are read
-// back by everybody.  A column costs three barriers and a few LDS latencies, 0.5 to 0.9 us.
+// back by everybody.  A column costs three barriers and a few LDS latencies: 1.0 us at 64, 1.9 at 145, 2.4 at 256.
 template <int KC>
 __global__ __launch_bounds__(16 * KC) void dir_td_small_kernel(const DirMat *mats, const int *list) {
     constexpr int G = KC / 4, NTH = 16 * KC, NW = NTH / 64, CMAX = 4 * KC;
@@ -713,7 +713,7 @@ __global__ __launch_bounds__(256) void dir_clear_kernel(const DirMat *mats) {
 }
 
 // ---- eigenvalues and eigenvectors of T ------------------------------------------------------------------------
-__device__ inline double hash_unit(int i) {   // in [-1, 1)
+__device__ inline double hash_unit(int i) {   // in [-1, 1): the output function of SplitMix64 (Steele, Lea, Flood 2014) and its constants
     unsigned long long z = (unsigned long long)(i + 1) * 0x9E3779B97F4A7C15ull;
     z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
     z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
@@ -1355,6 +1355,7 @@ struct DirPlan {
     struct Range { unsigned at, count; };
     int steps = 0;                        // of the reduction chain
     std::vector<Range> tiles, rows;       // per panel
+    std::vector<double> parts;            // per panel: partial products that its row blocks add up (64 rows each)
     std::vector<int> small[4];            // factors per register kernel: up to 64, 128, 192, 256
     unsigned small_at[4] = {0, 0, 0, 0};
     Range values{0, 0}, apply{0, 0}, gram{0, 0}, wyu{0, 0}, wyy{0, 0}, wys{0, 0}, wyz{0, 0}, lower{0, 0}, full{0, 0};
@@ -1380,6 +1381,7 @@ void dir_tables(DirPlan &P) {
         const int npanel = (P.steps + NB - 1) / NB;
         P.tiles.resize(npanel);
         P.rows.resize(npanel);
+        P.parts.assign(npanel, 0.0);
         for (int q = 0; q < npanel; ++q) {
             begin(P.tiles[q]);
             for (int m : order) {
@@ -1396,6 +1398,7 @@ void dir_tables(DirPlan &P) {
                 const int j = q * NB - M.off;
                 if (M.n <= TD_SMALL || j < 0 || j > M.n - 1) continue;
                 for (int r = j / TB * 2; r < 2 * M.nb; ++r) P.tab.push_back(pack(m, 0, r));
+                P.parts[q] += 2.0 * (M.nb - j / TB) * (M.nb - j / TB);
             }
             end(P.rows[q]);
         }
@@ -1497,7 +1500,7 @@ void enqueue_step(kfac_ctx *ctx, const DirRun &R, int t) {
             KfacProfScope prof(ctx, KC_EIG_REDUCE_GEMM, 2.0 * 2.0 * NB * TB * TB * tiles.count, 8.0 * TB * TB * tiles.count, st);
             hipLaunchKernelGGL(dir_update_kernel, dim3(tiles.count), dim3(NTHREADS), 0, st, R.dm, R.tab + tiles.at, t);
         }
-        KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 0.0, st);
+        KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 8.0 * RB * (NB + 1) * rows.count, st);
         hipLaunchKernelGGL(dir_column_kernel, dim3(rows.count), dim3(RB), 0, st, R.dm, R.tab + rows.at, t);
     }
     const double fl = 4.0 * TB * TB * tiles.count;
@@ -1509,7 +1512,8 @@ void enqueue_step(kfac_ctx *ctx, const DirRun &R, int t) {
         hipLaunchKernelGGL(dir_symv_kernel, dim3(tiles.count), dim3(256), 0, st, R.dm, R.tab + tiles.at, t);
     }
     if ((int)tiles.count > FUSE_MAX || t % NB == NB - 1) {
-        KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 0.0, st);
+        // the partial products, the panel's columns so far, column t + 1 and x read; v (three times), w and the next x written
+        KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 4.0 * RB * (R.P.parts[t / NB] + rows.count * (2.0 * (t % NB) + 7.0)), st);
         hipLaunchKernelGGL(dir_vector_kernel, dim3(rows.count), dim3(256), 0, st, R.dm, R.tab + rows.at, t);
     }
 }
@@ -1522,7 +1526,9 @@ int enqueue_finish(kfac_ctx *ctx, const DirRun &R) {
     const DirMat *dm = R.dm;
     const unsigned *tab = R.tab;
     {
-        KfacProfScope prof(ctx, KC_EIG_TRI, 0.0, 0.0, st);
+        // fp64: per eigenvalue 60 Sturm counts of two FMAs a row (bisection to its last bits), per eigenvector five recurrences of a
+        // division, i.e. five FMAs and a few more
+        KfacProfScope prof(ctx, KC_EIG_TRI, (60.0 * 4.0 + 5.0 * 12.0) * R.square, 0.0, st);
         if (P.nmax > TD_SMALL) hipLaunchKernelGGL(dir_clear_kernel, per_mat, dim3(256), 0, st, dm);
         hipLaunchKernelGGL(dir_scale_t_kernel, dim3(batch), dim3(256), 0, st, dm);
         // sixteen lanes per eigenvalue do 9/4 of the work of four in 4/7 of the passes: right where four leave the chip idle

@@ -1016,3 +1016,5 @@ def test_profile_reports_every_kernel_class(ctx):
     assert want <= set(stats), want - set(stats)
     for name, st in stats.items():
         assert st["launches"] > 0 and st["ms"] > 0.0, (name, st)
+    assert stats["eig_reduce_vec"]["bytes"] > 0.0 and stats["eig_reduce_mv"]["bytes"] > 0.0
+    assert all(stats[k]["flops"] > 0.0 for k in ("eig_tridiag_solve", "eig_reduce_update", "eig_back"))
