@@ -19,6 +19,7 @@ if ROOT not in sys.path:
 PEAK_MFMA_F32 = 157.3e12   # MI355X dense fp32 matrix FLOP/s
 PEAK_MFMA_F16 = 2.5e15     # dense fp16 matrix FLOP/s
 PEAK_VALU_F32 = 157.3e12   # fp32 vector FLOP/s (256 CUs x 128 lanes x 2 flops x 2.4 GHz)
+PEAK_VALU_F64 = 78.6e12    # fp64 vector FLOP/s
 PEAK_HBM = 8.0e12          # bytes/s
 
 BOUNDS = {  # kernel class -> (bound, peak, unit, which work figure)
@@ -46,7 +47,7 @@ BOUNDS = {  # kernel class -> (bound, peak, unit, which work figure)
     "eig_reduce_mv": ("hbm", PEAK_HBM, "GB/s", "bytes"),
     "eig_reduce_vec": ("hbm", PEAK_HBM, "GB/s", "bytes"),
     "eig_reduce_update": ("mfma", PEAK_MFMA_F32, "TFLOP/s", "flops"),
-    "eig_tridiag_solve": ("alu", PEAK_VALU_F32, "TFLOP/s", "flops"),
+    "eig_tridiag_solve": ("alu", PEAK_VALU_F64, "TFLOP/s", "flops"),
     "eig_back": ("mfma", PEAK_MFMA_F32, "TFLOP/s", "flops"),
 }
 
@@ -195,9 +196,9 @@ def main():
                     help="skip the measurements that are not part of `value` (warm start, decoupled schedule, split-fp16 "
                          "preconditioner): for short profiler runs")
     ap.add_argument("--eig-serial", action="store_true",
-                    help="run the eigensolver's groups one after another on one stream, so that a profiler's kernel "
-                         "durations are the kernels' own (as in the instrumented step); `value` is then NOT the "
-                         "product's figure and the line says so in config.eig_serial")
+                    help="run the groups of the eigensolver's Jacobi sweeps one after another on one stream, so that a "
+                         "profiler's kernel durations are the kernels' own (as in the instrumented step); the line says so "
+                         "in config.eig_serial")
     args = ap.parse_args()
     if args.eig_serial:
         os.environ["KFAC_EIG_SERIAL"] = "1"
@@ -273,8 +274,8 @@ def main():
     if args.no_extras:
         warm_ms, warm_sweeps = [0.0], None
 
-    # the eigendecomposition with every product on the fp32 matrix instructions (the default runs the orthogonalisation
-    # of factors with d >= 2048 on split-fp16 products): not part of `value`
+    # the eigendecomposition by Jacobi sweeps with every product on the fp32 matrix instructions (small eigenvalues accurate on
+    # their own scale; the default's errors are bounded relative to the factor's norm): not part of `value`
     fp32_ms, fp32_sweeps = None, None
     if not args.no_extras:
         run.update_factors(1, wl.decay)
@@ -355,9 +356,8 @@ def main():
     roofline = dict(kernels[dom])
     roofline["kernel"] = dom
     roofline["traffic"] = measured_traffic(dom) if args.workload == "resnet50" else None
-    roofline["timing"] = ("hipEvents around every launch of the class, over one instrumented step in which the eigensolver's "
-                          "groups run one after another on one stream (the kernel's own duration, no waiting behind other "
-                          "streams); in the timed steps the groups overlap on four streams")
+    roofline["timing"] = ("hipEvents around every launch of the class, over one instrumented step; the launches of a direct "
+                          "decomposition follow each other on one stream there as in the timed steps")
     roofline = {k: roofline[k] for k in ("kernel", "bound", "achieved", "peak", "unit", "frac", "traffic",
                                          "launches", "avg_ms", "total_ms", "algorithmic_bytes_per_launch", "algorithmic_tflops",
                                          "timing") if k in roofline}
@@ -388,7 +388,7 @@ def main():
                    "arithmetic": "factors, reduction to tridiagonal form, back-transformation, F Q, preconditioner: fp32 (fp32 "
                                  "MFMA); eigenpairs of the tridiagonal matrix, Rayleigh quotients: fp64; orthogonalisation step "
                                  "of factors with d >= 2048: split-fp16 MFMA (hi + lo halves, 3 products, fp32 accumulation); "
-                                 "derived.eig_fp32_only_ms is the same step's eigensolve with every product in fp32"},
+                                 "derived.eig_fp32_only_ms is the same step's eigensolve by Jacobi sweeps with every product in fp32"},
         "phases_ms": {k: round(v, 3) for k, v in phases.items()},
         "step_ms_median": round(step_ms[len(step_ms) // 2], 3), "step_ms_min": round(step_ms[0], 3),
         "derived": derived,

@@ -2,7 +2,7 @@
 // then the preconditioned gradient as two plain products Ginv * grad * Ainv (the method Sec. IV-A and Table I
 // compare the eigendecomposition with).  The inverse of a symmetric positive definite matrix is formed the
 // classical way, in fp32: blocked Cholesky factorisation F + gamma I = L L^T (128-wide block columns: the diagonal
-// block is factored, and inverted, by one workgroup in LDS; the panel below it is multiplied by that inverse and the
+// block is factored, and inverted, by one workgroup in registers; the panel below it is multiplied by that inverse and the
 // trailing matrix gets its rank-128 update on the fp32 MFMA tile engine), then the triangular inverse L^-1 by
 // doubling (two products per level), then L^-T L^-1 as one symmetric product.  n^3 flops in all, 3 n/128 + 2 log2(n/128) + 1
 // launches per factor.
@@ -309,7 +309,7 @@ int kfac_launch_invert_factors(kfac_ctx *ctx, int batch, const float *const *F, 
         int best = 0;
         for (int i = 1; i < nstreams; ++i) if (load[i] < load[best]) best = i;
         const double nt = inv_npad(g.n) / NB;
-        load[best] += nt * 250e-6 + (double)g.count * g.n * (double)g.n * g.n / 60e12;   // launch-latency floor + products
+        load[best] += nt * 165e-6 + (double)g.count * g.n * (double)g.n * g.n / 60e12;   // a block column's serial launches + products
         rc = inv_enqueue_group(ctx, ctx->aux[best], g, tab_dev, (float *)(pool + (size_t)best * region), damping);
         if (rc != KFAC_OK) break;
     }
