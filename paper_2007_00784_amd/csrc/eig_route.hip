@@ -113,9 +113,9 @@ __global__ __launch_bounds__(256) void probe_sum_kernel(const ProbeItem *items) 
     }
     __syncthreads();
     if (tid >= PC) return;
-    const double l = tot[tid] / tot[2 * PC + tid];
-    double res = fmax(tot[PC + tid] / tot[2 * PC + tid] - l * l, 0.0);
-    if (!(res < 1e300)) res = 1e300;     // (a column of zeros, not a number, ..: no basis to start from)
+    const double l = tot[tid] / tot[2 * PC + tid], raw = tot[PC + tid] / tot[2 * PC + tid] - l * l;
+    double res = raw > 0.0 ? raw : 0.0;
+    if (!(fabs(tot[2 * PC + tid] - 1.0) <= 1e-3) || !(raw < 1e300)) res = 1e300;     // zeros, not a number, ..: no basis to start from
     const int lost = __popcll(__ballot(tid >= PTOP && res > 0.09 * l * l));
     res *= tid < PTOP ? 1.0 : (double)(P.n - PTOP) / (double)(PC - PTOP);
 #pragma unroll
@@ -164,7 +164,8 @@ int probe_start_bases(kfac_ctx *ctx, const std::vector<int> &which, const float 
     KFAC_HIP_CHECK(hipStreamSynchronize(ctx->stream));
     for (int k = 0; k < m; ++k) {
         const double *o = ctx->pinned + 3 * k;
-        start[which[k]].rel = o[1] > 0.0 && o[1] < 1e300 ? std::sqrt(o[0] / o[1]) : (o[1] == 0.0 ? 0.0 : -1.0);
+        if (!(o[0] < 1e299) || !(o[1] < 1e300)) continue;
+        start[which[k]].rel = o[1] > 0.0 ? std::sqrt(o[0] / o[1]) : 0.0;
         start[which[k]].lost = o[2];
     }
     return KFAC_OK;

@@ -321,6 +321,30 @@ def test_eig_warm_start_from_eigenvectors_that_still_hold(ctx):
     assert float((q.T.contiguous() @ q - torch.eye(300, device=ctx.dev, dtype=torch.float64)).norm()) <= 300 * 2.0 ** -22
 
 
+@pytest.mark.parametrize("what", ["zeros", "nan", "scaled", "one column"])
+def test_eig_warm_start_from_what_is_no_basis(ctx, what):
+    """A first call with the option on, before there are eigenvectors: decomposed as without it."""
+    mats = [gram_factor(n, 2 * n, seed=90 + i) for i, n in enumerate([130, 300, 577])] + [np.zeros((200, 200), np.float32)]
+    Fd = [ctx.to_dev(f) for f in mats]
+    Q, lam = [torch.zeros_like(f) for f in Fd], [torch.zeros(f.shape[0], device=ctx.dev) for f in Fd]
+    if what != "zeros":
+        K.kfac_eig(ctx.h, Fd, Q, lam)
+    for q in Q:
+        if what == "nan":
+            q.fill_(float("nan"))
+        elif what == "scaled":
+            q.mul_(1.01)
+        elif what == "one column":
+            q[:, -1] = 0.0
+    info = K.kfac_eig(ctx.h, Fd, Q, lam, warm_start=True)
+    torch.cuda.synchronize()
+    assert all(c and s <= 1 for (s, _, c) in info), info
+    for i in range(3):
+        check_eigpairs(mats[i], lam[i].cpu().numpy(), Q[i].cpu().numpy(), what)
+    q = Q[3].double()
+    assert float((q.T.contiguous() @ q - torch.eye(200, device=ctx.dev, dtype=torch.float64)).norm()) <= 200 * 2.0 ** -22
+
+
 def _eig_seconds(ctx, mats, **kw):
     Fd = [ctx.to_dev(f) for f in mats]
     Q, lam = [torch.empty_like(f) for f in Fd], [torch.empty(f.shape[0], device=ctx.dev) for f in Fd]
