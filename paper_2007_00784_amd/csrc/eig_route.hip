@@ -4,9 +4,9 @@
 // The direct decomposition costs the same for every factor of a size.  Jacobi sweeps cost by how far the factor is from diagonal in
 // the basis they start from: none from the eigenvectors of a factor that has not moved since (7 ms at 4609, where the direct
 // decomposition takes 58), four and more after a running average moved by 5 % (88 ms).  So with a start basis, that distance is
-// estimated first (probe kernels below: 20 to 100 us), and the sweeps take the factors with which the call is cheaper.  Without one, it
-// is off(F)_F, which the direct route forms anyway: running averages that are still diagonal need no sweep (0.4 ms at 577, 1.2 at
-// 2100, in place of 5.3 and 19), and a loose tol needs few.
+// estimated first (probe kernels below: 18 us at 145, 64 at 2100, and a wait), and the sweeps take the factors with which the call is cheaper.  Without one, it
+// is off(F)_F, which the direct route forms anyway: running averages that are still diagonal need no sweep (0.55 ms at 577, 1.4 at
+// 2100, in place of 5.2 and 19), and a loose tol needs few.
 #include <algorithm>
 #include <climits>
 #include <cmath>
