@@ -42,11 +42,12 @@ BOUNDS = {  # kernel class -> (bound, peak, unit, which work figure)
     # 168 issued fp16 flop/byte against an fp16 ridge of 312, so the HBM roof is the one that binds
     "eig_outer_cols": ("hbm", PEAK_HBM, "GB/s", "bytes"),
     "eig_outer_rows": ("hbm", PEAK_HBM, "GB/s", "bytes"),
-    # direct route: Householder reduction (matrix-vector products over the lower tiles, vector steps, rank-64 updates),
-    # eigenpairs of the tridiagonal matrix, back-transformation
-    "eig_reduce_mv": ("hbm", PEAK_HBM, "GB/s", "bytes"),
+    # direct route: Householder reduction (products of the trailing matrix with a column, rank-2 updates of it, both in the
+    # registers of the whole chip and in the same launches: by their share of the operations; copies), eigenpairs of the
+    # tridiagonal matrix, back-transformation
+    "eig_reduce_mv": ("alu", PEAK_VALU_F32, "TFLOP/s", "flops"),
     "eig_reduce_vec": ("hbm", PEAK_HBM, "GB/s", "bytes"),
-    "eig_reduce_update": ("mfma", PEAK_MFMA_F32, "TFLOP/s", "flops"),
+    "eig_reduce_update": ("alu", PEAK_VALU_F32, "TFLOP/s", "flops"),
     "eig_tridiag_solve": ("alu", PEAK_VALU_F64, "TFLOP/s", "flops"),
     "eig_back": ("mfma", PEAK_MFMA_F32, "TFLOP/s", "flops"),
 }

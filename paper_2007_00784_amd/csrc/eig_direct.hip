@@ -19,6 +19,7 @@
 // so is the orthogonality of the eigenvectors before the last step; a factor with an unsound result is decomposed by
 // Jacobi iteration instead (eig.hip).
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -36,14 +37,12 @@ constexpr int NB = 32;            // columns of a panel
 constexpr int TB = 128;           // tile edge
 constexpr int RB = 64;            // rows per workgroup of the vector step
 constexpr int TD_SMALL = KFAC_EIG_REG;
-// Tiles of a launch up to which the vector step and the next column's products share it.  Measured with everything unfused, fused
-// up to 300 tiles, and up to 800: one 4609-wide factor (703 tiles and fewer as it shrinks) 61.5, 58.6, 61.1 ms; ResNet-32's factors
-// (135 tiles at the most) 9.81, 9.12, 9.14 ms; beyond 800 tiles fusing costs as much again as it saves (ResNet-50: 155 and 177 ms).
-constexpr int FUSE_MAX = 300;
 constexpr int WY = 128;           // reflectors of a compact WY block
 constexpr int WY_K = 512;         // contraction of one workgroup in Y = V^T Z
 constexpr int NPARTS = 64;         // parts of the Rayleigh quotients' sums
 constexpr int NORM_WGS = 256;      // workgroups per factor of the norms and copies: workgroup b has rows b, b + gridDim.x, ..; never more than rows
+constexpr int CHIP_RING = 4;      // columns whose words are in flight between the workgroups of a factor (eig_chip.h)
+constexpr unsigned long long CHIP_EMPTY = ~0ull;
 constexpr double PERTURB_REL = 0x1p-25;   // of every element of T: half the rounding it already carries
 constexpr double PERTURB_ABS = 1e-10;     // of the Gershgorin bound, added to the diagonal: breaks multiple zeros
 constexpr double NS_AGAIN = 4e-6;         // ||I - Q^T Q||_F^2 from which one Newton-Schulz step is not enough (it leaves 3/4 of this)
@@ -79,6 +78,7 @@ struct DirMat {
     int *ord;        // [np]: row of F that became row i of A (diagonal descending)
     double diag_tol2;   // a factor up to TD_SMALL wide with off^2 <= this ||F||^2 is diagonal as it stands (wider ones: see go_on)
     int n, np, ld, nb, off, split;
+    int chain;          // columns that the chain of launches reduces, before the matrix fits the chip
 };
 
 // Nothing to reduce: the eigenvectors are unit vectors.  (An identity or another diagonal factor: 64 wide 103 us in place of 267, 145 wide
@@ -98,6 +98,7 @@ __device__ inline float wave_sum_all(float v) {   // the sum over the wave, in e
 #undef KFAC_DPP_ADD
     return __int_as_float(__builtin_amdgcn_readlane(x, 63));
 }
+__device__ inline float lane_value(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
 __device__ inline float quad_sum(float v) {       // the sum over four neighbouring lanes, in each of them
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));   // quad_perm 1,0,3,2
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));   // quad_perm 2,3,0,1
@@ -194,7 +195,13 @@ __global__ __launch_bounds__(256) void dir_order_kernel(const DirMat *mats) {
     }
 }
 
-// A <- scale * F, reordered, with zero padding, for the factors reduced by the chain; the norms for all of them.
+// Empties the ring of a factor's first launch of the reduction on the chip: EMPTY, as 8-byte words, over the first half of apan's use.
+__device__ inline void empty_ring(const DirMat &M, int wg, int wgs) {
+    const global_ptr<unsigned long long> ring = as_global((unsigned long long *)M.apan);
+    for (int i = wg * 256 + (int)threadIdx.x; i < CHIP_RING * M.np; i += 256 * wgs) ring[i] = CHIP_EMPTY;
+}
+
+// A <- scale * F, reordered, with zero padding, for the factors wider than the register kernels take; the norms for all of them.
 __global__ __launch_bounds__(256) void dir_copy_kernel(const DirMat *mats) {
     const DirMat M = mats[blockIdx.y];
     double o2, d2;
@@ -206,6 +213,7 @@ __global__ __launch_bounds__(256) void dir_copy_kernel(const DirMat *mats) {
     const int n = M.n, np = M.np;
     if (blockIdx.x == 0)
         for (int i = n - 1 + (int)threadIdx.x; i < np; i += 256) M.tau[i] = 0.f;   // no reflectors there
+    if (M.chain == 0) empty_ring(M, blockIdx.x, gridDim.x);
     const global_ptr<const int> ord = as_global((const int *)M.ord);
     for (int r = blockIdx.x; r < np; r += gridDim.x) {
         const int64_t fr = r < n ? (int64_t)ord[r] * n : 0;
@@ -213,6 +221,8 @@ __global__ __launch_bounds__(256) void dir_copy_kernel(const DirMat *mats) {
             A[(int64_t)r * M.ld + c] = (r < n && c < n) ? sc * F[fr + ord[c]] : 0.f;
     }
 }
+
+#include "eig_chip.h"
 
 // ---- reduction, one workgroup (n <= 256) -------------------------------------------------------------------
 // Four threads per row, each with KC columns of it in registers (groups of four: group k covers columns 16 k + 4 q ..).
@@ -535,7 +545,6 @@ __device__ inline void vec_store(const DirMat &M, int j, int ip, int row, float 
         M.e[j] = (double)S.beta;
     }
 }
-__device__ inline float lane_value(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
 
 // Vector step of column j: w, the panel's new columns, reflector j, and (unless the panel ends here) column j + 1 with the
 // panel's updates applied.
@@ -595,79 +604,6 @@ __global__ __launch_bounds__(256) void dir_vector_kernel(const DirMat *mats, con
     if (lane == 0) B.npart[tr.J] = s;
 }
 
-// Both in one launch: the vector step of column j - 1, by every tile's workgroup for the rows of its own two blocks, then the
-// products of column j.  A tile reads up to 100 KB of panel and partial sums from L2 beside its own 64 KB: worth the launch
-// it saves (4 us) while the tiles of a launch are few (FUSE_MAX).
-__global__ __launch_bounds__(256, 2) void dir_fused_kernel(const DirMat *mats, const unsigned *tab, int t) {
-    __shared__ SymvSmem sm;
-    __shared__ VecSmem vs;
-    __shared__ __attribute__((aligned(16))) float ys[4][2 * TB], as_[4][2 * TB];
-    __shared__ float nd[2][2];
-    const TabRef tr = tab_ref(tab[blockIdx.x]);
-    const DirMat M = mats[tr.m];
-    const int j = t - M.off;            // the new column; j >= 1: a panel's first column is not fused
-    if (j > M.n - 1) return;
-    const int tid = threadIdx.x, lane = tid & 63, g = __builtin_amdgcn_readfirstlane(tid >> 6), I = tr.I, J = tr.J;
-    const int ip = (t & (NB - 1)) - 1, b0 = j / TB, ct = M.nb - b0, last = M.nb - 1;     // ip: column j - 1 in the panel
-    const bool diag = I == J, more = j < M.n - 1;
-    const StepBufs P = step_bufs(M, t - 1), B = step_bufs(M, t);
-    const global_ptr<const float> panel = as_global((const float *)M.panel);
-    const int row4 = (lane < 32 ? I : J) * TB + 4 * (lane & 31), row = (tid < TB ? I * TB : J * TB - TB) + tid;
-    VecLoads L;
-    vec_load(M, P, j - 1, ip, b0, L);
-    floatx4 yk[8], pv[NB / 4], pw[NB / 4];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) yk[u] = *(global_ptr<const floatx4>)(P.part + (int64_t)min(b0 + g + 4 * u, last) * M.np + row4);
-#pragma unroll
-    for (int u = 0; u < NB / 4; ++u) {
-        pv[u] = *(global_ptr<const floatx4>)(panel + (int64_t)(g + 4 * u) * M.ld + row4);
-        pw[u] = *(global_ptr<const floatx4>)(panel + (int64_t)(NB + g + 4 * u) * M.ld + row4);
-    }
-    const float acur = as_global((const float *)M.apan)[(int64_t)(ip + 1) * M.np + row], xv = P.acol[row];
-    TileLoads T;
-    tile_load(M, I, J, ip, T);
-    floatx4 y = {0.f, 0.f, 0.f, 0.f}, ac = y, yc = y;
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-        if (g + 4 * u < ct) y += yk[u];
-    for (int k = b0 + g + 32; k < M.nb; k += 4) y += *(global_ptr<const floatx4>)(P.part + (int64_t)k * M.np + row4);
-    vec_partial(M, P, ip, b0, L, vs);
-    __syncthreads();
-    const float rowj = (lane & (NB - 1)) < ip ? L.rowj : 0.f;
-    const VecScalars S = vec_scalars(M, ip, b0, L, rowj, vs);
-#pragma unroll
-    for (int u = 0; u < NB / 4; ++u) {
-        const int p = g + 4 * u;
-        if (p < ip) {
-            yc += pv[u] * lane_value(S.cf, NB + p) + pw[u] * lane_value(S.cf, p);
-            ac += pv[u] * lane_value(rowj, NB + p) + pw[u] * lane_value(rowj, p);
-        }
-    }
-    *(floatx4 *)(ys[g] + 4 * lane) = y * S.scale - yc;
-    *(floatx4 *)(as_[g] + 4 * lane) = ac;
-    __syncthreads();
-    const float yr = ys[0][tid] + ys[1][tid] + ys[2][tid] + ys[3][tid] - S.scale * S.beta * acur;
-    const float ar = as_[0][tid] + as_[1][tid] + as_[2][tid] + as_[3][tid];
-    const float v = row > j ? xv * S.scale : (row == j ? 1.f : 0.f);
-    const float w = row >= j ? fmaf(S.tau, yr, S.ah * v) : 0.f;
-    const float a = row >= j ? acur - ar - fmaf(v, S.wj, w) : 0.f;
-    const float x = row > j ? a : 0.f;
-    if (diag && tid < TB) {
-        vec_store(M, j - 1, ip, row, v, w, S);
-        if (row == j) M.d[j] = (double)a;
-        B.acol[row] = x;
-        const float s = wave_sum_all(row > j + 1 ? x * x : 0.f);
-        if (lane == 0) B.npart[2 * I + g] = s;
-        const float dv = wave_sum_all(v * x), dw = wave_sum_all(w * x);
-        if (lane == 0) { nd[g][0] = dv; nd[g][1] = dw; }
-    }
-    if (!more) return;
-    (tid < TB ? sm.xI : sm.xJ - TB)[tid] = x;
-    __syncthreads();
-    if (diag && tid < 2) B.dots[I * 2 * NB + NB * tid + ip] = nd[0][tid] + nd[1][tid];
-    tile_product(M, I, J, b0, ip, B, T, sm);
-}
-
 // C -= acc for the rows of the tile from `first` on, sixteen elements at a time (one accumulator's loads in flight, not 64)
 __device__ inline void subtract_tile(const floatx16 (&acc)[2][2], global_ptr<float> C, int64_t ld, int first) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lk = lane >> 5, lc = lane & 31;
@@ -699,6 +635,28 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(3))) v
     const global_ptr<float> C = as_global(M.A) + (int64_t)tr.I * TB * ld + tr.J * TB;
     gemm_tile(a, b, 0, 0, 0, 2 * NB, sm, acc);
     subtract_tile(acc, C, ld, t - M.off - tr.I * TB);      // rows of finished columns hold reflectors
+}
+
+// What the chain leaves of a factor, for the chip: the lower triangle of the trailing matrix (rows and columns from M.chain on)
+// copied to the upper, in 64 x 64 blocks.
+__global__ __launch_bounds__(256) void dir_mirror_kernel(const DirMat *mats) {
+    __shared__ float s[64][65];
+    const DirMat M = mats[blockIdx.y];
+    if (M.n <= TD_SMALL || M.chain == 0) return;
+    const global_ptr<float> A = as_global(M.A);
+    const int b0 = M.chain / 64, nblk = M.np / 64 - b0, c = threadIdx.x & 63;
+    empty_ring(M, blockIdx.x, gridDim.x);
+    for (int q = blockIdx.x; q < nblk * nblk; q += gridDim.x) {
+        const int I = b0 + q / nblk, J = b0 + q % nblk;
+        if (J > I) continue;
+        __syncthreads();
+        for (int r = threadIdx.x >> 6; r < 64; r += 4) s[r][c] = A[(int64_t)(I * 64 + r) * M.ld + J * 64 + c];
+        __syncthreads();
+        for (int r = threadIdx.x >> 6; r < 64; r += 4) {      // element (J 64 + r, I 64 + c)
+            const int gr = J * 64 + r, gc = I * 64 + c;
+            if (gr >= M.chain && gr < gc) A[(int64_t)gr * M.ld + gc] = s[c][r];
+        }
+    }
 }
 
 // Row p of A keeps reflector p only: zeros up to and including the diagonal.
@@ -1354,6 +1312,7 @@ struct DirPlan {
     std::vector<unsigned> tab;            // all tables, one after another
     struct Range { unsigned at, count; };
     int steps = 0;                        // of the reduction chain
+    std::vector<ChipLaunch> chip;         // launches of the reduction on the chip
     std::vector<Range> tiles, rows;       // per panel
     std::vector<double> parts;            // per panel: partial products that its row blocks add up (64 rows each)
     std::vector<int> small[4];            // factors per register kernel: up to 64, 128, 192, 256
@@ -1365,7 +1324,7 @@ struct DirPlan {
 
 unsigned pack(int m, int I, int J) { return (unsigned)m << 14 | (unsigned)I << 7 | (unsigned)J; }
 
-void dir_tables(DirPlan &P) {
+void dir_tables(DirPlan &P, int capacity) {
     const int nm = (int)P.mats.size();
     std::vector<int> order(nm);
     for (int i = 0; i < nm; ++i) order[i] = i;
@@ -1373,12 +1332,14 @@ void dir_tables(DirPlan &P) {
     auto begin = [&](DirPlan::Range &r) { r.at = (unsigned)P.tab.size(); };
     auto end = [&](DirPlan::Range &r) { r.count = (unsigned)P.tab.size() - r.at; };
     P.nmax = nm ? P.mats[order[0]].n : 0;
-    for (auto &M : P.mats)
-        if (M.n > TD_SMALL) M.off = (P.nmax - M.n) / NB * NB;
-    if (P.nmax > TD_SMALL) {
-        for (auto &M : P.mats)
-            if (M.n > TD_SMALL) P.steps = std::max(P.steps, M.off + M.n);
-        const int npanel = (P.steps + NB - 1) / NB;
+    const int widest = chip_widest(capacity);      // as many columns by the chain of launches as it takes to fit the chip
+    for (auto &M : P.mats) {
+        M.chain = M.n > TD_SMALL && M.n > widest ? (M.n - widest + NB - 1) / NB * NB : 0;
+        P.steps = std::max(P.steps, M.chain);
+    }
+    for (auto &M : P.mats) M.off = P.steps - M.chain;
+    if (P.steps > 0) {
+        const int npanel = P.steps / NB + 1;       // the last one: the update by the panel before it
         P.tiles.resize(npanel);
         P.rows.resize(npanel);
         P.parts.assign(npanel, 0.0);
@@ -1387,7 +1348,7 @@ void dir_tables(DirPlan &P) {
             for (int m : order) {
                 const DirMat &M = P.mats[m];
                 const int j = q * NB - M.off;
-                if (M.n <= TD_SMALL || j < 0 || j > M.n - 1) continue;
+                if (M.chain == 0 || j < 0 || j > M.n - 1) continue;
                 for (int I = j / TB; I < M.nb; ++I)
                     for (int J = j / TB; J <= I; ++J) P.tab.push_back(pack(m, I, J));
             }
@@ -1396,13 +1357,22 @@ void dir_tables(DirPlan &P) {
             for (int m : order) {
                 const DirMat &M = P.mats[m];
                 const int j = q * NB - M.off;
-                if (M.n <= TD_SMALL || j < 0 || j > M.n - 1) continue;
+                if (M.chain == 0 || j < 0 || j > M.n - 1) continue;
                 for (int r = j / TB * 2; r < 2 * M.nb; ++r) P.tab.push_back(pack(m, 0, r));
                 P.parts[q] += 2.0 * (M.nb - j / TB) * (M.nb - j / TB);
             }
             end(P.rows[q]);
         }
     }
+    std::vector<ChipFactor> left;
+    for (int m : order)
+        if (P.mats[m].n > TD_SMALL && P.mats[m].chain < P.mats[m].n - 1) left.push_back(ChipFactor{m, P.mats[m].n, P.mats[m].chain, 0});
+    std::vector<ChipJob> jobs;
+    chip_plan(left, capacity, jobs, P.chip);
+    for (auto &L : P.chip) L.at = (unsigned)(P.tab.size() + L.at * sizeof(ChipJob) / sizeof(unsigned));
+    const size_t at = P.tab.size();
+    P.tab.resize(at + jobs.size() * sizeof(ChipJob) / sizeof(unsigned));
+    if (!jobs.empty()) memcpy(P.tab.data() + at, jobs.data(), jobs.size() * sizeof(ChipJob));
     for (int m : order) {
         const int n = P.mats[m].n;
         if (n <= TD_SMALL) P.small[n <= 64 ? 0 : n <= 128 ? 1 : n <= 192 ? 2 : 3].push_back(m);
@@ -1492,30 +1462,55 @@ void enqueue_small(kfac_ctx *ctx, const DirRun &R) {
     }
 }
 
+void enqueue_update(kfac_ctx *ctx, const DirRun &R, int t) {
+    const DirPlan::Range tiles = R.P.tiles[t / NB];
+    KfacProfScope prof(ctx, KC_EIG_REDUCE_GEMM, 2.0 * 2.0 * NB * TB * TB * tiles.count, 8.0 * TB * TB * tiles.count, ctx->stream);
+    if (tiles.count) hipLaunchKernelGGL(dir_update_kernel, dim3(tiles.count), dim3(NTHREADS), 0, ctx->stream, R.dm, R.tab + tiles.at, t);
+}
+
 void enqueue_step(kfac_ctx *ctx, const DirRun &R, int t) {
     const hipStream_t st = ctx->stream;
     const DirPlan::Range tiles = R.P.tiles[t / NB], rows = R.P.rows[t / NB];
     if (t % NB == 0) {
-        if (t > 0) {
-            KfacProfScope prof(ctx, KC_EIG_REDUCE_GEMM, 2.0 * 2.0 * NB * TB * TB * tiles.count, 8.0 * TB * TB * tiles.count, st);
-            hipLaunchKernelGGL(dir_update_kernel, dim3(tiles.count), dim3(NTHREADS), 0, st, R.dm, R.tab + tiles.at, t);
-        }
+        if (t > 0) enqueue_update(ctx, R, t);
         KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 8.0 * RB * (NB + 1) * rows.count, st);
         hipLaunchKernelGGL(dir_column_kernel, dim3(rows.count), dim3(RB), 0, st, R.dm, R.tab + rows.at, t);
     }
     const double fl = 4.0 * TB * TB * tiles.count;
-    if ((int)tiles.count <= FUSE_MAX && t % NB != 0) {
-        KfacProfScope prof(ctx, KC_EIG_REDUCE_MV, fl, fl, st);
-        hipLaunchKernelGGL(dir_fused_kernel, dim3(tiles.count), dim3(256), 0, st, R.dm, R.tab + tiles.at, t);
-    } else {
+    {
         KfacProfScope prof(ctx, KC_EIG_REDUCE_MV, fl, fl, st);
         hipLaunchKernelGGL(dir_symv_kernel, dim3(tiles.count), dim3(256), 0, st, R.dm, R.tab + tiles.at, t);
     }
-    if ((int)tiles.count > FUSE_MAX || t % NB == NB - 1) {
-        // the partial products, the panel's columns so far, column t + 1 and x read; v (three times), w and the next x written
-        KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 4.0 * RB * (R.P.parts[t / NB] + rows.count * (2.0 * (t % NB) + 7.0)), st);
-        hipLaunchKernelGGL(dir_vector_kernel, dim3(rows.count), dim3(256), 0, st, R.dm, R.tab + rows.at, t);
+    // the partial products, the panel's columns so far, column t + 1 and x read; v (three times), w and the next x written
+    KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 4.0 * RB * (R.P.parts[t / NB] + rows.count * (2.0 * (t % NB) + 7.0)), st);
+    hipLaunchKernelGGL(dir_vector_kernel, dim3(rows.count), dim3(256), 0, st, R.dm, R.tab + rows.at, t);
+}
+
+int enqueue_reduction(kfac_ctx *ctx, const DirRun &R) {
+    const DirPlan &P = R.P;
+    const hipStream_t st = ctx->stream;
+    const dim3 per_mat((unsigned)std::min(NORM_WGS, P.nmax), (unsigned)P.mats.size());
+    for (int t = 0; t < P.steps; ++t) enqueue_step(ctx, R, t);
+    if (P.steps > 0) {
+        enqueue_update(ctx, R, P.steps);
+        KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 4.0 * R.square, st);
+        hipLaunchKernelGGL(dir_mirror_kernel, per_mat, dim3(256), 0, st, R.dm);
     }
+    for (const ChipLaunch &L : P.chip) {
+        const DirMat *dm = R.dm;
+        const ChipJob *jobs = (const ChipJob *)(R.tab + L.at);
+        int count = L.jobs;
+        void *args[] = {&dm, &jobs, &count};
+        // of three multiplications and additions per element, one belongs to the product and two to the update
+        KfacProfScope product(ctx, KC_EIG_REDUCE_MV, L.flops / 3.0, L.bytes / 3.0, st, 1.0 / 3.0);
+        KfacProfScope update(ctx, KC_EIG_REDUCE_GEMM, L.flops / 1.5, L.bytes / 1.5, st, 2.0 / 3.0);
+        KFAC_HIP_CHECK(hipLaunchCooperativeKernel((const void *)dir_chip_kernel, dim3((unsigned)L.wgs), dim3(CHIP_NT), args, 0, st));
+    }
+    if (P.nmax > TD_SMALL) {
+        KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 2.0 * R.square, st);
+        hipLaunchKernelGGL(dir_clear_kernel, per_mat, dim3(256), 0, st, R.dm);
+    }
+    return KFAC_OK;
 }
 
 int enqueue_finish(kfac_ctx *ctx, const DirRun &R) {
@@ -1529,7 +1524,6 @@ int enqueue_finish(kfac_ctx *ctx, const DirRun &R) {
         // fp64: per eigenvalue 60 Sturm counts of two FMAs a row (bisection to its last bits), per eigenvector five recurrences of a
         // division, i.e. five FMAs and a few more
         KfacProfScope prof(ctx, KC_EIG_TRI, (60.0 * 4.0 + 5.0 * 12.0) * R.square, 0.0, st);
-        if (P.nmax > TD_SMALL) hipLaunchKernelGGL(dir_clear_kernel, per_mat, dim3(256), 0, st, dm);
         hipLaunchKernelGGL(dir_scale_t_kernel, dim3(batch), dim3(256), 0, st, dm);
         // sixteen lanes per eigenvalue do 9/4 of the work of four in 4/7 of the passes: right where four leave the chip idle
         if (P.values.count <= BIS_WIDE_MAX)
@@ -1633,7 +1627,8 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
         R.square += (double)d[i] * d[i];
     }
     R.P.tab.reserve(dir_table_bound(batch, d));
-    dir_tables(R.P);
+    dir_tables(R.P, ctx->coop_wgs);
+    if (R.P.tab.size() > dir_table_bound(batch, d)) return KFAC_EWORKSPACE;
     KFAC_CHECK(kfac_upload(ctx, d_mats, R.P.mats.data(), R.P.mats.size() * sizeof(DirMat)));
     KFAC_CHECK(kfac_upload(ctx, d_tab, R.P.tab.data(), R.P.tab.size() * sizeof(unsigned)));
     enqueue_copy(ctx, R);
@@ -1650,8 +1645,8 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
             return KFAC_EIG_STOPPED;
         }
     }
-    for (int t = 0; t < R.P.steps; ++t) enqueue_step(ctx, R, t);
-    int rc = enqueue_finish(ctx, R);
+    int rc = enqueue_reduction(ctx, R);
+    if (rc == KFAC_OK) rc = enqueue_finish(ctx, R);
     if (rc == KFAC_OK && hipMemcpyAsync(stat, d_stat, (size_t)batch * 4 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess)
         rc = KFAC_EHIP;
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) rc = KFAC_EHIP;    // on an error, too: no kernel of this call is in flight after the return

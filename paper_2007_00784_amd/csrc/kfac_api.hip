@@ -125,6 +125,11 @@ int kfac_create(kfac_ctx **out, int device, void *hip_stream, void *workspace_de
     int lds = 0;
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess) lds = 65536;
     c->max_lds = lds;
+    int coop = 0, cus = 0;
+    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, device) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
+        coop = 0;
+    c->coop_wgs = coop ? cus : 0;
     *out = c;
     return KFAC_OK;
 }
@@ -305,7 +310,7 @@ int kfac_profile_end(kfac_ctx *ctx, kfac_kernel_stat *out, int max, int *n) {
         float ms = 0.f;
         KFAC_HIP_CHECK(hipEventElapsedTime(&ms, r.t0, r.t1));
         acc[r.cls].launches += 1;
-        acc[r.cls].ms += ms;
+        acc[r.cls].ms += ms * r.share;
         acc[r.cls].flops += r.flops;
         acc[r.cls].bytes += r.bytes;
         ctx->ev_pool.push_back(r.t0);

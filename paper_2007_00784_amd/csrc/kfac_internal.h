@@ -21,7 +21,7 @@ enum KfacKernelClass {
     KC_EIG_MISC, KC_EIG_POST, KC_EIG_COPY, KC_EIG_OUTER, KC_PRECOND_SCALE, KC_SYRK_B16, KC_PRECOND_GEMM_X3, KC_EIG_OUTER_ROWS, KC_INVERSE,
     KC_EIG_REDUCE_MV, KC_EIG_REDUCE_VEC, KC_EIG_REDUCE_GEMM, KC_EIG_TRI, KC_EIG_BACK, KC_COUNT
 };
-struct KfacProfRec { int cls; hipEvent_t t0, t1; double flops, bytes; };
+struct KfacProfRec { int cls; hipEvent_t t0, t1; double flops, bytes, share; };   // share: of the launch's time
 
 constexpr int KFAC_NUM_AUX_STREAMS = 4;   // internal streams of the eigensolver (default priority)
 constexpr int KFAC_MAX_GROUPS = 128;      // distinct block counts in one kfac_eig call (8192 / 64)
@@ -44,6 +44,7 @@ struct kfac_ctx {
     char *ws;            // caller-owned device workspace
     size_t ws_bytes;
     int max_lds;         // bytes of LDS one workgroup may use on this device
+    int coop_wgs;        // workgroups of a cooperative launch, one per compute unit (0: the device has none)
     bool prof_on;        // bracket every kernel launch with events
     std::vector<KfacProfRec> prof;
     std::vector<hipEvent_t> ev_pool;
@@ -56,9 +57,10 @@ struct KfacProfScope {
     KfacProfRec r;
     hipStream_t s;
     KfacProfScope(kfac_ctx *ctx, int cls, double flops, double bytes) : KfacProfScope(ctx, cls, flops, bytes, ctx->stream) {}
-    KfacProfScope(kfac_ctx *ctx, int cls, double flops, double bytes, hipStream_t st) : c(ctx), s(st) {
+    // (a launch that does the work of two classes is recorded under both, with its share of the time)
+    KfacProfScope(kfac_ctx *ctx, int cls, double flops, double bytes, hipStream_t st, double share = 1.0) : c(ctx), s(st) {
         if (!c->prof_on) return;
-        r.cls = cls; r.flops = flops; r.bytes = bytes;
+        r.cls = cls; r.flops = flops; r.bytes = bytes; r.share = share;
         r.t0 = get(); r.t1 = get();
         (void)hipEventRecord(r.t0, s);
     }

@@ -4,6 +4,7 @@ Tolerances (the benchmark spec): factors and preconditioned gradients rela
 <= 1e-4 in fp32 (<= 2e-2 with bf16 inputs); eigenpairs: ||F - Q diag(lam) Q^T||_F <= 1e-5 ||F||_F and
 eigenvalues within 1e-5 * lam_max of the oracle's; unfold is bit-exact (data movement only).
 """
+import threading
 import time
 
 import numpy as np
@@ -633,6 +634,64 @@ def test_eig_direct_many_large_factors(ctx):
         assert float((fd @ qd - qd * l.double()).norm() / fd.norm()) <= TOL_RES, n
         assert float((qd.T.contiguous() @ qd - torch.eye(n, device="cuda", dtype=torch.float64)).norm()) <= max(n, 16) * 2.0 ** -22, n
     c.close()
+
+
+def gram_on_device(dims, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    F = []
+    for n in dims:
+        X = torch.randn((2 * n, n), generator=gen, device="cuda")
+        G = X.T.contiguous() @ X / (2 * n)
+        F.append(((G + G.T) * 0.5).contiguous())
+    torch.cuda.synchronize()
+    return F
+
+
+def decompose_on_device(F):
+    """One call on the current stream: eigenvectors, eigenvalues, info."""
+    dims = [f.shape[0] for f in F]
+    c = Ctx(K.kfac_eig_workspace_bytes(dims) + 4096)
+    Q, lam = [torch.empty_like(f) for f in F], [torch.empty(n, device="cuda") for n in dims]
+    info = K.kfac_eig(c.h, F, Q, lam)
+    c.close()
+    return Q, lam, info
+
+
+# the reduction on the chip: first and last matrix of every number of column slots (512 k wide, without the first column), the widest one, the
+# narrowest that begins with columns by the chain of launches, more factors than fit at once
+@pytest.mark.parametrize("dims", [[257, 513], [514, 258], [1025, 1026], [1537, 1538], [2049, 2050], [2561, 2562], [3073, 3074], [3585, 3586], [4097, 4098],
+                                  [4609], [4610, 300], [1025] * 14 + [300] * 60])
+def test_eig_reduction_at_the_edges_of_its_column_slots(dims):
+    F = gram_on_device(dims, 11)
+    Q, lam, info = decompose_on_device(F)
+    for f, q, l, n, i in zip(F, Q, lam, dims, info):
+        assert i[2] and i[0] == 1, (n, i)          # one sweep: the direct route's own result
+        fd, qd = f.double(), q.double()
+        assert float((fd @ qd - qd * l.double()).norm() / fd.norm()) <= TOL_RES, n
+        assert float((qd.T.contiguous() @ qd - torch.eye(n, device="cuda", dtype=torch.float64)).norm()) <= max(n, 16) * 2.0 ** -22, n
+
+
+def test_eig_reductions_of_two_threads_at_once():
+    """Two contexts on streams of their own, each of which wants the whole chip: both come out as they do alone, bit by bit."""
+    F = [gram_on_device(d, 21) for d in ([2050, 700], [1600, 1600])]
+    alone = [decompose_on_device(f) for f in F]
+    got = [[], []]
+
+    def work(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(3):
+                got[k].append(decompose_on_device(F[k]))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for a, results in zip(alone, got):
+        assert len(results) == 3
+        for g in results:
+            assert a[2] == g[2]
+            assert all(torch.equal(x, y) for x, y in zip(a[0] + a[1], g[0] + g[1]))
 
 
 @pytest.mark.parametrize("N,d,T,bf16,layout", [(32, 144, 64, False, K.KFAC_LAYOUT_NDT), (9, 130, 49, False, K.KFAC_LAYOUT_NDT), (40, 257, 64, True, K.KFAC_LAYOUT_NDT),
