@@ -7,39 +7,47 @@
 // per column is one all-gather of the products between the workgroups of a factor.
 //
 //  - Workgroup p has rows [p R, p R + R) of the trailing matrix, thread i of it columns i, i + 512, .. of all R rows (S <= 9 column
-//    slots; R S <= 162 registers of a thread's 256).  The column x that is being reduced lies in registers the same way, in every
+//    slots; R S <= 192 registers of a thread's 256).  The column x that is being reduced lies in registers the same way, in every
 //    workgroup of the factor alike, so norms and inner products are formed by each for itself, in the same order.
 //  - Per column: products of the own rows with x (summed over the waves through LDS), published with the own rows' elements of the next
 //    column as one 8-byte word per row; then the words of all rows are gathered.  The word itself says whether it is there: the
 //    slots hold EMPTY before.  Everything after that is local: reflector, w, the next column, and ONE pass over the registers that
-//    applies the rank-2 update and forms the next products.
+//    applies the rank-2 update (on the matrix cores, as outer products: a third of the pass is left to the vector units) and forms the
+//    next products.
 //  - The words go through a ring of four columns.  A workgroup that has gathered column t knows that all have gathered t - 1, so it
 //    empties its own words of t - 1 then; the s_waitcnt before its next publication orders the two, and the words are looked at again
 //    only by who has seen that publication.  Loads and stores are relaxed agent-scope atomics of 8 bytes.
 //  - Polling too early costs more than it gains (the line is fetched empty, and the writer has to take it away again): measured between
 //    256 workgroups, 4608 words: 3.0 us a column polling at once, 2.3 after a pause of 1024 cycles; 64 workgroups: 2.3 and 1.5.
 //
-// Measured (one factor, whole decomposition): 577 wide 5.2 -> 2.6 ms, 2049 19.3 -> 10.2, 4609 57.6 -> 32.9; a column of a 4609-wide factor takes
-// 5.0 us at its beginning (2.6 of them arithmetic) and 2.6 at its end, where the chain of launches took 13 and 7.
+// Measured (whole decompositions): one factor 577 wide 5.2 -> 2.6 ms, 2049 19.3 -> 10.1, 4609 57.6 -> 32.1; three of 4609 62.5, twenty of 577
+// 3.4.  A column of a 4609-wide factor takes 4.3 us after a quarter of them (1.4 of it the exchange) and 2.2 at its end, where the chain of
+// launches took 13 and 7.  Also measured, and worse: shares of x^T A x among the words, so that nobody has to sum over its waves (a barrier less,
+// but every wave looks at up to 262 words more: 577 2.6 -> 3.0 ms, 4609 32.9 -> 37.0); tags beside the values in place of EMPTY (twice the words);
+// a flag per workgroup and plain loads after it.
 //
 // A launch takes every factor some columns further (ChipJob), then the trailing matrices go back to memory and are dealt out anew:
 // a matrix that has shrunk needs fewer workgroups, and others take their place.  All workgroups of a launch must be resident at once
 // (cooperative launch, one per compute unit).  Every wait is bounded; a reduction that gave up leaves a matrix
 // T that is not the factor's, which the measured residual shows, and the factor is decomposed by Jacobi iteration like any unsound one.
 
-constexpr int CHIP_NT = 512, CHIP_WAVES = CHIP_NT / 64;
 constexpr int CHIP_SLOTS = 9;
-constexpr int CHIP_MAX_N = CHIP_NT * CHIP_SLOTS + 1;      // the widest factor: its first column is never part of the trailing matrix
+constexpr int CHIP_WIDE = 512, CHIP_NARROW = 256;         // threads of a workgroup
+constexpr int CHIP_NARROW_SLOTS = 8;                      // nine would not leave the registers for anything else
+constexpr int CHIP_CROWD = 16;                            // rows of a wide workgroup from which narrow ones, two to a compute unit, are the better choice
+constexpr int CHIP_MAX_N = CHIP_WIDE * CHIP_SLOTS + 1;    // the widest factor: its first column is never part of the trailing matrix
 constexpr int CHIP_ROWS = 64;                             // rows of a workgroup, at most: the lanes of the wave that publishes
+constexpr int CHIP_ROWS_MIN = 8;                          // a workgroup with fewer saves less than one more in the exchange costs
+constexpr int CHIP_WGS = 256;                             // workgroups of a factor, at most
 constexpr int CHIP_JOBS = 64;                             // factors of a launch, at most: a workgroup finds its own by one ballot
-constexpr int CHIP_PAUSE_MANY = 12, CHIP_PAUSE_FEW = 6;  // of 64 cycles, before the first look at the others' words (more than 96 workgroups, or fewer)
+constexpr int CHIP_PAUSE = 6;                             // of 64 cycles, before the first look at the others' words
 constexpr int CHIP_WHOLE = 640, CHIP_STEPS_MIN = 96;      // up to here a factor goes in one launch; the fewest columns of a launch otherwise
 constexpr int CHIP_SPIN = 1 << 21;                        // polls (0.5 to 1 us each) before a wait is given up
 
-// Rows that a workgroup of S column slots can hold, and rows per piece of its pass: the sums of a piece are in registers together, and
-// a workgroup has whole pieces.
-constexpr int chip_piece(int S) { return S == 9 ? 9 : 8; }
-constexpr int chip_rows(int S) { return S == 9 ? 18 : S >= 7 ? 16 : S == 6 ? 24 : S == 5 ? 32 : S == 4 ? 40 : S == 3 ? 48 : 64; }
+// Rows that a workgroup of S column slots can hold, in groups of four (the rows of a matrix instruction; two rows of the nine-slot kind
+// are left to ordinary ones), and the rows whose sums are in registers together.
+constexpr int chip_rows(int S) { return S == 9 ? 18 : S == 8 ? 20 : S == 7 ? 24 : S == 6 ? 28 : S == 5 ? 32 : S == 4 ? 40 : S == 3 ? 48 : 64; }
+constexpr int chip_piece(int S) { return S >= 3 ? 8 : 16; }
 
 struct ChipJob {
     int m;               // factor
@@ -49,9 +57,10 @@ struct ChipJob {
     int turn;            // launches of this factor before this one; its parity says which half of the ring buffer (the other is emptied for the next)
 };
 
-struct ChipSmem {
-    float xs[CHIP_NT * CHIP_SLOTS + CHIP_ROWS], ys[CHIP_NT * CHIP_SLOTS + CHIP_ROWS];     // x and y by row, for those that need single elements
-    float col[CHIP_ROWS], part[CHIP_WAVES][CHIP_ROWS], nrm[CHIP_WAVES], dot[CHIP_WAVES];
+template <int NT> struct ChipSmem {
+    static constexpr int WAVES = NT / 64;
+    float xs[NT * CHIP_SLOTS + CHIP_ROWS], ys[NT * CHIP_SLOTS + CHIP_ROWS];     // x and y by row, for those that need single elements
+    float col[CHIP_ROWS], part[WAVES][CHIP_ROWS], nrm[WAVES], dot[WAVES];
     int failed;
 };
 
@@ -100,24 +109,39 @@ template <int N> __device__ inline float chip_fold(float (&v)[N], int lane) {
     return v[0];
 }
 
+// C + (rows' factors) (column's factor)^T for four rows, group g of the lanes that hold the rows' factors
+__device__ inline floatx4 chip_outer(float rows, float column, floatx4 c, int g) {
+    switch (g) {
+#define KFAC_CHIP_OUTER(G) case G: return __builtin_amdgcn_mfma_f32_4x4x1f32(rows, column, c, 4, G, 0);
+        KFAC_CHIP_OUTER(0) KFAC_CHIP_OUTER(1) KFAC_CHIP_OUTER(2) KFAC_CHIP_OUTER(3) KFAC_CHIP_OUTER(4) KFAC_CHIP_OUTER(5) KFAC_CHIP_OUTER(6) KFAC_CHIP_OUTER(7)
+        KFAC_CHIP_OUTER(8) KFAC_CHIP_OUTER(9) KFAC_CHIP_OUTER(10) KFAC_CHIP_OUTER(11) KFAC_CHIP_OUTER(12) KFAC_CHIP_OUTER(13) KFAC_CHIP_OUTER(14)
+#undef KFAC_CHIP_OUTER
+        default: return __builtin_amdgcn_mfma_f32_4x4x1f32(rows, column, c, 4, 15, 0);
+    }
+}
+
 // (all of it through global pointers: a flat access also counts on the LDS counter, and every wait for LDS behind it takes a trip to memory)
 typedef global_ptr<unsigned long long> ChipRing;
-__device__ inline unsigned long long chip_load(ChipRing p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// word i of those at `base`: a scalar base and 32 bits of offset, so that no lane keeps 64-bit addresses
+__device__ inline unsigned long long chip_load(ChipRing base, unsigned i) { return __hip_atomic_load(base + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline void chip_store(ChipRing p, unsigned long long v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-template <int S>
-__device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, ChipSmem &sm) {
-    constexpr int R = chip_rows(S), CH = chip_piece(S), PIECES = R / CH;
-    static_assert(R % CH == 0 && R <= CHIP_ROWS, "whole pieces");
+template <int CHIP_NT, int S>
+__device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, ChipSmem<CHIP_NT> &sm) {
+    constexpr int CHIP_WAVES = CHIP_NT / 64, R = chip_rows(S), G = R / 4, X = R % 4, PIECE = chip_piece(S), PIECES = (4 * G + PIECE - 1) / PIECE;
+    static_assert((X == 0 || 4 * G % PIECE == 0) && R <= CHIP_ROWS, "extra rows follow whole pieces");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = M.n - 1 - J.k0, r0 = p * J.rows, nr = min(J.rows, m - r0);     // nr >= 1: the last workgroup has row m - 1
     const bool last = p == J.wgs - 1, tail = tid + CHIP_NT * (S - 1) < m;        // only the last column slot reaches past the matrix
+    const int j1 = m > 64 * wave ? (m - 1 - 64 * wave) / CHIP_NT : -1;           // the last slot in which this wave has columns
     const int64_t ld = M.ld;
     const global_ptr<float> A0 = as_global(M.A) + (int64_t)J.k0 * ld + J.k0 + 1;      // row k0, from the element beside the diagonal on
     const ChipRing ring = as_global((unsigned long long *)M.apan) + (size_t)(J.turn & 1) * CHIP_RING * M.np;
     const global_ptr<double> Md = as_global(M.d), Me = as_global(M.e);
     const global_ptr<float> Mtau = as_global(M.tau);
-    float a[R][S], x[S], v[S], w[S], s2 = 0.f;
+    floatx4 a[G][S];
+    float ax[X ? X : 1][S];          // the rows past the groups
+    float x[S], v[S], w[S], s2 = 0.f;
 #pragma unroll
     for (int j = 0; j < S; ++j) {
         const int c = tid + CHIP_NT * j;
@@ -130,12 +154,12 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
     for (int i = 0; i < R; ++i) {
         const global_ptr<const float> row = A0 + (int64_t)(1 + r0 + min(i, nr - 1)) * ld + tid;
 #pragma unroll
-        for (int j = 0; j < S - 1; ++j) a[i][j] = row[CHIP_NT * j];
-        a[i][S - 1] = 0.f;
+        for (int j = 0; j < S; ++j) {
+            const float e = (j < S - 1 || tail) ? row[CHIP_NT * j] : 0.f;
+            if (i < 4 * G) a[i >> 2][j][i & 3] = e;
+            else ax[X ? i - 4 * G : 0][j] = e;
+        }
     }
-    if (tail)
-#pragma unroll
-        for (int i = 0; i < R; ++i) a[i][S - 1] = A0[(int64_t)(1 + r0 + min(i, nr - 1)) * ld + tid + CHIP_NT * (S - 1)];
     if (J.turn == 0 && last && tid == 0) Md[J.k0] = (double)A0[-1];
     if (tid < nr) {
         const ChipRing other = as_global((unsigned long long *)M.apan) + (size_t)(~J.turn & 1) * CHIP_RING * M.np + r0 + tid;
@@ -149,43 +173,62 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
         // s2: this thread's share of the squared norm below the column's first element.
         s2 = wave_sum_all(s2);
         if (lane == 0) sm.nrm[wave] = s2;
-        // A <- A - v w^T - w v^T and A x in one pass; rows and columns before t are finished
+        // A <- A - v w^T - w v^T and A x in one pass; rows and columns before t are finished.  The update goes to the matrix cores: 4 x 4 x 1
+        // outer products have the lane's own column and four rows in each lane, the rows' factors broadcast from the lanes that have them.
         const int j0 = max(0, (t - 64 * wave - 63 + CHIP_NT - 1) / CHIP_NT);
 #pragma unroll
-        for (int q = 0; q < PIECES; ++q) {
-            if (q * CH >= nr || r0 + q * CH + CH <= t) continue;
-            float acc[CH], rv[CH], rw[CH];
+        for (int q = 0; q < PIECES; ++q)
+            if (q * PIECE < nr && r0 + q * PIECE + PIECE > t) {
+                float acc[PIECE];
 #pragma unroll
-            for (int i = 0; i < CH; ++i) {
-                acc[i] = 0.f;
-                rv[i] = lane_value(nv, q * CH + i);
-                rw[i] = lane_value(nw, q * CH + i);
+                for (int i = 0; i < PIECE; ++i) acc[i] = 0.f;
+#pragma unroll
+                for (int h = 0; h < PIECE; h += 8)
+                    if (q * PIECE + h < nr)
+#pragma unroll
+                        for (int j = 0; j < S; ++j)
+                            if (j >= j0 && j <= j1)
+#pragma unroll
+                                for (int g = (q * PIECE + h) / 4; g < (q * PIECE + h) / 4 + 2 && g < G; ++g) {
+                                    floatx4 e = chip_outer(nw, v[j], a[g][j], g);
+                                    e = chip_outer(nv, w[j], e, g);
+                                    a[g][j] = e;
+#pragma unroll
+                                    for (int i = 0; i < 4; ++i) acc[4 * g - q * PIECE + i] = fmaf(e[i], x[j], acc[4 * g - q * PIECE + i]);
+                                }
+                const float sum = chip_fold<PIECE>(acc, lane);
+                const int at = chip_fold_index<PIECE>(lane);
+                if (at < PIECE) sm.part[wave][q * PIECE + at] = sum;
             }
+        if (X > 0 && 4 * G < nr && r0 + R > t)
 #pragma unroll
-            for (int j = 0; j < S; ++j) {
-                if (j < j0) continue;
+            for (int i = 0; i < X; ++i) {
+                const float rv = lane_value(nv, 4 * G + i), rw = lane_value(nw, 4 * G + i);
+                float acc = 0.f;
 #pragma unroll
-                for (int i = 0; i < CH; ++i) {
-                    float &e = a[q * CH + i][j];
-                    e = fmaf(rv[i], w[j], fmaf(rw[i], v[j], e));
-                    acc[i] = fmaf(e, x[j], acc[i]);
-                }
+                for (int j = 0; j < S; ++j)
+                    if (j >= j0 && j <= j1) {
+                        ax[i][j] = fmaf(rv, w[j], fmaf(rw, v[j], ax[i][j]));
+                        acc = fmaf(ax[i][j], x[j], acc);
+                    }
+                acc = wave_sum_all(acc);
+                if (lane == 0) sm.part[wave][4 * G + i] = acc;
             }
-            const float sum = chip_fold<CH>(acc, lane);
-            const int at = chip_fold_index<CH>(lane);
-            if (at < CH) sm.part[wave][q * CH + at] = sum;
-        }
         if (t == J.steps) break;
         if (r0 + nr <= t) return;          // all rows of this workgroup are finished
         if (wave == ((t >> 6) & (CHIP_WAVES - 1))) {      // the own rows' elements of column t, by the lane that has it
 #pragma unroll
             for (int j = 0; j < S; ++j)
-                if (j == t / CHIP_NT)
+                if (j == t / CHIP_NT && lane == (t & 63))
 #pragma unroll
-                    for (int q = 0; q < PIECES; ++q)
-                        if (q * CH < nr && lane == (t & 63))
+                    for (int g = 0; g < G; ++g)
+                        if (g * 4 < nr) *(floatx4 *)(sm.col + 4 * g) = a[g][j];
+            if (X > 0)
 #pragma unroll
-                            for (int i = q * CH; i < q * CH + CH; ++i) sm.col[i] = a[i][j];
+                for (int j = 0; j < S; ++j)
+                    if (j == t / CHIP_NT && lane == (t & 63))
+#pragma unroll
+                        for (int i = 0; i < X; ++i) sm.col[4 * G + i] = ax[i][j];
         }
         __syncthreads();
         const ChipRing slot = ring + (size_t)(t & (CHIP_RING - 1)) * M.np;
@@ -211,14 +254,13 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
             tau = (beta - alpha) / beta;
             scale = 1.f / (alpha - beta);
         }
-        if (J.wgs > 96) __builtin_amdgcn_s_sleep(CHIP_PAUSE_MANY);
-        else __builtin_amdgcn_s_sleep(CHIP_PAUSE_FEW);
+        __builtin_amdgcn_s_sleep(CHIP_PAUSE);
         unsigned long long u[S];
 #pragma unroll
         for (int j = 0; j < S; ++j) {
             const int c = tid + CHIP_NT * j;
             u[j] = 0;
-            if (c >= t && (j < S - 1 || tail)) u[j] = chip_load(slot + c);
+            if (c >= t && (j < S - 1 || tail)) u[j] = chip_load(slot + CHIP_NT * j, tid);
         }
         for (int spin = 0;; ++spin) {
             bool there = true;
@@ -226,7 +268,7 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
             for (int j = 0; j < S; ++j)
                 if (u[j] == CHIP_EMPTY) {
                     there = false;
-                    u[j] = chip_load(slot + tid + CHIP_NT * j);
+                    u[j] = chip_load(slot + CHIP_NT * j, tid);
                 }
             if (__all(there)) break;
             if (spin > CHIP_SPIN) { sm.failed = 1; break; }
@@ -234,7 +276,7 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
         float dot = 0.f;
 #pragma unroll
         for (int j = 0; j < S; ++j) {
-            if (j < j0) continue;
+            if (j < j0 || j > j1) continue;
             const int c = tid + CHIP_NT * j;
             const float ac = __uint_as_float((unsigned)(u[j] >> 32));
             w[j] = scale * fmaf(-beta, ac, __uint_as_float((unsigned)u[j]));      // y; w = tau y + cw v follows once the inner product is known
@@ -259,7 +301,7 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
         s2 = 0.f;
 #pragma unroll
         for (int j = 0; j < S; ++j) {
-            if (j < j0) continue;
+            if (j < j0 || j > j1) continue;
             const int c = tid + CHIP_NT * j;
             w[j] = fmaf(tau, w[j], cw * v[j]);
             x[j] = c > t ? x[j] - fmaf(v[j], wt, w[j]) : 0.f;
@@ -284,7 +326,7 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
         const global_ptr<float> row = A0 + (int64_t)(1 + r0 + i) * ld + tid;
 #pragma unroll
         for (int j = 0; j < S; ++j)
-            if (tid + CHIP_NT * j >= T && (j < S - 1 || tail)) row[CHIP_NT * j] = a[i][j];
+            if (tid + CHIP_NT * j >= T && (j < S - 1 || tail)) row[CHIP_NT * j] = i < 4 * G ? a[i < 4 * G ? i >> 2 : 0][j][i & 3] : ax[X && i >= 4 * G ? i - 4 * G : 0][j];
     }
     if (last)
 #pragma unroll
@@ -294,71 +336,77 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
         }
 }
 
-__global__ __launch_bounds__(CHIP_NT, 2) void dir_chip_kernel(const DirMat *mats, const ChipJob *jobs, int count) {
-    __shared__ ChipSmem sm;
+template <int NT> __global__ __launch_bounds__(NT, 2) void dir_chip_kernel(const DirMat *mats, const ChipJob *jobs, int count) {
+    __shared__ __attribute__((aligned(16))) ChipSmem<NT> sm;
     const int lane = threadIdx.x & 63;
     const int base = lane < count ? jobs[lane].base : INT_MAX;      // ascending
     const ChipJob J = jobs[__popcll(__ballot(base <= (int)blockIdx.x)) - 1];
     const DirMat M = mats[J.m];
     const int p = (int)blockIdx.x - J.base;
     switch (J.slots) {
-        case 1: chip_reduce<1>(M, J, p, sm); break;
-        case 2: chip_reduce<2>(M, J, p, sm); break;
-        case 3: chip_reduce<3>(M, J, p, sm); break;
-        case 4: chip_reduce<4>(M, J, p, sm); break;
-        case 5: chip_reduce<5>(M, J, p, sm); break;
-        case 6: chip_reduce<6>(M, J, p, sm); break;
-        case 7: chip_reduce<7>(M, J, p, sm); break;
-        case 8: chip_reduce<8>(M, J, p, sm); break;
-        default: chip_reduce<9>(M, J, p, sm); break;
+        case 1: chip_reduce<NT, 1>(M, J, p, sm); break;
+        case 2: chip_reduce<NT, 2>(M, J, p, sm); break;
+        case 3: chip_reduce<NT, 3>(M, J, p, sm); break;
+        case 4: chip_reduce<NT, 4>(M, J, p, sm); break;
+        case 5: chip_reduce<NT, 5>(M, J, p, sm); break;
+        case 6: chip_reduce<NT, 6>(M, J, p, sm); break;
+        case 7: chip_reduce<NT, 7>(M, J, p, sm); break;
+        case 8: chip_reduce<NT, 8>(M, J, p, sm); break;
+        default:
+            if constexpr (NT == CHIP_WIDE) chip_reduce<NT, 9>(M, J, p, sm);
     }
 }
 
 // ---- which factor takes how many columns further in which launch ----
-struct ChipLaunch { unsigned at; int jobs, wgs; double flops, bytes; };     // at: index of its first job
-struct ChipFactor { int m, n, k, turn; };                                  // width n, k columns reduced
+struct ChipLaunch { unsigned at; int jobs, wgs, threads; double flops, bytes; };     // at: index of its first job
+struct ChipFactor { int m, n, k, turn; };                                           // width n, k columns reduced
 
-inline int chip_slots(int size) { return (size + CHIP_NT - 1) / CHIP_NT; }
-inline int chip_need(int size) {      // workgroups that hold a trailing matrix of this size
-    const int rows = chip_rows(chip_slots(size));
+inline int chip_slots(int size, int threads) { return (size + threads - 1) / threads; }
+inline int chip_need(int size, int threads) {      // workgroups that hold a trailing matrix of this size
+    const int rows = chip_rows(chip_slots(size, threads));
     return (size + rows - 1) / rows;
 }
-inline int chip_widest(int capacity) {      // widest factor that fits (0: none does)
+inline int chip_widest(int cus) {      // widest factor that fits (0: none does)
     int n = CHIP_MAX_N;
-    while (n > 1 && chip_need(n - 1) > capacity) --n;
+    while (n > 1 && chip_need(n - 1, CHIP_WIDE) > std::min(cus, CHIP_WGS)) --n;
     return n > 1 ? n : 0;
 }
 
 // The widest factors that are left come first; narrower ones fill what they leave free.
-inline void chip_plan(std::vector<ChipFactor> left, int capacity, std::vector<ChipJob> &jobs, std::vector<ChipLaunch> &launches) {
+inline void chip_plan(std::vector<ChipFactor> left, int cus, std::vector<ChipJob> &jobs, std::vector<ChipLaunch> &launches) {
     auto size = [](const ChipFactor &f) { return f.n - 1 - f.k; };
     while (!left.empty()) {
         std::stable_sort(left.begin(), left.end(), [&](const ChipFactor &a, const ChipFactor &b) { return size(a) > size(b); });
         const int widest = size(left[0]);
+        // Two narrow workgroups of a compute unit hide each other's exchange where the chip is full of factors; one factor alone has fewer
+        // column slots, and shorter sections between the exchanges, in wide ones.
+        int crowd = 0;
+        for (const ChipFactor &f : left) crowd += (size(f) + CHIP_CROWD - 1) / CHIP_CROWD;
+        const int threads = crowd > cus && widest <= CHIP_NARROW * CHIP_NARROW_SLOTS ? CHIP_NARROW : CHIP_WIDE;
         // dealing a matrix out anew costs its bytes and a launch, some 50 us for the widest: a sixth of its columns take 40 times that
         const int steps = widest <= CHIP_WHOLE ? widest : std::max(CHIP_STEPS_MIN, widest / 6);
-        ChipLaunch L{(unsigned)jobs.size(), 0, 0, 0.0, 0.0};
-        int free = capacity;
+        ChipLaunch L{(unsigned)jobs.size(), 0, 0, threads, 0.0, 0.0};
+        int free = cus * (CHIP_WIDE / threads);
         std::vector<size_t> taken, sizes;
         for (size_t q = 0; q < left.size() && taken.size() < CHIP_JOBS; ++q) {
-            const int z = size(left[q]), need = chip_need(z);
+            const int z = size(left[q]), need = chip_need(z, threads), S = chip_slots(z, threads);
             if (need > free) continue;
             free -= need;
             taken.push_back(q);
             sizes.push_back(z);
-            jobs.push_back(ChipJob{left[q].m, left[q].k, std::min(steps, z), chip_rows(chip_slots(z)), need, 0, chip_slots(z), left[q].turn});
+            jobs.push_back(ChipJob{left[q].m, left[q].k, std::min(steps, z), chip_rows(S), need, 0, S, left[q].turn});
         }
-        // what is free goes to those that do the most per workgroup, a piece less each time
+        // what is free goes to those that do the most per workgroup, a group less each time
         for (;;) {
             int most = -1;
             for (size_t q = 0; q < taken.size(); ++q) {
                 const ChipJob &J = jobs[L.at + q];
-                if (J.rows > chip_piece(J.slots) && (most < 0 || J.rows * J.slots > jobs[L.at + most].rows * jobs[L.at + most].slots)) most = (int)q;
+                if (J.rows - 4 >= CHIP_ROWS_MIN && (most < 0 || J.rows * J.slots > jobs[L.at + most].rows * jobs[L.at + most].slots)) most = (int)q;
             }
             if (most < 0) break;
             ChipJob &J = jobs[L.at + most];
-            const int rows = J.rows - chip_piece(J.slots), want = ((int)sizes[most] + rows - 1) / rows;
-            if (want - J.wgs > free) break;
+            const int rows = (J.rows - 1) / 4 * 4, want = ((int)sizes[most] + rows - 1) / rows;
+            if (want - J.wgs > free || want > CHIP_WGS) break;
             free -= want - J.wgs;
             J.rows = rows;
             J.wgs = want;

@@ -1504,7 +1504,8 @@ int enqueue_reduction(kfac_ctx *ctx, const DirRun &R) {
         // of three multiplications and additions per element, one belongs to the product and two to the update
         KfacProfScope product(ctx, KC_EIG_REDUCE_MV, L.flops / 3.0, L.bytes / 3.0, st, 1.0 / 3.0);
         KfacProfScope update(ctx, KC_EIG_REDUCE_GEMM, L.flops / 1.5, L.bytes / 1.5, st, 2.0 / 3.0);
-        KFAC_HIP_CHECK(hipLaunchCooperativeKernel((const void *)dir_chip_kernel, dim3((unsigned)L.wgs), dim3(CHIP_NT), args, 0, st));
+        const void *kernel = L.threads == CHIP_WIDE ? (const void *)dir_chip_kernel<CHIP_WIDE> : (const void *)dir_chip_kernel<CHIP_NARROW>;
+        KFAC_HIP_CHECK(hipLaunchCooperativeKernel(kernel, dim3((unsigned)L.wgs), dim3((unsigned)L.threads), args, 0, st));
     }
     if (P.nmax > TD_SMALL) {
         KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 2.0 * R.square, st);
