@@ -184,10 +184,12 @@ __device__ inline void grp_mfma(const uint4 (&fa)[4][2], const uint4 (&fb)[4][2]
 // acc = A B^T over groups [q0, q_end) (both operands as elem(row, position)); DIAG: B is the same row block
 // as A and is neither loaded nor staged.  With COLSUM every thread also accumulates, per u, the sum of the
 // A-operand elements it fetches (csum[u]); summed over the eight threads that share a row this is the row's
-// sum over all positions.
-template <typename E, bool DIAG, bool COLSUM>
-__device__ inline void gemm_tile_grouped(GrpOpNDT<E> &A, GrpOpNDT<E> &B, int i0, int j0, int q0, int q_end, GrpSmem &sm,
-                                         floatx16 (&acc)[2][2], float *csum) {
+// sum over all positions.  Returns what every wave has computed.
+// SLICES: a tile below the diagonal of which only the first 64 rows exist, cut into four slices of 32 columns, one per wave: under the map of
+// quadrants two waves had all of its work and two had none, and it took as long as a whole tile (576 features: four of fifteen tiles).
+template <typename E, bool DIAG, bool COLSUM, bool SLICES = false>
+__device__ inline WaveMap gemm_tile_grouped(GrpOpNDT<E> &A, GrpOpNDT<E> &B, int i0, int j0, int q0, int q_end, GrpSmem &sm,
+                                            floatx16 (&acc)[2][2], float *csum) {
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     // In a diagonal tile the quadrant above the diagonal (wave 1's) is never read, while the one below it is the
@@ -195,7 +197,8 @@ __device__ inline void gemm_tile_grouped(GrpOpNDT<E> &A, GrpOpNDT<E> &B, int i0,
     // of wave 2's work: both multiply the lower-left quadrant, each over two of a slab's four k-steps, and the two
     // sums are added through LDS at the end.  No wave then has more than 12 of a slab's block-steps instead of 16.
     const bool helper = DIAG && wave == 1;
-    const int wm = helper ? 64 : (wave >> 1) * 64, wn = helper ? 0 : (wave & 1) * 64;
+    const int wm = SLICES ? 0 : helper ? 64 : (wave >> 1) * 64, wn = SLICES ? 32 * wave : helper ? 0 : (wave & 1) * 64;
+    constexpr int CB = SLICES ? 1 : 2;       // column blocks of a wave
     const unsigned ksteps = __builtin_amdgcn_readfirstlane(!DIAG ? 0xFu : wave == 1 ? 0xCu : wave == 2 ? 0x3u : 0xFu);
     const int lk = lane >> 5, lc = lane & 31;
 #pragma unroll
@@ -205,7 +208,7 @@ __device__ inline void gemm_tile_grouped(GrpOpNDT<E> &A, GrpOpNDT<E> &B, int i0,
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     const int nslab = (q_end - q0 + GRP_GROUPS - 1) / GRP_GROUPS;
-    if (nslab <= 0) return;
+    if (nslab <= 0) return WaveMap{wm, wn, SLICES ? 5u : helper ? 0u : 0xFu};
     // Two LDS buffers.  Step s: wait for this wave's loads of slab s, clear overlapping positions, barrier (slab s is
     // complete and nobody reads slab s-1 any more), start the loads of slab s+1 into the buffer slab s-1 used, then
     // multiply slab s.  The loads fly during the MFMAs of the slab before; the second workgroup on the compute unit
@@ -221,7 +224,7 @@ __device__ inline void gemm_tile_grouped(GrpOpNDT<E> &A, GrpOpNDT<E> &B, int i0,
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < CB; ++j)
             if (i0 + wm + 32 * i < A.d && j0 + wn + 32 * j < A.d && (!DIAG || wn + 32 * j <= wm + 32 * i)) blocks |= 1u << (2 * i + j);
     blocks = __builtin_amdgcn_readfirstlane(blocks);
     for (int s = 0; s < nslab; ++s) {
@@ -242,7 +245,7 @@ __device__ inline void gemm_tile_grouped(GrpOpNDT<E> &A, GrpOpNDT<E> &B, int i0,
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 fa[ks][i] = *reinterpret_cast<const uint4 *>(pa + (wm + 32 * i + lc) * GRP_ROWB + (((2 * ks + lk) ^ swz) * 16));
-                fb[ks][i] = *reinterpret_cast<const uint4 *>(pb + (wn + 32 * i + lc) * GRP_ROWB + (((2 * ks + lk) ^ swz) * 16));
+                fb[ks][i] = *reinterpret_cast<const uint4 *>(pb + (wn + (i < CB ? 32 * i : 0) + lc) * GRP_ROWB + (((2 * ks + lk) ^ swz) * 16));
             }
         __builtin_amdgcn_sched_barrier(0);
         grp_mfma<0, 1>(fa, fb, acc, blocks, ksteps, E());
@@ -283,14 +286,15 @@ __device__ inline void gemm_tile_grouped(GrpOpNDT<E> &A, GrpOpNDT<E> &B, int i0,
         }
         __syncthreads();
     }
+    return WaveMap{wm, wn, helper ? 0u : blocks};
 }
 
-// The single (diagonal) tile of a factor with at most 64 rows.  A 128 x 128 tile would spend three quarters of its
-// MFMAs on rows and columns that do not exist; here all four waves compute the same 64 x 64 block, each over a
-// quarter of every slab (k-step `wave`), and the four partial sums are added through LDS at the end.  On return
-// wave 0 holds the block in the usual accumulator layout and the other waves hold zeros.
+// A diagonal tile of which at most the first 64 rows exist (the only one of a factor that narrow, or the last one).  A 128 x 128 tile would
+// spend three quarters of its MFMAs on rows and columns that do not exist; here all four waves compute the same 64 x 64 block
+// (the 32 x 32 one, if that is all; never the one above the diagonal), each over a quarter of every slab (k-step `wave`), and the four partial sums
+// are added through LDS at the end.  On return wave 0 holds the block in the usual accumulator layout and the other waves hold zeros.
 template <typename E, bool COLSUM>
-__device__ inline void gemm_tile_grouped_small(GrpOpNDT<E> &A, int q0, int q_end, GrpSmem &sm, floatx16 (&acc)[2][2], float *csum) {
+__device__ inline WaveMap gemm_tile_grouped_small(GrpOpNDT<E> &A, int i0, int q0, int q_end, GrpSmem &sm, floatx16 (&acc)[2][2], float *csum) {
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int lk = lane >> 5, lc = lane & 31;
@@ -300,10 +304,12 @@ __device__ inline void gemm_tile_grouped_small(GrpOpNDT<E> &A, int q0, int q_end
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    const bool two = A.d - i0 > 32;
+    const WaveMap map{0, 0, wave != 0 ? 0u : two ? 0xDu : 1u};
     const int nslab = (q_end - q0 + GRP_GROUPS - 1) / GRP_GROUPS;
-    if (nslab <= 0) return;
+    if (nslab <= 0) return map;
     A.q_end = q_end;
-    A.start(tid, 0, q0);
+    A.start(tid, i0, q0);
     int sha = A.issue(sm.a[0], tid);
     const int swz = (lc >> 1) & 7;
     for (int s = 0; s < nslab; ++s) {
@@ -328,19 +334,21 @@ __device__ inline void gemm_tile_grouped_small(GrpOpNDT<E> &A, int q0, int q_end
             const unsigned a[2][4] = {{f[0].x, f[0].y, f[0].z, f[0].w}, {f[1].x, f[1].y, f[1].z, f[1].w}};
 #pragma unroll
             for (int e = 0; e < 4; ++e)
+                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[0][e]), __uint_as_float(a[0][e]), acc[0][0], 0, 0, 0);
+            if (two)
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
+                for (int e = 0; e < 4; ++e)
 #pragma unroll
                     for (int j = 0; j < 2; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[i][e]), __uint_as_float(a[j][e]), acc[i][j], 0, 0, 0);
+                        acc[1][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[1][e]), __uint_as_float(a[j][e]), acc[1][j], 0, 0, 0);
         } else {
             bf16x8 x[2];
             __builtin_memcpy(&x[0], &f[0], 16);
             __builtin_memcpy(&x[1], &f[1], 16);
+            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], x[0], acc[0][0], 0, 0, 0);
+            if (two)
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[i], x[j], acc[i][j], 0, 0, 0);
+                for (int j = 0; j < 2; ++j) acc[1][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], x[j], acc[1][j], 0, 0, 0);
         }
     }
     __syncthreads();
@@ -368,6 +376,7 @@ __device__ inline void gemm_tile_grouped_small(GrpOpNDT<E> &A, int q0, int q_end
                     for (int r = 0; r < 16; ++r) acc[i][j][r] += scratch[((w * 64) + (i * 2 + j) * 16 + r) * 64 + lane];
     }
     __syncthreads();   // callers reuse the slab buffers
+    return map;
 }
 
 }  // namespace kfac

@@ -97,10 +97,10 @@ template <> __device__ inline OpStrided<unsigned short, false> make_op(const Syr
 
 // Final sum of a tile (running average applied, mirrored) or this split's partial.
 __device__ inline void syrk_epilogue(const SyrkArgs &g, const SyrkJob &job, int ti, int tj, bool want_cs,
-                                     const floatx16 (&acc)[2][2], const float *cs) {
+                                     const floatx16 (&acc)[2][2], const float *cs, const WaveMap map = wave_map_full()) {
     const bool diag = ti == tj;
     if (g.nsplit == 1) {
-        for_each_acc(acc, [&](int r, int c, float v) {
+        for_each_acc(acc, map, [&](int r, int c, float v) {
             const int gr = ti * BM + r, gc = tj * BM + c;
             if (gr < g.d && gc < g.d && (!diag || gc <= gr))
                 ema_store(g.F, g.D, gr, gc, v, g.alpha, g.decay, gr != gc);
@@ -112,7 +112,7 @@ __device__ inline void syrk_epilogue(const SyrkArgs &g, const SyrkJob &job, int 
         }
     } else {
         float *dst = g.partial + ((int64_t)job.split * g.ntri + job.tri) * PART;
-        for_each_acc(acc, [&](int r, int c, float v) { dst[r * BM + c] = v; });
+        for_each_acc(acc, map, [&](int r, int c, float v) { dst[r * BM + c] = v; });
         if (want_cs && threadIdx.x < BM) dst[BM * BM + threadIdx.x] = cs[threadIdx.x];
     }
 }
@@ -169,12 +169,14 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     float csum[GRP_RPT];
 #pragma unroll
     for (int u = 0; u < GRP_RPT; ++u) csum[u] = 0.f;
-    if (g.d <= 64) {   // one tile, a quarter of it in use: contraction split over the waves instead
-        if (want_cs) gemm_tile_grouped_small<E, true>(a, q0, q_end, sm, acc, csum);
-        else gemm_tile_grouped_small<E, false>(a, q0, q_end, sm, acc, csum);
-    } else if (want_cs) gemm_tile_grouped<E, true, true>(a, b, ti * BM, tj * BM, q0, q_end, sm, acc, csum);
-    else if (diag) gemm_tile_grouped<E, true, false>(a, b, ti * BM, tj * BM, q0, q_end, sm, acc, csum);
-    else gemm_tile_grouped<E, false, false>(a, b, ti * BM, tj * BM, q0, q_end, sm, acc, csum);
+    WaveMap map;
+    if (diag && g.d - ti * BM <= 64) {   // a quarter of the tile in use: contraction split over the waves instead
+        if (want_cs) map = gemm_tile_grouped_small<E, true>(a, ti * BM, q0, q_end, sm, acc, csum);
+        else map = gemm_tile_grouped_small<E, false>(a, ti * BM, q0, q_end, sm, acc, csum);
+    } else if (want_cs) map = gemm_tile_grouped<E, true, true>(a, b, ti * BM, tj * BM, q0, q_end, sm, acc, csum);
+    else if (diag) map = gemm_tile_grouped<E, true, false>(a, b, ti * BM, tj * BM, q0, q_end, sm, acc, csum);
+    else if (g.d - ti * BM > 64) map = gemm_tile_grouped<E, false, false>(a, b, ti * BM, tj * BM, q0, q_end, sm, acc, csum);
+    else map = gemm_tile_grouped<E, false, false, true>(a, b, ti * BM, tj * BM, q0, q_end, sm, acc, csum);
     if (want_cs) {   // the K loop ended on a barrier, so the slab buffers are free: sum the eight threads of a row in order
         const int tid = threadIdx.x;
         float *scratch = reinterpret_cast<float *>(sm.a[0]);
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         }
         __syncthreads();
     }
-    syrk_epilogue(g, job, ti, tj, want_cs, acc, cs);
+    syrk_epilogue(g, job, ti, tj, want_cs, acc, cs, map);
 }
 
 // Sum the split partials of each tile in split order, then apply the running average and mirror.
@@ -298,9 +300,13 @@ void plan_item(int n, const kfac_factor_item &it, int shift, int &ntri, int &nsp
     else plan_batched(it.d, R, BK, JOB_SLABS >> shift, ntri, nsplit, kchunk);
 }
 
-// A batch with fewer jobs than compute units: half the slabs per job, and again, down to a sixteenth.  (One conv layer, factors 145
-// and 16 wide from 2048 samples: 4 jobs of 64 slabs took 131 us, 16 of 16 slabs and the reducer 38.)
-constexpr int MIN_JOBS = 256, MAX_SHIFT = 4;
+// A batch with fewer jobs than this: half the slabs per job, and again, down to a sixteenth.  Two jobs share a compute unit, so 512 run at
+// a time; with few jobs per slot the last round is mostly empty, and whole tiles wait beside edge tiles that are done in a quarter
+// of their time.  (One conv layer, factors 145 and 16 wide from 2048 samples: 4 jobs of 64 slabs took 131 us, 16 of 16 slabs and the reducer
+// 38.  From 256, 1024, 2048 and 4096 jobs on as they are: the ResNet-32 step 5880, 5876, 5326, 5212 us; fp32 factors of a net of thirty
+// convolutions 8 to 56 wide 1635, 1378, 1197, 1148.  Its jobs being three times as fast, the bf16 engine gains less and loses by short ones
+// sooner: factors of eight blocks 17 to 136 wide 446, 243, 278, 278, of seven blocks 53 to 424 wide 806, 805, 801, 871.)
+constexpr int MIN_JOBS_F32 = 4096, MIN_JOBS_B16 = 1024, MAX_SHIFT = 4;
 int plan_shift(int n, const kfac_factor_item *items) {
     for (int shift = 0; shift < MAX_SHIFT && n > 1; ++shift) {
         int64_t jobs = 0;
@@ -309,7 +315,7 @@ int plan_shift(int n, const kfac_factor_item *items) {
             plan_item(n, items[i], shift, ntri, nsplit, kchunk);
             jobs += (int64_t)ntri * nsplit;
         }
-        if (jobs >= MIN_JOBS) return shift;
+        if (jobs >= (form_of(items[0]) == 4 ? MIN_JOBS_B16 : MIN_JOBS_F32)) return shift;
     }
     return n > 1 ? MAX_SHIFT : 0;
 }

@@ -714,6 +714,28 @@ def test_update_factors_batch_too_small_for_the_machine(N, d, T, bf16, layout):
             assert relfro(f.cpu().numpy(), oracle.gram(rows, 1, 1.0 / (N * T))) <= 1e-6, (ws, x.shape)
 
 
+# 128 m and up to 64 more features: the last row of tiles in slices of 32 columns, its diagonal tile with the contraction shared by the waves
+# (one or two 32-wide blocks of it); more than 64: under the map of quadrants
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("d", [31, 33, 64, 129, 144, 160, 161, 192, 193, 320, 321])
+def test_update_factors_ragged_last_tiles(d, bf16):
+    """Sums of products of integers up to 8, below 2^24: exact in fp32 whatever the order."""
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    N, T = 6, 49
+    X = torch.randint(-8, 9, (N, d, T), generator=gen, device="cuda").to(torch.bfloat16 if bf16 else torch.float32)
+    rows = torch.cat([X.double().permute(0, 2, 1).reshape(N * T, d), torch.ones((N * T, 1), device="cuda", dtype=torch.float64)], 1)
+    want = (rows.T.contiguous() @ rows).float()
+    c = Ctx(64 << 20)
+    F = [torch.full((d + 1, d + 1), float("nan"), device="cuda") for _ in range(3)]
+    K.kfac_update_factors(c.h, X, K.KFAC_LAYOUT_NDT, N, d, T, 1, 1.0, 0.0, F[0], dtype=K.KFAC_BF16 if bf16 else K.KFAC_F32)
+    K.kfac_update_factors_batched(c.h, [dict(X=X, dtype=K.KFAC_BF16 if bf16 else K.KFAC_F32, layout=K.KFAC_LAYOUT_NDT, N=N, d=d, T=T, append_ones=1,
+                                             scale=1.0, decay=0.0, F=f) for f in F[1:]])
+    torch.cuda.synchronize()
+    c.close()
+    for f in F:
+        assert torch.equal(f, want)
+
+
 # ------------------------------------------------------------------ precondition
 # (230, 100) and (97, 200): edge tiles between 65 and 127 wide and tall (accumulator blocks masked under the full
 # wave map); the others: edge tiles at most 64 wide or tall (the waves share them in slices)
