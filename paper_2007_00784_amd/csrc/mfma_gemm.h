@@ -461,6 +461,97 @@ __device__ inline void gemm_tile_ragged(OpA &a, OpB &b, int i0, int j0, int K, i
     }
 }
 
+// ---- 64 x 64 tiles, their contraction shared by the four waves: for products with few tiles --------------------------
+// A workgroup of the engine above that has a compute unit to itself waits for every slab of 16; here a slab is 64 deep, every wave multiplies
+// the whole tile over a quarter of it, there are four times the tiles, and the four sums are added in LDS at the end, in order.
+constexpr int SMALL_EDGE = 64, SMALL_K = 64, SMALL_LD = SMALL_EDGE + 1;
+constexpr int SMALL_EPT = SMALL_EDGE * SMALL_K / NTHREADS;      // elements per thread and operand of a slab: 16
+union SmallTileSmem {
+    struct { float a[SMALL_K][SMALL_LD], b[SMALL_K][SMALL_LD]; } slab;
+    float sums[4][3][16][64];     // [block][from][accumulator element][lane]
+};
+
+// The slab of `op` that begins at contraction index k0 for rows i0 ..: consecutive threads along the index that is contiguous in memory.
+template <class E, bool KFAST>
+__device__ inline void small_fetch(const OpStrided<E, KFAST> &op, int i0, int k0, int K, E (&r)[SMALL_EPT]) {
+    const int tid = threadIdx.x, f = tid & 63, g = tid >> 6;
+    const __amdgpu_buffer_rsrc_t rs = buffer_at(op.p + (int64_t)i0 * op.si + (int64_t)k0 * op.sk);
+#pragma unroll
+    for (int s = 0; s < SMALL_EPT; ++s) {
+        const int i = KFAST ? g + 4 * s : f, k = KFAST ? f : g + 4 * s;
+        const bool in = i0 + i < op.I && k0 + k < K;
+        buffer_load(rs, in ? (unsigned)(((int64_t)i * op.si + (int64_t)k * op.sk) * (int64_t)sizeof(E)) : BUF_OUTSIDE, r[s]);
+    }
+}
+template <class E, bool KFAST> __device__ inline void small_store(const OpStrided<E, KFAST> &, const E (&r)[SMALL_EPT], float (*dst)[SMALL_LD]) {
+    const int f = threadIdx.x & 63, g = threadIdx.x >> 6;
+#pragma unroll
+    for (int s = 0; s < SMALL_EPT; ++s) {
+        if (KFAST) dst[f][g + 4 * s] = to_float(r[s]);
+        else dst[g + 4 * s][f] = to_float(r[s]);
+    }
+}
+
+// epi(row, col, value) for every element of the tile inside the M x N matrix; the offsets of a slab have to stay below 2^31 bytes.
+template <class OpA, class OpB, class Epi>
+__device__ inline void gemm_tile_small(const OpA &A, const OpB &B, int i0, int j0, int K, int M, int N, SmallTileSmem &sm, Epi epi) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lk = lane >> 5, lc = lane & 31;
+    floatx16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    typename OpA::Raw ra[SMALL_EPT];
+    typename OpB::Raw rb[SMALL_EPT];
+    small_fetch(A, i0, 0, K, ra);
+    small_fetch(B, j0, 0, K, rb);
+    for (int k0 = 0; k0 < K; k0 += SMALL_K) {
+        small_store(A, ra, sm.slab.a);
+        small_store(B, rb, sm.slab.b);
+        __syncthreads();
+        if (k0 + SMALL_K < K) {
+            small_fetch(A, i0, k0 + SMALL_K, K, ra);
+            small_fetch(B, j0, k0 + SMALL_K, K, rb);
+        }
+        float a[2][8], b[2][8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                a[i][j] = sm.slab.a[16 * wave + 2 * j + lk][32 * i + lc];
+                b[i][j] = sm.slab.b[16 * wave + 2 * j + lk][32 * i + lc];
+            }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) acc[i][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][j], b[c][j], acc[i][c], 0, 0, 0);
+        __syncthreads();
+    }
+    // wave w ends with block w of the four
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (q != wave)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sm.sums[q][wave - (wave > q ? 1 : 0)][r][lane] = acc[q >> 1][q & 1][r];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (q == wave)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                float v = 0.f;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) v += w == q ? acc[q >> 1][q & 1][r] : sm.sums[q][w - (w > q ? 1 : 0)][r][lane];
+                const int gr = i0 + 32 * (q >> 1) + 8 * (r >> 2) + 4 * lk + (r & 3), gc = j0 + 32 * (q & 1) + lc;
+                if (gr < M && gc < N) epi(gr, gc, v);
+            }
+}
+
 // Epilogue objects are called as epi(row, col, value) for every in-range element of a tile.
 struct EpiStore {
     float *C;

@@ -13,6 +13,7 @@
 // longest contraction first), so small layers do not leave the machine idle and a 54-layer network
 // costs four launches instead of 216.  T and V2 live in the context workspace.
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 #include "kfac_internal.h"
 #include "mfma_gemm.h"
@@ -48,17 +49,23 @@ template <class OpA, class OpB, class Epi>
 __device__ inline void run_tile(OpA a, OpB b, int i0, int j0, int K, int M, int N, TileSmem &sm, Epi epi) {
     gemm_tile_ragged(a, b, i0, j0, K, M, N, sm, epi);
 }
+template <class OpA, class OpB, class Epi>
+__device__ inline void run_tile(OpA a, OpB b, int i0, int j0, int K, int M, int N, SmallTileSmem &sm, Epi epi) {
+    gemm_tile_small(a, b, i0, j0, K, M, N, sm, epi);
+}
 
-template <int STAGE>
+// SMALL: tiles of 64 x 64, whose contraction the four waves share, for calls with few tiles (SMALL_MAX).
+template <int STAGE, bool SMALL>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void precond_stage_kernel(const LayerDev *layers, const TileRef *tiles,
                                                                                                        double *dots) {
-    __shared__ TileSmem sm;
+    __shared__ typename std::conditional<SMALL, SmallTileSmem, TileSmem>::type sm;
     const TileRef tr = tiles[blockIdx.x];
     const LayerDev L = layers[tr.layer];
     if (L.split) return;
+    constexpr int TE = SMALL ? SMALL_EDGE : BM;
     const int dA = L.dA, dG = L.dG;
-    const int tn = (dA + BM - 1) / BM;
-    const int i0 = (tr.tile / tn) * BM, j0 = (tr.tile % tn) * BM;
+    const int tn = (dA + TE - 1) / TE;
+    const int i0 = (tr.tile / tn) * TE, j0 = (tr.tile % tn) * TE;
     if (STAGE == 0) {
         // T = QG^T grad : A(m,k) = QG[k][m] (m contiguous), B(k,n) = grad[k][n] (n contiguous)
         OpStrided<float, false> qgt{L.QG, 1, dG, dG, dG, -1};
@@ -265,11 +272,11 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 }
 
 // nu from the per-tile inner products (layer sums and the sum over layers in fixed order), one thread.
-__global__ void precond_nu_kernel(const LayerDev *layers, int n, const double *dots, float kappa, float lr, float *nu) {
+__global__ void precond_nu_kernel(const LayerDev *layers, int n, int edge, const double *dots, float kappa, float lr, float *nu) {
     if (blockIdx.x != 0 || threadIdx.x != 0) return;
     double total = 0.0;
     for (int l = 0; l < n; ++l) {
-        const int nt = ((layers[l].dG + BM - 1) / BM) * ((layers[l].dA + BM - 1) / BM);
+        const int nt = ((layers[l].dG + edge - 1) / edge) * ((layers[l].dA + edge - 1) / edge);
         double d = 0.0;
         for (int t = 0; t < nt; ++t) d += dots[layers[l].tile_base + t];
         total += fabs(d);
@@ -296,11 +303,27 @@ __global__ __launch_bounds__(256) void precond_scale_kernel(const LayerDev *laye
     }
 }
 
-size_t layout(int n, const kfac_precond_item *it, size_t &off_tiles, size_t &off_tv, size_t &ntiles) {
-    ntiles = 0;
+size_t count_tiles(int n, const kfac_precond_item *it, int edge) {
+    size_t t = 0;
+    for (int i = 0; i < n; ++i) t += (size_t)((it[i].dG + edge - 1) / edge) * ((it[i].dA + edge - 1) / edge);
+    return t;
+}
+
+// Up to this many tiles of 128 small ones are faster: with one tile or little more for a compute unit its four waves wait for every slab.
+// Whole chains in us, tiles of 128 and small ones: one layer 3025 x 314 (72 tiles) 607 and 220, twelve layers up to 127 x 248 (60) 320 and 137,
+// twenty up to 280 x 496 (249) 605 and 321, one 2400 x 2401 (361) 1449 and 1213, one 2700 x 2501 (440) 1539 and 1707, seven of 1000 x 1001
+// (448) 660 and 719, three up to 2048 (680) 1900 and 2050.
+constexpr size_t SMALL_MAX = 384;
+int tile_edge(int n, const kfac_precond_item *it) {
+    for (int i = 0; i < n; ++i)
+        if (it[i].split_f16) return BM;
+    return count_tiles(n, it, BM) <= SMALL_MAX ? SMALL_EDGE : BM;
+}
+
+size_t layout(int n, const kfac_precond_item *it, int edge, size_t &off_tiles, size_t &off_tv, size_t &ntiles) {
+    ntiles = count_tiles(n, it, edge);
     size_t tv = 0;
     for (int i = 0; i < n; ++i) {
-        ntiles += (size_t)((it[i].dG + BM - 1) / BM) * ((it[i].dA + BM - 1) / BM);
         tv += 2 * kfac_align_up((size_t)it[i].dG * it[i].dA, 64);
     }
     off_tiles = kfac_align_up((size_t)n * sizeof(LayerDev), 256);
@@ -314,14 +337,17 @@ size_t layout(int n, const kfac_precond_item *it, size_t &off_tiles, size_t &off
 
 size_t kfac_precond_ws_bytes_impl(int n, const kfac_precond_item *items) {
     size_t a, b, c;
-    return layout(n, items, a, b, c);
+    return layout(n, items, tile_edge(n, items), a, b, c);
 }
 
 int kfac_launch_precondition_batched(kfac_ctx *ctx, int n, const kfac_precond_item *items, bool scaled, float kappa, float lr,
                                      float *nu) {
     size_t off_tiles, off_tv, ntiles;
-    const size_t need = layout(n, items, off_tiles, off_tv, ntiles);
-    if (need > ctx->ws_bytes) return KFAC_EWORKSPACE;
+    int edge = tile_edge(n, items);
+    if (layout(n, items, edge, off_tiles, off_tv, ntiles) > ctx->ws_bytes) {      // (the tables of small tiles are a little longer)
+        edge = BM;
+        if (layout(n, items, edge, off_tiles, off_tv, ntiles) > ctx->ws_bytes) return KFAC_EWORKSPACE;
+    }
     std::vector<LayerDev> dev(n);
     float *tv = (float *)(ctx->ws + off_tv);
     const size_t off_dots = off_tiles + kfac_align_up(2 * ntiles * sizeof(TileRef), 256);
@@ -336,7 +362,7 @@ int kfac_launch_precondition_batched(kfac_ctx *ctx, int n, const kfac_precond_it
         dev[i] = LayerDev{p.QA, p.lamA, p.QG, p.lamG, p.grad, tv, tv + e, p.dA, p.dG, p.damping, p.grad_dtype == KFAC_BF16, tile_base, p.factored_damping,
                           p.split_f16, d_gnorm + (size_t)i * NORM_PARTS, d_vnorm + tile_base};
         (p.split_f16 ? any_split : any_plain) = true;
-        tile_base += ((p.dG + BM - 1) / BM) * ((p.dA + BM - 1) / BM);
+        tile_base += (int)count_tiles(1, &p, edge);
         tv += 2 * e;
         flops += 4.0 * p.dA * p.dG * ((double)p.dA + p.dG);
         bytes += 4.0 * ((double)p.dA * p.dA + (double)p.dG * p.dG) * 2 + 4.0 * 8 * p.dA * p.dG;
@@ -345,7 +371,7 @@ int kfac_launch_precondition_batched(kfac_ctx *ctx, int n, const kfac_precond_it
     std::vector<TileRef> byG, byA;
     byG.reserve(ntiles);
     for (int i = 0; i < n; ++i) {
-        const int nt = ((items[i].dG + BM - 1) / BM) * ((items[i].dA + BM - 1) / BM);
+        const int nt = (int)count_tiles(1, &items[i], edge);
         for (int t = 0; t < nt; ++t) byG.push_back(TileRef{i, t});
     }
     byA = byG;
@@ -358,6 +384,7 @@ int kfac_launch_precondition_batched(kfac_ctx *ctx, int n, const kfac_precond_it
     KFAC_CHECK(kfac_upload(ctx, d_byG, byG.data(), ntiles * sizeof(TileRef)));
     KFAC_CHECK(kfac_upload(ctx, d_byA, byA.data(), ntiles * sizeof(TileRef)));
     const dim3 grid((unsigned)ntiles), block(NTHREADS);
+    const bool small = edge == SMALL_EDGE;
     if (any_split) {
         KfacProfScope prof(ctx, KC_PRECOND_SCALE, 0.0, bytes / 16);   // one read of every gradient
         hipLaunchKernelGGL(precond_norm_kernel, dim3(NORM_PARTS, n), dim3(256), 0, ctx->stream, d_layers);
@@ -369,10 +396,10 @@ int kfac_launch_precondition_batched(kfac_ctx *ctx, int n, const kfac_precond_it
         if (any_plain) {
             KfacProfScope prof(ctx, KC_PRECOND_GEMM, any_split ? 0.0 : flops / 4, any_split ? 0.0 : bytes / 4);
             switch (stage) {
-                case 0: hipLaunchKernelGGL(precond_stage_kernel<0>, grid, block, 0, ctx->stream, d_layers, order, dots); break;
-                case 1: hipLaunchKernelGGL(precond_stage_kernel<1>, grid, block, 0, ctx->stream, d_layers, order, dots); break;
-                case 2: hipLaunchKernelGGL(precond_stage_kernel<2>, grid, block, 0, ctx->stream, d_layers, order, dots); break;
-                default: hipLaunchKernelGGL(precond_stage_kernel<3>, grid, block, 0, ctx->stream, d_layers, order, dots); break;
+                case 0: hipLaunchKernelGGL((small ? precond_stage_kernel<0, true> : precond_stage_kernel<0, false>), grid, block, 0, ctx->stream, d_layers, order, dots); break;
+                case 1: hipLaunchKernelGGL((small ? precond_stage_kernel<1, true> : precond_stage_kernel<1, false>), grid, block, 0, ctx->stream, d_layers, order, dots); break;
+                case 2: hipLaunchKernelGGL((small ? precond_stage_kernel<2, true> : precond_stage_kernel<2, false>), grid, block, 0, ctx->stream, d_layers, order, dots); break;
+                default: hipLaunchKernelGGL((small ? precond_stage_kernel<3, true> : precond_stage_kernel<3, false>), grid, block, 0, ctx->stream, d_layers, order, dots); break;
             }
         }
         if (any_split) {
@@ -389,7 +416,7 @@ int kfac_launch_precondition_batched(kfac_ctx *ctx, int n, const kfac_precond_it
         double total = 0.0;
         for (int i = 0; i < n; ++i) total += (double)items[i].dG * items[i].dA;
         KfacProfScope prof(ctx, KC_PRECOND_SCALE, 0.0, 8.0 * total);   // read + write of every gradient (when nu < 1)
-        hipLaunchKernelGGL(precond_nu_kernel, dim3(1), dim3(64), 0, ctx->stream, d_layers, n, d_dots, kappa, lr, nu);
+        hipLaunchKernelGGL(precond_nu_kernel, dim3(1), dim3(64), 0, ctx->stream, d_layers, n, edge, d_dots, kappa, lr, nu);
         hipLaunchKernelGGL(precond_scale_kernel, dim3(64, n), dim3(256), 0, ctx->stream, d_layers, nu);
     }
     KFAC_HIP_CHECK(hipGetLastError());

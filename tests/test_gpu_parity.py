@@ -763,6 +763,31 @@ def test_precondition_matches_oracle(ctx, dA, dG, bf16):
     assert relfro(got, ref) <= (TOL_BF16 if bf16 else TOL_F32)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+def test_precondition_in_small_and_large_tiles(bf16):
+    """The same layers in a call of few tiles and beside a layer that fills the machine (tiles of 64 and of 128), against fp64.  Four products of
+    up to 600 terms with orthogonal matrices: fp32 sums are off by less than 4 sqrt(600) 2^-24 = 6e-6; a rounding of the result to bf16 by 2^-9."""
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    sizes = PRECOND_CASES + [(64, 64), (128, 65), (129, 63), (4, 1), (2500, 2500)]
+    basis = lambda n: torch.linalg.qr(torch.randn((n, n), generator=gen, device="cuda", dtype=torch.float64))[0].contiguous()
+    QA, QG = [basis(a) for a, _ in sizes], [basis(g) for _, g in sizes]
+    lamA, lamG = [torch.rand(a, generator=gen, device="cuda") for a, _ in sizes], [torch.rand(g, generator=gen, device="cuda") for _, g in sizes]
+    grads = [torch.randn((g, a), generator=gen, device="cuda").to(torch.bfloat16 if bf16 else torch.float32) for a, g in sizes]
+    c = Ctx(256 << 20)
+    for count in (len(sizes) - 1, len(sizes)):
+        got = [g.clone() for g in grads[:count]]
+        nu = torch.empty(1, device="cuda")
+        K.kfac_precondition_batched_scaled(c.h, [q.float() for q in QA[:count]], lamA[:count], [q.float() for q in QG[:count]], lamG[:count], 0.1, got,
+                                           kappa=1e30, lr=0.1, nu=nu)
+        torch.cuda.synchronize()
+        assert float(nu) == 1.0
+        for qa, qg, la, lg, g, x in zip(QA, QG, lamA, lamG, grads, got):
+            v = (qg.T.contiguous() @ g.double() @ qa) / (lg.double()[:, None] * la.double()[None, :] + 0.1)
+            want = qg @ v @ qa.T.contiguous()
+            assert float((x.double() - want).norm() / want.norm()) <= (2.0 ** -8 if bf16 else 1.5e-5), (count, x.shape)
+    c.close()
+
+
 @pytest.mark.parametrize("dA,dG", PRECOND_CASES + [(1000, 300), (4, 1)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_precondition_split_f16_matches_oracle(ctx, dA, dG, bf16):
