@@ -302,11 +302,12 @@ void plan_item(int n, const kfac_factor_item &it, int shift, int &ntri, int &nsp
 
 // A batch with fewer jobs than this: half the slabs per job, and again, down to a sixteenth.  Two jobs share a compute unit, so 512 run at
 // a time; with few jobs per slot the last round is mostly empty, and whole tiles wait beside edge tiles that are done in a quarter
-// of their time.  (One conv layer, factors 145 and 16 wide from 2048 samples: 4 jobs of 64 slabs took 131 us, 16 of 16 slabs and the reducer
-// 38.  From 256, 1024, 2048 and 4096 jobs on as they are: the ResNet-32 step 5880, 5876, 5326, 5212 us; fp32 factors of a net of thirty
-// convolutions 8 to 56 wide 1635, 1378, 1197, 1148.  Its jobs being three times as fast, the bf16 engine gains less and loses by short ones
-// sooner: factors of eight blocks 17 to 136 wide 446, 243, 278, 278, of seven blocks 53 to 424 wide 806, 805, 801, 871.)
-constexpr int MIN_JOBS_F32 = 4096, MIN_JOBS_B16 = 1024, MAX_SHIFT = 4;
+// of their time.  But a job's partial sums are 64 KB out and in again, as much as four of its slabs: two halvings for MIN_JOBS (bf16, whose
+// jobs are three times as fast: none), more only for MIN_JOBS_SHORT.  us, at the start of it (256 jobs in all cases), with 1024, 2048, 4096 and
+// with 4096 down to a sixteenth: the ResNet-32 step 5880, 5870, 5330, 5228, 5270; fp32 factors of thirty convolutions 8 to 56 wide 1717, 1378, 1193,
+// 1195, 1150, of eighteen blocks up to 928 1055, 1056, 1053, 887, 934, of one layer 4608 and 512 1075, 930, 930, 929, 1011; bf16 ones of eight
+// blocks 17 to 136 wide 442, 244, 244, 248, 281, of seven blocks 53 to 424 798, 802, 803, 801, 871.
+constexpr int MIN_JOBS = 4096, MIN_JOBS_SHORT = 1024, MAX_SHIFT = 4;
 int plan_shift(int n, const kfac_factor_item *items) {
     for (int shift = 0; shift < MAX_SHIFT && n > 1; ++shift) {
         int64_t jobs = 0;
@@ -315,7 +316,7 @@ int plan_shift(int n, const kfac_factor_item *items) {
             plan_item(n, items[i], shift, ntri, nsplit, kchunk);
             jobs += (int64_t)ntri * nsplit;
         }
-        if (jobs >= (form_of(items[0]) == 4 ? MIN_JOBS_B16 : MIN_JOBS_F32)) return shift;
+        if (jobs >= (form_of(items[0]) == 4 || shift >= 2 ? MIN_JOBS_SHORT : MIN_JOBS)) return shift;
     }
     return n > 1 ? MAX_SHIFT : 0;
 }
