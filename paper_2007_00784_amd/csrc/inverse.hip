@@ -4,7 +4,7 @@
 // classical way, in fp32: blocked Cholesky factorisation F + gamma I = L L^T (128-wide block columns: the diagonal
 // block is factored, and inverted, by one workgroup in registers; the panel below it is multiplied by that inverse and the
 // trailing matrix gets its rank-128 update on the fp32 MFMA tile engine), then the triangular inverse L^-1 by
-// doubling (two products per level), then L^-T L^-1 as one symmetric product.  n^3 flops in all, 3 n/128 + 2 log2(n/128) + 1
+// doubling (two products per level), then L^-T L^-1 as one symmetric product.  n^3 flops in all, 2 n/128 + 2 log2(n/128) + 1
 // launches per factor.
 #include <algorithm>
 #include <cmath>
@@ -63,10 +63,11 @@ __device__ inline float quotient(float x, float d, float r) {
     const float q = x * r;
     return fmaf(fmaf(-q, d, x), r, q);
 }
-__global__ __launch_bounds__(256) void inv_diag_kernel(InvArgs a) {
-    __shared__ float col[2][NB], xrow[2][NB];
-    const int tid = threadIdx.x, f = blockIdx.x, ty = tid >> 4, tx = tid & 15;
-    float *blk = a.L(f) + ((int64_t)a.k * NB) * a.ld + (int64_t)a.k * NB;
+struct DiagSmem { float col[2][NB], xrow[2][NB]; };
+__device__ inline void inv_diag_block(const InvArgs &a, int f, int k, DiagSmem &sm) {
+    float (&col)[2][NB] = sm.col, (&xrow)[2][NB] = sm.xrow;
+    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+    const global_ptr<float> blk = as_global(a.L(f)) + ((int64_t)k * NB) * a.ld + (int64_t)k * NB;
     float S[DT][DT], X[DT][DT];
 #pragma unroll
     for (int p = 0; p < DT; ++p)
@@ -109,8 +110,8 @@ __global__ __launch_bounds__(256) void inv_diag_kernel(InvArgs a) {
 #pragma unroll
                 for (int q = 0; q <= jb; ++q) X[jb][q] = xs[q];
         }
-    float *Dk = a.D(f) + (int64_t)a.k * NB * NB;
-    float *Lik = a.Li(f) + ((int64_t)a.k * NB) * a.ld + (int64_t)a.k * NB;
+    const global_ptr<float> Dk = as_global(a.D(f)) + (int64_t)k * NB * NB;
+    const global_ptr<float> Lik = as_global(a.Li(f)) + ((int64_t)k * NB) * a.ld + (int64_t)k * NB;
 #pragma unroll
     for (int p = 0; p < DT; ++p)
 #pragma unroll
@@ -121,6 +122,10 @@ __global__ __launch_bounds__(256) void inv_diag_kernel(InvArgs a) {
             Dk[r * NB + c] = x;
             Lik[(int64_t)r * a.ld + c] = x;
         }
+}
+__global__ __launch_bounds__(256) void inv_diag_kernel(InvArgs a) {
+    __shared__ DiagSmem sm;
+    inv_diag_block(a, blockIdx.x, a.k, sm);
 }
 
 __device__ inline void inv_tri_decode(int idx, int &ti, int &tj) {   // idx = ti (ti + 1) / 2 + tj, tj <= ti
@@ -134,6 +139,7 @@ __device__ inline void inv_tri_decode(int idx, int &ti, int &tj) {   // idx = ti
 // The five products, one 128 x 128 output tile per workgroup (all operands are padded to whole tiles):
 //   PANEL   L[i,k] <- L[i,k] D_k^T                                      i > k              (grid: nt-k-1)
 //   UPDATE  L[i,j] <- L[i,j] - L[i,k] L[j,k]^T                          i >= j > k         (grid: lower tiles)
+//           and then, by the workgroup of the first of them, the diagonal block k + 1: the others' tiles hide its chain of pivots
 //   HALF    Li[j,i] <- sum_{c = j}^{m-1} L[i,c] Li[c,j]    scratch: block (i, j) of L21 Li11, kept above the diagonal
 //   JOIN    Li[i,j] <- -sum_{c = m}^{i} Li[i,c] Li[j,c]    (block (c, j) of the scratch is at (j, c))
 //           for every pair of neighbouring index ranges [m - s, m), [m, m + s) of s = a.k blocks whose inverses are there:
@@ -142,10 +148,12 @@ __device__ inline void inv_tri_decode(int idx, int &ti, int &tj) {   // idx = ti
 enum { INV_PANEL = 0, INV_UPDATE, INV_HALF, INV_JOIN, INV_GRAM };
 template <int MODE>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void inv_gemm_kernel(InvArgs a) {
-    __shared__ TileSmem sm;
+    __shared__ union { TileSmem tile; DiagSmem diag; } shared;
+    TileSmem &sm = shared.tile;
     floatx16 acc[2][2];
     const int64_t ld = a.ld;
-    const int npad = a.nt * NB, f = blockIdx.y;
+    // UPDATE goes round the factors first, so that every factor's first tile, which has the pivots behind it, starts at once
+    const int npad = a.nt * NB, f = MODE == INV_UPDATE ? blockIdx.x : blockIdx.y, tile = MODE == INV_UPDATE ? blockIdx.y : blockIdx.x;
     float *const L = a.L(f), *const Li = a.Li(f), *const D = a.D(f);
     if (MODE == INV_PANEL) {
         const int i = a.k + 1 + blockIdx.x;
@@ -156,13 +164,17 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         for_each_acc(acc, [&](int r, int c, float v) { Lik[(int64_t)r * ld + c] = v; });
     } else if (MODE == INV_UPDATE) {
         int ti, tj;
-        inv_tri_decode(blockIdx.x, ti, tj);
+        inv_tri_decode(tile, ti, tj);
         const int i = a.k + 1 + ti, j = a.k + 1 + tj;
         OpStrided<float, true> A{L + ((int64_t)i * NB) * ld + (int64_t)a.k * NB, ld, 1, NB, NB, -1};
         OpStrided<float, true> B{L + ((int64_t)j * NB) * ld + (int64_t)a.k * NB, ld, 1, NB, NB, -1};
         gemm_tile(A, B, 0, 0, 0, NB, sm, acc);
         float *Lij = L + ((int64_t)i * NB) * ld + (int64_t)j * NB;
         for_each_acc(acc, [&](int r, int c, float v) { Lij[(int64_t)r * ld + c] -= v; });
+        if (tile == 0) {
+            __syncthreads();       // the tile is written
+            inv_diag_block(a, f, a.k + 1, shared.diag);
+        }
     } else if (MODE == INV_HALF || MODE == INV_JOIN) {
         const int s = a.k, idx = blockIdx.x, pair = idx / (s * s), m = (2 * pair + 1) * s;
         const int i = m + (idx / s) % s, j = m - s + idx % s;
@@ -246,14 +258,12 @@ int inv_enqueue_group(kfac_ctx *ctx, hipStream_t st, const InvGroup &g, const In
         KfacProfScope prof(ctx, KC_INVERSE, n3 / 3.0, 0.0, st);
         hipLaunchKernelGGL(inv_init_kernel, dim3((unsigned)std::min<int64_t>(((int64_t)np * np + 255) / 256, 2048), nm), dim3(256), 0, st,
                            damping, a);
-        for (int k = 0; k < nt; ++k) {
+        hipLaunchKernelGGL(inv_diag_kernel, dim3(nm), dim3(256), 0, st, a);
+        for (int k = 0; k + 1 < nt; ++k) {
             a.k = k;
-            hipLaunchKernelGGL(inv_diag_kernel, dim3(nm), dim3(256), 0, st, a);
             const int rest = nt - k - 1;
-            if (rest > 0) {
-                hipLaunchKernelGGL(inv_gemm_kernel<INV_PANEL>, dim3(rest, nm), dim3(NTHREADS), 0, st, a);
-                hipLaunchKernelGGL(inv_gemm_kernel<INV_UPDATE>, dim3(rest * (rest + 1) / 2, nm), dim3(NTHREADS), 0, st, a);
-            }
+            hipLaunchKernelGGL(inv_gemm_kernel<INV_PANEL>, dim3(rest, nm), dim3(NTHREADS), 0, st, a);
+            hipLaunchKernelGGL(inv_gemm_kernel<INV_UPDATE>, dim3(nm, rest * (rest + 1) / 2), dim3(NTHREADS), 0, st, a);
         }
     }
     {
