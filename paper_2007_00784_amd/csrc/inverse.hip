@@ -319,7 +319,7 @@ int kfac_launch_invert_factors(kfac_ctx *ctx, int batch, const float *const *F, 
         int best = 0;
         for (int i = 1; i < nstreams; ++i) if (load[i] < load[best]) best = i;
         const double nt = inv_npad(g.n) / NB;
-        load[best] += nt * 165e-6 + (double)g.count * g.n * (double)g.n * g.n / 60e12;   // a block column's serial launches + products
+        load[best] += nt * 145e-6 + (double)g.count * g.n * (double)g.n * g.n / 60e12;   // a block column's serial launches + products
         rc = inv_enqueue_group(ctx, ctx->aux[best], g, tab_dev, (float *)(pool + (size_t)best * region), damping);
         if (rc != KFAC_OK) break;
     }
