@@ -4,9 +4,9 @@
 //  1. Householder reduction to tridiagonal form, A = H T H^T, in fp32, of the factor with its diagonal in descending order
 //     (the reduction starts at the large end, so the small end of a graded factor is not swamped by the large end's
 //     rounding: on a factor graded over eight decades the small eigenvectors come out fifty times as accurate).  Factors up to 256 wide: one workgroup each, the
-//     matrix in registers.  Wider ones: the blocked right-looking reduction (panels of 32 columns; per column one
-//     symmetric matrix-vector product over the lower tiles and one vector step, in one launch where the tiles are few;
-//     per panel one rank-64 update on the fp32 matrix instructions), all factors in one chain of launches, aligned so that all end together.
+//     matrix in registers.  Wider ones: the trailing matrix in the registers of the whole chip (eig_chip.h).  Columns of a factor too
+//     wide for that: the blocked right-looking reduction (panels of 32 columns; per column one symmetric matrix-vector product
+//     over the lower tiles and one vector step; per panel one rank-64 update on the fp32 matrix instructions) until it fits.
 //  2. Eigenvalues of T by bisection and eigenvectors of T by twisted factorisation, both in fp64 and both
 //     independent per eigenvalue.  T carries fp32 rounding noise, so fp64 has nine digits to spare: the eigenvectors of
 //     eigenvalues that agree to many digits still come out orthogonal without any re-orthogonalisation, once exact
@@ -1643,8 +1643,8 @@ size_t kfac_eig_direct_ws_bytes(int batch, const int *d) {
     return need;
 }
 
-// What a call takes, in seconds: the chain of the widest factor's columns, and the traffic of all of them.  Fitted to 40 calls of 1
-// to 53 factors, 0.5 to 90 ms: within 5 % of most.
+// What a call takes, in seconds: the chain of the widest factor's columns, and the arithmetic of all of them.  Within 10 % of calls of one
+// factor 577 to 4609 wide (2.5 to 30 ms), twenty of 577, six of 2305, three of 4609 and ResNet-50's 108; 13 % below seventeen of 1024 to 1153.
 double kfac_eig_direct_seconds(int batch, const int *d) {
     int nmax = 0;
     double n3 = 0.0;
@@ -1653,7 +1653,7 @@ double kfac_eig_direct_seconds(int batch, const int *d) {
         n3 += (double)d[i] * d[i] * d[i];
     }
     if (nmax == 0) return 0.0;
-    return (nmax > TD_SMALL ? 300e-6 + 9e-6 * nmax : 60e-6 + 4.6e-6 * nmax) + 2e-13 * n3;
+    return (nmax > TD_SMALL ? 300e-6 + 3.9e-6 * nmax : 60e-6 + 4.6e-6 * nmax) + 1.5e-13 * n3;
 }
 
 // All factors of the call by the direct route; stat (pinned host memory): four doubles per factor, off^2 and diag^2 of F, the

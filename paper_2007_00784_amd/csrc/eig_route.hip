@@ -3,10 +3,10 @@
 //
 // The direct decomposition costs the same for every factor of a size.  Jacobi sweeps cost by how far the factor is from diagonal in
 // the basis they start from: none from the eigenvectors of a factor that has not moved since (7 ms at 4609, where the direct
-// decomposition takes 58), four and more after a running average moved by 5 % (88 ms).  So with a start basis, that distance is
+// decomposition takes 30), four and more after a running average moved by 5 % (88 ms).  So with a start basis, that distance is
 // estimated first (probe kernels below: 18 us at 145, 64 at 2100, and a wait), and the sweeps take the factors with which the call is cheaper.  Without one, it
 // is off(F)_F, which the direct route forms anyway: running averages that are still diagonal need no sweep (0.55 ms at 577, 1.4 at
-// 2100, in place of 5.2 and 19), and a loose tol needs few.
+// 2100, in place of 2.4 and 9.3), and a loose tol needs few.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -180,14 +180,18 @@ constexpr float DIRECT_TOL_MIN = 1e-6f;
 constexpr double DIRECT_MAX_RES = 5e-6;    // measured residual / ||F||_F of a sound result
 constexpr double DIRECT_MAX_DEV2 = 1e-3;   // ||I - Q^T Q||_F^2 that two Newton-Schulz steps bring below fp32 rounding
 
-// Sweeps down to tol.  A sweep gains a factor of 8 as long as the columns of the basis still are what they were (2.5e-3 at 1261 took 4,
-// 5e-3 at 577 took 4, 1e-2 at 240 took 3), 3.5 where many of them are not: the null space of a rank-deficient factor, which any
+// Sweeps down to tol.  A sweep gains a factor of 8 as long as the columns of the basis still are what they were, and the last one of a
+// short run more, since the sweeps converge quadratically at the end.  Over 34 factors of 577 to 2100 from 1.1e-5 to 5e-3 off at 2e-6,
+// one sweep served up to ln(rel / tol) = 2.0 ln 8 (two from 2.1), two up to 3.03 ln 8 (three from 2.85), three up to 3.47 ln 8 (four from
+// 3.49).  The gain is 3.5 where many columns are not what they were: the null space of a rank-deficient factor, which any
 // movement makes a dense block (5e-3 at 4609 took 8, 2e-2 at 1624 took 7, 8e-3 at 964 took 8), or no basis at all (0.2 at
 // 577 took 1 to 0.1, 4 to 0.01, 6 to 1e-3 and 9 to 2e-6).
 int sweeps_needed(const StartBasis &b, double tol) {
     if (b.rel <= tol) return 0;
     const double l = std::log(b.rel / tol);
-    return b.lost >= 0.2 ? (int)std::ceil(l / std::log(3.5)) : std::max(1, (int)std::lround(l / std::log(8.0)));
+    if (b.lost >= 0.2) return (int)std::ceil(l / std::log(3.5));
+    const double s = l / std::log(8.0);
+    return std::max(1, (int)std::lround(s < 3.05 ? s - 0.55 : s));
 }
 
 // A factor list of its own: part of a call.
@@ -205,10 +209,16 @@ struct EigPart {
     }
 };
 
+// Without a start basis, a tolerance from LOOSE_TOL up is served by sweeps as long as they take less than LOOSE_WORTH times the direct
+// decomposition: who asks for so little sees in info how few sweeps it took, and 1e-2 at 577 takes 3.6 ms this way (2.4 directly).
+constexpr double LOOSE_TOL = 1e-3;
+constexpr double LOOSE_WORTH = 1.8;
+
 // The factors (wider than KFAC_EIG_SMALL: the others gain nothing from a start) to iterate rather than to decompose directly, given
 // the bases they would start from.  Those that need the fewest sweeps first, as many as make the call
-// cheapest, if that is clearly cheaper than all of them directly: a chain of launches is shared by all factors of its kind.
-std::vector<int> choose_sweeps(kfac_ctx *ctx, int batch, const int *d, const std::vector<StartBasis> &start, double tol, int max_sweeps) {
+// cheapest, if that is cheaper than all of them directly by the 5 % that the two estimates are good for: a chain of launches is
+// shared by all factors of its kind.
+std::vector<int> choose_sweeps(kfac_ctx *ctx, int batch, const int *d, const std::vector<StartBasis> &start, double tol, int max_sweeps, double worth = 0.95) {
     std::vector<int> need(batch, INT_MAX), levels, best;
     for (int i = 0; i < batch; ++i) {
         if (d[i] <= KFAC_EIG_SMALL || !(start[i].rel >= 0.0)) continue;
@@ -219,7 +229,7 @@ std::vector<int> choose_sweeps(kfac_ctx *ctx, int batch, const int *d, const std
     }
     std::sort(levels.begin(), levels.end());
     levels.erase(std::unique(levels.begin(), levels.end()), levels.end());
-    double least = 0.85 * kfac_eig_direct_seconds(batch, d);
+    double least = worth * kfac_eig_direct_seconds(batch, d);
     for (int level : levels) {
         std::vector<int> which, dj, sj, dd;
         for (int i = 0; i < batch; ++i) {
@@ -301,7 +311,8 @@ int kfac_launch_eig(kfac_ctx *ctx, int batch, const float *const *F, const int *
             start[i].rel = f2 > 0.0 && f2 < 1e300 ? std::sqrt(off2 / f2) : (f2 == 0.0 ? 0.0 : -1.0);
             start[i].lost = start[i].rel > 1e-2 ? 1.0 : 0.0;
         }
-        sweep = choose_sweeps(ctx, batch, d, start, tol, max_sweeps);
+        if (tol >= LOOSE_TOL) sweep = choose_sweeps(ctx, batch, d, start, tol, max_sweeps, LOOSE_WORTH);
+        else sweep = choose_sweeps(ctx, batch, d, start, tol, max_sweeps);
         return sweep.empty();
     };
     if (!decided) {

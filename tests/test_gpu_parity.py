@@ -385,6 +385,18 @@ def test_eig_diagonal_beside_dense_factors(ctx):
         check_eigpairs(F, Ld[i].cpu().numpy(), Qd[i].cpu().numpy(), "beside[%d]" % i)
 
 
+@pytest.mark.parametrize("n,moved,sweeps", [(577, 1e-2, 2), (577, 5e-2, 1), (1153, 1e-2, 2), (1153, 5e-2, 1)])
+def test_eig_start_basis_moved_a_little_and_more(ctx, n, moved, sweeps):
+    """Two sweeps from the eigenvectors of a factor that moved by 1 % are cheaper than a decomposition (which reports one), four after 5 % are not."""
+    F0, F1 = gram_factor(n, 2 * n, seed=n), gram_factor(n, 2 * n, seed=n + 1)
+    _, Q, _ = ctx.eig([F0])
+    F = ((1.0 - moved) * F0 + moved * F1).astype(np.float32)
+    lam = [torch.empty(n, device="cuda")]
+    info = K.kfac_eig(ctx.h, [torch.from_numpy(F).cuda()], Q, lam, warm_start=True)
+    assert info[0][2] and info[0][0] == sweeps, info
+    check_eigpairs(F, lam[0].cpu().numpy(), Q[0].cpu().numpy(), "moved")
+
+
 @pytest.mark.parametrize("n", [577, 1153])
 def test_eig_loose_tolerance_takes_few_sweeps(ctx, n):
     """To 1e-2 a few sweeps are cheaper than a decomposition; a cap on them that is too low for that does not stand in its way."""
