@@ -14,9 +14,9 @@
 //    slots hold EMPTY before.  Everything after that is local: reflector, w, the next column, and ONE pass over the registers that
 //    applies the rank-2 update (on the matrix cores, as outer products: a third of the pass is left to the vector units) and forms the
 //    next products.
-//  - The words go through a ring of four columns.  A workgroup that has gathered column t knows that all have gathered t - 1, so it
-//    empties its own words of t - 1 then; the s_waitcnt before its next publication orders the two, and the words are looked at again
-//    only by who has seen that publication.  Loads and stores are relaxed agent-scope atomics of 8 bytes.
+//  - The words go through a ring of four columns (eig_chip_ring.h: who publishes, waits and empties when, and why no word is emptied
+//    that somebody still looks for).  The s_waitcnt before a publication orders it after what its wave has emptied.  Loads and stores
+//    are relaxed agent-scope atomics of 8 bytes.
 //  - Polling too early costs more than it gains (the line is fetched empty, and the writer has to take it away again): measured between
 //    256 workgroups, 4608 words: 3.0 us a column polling at once, 2.3 after a pause of 1024 cycles; 64 workgroups: 2.3 and 1.5.
 //
@@ -121,10 +121,10 @@ __device__ inline floatx4 chip_outer(float rows, float column, floatx4 c, int g)
 }
 
 // (all of it through global pointers: a flat access also counts on the LDS counter, and every wait for LDS behind it takes a trip to memory)
-typedef global_ptr<unsigned long long> ChipRing;
+typedef global_ptr<unsigned long long> ChipWords;
 // word i of those at `base`: a scalar base and 32 bits of offset, so that no lane keeps 64-bit addresses
-__device__ inline unsigned long long chip_load(ChipRing base, unsigned i) { return __hip_atomic_load(base + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline void chip_store(ChipRing p, unsigned long long v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline unsigned long long chip_load(ChipWords base, unsigned i) { return __hip_atomic_load(base + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void chip_store(ChipWords p, unsigned long long v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 template <int CHIP_NT, int S>
 __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, ChipSmem<CHIP_NT> &sm) {
@@ -136,7 +136,7 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
     const int j1 = m > 64 * wave ? (m - 1 - 64 * wave) / CHIP_NT : -1;           // the last slot in which this wave has columns
     const int64_t ld = M.ld;
     const global_ptr<float> A0 = as_global(M.A) + (int64_t)J.k0 * ld + J.k0 + 1;      // row k0, from the element beside the diagonal on
-    const ChipRing ring = as_global((unsigned long long *)M.apan) + (size_t)(J.turn & 1) * CHIP_RING * M.np;
+    const ChipWords ring = as_global((unsigned long long *)M.apan) + (size_t)(J.turn & 1) * CHIP_RING * M.np;
     const global_ptr<double> Md = as_global(M.d), Me = as_global(M.e);
     const global_ptr<float> Mtau = as_global(M.tau);
     floatx4 a[G][S];
@@ -162,7 +162,7 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
     }
     if (J.turn == 0 && last && tid == 0) Md[J.k0] = (double)A0[-1];
     if (tid < nr) {
-        const ChipRing other = as_global((unsigned long long *)M.apan) + (size_t)(~J.turn & 1) * CHIP_RING * M.np + r0 + tid;
+        const ChipWords other = as_global((unsigned long long *)M.apan) + (size_t)(~J.turn & 1) * CHIP_RING * M.np + r0 + tid;
 #pragma unroll
         for (int q = 0; q < CHIP_RING; ++q) other[(size_t)q * M.np] = CHIP_EMPTY;
     }
@@ -215,7 +215,11 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
                 if (lane == 0) sm.part[wave][4 * G + i] = acc;
             }
         if (t == J.steps) break;
-        if (r0 + nr <= t) return;          // all rows of this workgroup are finished
+        const ChipWords slot = ring + (size_t)ChipRing::slot(t) * M.np;
+        if (ChipRing::leaves(r0, nr, t)) {         // all rows of this workgroup are finished, and all its waves have gathered column t - 1
+            if (tid == 0 && ChipRing::receipt(r0, nr, t) >= 0) chip_store(slot + ChipRing::receipt(r0, nr, t), 0);
+            return;
+        }
         if (wave == ((t >> 6) & (CHIP_WAVES - 1))) {      // the own rows' elements of column t, by the lane that has it
 #pragma unroll
             for (int j = 0; j < S; ++j)
@@ -231,7 +235,6 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
                         for (int i = 0; i < X; ++i) sm.col[4 * G + i] = ax[i][j];
         }
         __syncthreads();
-        const ChipRing slot = ring + (size_t)(t & (CHIP_RING - 1)) * M.np;
         const int r = r0 + lane, k = J.k0 + t;
         float art = 0.f;
         if (tid < nr) {
@@ -241,7 +244,8 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
             for (int g = 0; g < CHIP_WAVES; ++g) y += sm.part[g][tid];
             unsigned long long word = (unsigned long long)__float_as_uint(y) | (unsigned long long)__float_as_uint(art) << 32;
             if (word == CHIP_EMPTY) word = 0x7fc000007fc00000ull;      // two NaNs that look like an empty slot
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // what was emptied for column t - 1 is empty
+            if (r < t) word = 0;                                       // a finished row's word is only waited for
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // what was emptied after column t - 1 is empty
             chip_store(slot + r0 + tid, word);
         }
         const float alpha = sm.xs[t], xr = sm.xs[r];
@@ -260,7 +264,7 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
         for (int j = 0; j < S; ++j) {
             const int c = tid + CHIP_NT * j;
             u[j] = 0;
-            if (c >= t && (j < S - 1 || tail)) u[j] = chip_load(slot + CHIP_NT * j, tid);
+            if (c >= ChipRing::first(t) && (j < S - 1 || tail)) u[j] = chip_load(slot + CHIP_NT * j, tid);
         }
         for (int spin = 0;; ++spin) {
             bool there = true;
@@ -310,8 +314,8 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
         }
         if (wave == CHIP_WAVES - 1 && lane < nr) A0[(int64_t)t * ld + r] = vr;     // row k: everybody has published, so has read it
         if (tid < nr && r == t) Md[k + 1] = (double)(art - 2.f * wt);
-        // all have published t, so all have gathered t - 1
-        if (t >= 1 && tid < nr) chip_store(ring + (size_t)((t - 1) & (CHIP_RING - 1)) * M.np + r0 + tid, CHIP_EMPTY);
+        const int done = ChipRing::emptied(t);      // nobody looks for its words any more
+        if (done >= 0 && tid < nr) chip_store(ring + (size_t)ChipRing::slot(done) * M.np + r0 + tid, CHIP_EMPTY);
         if (last && tid == 64) {
             Mtau[k] = tau;
             Me[k] = (double)beta;

@@ -23,6 +23,7 @@
 #include <cmath>
 #include <cstring>
 #include <vector>
+#include "eig_chip_ring.h"
 #include "kfac_internal.h"
 #include "mfma_gemm.h"
 #include "mfma_gemm_x3.h"
@@ -41,7 +42,6 @@ constexpr int WY = 128;           // reflectors of a compact WY block
 constexpr int WY_K = 512;         // contraction of one workgroup in Y = V^T Z
 constexpr int NPARTS = 64;         // parts of the Rayleigh quotients' sums
 constexpr int NORM_WGS = 256;      // workgroups per factor of the norms and copies: workgroup b has rows b, b + gridDim.x, ..; never more than rows
-constexpr int CHIP_RING = 4;      // columns whose words are in flight between the workgroups of a factor (eig_chip.h)
 constexpr unsigned long long CHIP_EMPTY = ~0ull;
 constexpr double PERTURB_REL = 0x1p-25;   // of every element of T: half the rounding it already carries
 constexpr double PERTURB_ABS = 1e-10;     // of the Gershgorin bound, added to the diagonal: breaks multiple zeros
