@@ -60,7 +60,8 @@ struct ChipJob {
 template <int NT> struct ChipSmem {
     static constexpr int WAVES = NT / 64;
     float xs[NT * CHIP_SLOTS + CHIP_ROWS], ys[NT * CHIP_SLOTS + CHIP_ROWS];     // x and y by row, for those that need single elements
-    float col[CHIP_ROWS], part[WAVES][CHIP_ROWS], nrm[WAVES], dot[WAVES];
+    float col[CHIP_ROWS], part[WAVES][CHIP_ROWS], nrm[WAVES];
+    double dot[WAVES];
     int failed;
 };
 
@@ -277,7 +278,7 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
             if (__all(there)) break;
             if (spin > CHIP_SPIN) { sm.failed = 1; break; }
         }
-        float dot = 0.f;
+        double dot = 0.0;
 #pragma unroll
         for (int j = 0; j < S; ++j) {
             if (j < j0 || j > j1) continue;
@@ -287,18 +288,18 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
             v[j] = c == t ? 1.f : x[j] * scale;
             x[j] = ac;
             sm.ys[c] = w[j];
-            dot = fmaf(v[j], w[j], dot);
+            dot = fma((double)v[j], (double)w[j], dot);
         }
-        dot = wave_sum_all(dot);
+        dot = wave_sum_f64(dot);
         if (lane == 0) sm.dot[wave] = dot;
         __syncthreads();
         const float yt = sm.ys[t], yr = sm.ys[r];
         const int failed = sm.failed;
-        dot = 0.f;
+        dot = 0.0;
 #pragma unroll
         for (int g = 0; g < CHIP_WAVES; ++g) dot += sm.dot[g];
         if (failed) return;                // the result is not sound, and is found not to be
-        const float cw = -0.5f * tau * tau * dot, wt = fmaf(tau, yt, cw);
+        const float cw = (float)(-0.5 * tau * tau * dot), wt = fmaf(tau, yt, cw);
         const float vr = lane < nr && r >= t ? (r == t ? 1.f : xr * scale) : 0.f;
         nv = -vr;
         nw = lane < nr && r >= t ? -fmaf(tau, yr, cw * vr) : 0.f;

@@ -13,7 +13,8 @@
 //     multiplicities are broken by a perturbation of T below its rounding noise (PERTURB_REL, PERTURB_ABS).
 //  3. Back-transformation by the reflectors: compact WY blocks of 128 on the fp32 matrix instructions, or (small
 //     factors) a wave per four columns with the columns in registers.
-//  4. One Newton-Schulz step on Q, Rayleigh quotients against the caller's F, ascending order.
+//  4. One Newton-Schulz step on Q and Rayleigh quotients against the caller's F; where the reduction on the chip has rounded the factor more
+//     than the rest of it all does (CORRECT_FROM), a first-order correction of Q and the quotients again; ascending order.
 //
 // The residual ||F Q - Q diag(lam)||_F = off(Q^T F Q) of the result is measured (it falls out of the Rayleigh quotients), and
 // so is the orthogonality of the eigenvectors before the last step; a factor with an unsound result is decomposed by
@@ -46,6 +47,15 @@ constexpr unsigned long long CHIP_EMPTY = ~0ull;
 constexpr double PERTURB_REL = 0x1p-25;   // of every element of T: half the rounding it already carries
 constexpr double PERTURB_ABS = 1e-10;     // of the Gershgorin bound, added to the diagonal: breaks multiple zeros
 constexpr double NS_AGAIN = 4e-6;         // ||I - Q^T Q||_F^2 from which one Newton-Schulz step is not enough (it leaves 3/4 of this)
+// Updates of the trailing matrix in the registers of the chip that an element of the factor has been through, on average over ||F||_F^2 (T's elements say
+// what is left in the trailing matrices), from which the eigenvectors are corrected.  Every update rounds, 2.3e-8 of the element
+// as measured, so this is 1.8e-7 ||F|| beside the 4 to 6e-7 of everything else; a Gram matrix of independent features gets to n / 2 and
+// 1.6e-6 at 4609, factors with a few large eigenvalues or a graded diagonal stay below 64.  1e7 residual / ||F||, by the chain of launches, on the
+// chip, and on the chip and corrected: Gram matrices of 2 n samples 577 5.6, 8.0, 3.0, 2305 6.1, 12.7, 3.2, 4609 6.5, 17.0, 3.6, of 30 n samples
+// 4609 4.6, 18.5, 3.6, random symmetric 4609 10.3, 17.4, 4.3; ReLU activations (not corrected) 4609 4.8, 4.8.  ||I - Q^T Q||_F: the
+// same in all of them.  A corrected factor costs 2.5 ms more at 4609 (31.0), 0.5 at 2305 (11.2), 0.15 at 577 (2.6).
+constexpr double CORRECT_FROM = 64.0;
+constexpr double CORRECT_GAP = 0x1p11;    // gap of two eigenvalues, in residuals of their columns, below which they are left as they are
 constexpr double BIS_REL = 0x1p-51, BIS_ABS = 1e-25;   // width at which an eigenvalue's interval is done, of its size and of the bound
 constexpr int BIS_WIDE_MAX = 160;         // up to this many groups of 64 eigenvalues, sixteen lanes each
 constexpr double E_MIN = 1e-20;     // of the same: no off-diagonal element of T is exactly zero
@@ -53,7 +63,7 @@ constexpr double PIVOT_MIN = 1e-30;
 
 struct DirMat {
     const float *F;
-    float *Q, *lam;
+    float *Q, *lam;  // (Q holds the residual of a correction, and the corrected F Q, before it receives the result)
     float *A;        // [np][ld]: the matrix, its lower tiles reduced in place; row p of the upper part receives reflector p
     float *Z;        // [np][ld]: eigenvectors of T, then of A
     float *B1, *B2;  // [np][ld] each, adjacent: together the fp64 pivots of the eigenvectors; then scratch
@@ -62,7 +72,7 @@ struct DirMat {
     // what a column's launch leaves for the next, twice:
     float *part;     // [2][nb][np]: partial products of the column's matrix-vector product
     float *dots;     // [2][nb][2 NB]: partial V^T x, W^T x per row block
-    double *tsum;    // [2] per tile: its share of x^T A x
+    double *tsum;    // [2] per tile: its share of x^T A x; later [0] mean number of updates, [1] scale of the residual in a correction (0: there is none)
     float *acol;     // [2][np]: the column x, not yet scaled
     float *npart;    // [2][np / RB]: its squared norm, per workgroup
     float *tau;      // [np]
@@ -70,7 +80,7 @@ struct DirMat {
     double2 *td;     // [np]: T perturbed and divided by its Gershgorin bound: {d_i, e_i^2}; |e_i| is kept away from zero
     double *te;      // [np]: e_i of the same; later 1 / norm of every eigenvector
     double *lam64;   // [np]: eigenvalues of T, later the Rayleigh quotients
-    double *sums;    // [min(NPARTS, n)][3][np] partial sums of the Rayleigh quotients
+    double *sums;    // [min(NPARTS, n)][3][np] partial traces; partial sums of the Rayleigh quotients
     double *npartd;  // [NORM_WGS][2] partial norms: off^2, diag^2 of the first min(NORM_WGS, n); later of D and of the residual
     double *stat;    // off^2, diag^2, residual^2, ||I - Q^T Q||^2
     float *Tm;       // [nb][WY][WY]: Gram matrices of the WY blocks, then their T
@@ -128,13 +138,20 @@ __global__ __launch_bounds__(256) void dir_norm_kernel(const DirMat *mats) {
     const global_ptr<const float> F = as_global(M.F);
     const int n = M.n;
     if ((int)blockIdx.x >= n) return;
-    double o2 = 0.0, d2 = 0.0;
+    double o2 = 0.0, d2 = 0.0, tr = 0.0;
     for (int r = blockIdx.x; r < n; r += gridDim.x)
         for (int c = threadIdx.x; c < n; c += 256) {
             const double v = (double)F[(int64_t)r * n + c];
-            if (c == r) d2 += v * v; else o2 += v * v;
+            if (c == r) { d2 += v * v; tr += v; } else o2 += v * v;
         }
     __shared__ double red[8];
+    if (n > TD_SMALL) {
+        tr = wave_sum_f64(tr);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = tr;
+        __syncthreads();
+        if (threadIdx.x == 0) M.sums[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+        __syncthreads();
+    }
     o2 = wave_sum_f64(o2);
     d2 = wave_sum_f64(d2);
     if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6] = o2; red[4 + (threadIdx.x >> 6)] = d2; }
@@ -145,7 +162,11 @@ __global__ __launch_bounds__(256) void dir_norm_kernel(const DirMat *mats) {
     }
 }
 
-// off^2 and diag^2 from the partial norms (a wave; fixed order), and the power of two that brings ||F||_F into [1, 2)
+__device__ inline float norm_scale(double f2) {      // the power of two that brings ||F||_F into [1, 2)
+    if (!(f2 > 0.0) || !(f2 < 1e300)) return 1.f;
+    return ldexpf(1.f, min(max(-ilogb(sqrt(f2)), -120), 120));
+}
+// off^2 and diag^2 from the partial norms (a wave; fixed order), and that scale
 __device__ inline float dir_norms(const DirMat &M, double &o2, double &d2) {
     const int lane = threadIdx.x & 63;
     o2 = d2 = 0.0;
@@ -157,9 +178,20 @@ __device__ inline float dir_norms(const DirMat &M, double &o2, double &d2) {
     }
     o2 = wave_sum_f64(o2);
     d2 = wave_sum_f64(d2);
-    const double f2 = o2 + d2;
-    if (!(f2 > 0.0) || !(f2 < 1e300)) return 1.f;
-    return ldexpf(1.f, min(max(-ilogb(sqrt(f2)), -120), 120));
+    return norm_scale(o2 + d2);
+}
+// What is taken from the diagonal of a factor before it is reduced on the chip: its mean, if the factor is little else (less than a quarter of
+// ||F||_F^2 is left).  Every update rounds what is left, not what was taken.  residual / ||F||: Gram matrices of 30 n samples 1.07e-6 -> 2.1e-7 at
+// 1153; eigenvalues that differ by 2 % at most, whose vectors could not be corrected afterwards, 1.7e-6 -> 4.0e-8 at 1153, and 4609, which missed tol and
+// took 145 ms with the sweeps that followed, 3.7e-8 in 31.8.  (A graded or rank-deficient factor is never that close to its mean.)  The
+// eigenvectors are the same, and the eigenvalues come from the caller's F.
+__device__ inline double dir_shift(const DirMat &M, double f2) {
+    const int lane = threadIdx.x & 63;
+    double tr = 0.0;
+#pragma unroll
+    for (int i = 0; i < NORM_WGS / 64; ++i) tr += M.sums[64 * i + lane];
+    tr = wave_sum_f64(tr);
+    return tr * tr > 0.75 * f2 * M.n ? tr / M.n : 0.0;
 }
 
 // ord[rank] = index of the rank-th largest diagonal element (ties and NaNs by index: always a permutation)
@@ -201,7 +233,7 @@ __device__ inline void empty_ring(const DirMat &M, int wg, int wgs) {
     for (int i = wg * 256 + (int)threadIdx.x; i < CHIP_RING * M.np; i += 256 * wgs) ring[i] = CHIP_EMPTY;
 }
 
-// A <- scale * F, reordered, with zero padding, for the factors wider than the register kernels take; the norms for all of them.
+// A <- scale * (F - shift), reordered, with zero padding, for the factors wider than the register kernels take; the norms for all of them.
 __global__ __launch_bounds__(256) void dir_copy_kernel(const DirMat *mats) {
     const DirMat M = mats[blockIdx.y];
     double o2, d2;
@@ -211,14 +243,18 @@ __global__ __launch_bounds__(256) void dir_copy_kernel(const DirMat *mats) {
     const global_ptr<const float> F = as_global(M.F);
     const global_ptr<float> A = as_global(M.A);
     const int n = M.n, np = M.np;
+    const double shift = dir_shift(M, o2 + d2);
     if (blockIdx.x == 0)
         for (int i = n - 1 + (int)threadIdx.x; i < np; i += 256) M.tau[i] = 0.f;   // no reflectors there
     if (M.chain == 0) empty_ring(M, blockIdx.x, gridDim.x);
     const global_ptr<const int> ord = as_global((const int *)M.ord);
     for (int r = blockIdx.x; r < np; r += gridDim.x) {
         const int64_t fr = r < n ? (int64_t)ord[r] * n : 0;
-        for (int c = threadIdx.x; c < np; c += 256)
-            A[(int64_t)r * M.ld + c] = (r < n && c < n) ? sc * F[fr + ord[c]] : 0.f;
+        for (int c = threadIdx.x; c < np; c += 256) {
+            float v = (r < n && c < n) ? F[fr + ord[c]] : 0.f;
+            if (c == r && r < n) v = (float)((double)v - shift);
+            A[(int64_t)r * M.ld + c] = sc * v;
+        }
     }
 }
 
@@ -679,7 +715,7 @@ __device__ inline double hash_unit(int i) {   // in [-1, 1): the output function
     return (double)(long long)(z >> 11) * (1.0 / 4503599627370496.0) - 1.0;
 }
 
-// td <- T / (Gershgorin bound), its diagonal perturbed; zeros where the matrix is not finite.
+// td <- T / (Gershgorin bound), its diagonal perturbed; zeros where the matrix is not finite.  tsum[0]: see CORRECT_FROM.
 __global__ __launch_bounds__(256) void dir_scale_t_kernel(const DirMat *mats) {
     const DirMat M = mats[blockIdx.x];
     const int n = M.n;
@@ -693,6 +729,19 @@ __global__ __launch_bounds__(256) void dir_scale_t_kernel(const DirMat *mats) {
     __syncthreads();
     g = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
     const double inv = (g > 0.0 && g < 1e300) ? 1.0 / g : 0.0;
+    if (n > TD_SMALL) {
+        const double f2 = M.stat[0] + M.stat[1], sc = norm_scale(f2);
+        double often = 0.0;
+        for (int i = threadIdx.x; i < n; i += 256) {
+            const double d = M.d[i], e = i < n - 1 ? M.e[i] : 0.0;
+            often += (d * d + 2.0 * e * e) * max(i - M.chain, 0);
+        }
+        often = wave_sum_f64(often);
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = often;
+        __syncthreads();
+        if (threadIdx.x == 0) M.tsum[0] = (red[0] + red[1] + red[2] + red[3]) / (sc * sc * f2);
+    }
     for (int i = threadIdx.x; i < n; i += 256) {
         const double e = i < n - 1 ? M.e[i] : 0.0, d = M.d[i];
         double en = fabs(e) < 1e300 ? e * inv * (1.0 + PERTURB_REL * hash_unit(-2 - i)) : 0.0;
@@ -1114,24 +1163,39 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(3))) v
     subtract_tile(acc, as_global(M.Z) + (int64_t)tr.I * TB * ld + tr.J * TB, ld, 0);
 }
 
-// ---- Newton-Schulz step and F Q, all factors in one launch each (tables: largest factor first) ------------------
+// ---- Newton-Schulz step, F Q and the correction, all factors in one launch each (tables: largest factor first) -------------
 // ORTH: B1 = (I - Q^T Q) / 2 (lower tiles and their mirror images).  STEP: Q' = Q + Q B1.  Q is Z, Q' is B2 with its rows back
 // in the caller's order; for the few factors that need a second step (nearly equal eigenvalues of T whose eigenvectors
 // were off by more than 1e-3) Q is B2 and Q' is Z.  TIMES_F: B1 = F Q'.
-enum { ORTH, STEP, TIMES_F };
+//
+// A correction (CORRECT_FROM) begins with the residual R = F Q - Q diag(lam), which dir_residual_kernel puts into the caller's Q for the time being.
+// TURN: A = X, X_ij = (q_i^T r_j + q_j^T r_i) / 2 (lam_j - lam_i): to first order, the rotation that makes Q^T F Q = diag(lam) + Q^T R diagonal
+// (lower tiles and their mirror images.  With q_i^T r_j alone, which differs from q_j^T r_i by the rounding of F Q, X is not antisymmetric, and
+// ||I - Q^T Q||_F comes out twenty times as large).  FOLLOW: Q' = Q + Q X, into the other of Z and B2, and F Q' = F Q + (F Q) X, into the caller's Q.
+// Where eigenvalues are close there is nothing to gain and X would not be small, so the quotient is
+// damped: gap / (gap^2 + delta^2) with delta = CORRECT_GAP times the larger residual of the two columns.  Every column of X is then shorter
+// than 2^-12, whatever the spectrum, and the orthogonality that is lost (X^T X) at the level of fp32 rounding.  Both products have a factor
+// that is this small, so the 22 bits of the split-fp16 products are more than fp32 would keep of their results, at any width.
+enum { ORTH, STEP, TIMES_F, TURN, FOLLOW };
 __device__ inline bool needs_second_step(const DirMat &M) { return M.stat[3] > NS_AGAIN; }
-__device__ inline float *final_q(const DirMat &M) { return needs_second_step(M) ? M.Z : M.B2; }
+// (a choice between two members as a choice of values: as one of addresses it puts the whole DirMat into scratch memory, and 180 us into a kernel)
+__device__ inline float *pick(bool first, float *a, float *b) { return (float *)((uintptr_t)b ^ (((uintptr_t)a ^ (uintptr_t)b) & -(uintptr_t)first)); }
+__device__ inline bool corrected(const DirMat &M) { return M.n > TD_SMALL && M.tsum[1] > 0.0; }      // (from dir_residual_kernel on)
+__device__ inline float *orthonormal_q(const DirMat &M) { return pick(needs_second_step(M), M.Z, M.B2); }
+__device__ inline float *final_q(const DirMat &M) { return pick(needs_second_step(M) != corrected(M), M.Z, M.B2); }
 
 template <int WHAT, bool X3>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void dir_product_kernel(const DirMat *mats, const unsigned *tab, int second) {
     __shared__ typename std::conditional<X3, X3Smem, TileSmem>::type sm;
     const TabRef tr = tab_ref(tab[blockIdx.x]);
     const DirMat M = mats[tr.m];
-    if (WHAT != TIMES_F && ((M.split != 0) != X3 || (second && !needs_second_step(M)))) return;
+    if ((WHAT == ORTH || WHAT == STEP) && ((M.split != 0) != X3 || (second && !needs_second_step(M)))) return;
+    if ((WHAT == TURN || WHAT == FOLLOW) && !corrected(M)) return;
     const int n = M.n, i0 = tr.I * TB, j0 = tr.J * TB;
     const int64_t ld = M.ld;
-    const float *Q = second ? M.B2 : M.Z;
-    constexpr float SC = 16384.f, OUT = 1.f / (SC * SC);     // entries of Q and of the correction are below 1
+    const float *Q = WHAT == ORTH || WHAT == STEP ? pick(second, M.B2, M.Z) : orthonormal_q(M);
+    constexpr float SC = 16384.f, OUT = 1.f / (SC * SC);     // entries of Q, of the step and of the scaled residual are below 2
+    constexpr float TURNS = 1024.f;                          // those of X far below: to keep their low halves from underflow
     floatx16 acc[2][2];
     if constexpr (WHAT == ORTH) {
         if constexpr (X3) {
@@ -1152,7 +1216,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         if (j0 < i0) for_each_acc_transposed(acc, reinterpret_cast<float *>(&sm), [&](int r, int c, float v) { epi(j0 + r, i0 + c, v); });
     } else if constexpr (WHAT == STEP) {
         const global_ptr<const float> Qi = as_global(Q);
-        const global_ptr<float> O = as_global(second ? M.Z : M.B2);
+        const global_ptr<float> O = as_global(pick(second, M.Z, M.B2));
         const global_ptr<const int> ord = as_global((const int *)M.ord);
         auto epi = [&](int gr, int gc, float v) { O[(int64_t)(second ? gr : ord[gr]) * ld + gc] = Qi[(int64_t)gr * ld + gc] + v; };
         if constexpr (X3) {
@@ -1167,9 +1231,44 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
             OpStrided<float, false> b{M.B1, 1, ld, n, n, -1};
             gemm_tile_ragged(a, b, i0, j0, n, n, n, sm, epi);
         }
+    } else if constexpr (WHAT == TURN) {
+        const global_ptr<float> X = as_global(M.A);
+        const global_ptr<const double> lam = as_global((const double *)M.lam64), rho = as_global((const double *)M.sums);
+        const double half = 0.5 * OUT / M.tsum[1];
+        X3OpG<float, false> a{Q, ld, SC, n, n}, b{M.Q, n, SC, n, n}, c{M.Q, n, SC, n, n}, d{Q, ld, SC, n, n};
+        a.start(threadIdx.x, i0);
+        b.start(threadIdx.x, j0);
+        gemm_tile_x3(a, b, n, sm, acc);
+        __syncthreads();
+        c.start(threadIdx.x, i0);
+        d.start(threadIdx.x, j0);
+        gemm_tile_x3(c, d, n, sm, acc, false);
+        auto epi = [&](int gr, int gc, float v) {
+            if (gr >= n || gc >= n) return;
+            const double gap = lam[gc] - lam[gr], delta = CORRECT_GAP * fmax(rho[gr], rho[gc]), den = fma(gap, gap, delta * delta);
+            X[(int64_t)gr * ld + gc] = den > 0.0 ? (float)(half * v * gap / den) : 0.f;
+        };
+        for_each_acc(acc, [&](int r, int c, float v) { epi(i0 + r, j0 + c, v); });
+        if (j0 < i0) for_each_acc_transposed(acc, reinterpret_cast<float *>(&sm), [&](int r, int c, float v) { epi(j0 + r, i0 + c, v); });
+    } else if constexpr (WHAT == FOLLOW) {
+        const bool fq = blockIdx.y != 0;
+        const float sc = fq ? SC * norm_scale(M.stat[0] + M.stat[1]) : SC;     // ||F||_F bounds the entries of F Q
+        const float *Y = pick(fq, M.B1, orthonormal_q(M));
+        const global_ptr<const float> Yi = as_global(Y);
+        const global_ptr<float> O = as_global(pick(fq, M.Q, pick(needs_second_step(M), M.B2, M.Z)));
+        const int64_t lo = fq ? n : ld;
+        const float os = 1.f / (sc * (SC * TURNS));
+        X3OpG<float, true> a{Y, ld, sc, n, n};
+        X3OpG<float, false> b{M.A, ld, SC * TURNS, n, n};
+        a.start(threadIdx.x, i0);
+        b.start(threadIdx.x, j0);
+        gemm_tile_x3(a, b, n, sm, acc);
+        for_each_acc(acc, [&](int r, int c, float v) {
+            if (i0 + r < n && j0 + c < n) O[(int64_t)(i0 + r) * lo + j0 + c] = Yi[(int64_t)(i0 + r) * ld + j0 + c] + v * os;
+        });
     } else {
         OpStrided<float, true> a{M.F, n, 1, n, n, -1};
-        OpStrided<float, false> b{final_q(M), 1, ld, n, n, -1};
+        OpStrided<float, false> b{Q, 1, ld, n, n, -1};
         const global_ptr<float> O = as_global(M.B1);
         gemm_tile_ragged<512>(a, b, i0, j0, n, n, n, sm, [&](int gr, int gc, float v) { O[(int64_t)gr * ld + gc] = v; });
     }
@@ -1204,15 +1303,17 @@ __global__ __launch_bounds__(64) void dir_dev_sum_kernel(const DirMat *mats) {
 }
 
 // Per column: sums of q fq, fq^2 and q^2 over the rows of part blockIdx.y.
-__global__ __launch_bounds__(256) void dir_rayleigh_kernel(const DirMat *mats) {
+__global__ __launch_bounds__(256) void dir_rayleigh_kernel(const DirMat *mats, int again) {
     const DirMat M = mats[blockIdx.z];
     const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= M.n || (int)blockIdx.y >= M.n) return;
-    const global_ptr<const float> Q = as_global((const float *)final_q(M)) + c, FQ = as_global((const float *)M.B1) + c;
+    if (c >= M.n || (int)blockIdx.y >= M.n || (again && !corrected(M))) return;
+    const global_ptr<const float> Q = as_global((const float *)pick(needs_second_step(M) != (again != 0), M.Z, M.B2)) + c;
+    const global_ptr<const float> FQ = as_global((const float *)pick(again, M.Q, M.B1)) + c;
+    const int64_t lf = again ? M.n : M.ld;
     const int per = (M.n + NPARTS - 1) / NPARTS, r0 = blockIdx.y * per, r1 = min(M.n, r0 + per);
     double s1 = 0.0, s2 = 0.0, s3 = 0.0;
     for (int r = r0; r < r1; ++r) {
-        const double q = (double)Q[(int64_t)r * M.ld], f = (double)FQ[(int64_t)r * M.ld];
+        const double q = (double)Q[(int64_t)r * M.ld], f = (double)FQ[r * lf];
         s1 = fma(q, f, s1);
         s2 = fma(f, f, s2);
         s3 = fma(q, q, s3);
@@ -1222,10 +1323,12 @@ __global__ __launch_bounds__(256) void dir_rayleigh_kernel(const DirMat *mats) {
     o[M.np] = s2;
     o[2 * M.np] = s3;
 }
-// lam64 = q^T F q / q^T q, and the factor that makes the column a unit vector; its residual is then s2 / s3 - lam^2
-__global__ __launch_bounds__(256) void dir_lambda_kernel(const DirMat *mats) {
+// lam64 = q^T F q / q^T q, and the factor that makes the column a unit vector; its residual is then s2 / s3 - lam^2 (the root of it
+// in the place of the column's first sum, for the correction)
+__global__ __launch_bounds__(256) void dir_lambda_kernel(const DirMat *mats, int again) {
     const DirMat M = mats[blockIdx.y];
     const int c = blockIdx.x * 256 + threadIdx.x;
+    if (again && !corrected(M)) return;
     double res = 0.0;
     if (c < M.n) {
         double s1 = 0.0, s2 = 0.0, s3 = 0.0;
@@ -1251,12 +1354,35 @@ __global__ __launch_bounds__(256) void dir_lambda_kernel(const DirMat *mats) {
         M.lam64[c] = l;
         M.te[c] = 1.0 / sqrt(s3);
         res = s2 / s3 - l * l;
+        M.sums[c] = sqrt(fmax(res, 0.0));
     }
     __shared__ double red[4];
     res = wave_sum_f64(res);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = res;
     __syncthreads();
     if (threadIdx.x == 0 && (int)blockIdx.x * 256 < M.n) M.npartd[NORM_WGS + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+}
+
+// s (F Q - Q diag(lam)), s the power of two that brings its norm into [1, 2), for the factors that are to be corrected: into the caller's Q
+__global__ __launch_bounds__(256) void dir_residual_kernel(const DirMat *mats) {
+    const DirMat M = mats[blockIdx.y];
+    const int n = M.n;
+    if (n <= TD_SMALL) return;
+    const int lane = threadIdx.x & 63, nr = (n + 255) / 256;
+    const double res = wave_sum_f64(lane < nr ? M.npartd[NORM_WGS + lane] : 0.0);
+    const bool fix = M.tsum[0] >= CORRECT_FROM && res > 1e-200 && res < 1e200;
+    const double s = fix ? ldexp(1.0, -ilogb(sqrt(res))) : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) M.tsum[1] = s;
+    if (!fix) return;
+    const global_ptr<const float> Q = as_global((const float *)orthonormal_q(M));
+    const global_ptr<const float> FQ = as_global((const float *)M.B1);
+    const global_ptr<const double> lam = as_global((const double *)M.lam64);
+    const global_ptr<float> R = as_global(M.Q);
+    for (int r = blockIdx.x; r < n; r += gridDim.x)
+        for (int c = threadIdx.x; c < n; c += 256) {
+            const int64_t i = (int64_t)r * M.ld + c;
+            R[(int64_t)r * n + c] = (float)(s * fma(-lam[c], (double)Q[i], (double)FQ[i]));
+        }
 }
 
 // perm[rank] = index of the rank-th smallest Rayleigh quotient (ties and NaNs by index: always a permutation)
@@ -1623,10 +1749,25 @@ int enqueue_finish(kfac_ctx *ctx, const DirRun &R) {
         }
         hipLaunchKernelGGL((dir_product_kernel<TIMES_F, false>), fu, b, 0, st, dm, tf, 0);
     }
-    {
+    auto quotients = [&](int again) {
         KfacProfScope prof(ctx, KC_EIG_MISC, 0.0, 16.0 * R.square, st);
-        hipLaunchKernelGGL(dir_rayleigh_kernel, dim3((P.nmax + 255) / 256, std::min(NPARTS, P.nmax), batch), dim3(256), 0, st, dm);
-        hipLaunchKernelGGL(dir_lambda_kernel, dim3((P.nmax + 255) / 256, batch), dim3(256), 0, st, dm);
+        hipLaunchKernelGGL(dir_rayleigh_kernel, dim3((P.nmax + 255) / 256, std::min(NPARTS, P.nmax), batch), dim3(256), 0, st, dm, again);
+        hipLaunchKernelGGL(dir_lambda_kernel, dim3((P.nmax + 255) / 256, batch), dim3(256), 0, st, dm, again);
+    };
+    quotients(0);
+    if (P.nmax > TD_SMALL) {      // which factors are corrected is known on the device only: no work of it is credited
+        {
+            KfacProfScope prof(ctx, KC_EIG_POST, 0.0, 0.0, st);
+            const dim3 lo(P.lower.count), fu(P.full.count), b(NTHREADS);
+            const unsigned *tl = tab + P.lower.at, *tf = tab + P.full.at;
+            hipLaunchKernelGGL(dir_residual_kernel, per_mat, dim3(256), 0, st, dm);
+            hipLaunchKernelGGL((dir_product_kernel<TURN, true>), lo, b, 0, st, dm, tl, 0);
+            hipLaunchKernelGGL((dir_product_kernel<FOLLOW, true>), dim3(fu.x, 2), b, 0, st, dm, tf, 0);
+        }
+        quotients(1);
+    }
+    {
+        KfacProfScope prof(ctx, KC_EIG_MISC, 0.0, 0.0, st);
         hipLaunchKernelGGL(dir_rank_kernel, dim3((P.nmax + RANK_IPB - 1) / RANK_IPB, batch), dim3(256), 0, st, dm);
         hipLaunchKernelGGL(dir_gather_kernel, per_mat, dim3(256), 0, st, dm);
     }

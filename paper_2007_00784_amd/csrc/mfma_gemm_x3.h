@@ -251,13 +251,15 @@ __device__ inline void x3_slabs(OpA &A, OpB &B, int nslab, bool advance, X3Smem 
 // and the ragged last slab, if there is one, on the checked fetch, as a second short pipeline.
 // The caller has already called start() on both loaders.
 template <class OpA, class OpB>
-__device__ inline void gemm_tile_x3(OpA &A, OpB &B, int K, X3Smem &sm, floatx16 (&acc)[2][2]) {
+__device__ inline void gemm_tile_x3(OpA &A, OpB &B, int K, X3Smem &sm, floatx16 (&acc)[2][2], bool zero_acc = true) {
+    if (zero_acc) {   // false: keep accumulating into acc
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    }
     const int nslab = (K + BK - 1) / BK;   // loaders without an extent of their own are given whole slabs
     if (nslab <= 0) return;
     constexpr bool TWO = OpA::HAS_BULK && OpB::HAS_BULK;
