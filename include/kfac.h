@@ -172,6 +172,9 @@ size_t kfac_static_scratch_bytes(void);
  *               Q_i [d_i][d_i], lam_i [d_i]
  *   d         : host array of dimensions, 1 <= d_i <= 8192
  *   opts      : host, may be NULL for defaults;  info: host array [batch], may be NULL
+ * Factors wider than 256 are decomposed by launches that need every compute unit the stream may use, all at once.
+ * While other work holds some of them (a kernel that waits, another process), such a launch waits with it, 0.1 to 0.3 s at the
+ * most; then, or if the device refuses the launch, the call goes on without launches of that kind, about half as fast.
  * Returns KFAC_ENOCONV if any factor missed the tolerance within max_sweeps (all outputs are
  * still the current iterate).  Non-finite input gives non-finite output and KFAC_ENOCONV.  */
 int kfac_eig(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q,

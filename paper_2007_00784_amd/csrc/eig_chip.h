@@ -28,8 +28,10 @@
 //
 // A launch takes every factor some columns further (ChipJob), then the trailing matrices go back to memory and are dealt out anew:
 // a matrix that has shrunk needs fewer workgroups, and others take their place.  All workgroups of a launch must be resident at once
-// (cooperative launch, one per compute unit).  Every wait is bounded; a reduction that gave up leaves a matrix
-// T that is not the factor's, which the measured residual shows, and the factor is decomposed by Jacobi iteration like any unsound one.
+// (cooperative launch, one per compute unit that the stream may use).  Another kernel may hold compute units for long all the same (a
+// collective that waits for its peer, another process), so every wait is bounded, by KFAC_CHIP_POLLS: 0.1 to 0.3 s.  A workgroup that gives
+// up says so (chip_flags); the others of the call and the launches after it look at that and leave.  Factors whose reduction was
+// given up are decomposed again with the chain of launches, which needs no two workgroups at once.
 
 constexpr int CHIP_SLOTS = 9;
 constexpr int CHIP_WIDE = 512, CHIP_NARROW = 256;         // threads of a workgroup
@@ -42,7 +44,7 @@ constexpr int CHIP_WGS = 256;                             // workgroups of a fac
 constexpr int CHIP_JOBS = 64;                             // factors of a launch, at most: a workgroup finds its own by one ballot
 constexpr int CHIP_PAUSE = 6;                             // of 64 cycles, before the first look at the others' words
 constexpr int CHIP_WHOLE = 640, CHIP_STEPS_MIN = 96;      // up to here a factor goes in one launch; the fewest columns of a launch otherwise
-constexpr int CHIP_SPIN = 1 << 21;                        // polls (0.5 to 1 us each) before a wait is given up
+constexpr int CHIP_LOOK = 256;                            // polls between two looks at whether the call has been given up
 
 // Rows that a workgroup of S column slots can hold, in groups of four (the rows of a matrix instruction; two rows of the nine-slot kind
 // are left to ordinary ones), and the rows whose sums are in registers together.
@@ -125,10 +127,12 @@ __device__ inline floatx4 chip_outer(float rows, float column, floatx4 c, int g)
 typedef global_ptr<unsigned long long> ChipWords;
 // word i of those at `base`: a scalar base and 32 bits of offset, so that no lane keeps 64-bit addresses
 __device__ inline unsigned long long chip_load(ChipWords base, unsigned i) { return __hip_atomic_load(base + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// of a factor: [0] its reduction was given up (of the one that the launches of a call have in common also [1]: some reduction of the call was)
+__device__ inline ChipWords chip_flags(const DirMat &M) { return as_global((unsigned long long *)M.apan) + (size_t)2 * CHIP_RING * M.np; }
 __device__ inline void chip_store(ChipWords p, unsigned long long v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 template <int CHIP_NT, int S>
-__device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, ChipSmem<CHIP_NT> &sm) {
+__device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, ChipWords call, int polls, ChipSmem<CHIP_NT> &sm) {
     constexpr int CHIP_WAVES = CHIP_NT / 64, R = chip_rows(S), G = R / 4, X = R % 4, PIECE = chip_piece(S), PIECES = (4 * G + PIECE - 1) / PIECE;
     static_assert((X == 0 || 4 * G % PIECE == 0) && R <= CHIP_ROWS, "extra rows follow whole pieces");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -167,7 +171,6 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
 #pragma unroll
         for (int q = 0; q < CHIP_RING; ++q) other[(size_t)q * M.np] = CHIP_EMPTY;
     }
-    if (tid == 0) sm.failed = 0;
     float nv = 0.f, nw = 0.f;       // lane i: -v and -w of row r0 + i
     for (int t = 0;; ++t) {
         // x: column k0 + t, rows t .. m - 1 of the trailing matrix (zero before).  v, w: the reflector before it, not yet applied.
@@ -276,7 +279,7 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
                     u[j] = chip_load(slot + CHIP_NT * j, tid);
                 }
             if (__all(there)) break;
-            if (spin > CHIP_SPIN) { sm.failed = 1; break; }
+            if (spin >= polls || (spin % CHIP_LOOK == CHIP_LOOK - 1 && chip_load(call, 0) != 0)) { sm.failed = 1; break; }
         }
         double dot = 0.0;
 #pragma unroll
@@ -298,7 +301,13 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
         dot = 0.0;
 #pragma unroll
         for (int g = 0; g < CHIP_WAVES; ++g) dot += sm.dot[g];
-        if (failed) return;                // the result is not sound, and is found not to be
+        if (failed) {
+            if (tid == 0) {
+                chip_store(chip_flags(M), 1);
+                chip_store(call, 1);
+            }
+            return;
+        }
         const float cw = (float)(-0.5 * tau * tau * dot), wt = fmaf(tau, yt, cw);
         const float vr = lane < nr && r >= t ? (r == t ? 1.f : xr * scale) : 0.f;
         nv = -vr;
@@ -341,24 +350,31 @@ __device__ inline void chip_reduce(const DirMat &M, const ChipJob &J, int p, Chi
         }
 }
 
-template <int NT> __global__ __launch_bounds__(NT, 2) void dir_chip_kernel(const DirMat *mats, const ChipJob *jobs, int count) {
+template <int NT> __global__ __launch_bounds__(NT, 2) void dir_chip_kernel(const DirMat *mats, const ChipJob *jobs, int count, int lead, int polls) {
     __shared__ __attribute__((aligned(16))) ChipSmem<NT> sm;
     const int lane = threadIdx.x & 63;
     const int base = lane < count ? jobs[lane].base : INT_MAX;      // ascending
     const ChipJob J = jobs[__popcll(__ballot(base <= (int)blockIdx.x)) - 1];
     const DirMat M = mats[J.m];
     const int p = (int)blockIdx.x - J.base;
+    const ChipWords call = as_global((unsigned long long *)mats[lead].apan) + (size_t)2 * CHIP_RING * mats[lead].np + 1;
+    if (threadIdx.x == 0) sm.failed = chip_load(call, 0) != 0;
+    __syncthreads();
+    if (sm.failed) {       // given up, by an earlier launch or in this one
+        if (threadIdx.x == 0) chip_store(chip_flags(M), 1);
+        return;
+    }
     switch (J.slots) {
-        case 1: chip_reduce<NT, 1>(M, J, p, sm); break;
-        case 2: chip_reduce<NT, 2>(M, J, p, sm); break;
-        case 3: chip_reduce<NT, 3>(M, J, p, sm); break;
-        case 4: chip_reduce<NT, 4>(M, J, p, sm); break;
-        case 5: chip_reduce<NT, 5>(M, J, p, sm); break;
-        case 6: chip_reduce<NT, 6>(M, J, p, sm); break;
-        case 7: chip_reduce<NT, 7>(M, J, p, sm); break;
-        case 8: chip_reduce<NT, 8>(M, J, p, sm); break;
+        case 1: chip_reduce<NT, 1>(M, J, p, call, polls, sm); break;
+        case 2: chip_reduce<NT, 2>(M, J, p, call, polls, sm); break;
+        case 3: chip_reduce<NT, 3>(M, J, p, call, polls, sm); break;
+        case 4: chip_reduce<NT, 4>(M, J, p, call, polls, sm); break;
+        case 5: chip_reduce<NT, 5>(M, J, p, call, polls, sm); break;
+        case 6: chip_reduce<NT, 6>(M, J, p, call, polls, sm); break;
+        case 7: chip_reduce<NT, 7>(M, J, p, call, polls, sm); break;
+        case 8: chip_reduce<NT, 8>(M, J, p, call, polls, sm); break;
         default:
-            if constexpr (NT == CHIP_WIDE) chip_reduce<NT, 9>(M, J, p, sm);
+            if constexpr (NT == CHIP_WIDE) chip_reduce<NT, 9>(M, J, p, call, polls, sm);
     }
 }
 

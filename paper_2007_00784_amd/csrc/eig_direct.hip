@@ -55,6 +55,7 @@ constexpr double NS_AGAIN = 4e-6;         // ||I - Q^T Q||_F^2 from which one Ne
 // 4609 4.6, 18.5, 3.6, random symmetric 4609 10.3, 17.4, 4.3; ReLU activations (not corrected) 4609 4.8, 4.8.  ||I - Q^T Q||_F: the
 // same in all of them.  A corrected factor costs 2.5 ms more at 4609 (31.0), 0.5 at 2305 (11.2), 0.15 at 577 (2.6).
 constexpr double CORRECT_FROM = 64.0;
+constexpr double REDUCTION_GIVEN_UP = -1.0;
 constexpr double CORRECT_GAP = 0x1p11;    // gap of two eigenvalues, in residuals of their columns, below which they are left as they are
 constexpr double BIS_REL = 0x1p-51, BIS_ABS = 1e-25;   // width at which an eigenvalue's interval is done, of its size and of the bound
 constexpr int BIS_WIDE_MAX = 160;         // up to this many groups of 64 eigenvalues, sixteen lanes each
@@ -227,10 +228,12 @@ __global__ __launch_bounds__(256) void dir_order_kernel(const DirMat *mats) {
     }
 }
 
-// Empties the ring of a factor's first launch of the reduction on the chip: EMPTY, as 8-byte words, over the first half of apan's use.
+// Empties the ring of a factor's first launch of the reduction on the chip: EMPTY, as 8-byte words, over the first half of apan's use; and
+// clears the two words that say whether a reduction was given up, behind both halves.
 __device__ inline void empty_ring(const DirMat &M, int wg, int wgs) {
     const global_ptr<unsigned long long> ring = as_global((unsigned long long *)M.apan);
     for (int i = wg * 256 + (int)threadIdx.x; i < CHIP_RING * M.np; i += 256 * wgs) ring[i] = CHIP_EMPTY;
+    if (wg == 0 && threadIdx.x < 2) ring[(size_t)2 * CHIP_RING * M.np + threadIdx.x] = 0;
 }
 
 // A <- scale * (F - shift), reordered, with zero padding, for the factors wider than the register kernels take; the norms for all of them.
@@ -1292,14 +1295,14 @@ __global__ __launch_bounds__(256) void dir_dev_kernel(const DirMat *mats) {
     if (threadIdx.x == 0) M.npartd[blockIdx.x] = 4.0 * (red[0] + red[1] + red[2] + red[3]);
 }
 
-// the sum over the workgroups: stat[3]
+// the sum over the workgroups: stat[3]; REDUCTION_GIVEN_UP for a factor whose T is not its own
 __global__ __launch_bounds__(64) void dir_dev_sum_kernel(const DirMat *mats) {
     const DirMat M = mats[blockIdx.x];
     double dev = 0.0;
 #pragma unroll
     for (int i = 0; i < NORM_WGS / 64; ++i) dev += 64 * i + (int)threadIdx.x < M.n ? M.npartd[64 * i + (int)threadIdx.x] : 0.0;
     dev = wave_sum_f64(dev);
-    if (threadIdx.x == 0) M.stat[3] = dev;
+    if (threadIdx.x == 0) M.stat[3] = M.n > TD_SMALL && M.chain < M.n - 1 && chip_load(chip_flags(M), 0) != 0 ? REDUCTION_GIVEN_UP : dev;
 }
 
 // Per column: sums of q fq, fq^2 and q^2 over the rows of part blockIdx.y.
@@ -1501,7 +1504,7 @@ struct DirPlan {
     std::vector<int> small[4];            // factors per register kernel: up to 64, 128, 192, 256
     unsigned small_at[4] = {0, 0, 0, 0};
     Range values{0, 0}, apply{0, 0}, gram{0, 0}, wyu{0, 0}, wyy{0, 0}, wys{0, 0}, wyz{0, 0}, lower{0, 0}, full{0, 0};
-    int wy_steps = 0, nmax = 0;
+    int wy_steps = 0, nmax = 0, lead = 0;     // lead: the widest factor
     bool any_split = false, any_plain = false;
 };
 
@@ -1515,6 +1518,7 @@ void dir_tables(DirPlan &P, int capacity) {
     auto begin = [&](DirPlan::Range &r) { r.at = (unsigned)P.tab.size(); };
     auto end = [&](DirPlan::Range &r) { r.count = (unsigned)P.tab.size() - r.at; };
     P.nmax = nm ? P.mats[order[0]].n : 0;
+    P.lead = nm ? order[0] : 0;
     const int widest = chip_widest(capacity);      // as many columns by the chain of launches as it takes to fit the chip
     for (auto &M : P.mats) {
         M.chain = M.n > TD_SMALL && M.n > widest ? (M.n - widest + NB - 1) / NB * NB : 0;
@@ -1682,13 +1686,16 @@ int enqueue_reduction(kfac_ctx *ctx, const DirRun &R) {
     for (const ChipLaunch &L : P.chip) {
         const DirMat *dm = R.dm;
         const ChipJob *jobs = (const ChipJob *)(R.tab + L.at);
-        int count = L.jobs;
-        void *args[] = {&dm, &jobs, &count};
+        int count = L.jobs, lead = P.lead, polls = ctx->chip_polls;
+        void *args[] = {&dm, &jobs, &count, &lead, &polls};
         // of three multiplications and additions per element, one belongs to the product and two to the update
         KfacProfScope product(ctx, KC_EIG_REDUCE_MV, L.flops / 3.0, L.bytes / 3.0, st, 1.0 / 3.0);
         KfacProfScope update(ctx, KC_EIG_REDUCE_GEMM, L.flops / 1.5, L.bytes / 1.5, st, 2.0 / 3.0);
         const void *kernel = L.threads == CHIP_WIDE ? (const void *)dir_chip_kernel<CHIP_WIDE> : (const void *)dir_chip_kernel<CHIP_NARROW>;
-        KFAC_HIP_CHECK(hipLaunchCooperativeKernel(kernel, dim3((unsigned)L.wgs), dim3((unsigned)L.threads), args, 0, st));
+        if (hipLaunchCooperativeKernel(kernel, dim3((unsigned)L.wgs), dim3((unsigned)L.threads), args, 0, st) != hipSuccess) {
+            (void)hipGetLastError();
+            return KFAC_EIG_REFUSED;
+        }
     }
     if (P.nmax > TD_SMALL) {
         KfacProfScope prof(ctx, KC_EIG_REDUCE_VEC, 0.0, 2.0 * R.square, st);
@@ -1801,8 +1808,9 @@ double kfac_eig_direct_seconds(int batch, const int *d) {
 // squared residual ||F Q - Q diag(lam)||_F^2 and ||I - Q^T Q||_F^2 before it was orthogonalised.  Waits for the result.
 // diag_tol: off(F)_F / ||F||_F up to which a factor counts as diagonal.  go_on (may be null): called, if a factor is wider than
 // KFAC_EIG_REG, once off^2 and diag^2 of all factors are in stat; if it returns false, nothing more is done (KFAC_EIG_STOPPED).
-int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
-                           double diag_tol, double *stat, const std::function<bool()> *go_on) {
+// capacity: workgroups that the reduction on the chip may use at once; with none, everything is reduced by the chain of launches.
+static int direct_by(kfac_ctx *ctx, int capacity, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
+                     double diag_tol, double *stat, const std::function<bool()> *go_on) {
     if (kfac_eig_direct_ws_bytes(batch, d) > ctx->ws_bytes) return KFAC_EWORKSPACE;
     DirMat *d_mats = (DirMat *)ctx->ws;
     double *d_stat = (double *)(ctx->ws + kfac_align_up((size_t)batch * sizeof(DirMat), 256));
@@ -1826,7 +1834,7 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
         R.square += (double)d[i] * d[i];
     }
     R.P.tab.reserve(dir_table_bound(batch, d));
-    dir_tables(R.P, ctx->coop_wgs);
+    dir_tables(R.P, capacity);
     if (R.P.tab.size() > dir_table_bound(batch, d)) return KFAC_EWORKSPACE;
     KFAC_CHECK(kfac_upload(ctx, d_mats, R.P.mats.data(), R.P.mats.size() * sizeof(DirMat)));
     KFAC_CHECK(kfac_upload(ctx, d_tab, R.P.tab.data(), R.P.tab.size() * sizeof(unsigned)));
@@ -1850,4 +1858,34 @@ int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, cons
         rc = KFAC_EHIP;
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) rc = KFAC_EHIP;    // on an error, too: no kernel of this call is in flight after the return
     return rc;
+}
+
+int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
+                           double diag_tol, double *stat, const std::function<bool()> *go_on) {
+    int rc = direct_by(ctx, ctx->coop_wgs, batch, F, d, Q, lam, diag_tol, stat, go_on);
+    if (rc == KFAC_EIG_REFUSED) return direct_by(ctx, 0, batch, F, d, Q, lam, diag_tol, stat, nullptr);
+    if (rc != KFAC_OK) return rc;
+    std::vector<int> which, dd;
+    std::vector<const float *> FF;
+    std::vector<float *> QQ, ll;
+    for (int i = 0; i < batch; ++i)
+        if (stat[4 * i + 3] == REDUCTION_GIVEN_UP) {
+            which.push_back(i);
+            dd.push_back(d[i]);
+            FF.push_back(F[i]);
+            QQ.push_back(Q[i]);
+            ll.push_back(lam[i]);
+        }
+    if (which.empty()) return KFAC_OK;
+    std::vector<double> all(stat, stat + (size_t)4 * batch);
+    rc = direct_by(ctx, 0, (int)which.size(), FF.data(), dd.data(), QQ.data(), ll.data(), diag_tol, stat, nullptr);
+    if (rc != KFAC_OK) return rc;
+    for (size_t k = 0; k < which.size(); ++k) std::copy(stat + 4 * k, stat + 4 * k + 4, all.begin() + 4 * which[k]);
+    std::copy(all.begin(), all.end(), stat);
+    return KFAC_OK;
+}
+
+void kfac_limit_chip(kfac_ctx *ctx, int workgroups, int polls) {
+    ctx->coop_wgs = workgroups;
+    ctx->chip_polls = polls;
 }

@@ -129,7 +129,13 @@ int kfac_create(kfac_ctx **out, int device, void *hip_stream, void *workspace_de
     if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, device) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
         coop = 0;
+    uint32_t mask[32] = {};      // compute units that the stream may use
+    if (coop && hipExtStreamGetCUMask(c->stream, 32, mask) != hipSuccess) (void)hipGetLastError();
+    int units = 0;
+    for (uint32_t m : mask) units += __builtin_popcount(m);
+    if (units > 0) cus = std::min(cus, units);
     c->coop_wgs = coop ? cus : 0;
+    c->chip_polls = KFAC_CHIP_POLLS;
     *out = c;
     return KFAC_OK;
 }

@@ -44,7 +44,8 @@ struct kfac_ctx {
     char *ws;            // caller-owned device workspace
     size_t ws_bytes;
     int max_lds;         // bytes of LDS one workgroup may use on this device
-    int coop_wgs;        // workgroups of a cooperative launch, one per compute unit (0: the device has none)
+    int coop_wgs;        // workgroups of a cooperative launch, one per compute unit that the stream may use (0: the device has none)
+    int chip_polls;      // looks of such a workgroup at the words it waits for, before it gives up
     bool prof_on;        // bracket every kernel launch with events
     std::vector<KfacProfRec> prof;
     std::vector<hipEvent_t> ev_pool;
@@ -139,6 +140,10 @@ double kfac_eig_direct_seconds(int batch, const int *d);
 int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
                            double diag_tol, double *stat /* pinned, 4 per factor */, const std::function<bool()> *go_on);
 constexpr int KFAC_EIG_STOPPED = 1;  // its result if go_on() said no
+constexpr int KFAC_EIG_REFUSED = 2;  // (inside it) a launch that needs all its workgroups at once was refused
+constexpr int KFAC_CHIP_POLLS = 1 << 18;   // 0.5 to 1 us each
+// For tests: another number of workgroups of a cooperative launch (0: none), and of looks before a wait is given up (0: at once).
+extern "C" void kfac_limit_chip(kfac_ctx *ctx, int workgroups, int polls);
 size_t kfac_invert_ws_bytes_impl(int batch, const int *d);
 int kfac_launch_invert_factors(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float damping, float *const *Finv);
 size_t kfac_precondition_inverse_ws_bytes_impl(int n, const kfac_precond_inv_item *items);

@@ -4,6 +4,9 @@ Tolerances (the benchmark spec): factors and preconditioned gradients rela
 <= 1e-4 in fp32 (<= 2e-2 with bf16 inputs); eigenpairs: ||F - Q diag(lam) Q^T||_F <= 1e-5 ||F||_F and
 eigenvalues within 1e-5 * lam_max of the oracle's; unfold is bit-exact (data movement only).
 """
+import os
+import subprocess
+import sys
 import threading
 import time
 
@@ -728,6 +731,68 @@ def test_eig_corrected_eigenvectors(n, scale, kind):
     assert float((fd @ qd - qd * lam[0].double()).norm() / fd.norm()) <= 7e-7
     assert float((qd.T.contiguous() @ qd - torch.eye(n, device="cuda", dtype=torch.float64)).norm()) <= n * 2.0 ** -22
     assert float((lam[0].double() - scale * lam64.sort().values).abs().max()) <= 1e-6 * scale * float(lam64.abs().max())
+
+
+def decompose_with(F, workgroups, polls):
+    """As decompose_on_device(), the reduction on the chip limited to so many workgroups and looks at the others' words."""
+    dims = [f.shape[0] for f in F]
+    c = Ctx(K.kfac_eig_workspace_bytes(dims) + 4096)
+    K.lib().kfac_limit_chip(c.h, workgroups, polls)
+    Q, lam = [torch.empty_like(f) for f in F], [torch.empty(n, device="cuda") for n in dims]
+    info = K.kfac_eig(c.h, F, Q, lam)
+    c.close()
+    for f, q, l, n, i in zip(F, Q, lam, dims, info):
+        assert i[2] and i[0] == 1, (n, i)
+        fd, qd = f.double(), q.double()
+        assert float((fd @ qd - qd * l.double()).norm() / fd.norm()) <= 7e-7, n
+        assert float((qd.T.contiguous() @ qd - torch.eye(n, device="cuda", dtype=torch.float64)).norm()) <= max(n, 16) * 2.0 ** -22, n
+    return Q + lam
+
+
+# compute units held by other kernels: a workgroup that does not find the others' words gives up (here: at its first look).  The factor is then
+# decomposed with the chain of launches, to the last bit as if there were nothing else
+@pytest.mark.parametrize("dims", [[1025], [4611], [2050, 300, 100, 700, 257]])
+def test_eig_reduction_on_the_chip_given_up(dims):
+    F = gram_on_device(dims, 31)
+    got, chain = decompose_with(F, 256, 0), decompose_with(F, 0, 0)
+    assert len(dims) > 1 or all(torch.equal(a, b) for a, b in zip(got, chain))
+
+
+# a stream that may use few compute units (columns by the chain of launches until the rest fits), a device without launches of that kind, and
+# more workgroups than can be resident: the launch is refused, and the chain serves the call
+@pytest.mark.parametrize("workgroups", [0, 1, 5, 40, 64, 4096])
+def test_eig_reduction_on_part_of_the_chip(workgroups):
+    decompose_with(gram_on_device([1300, 700] + [1025] * (14 if workgroups > 256 else 1) + [90], 41), workgroups, 1 << 18)
+
+
+OTHER_PROCESS = """
+import sys
+sys.path[:0] = [{root!r}, {tests!r}]
+import torch
+from test_gpu_parity import decompose_on_device, gram_on_device
+F = gram_on_device([1300, 600], 51)
+print("ready", flush=True)
+for _ in range(40):
+    assert all(i[2] and i[0] == 1 for i in decompose_on_device(F)[2])
+print("done", flush=True)
+"""
+
+
+def test_eig_of_two_processes_at_once():
+    """The device serves launches that need all their workgroups at once to one process at a time and refuses them to others: these calls
+    get the chain of launches."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = OTHER_PROCESS.format(root=root, tests=os.path.join(root, "tests"))
+    other = subprocess.Popen([sys.executable, "-c", code], stdout=subprocess.PIPE, text=True)
+    try:
+        assert other.stdout.readline() == "ready\n"
+        F = gram_on_device([1300, 600], 52)
+        while other.poll() is None:
+            assert all(i[2] and i[0] == 1 for i in decompose_on_device(F)[2])
+        assert other.wait() == 0 and other.stdout.read() == "done\n"
+    finally:
+        other.kill()
+        other.wait()
 
 
 def test_eig_reductions_of_two_threads_at_once():
