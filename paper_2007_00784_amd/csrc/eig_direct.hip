@@ -1791,17 +1791,25 @@ size_t kfac_eig_direct_ws_bytes(int batch, const int *d) {
     return need;
 }
 
-// What a call takes, in seconds: the chain of the widest factor's columns, and the arithmetic of all of them.  Within 10 % of calls of one
-// factor 577 to 4609 wide (2.5 to 30 ms), twenty of 577, six of 2305, three of 4609 and ResNet-50's 108; 13 % below seventeen of 1024 to 1153.
-double kfac_eig_direct_seconds(int batch, const int *d) {
-    int nmax = 0;
-    double n3 = 0.0;
+// What a call takes, in seconds: the widest factor's columns one after another, the arithmetic of all of them, and what columns by the
+// chain of launches take on top, by their number and the bytes of the trailing matrices.  Measured, and by this: one factor of ReLU features
+// 577 wide 2.50 ms, 2.58, 1153 5.28, 5.03, 2305 11.1, 11.1, 4609 31.1, 33.0, 6145 71.5, 73.6, 8192 156.8, 156.6; seventeen of 1100 8.9, 8.0, six of 2305 21.1,
+// 20.3, three of 4609 62.5, 62.4, ResNet-50's 108 87.1, 86.1; without cooperative launches 1153 11.7, 10.3, 4609 58.5, 59.2, 8192 187.3, 182.9.  Factors
+// whose eigenvectors are corrected take 4 to 12 % more, which only the decomposition shows.
+double kfac_eig_direct_seconds(int capacity, int batch, const int *d) {
+    const int widest = chip_widest(capacity);
+    int nmax = 0, chain = 0;
+    double n3 = 0.0, chain3 = 0.0;
     for (int i = 0; i < batch; ++i) {
+        const double cube = (double)d[i] * d[i] * d[i];
         nmax = std::max(nmax, d[i]);
-        n3 += (double)d[i] * d[i] * d[i];
+        n3 += cube;
+        if (d[i] <= TD_SMALL || d[i] <= widest) continue;
+        chain = std::max(chain, d[i] - widest);
+        chain3 += cube - (double)widest * widest * widest;
     }
     if (nmax == 0) return 0.0;
-    return (nmax > TD_SMALL ? 300e-6 + 3.9e-6 * nmax : 60e-6 + 4.6e-6 * nmax) + 1.5e-13 * n3;
+    return (nmax > TD_SMALL ? 300e-6 + 3.9e-6 * nmax : 60e-6 + 4.6e-6 * nmax) + 1.5e-13 * n3 + 4.5e-6 * chain + 5.7e-14 * chain3;
 }
 
 // All factors of the call by the direct route; stat (pinned host memory): four doubles per factor, off^2 and diag^2 of F, the

@@ -229,14 +229,14 @@ std::vector<int> choose_sweeps(kfac_ctx *ctx, int batch, const int *d, const std
     }
     std::sort(levels.begin(), levels.end());
     levels.erase(std::unique(levels.begin(), levels.end()), levels.end());
-    double least = worth * kfac_eig_direct_seconds(batch, d);
+    double least = worth * kfac_eig_direct_seconds(ctx->coop_wgs, batch, d);
     for (int level : levels) {
         std::vector<int> which, dj, sj, dd;
         for (int i = 0; i < batch; ++i) {
             if (need[i] <= level) { which.push_back(i); dj.push_back(d[i]); sj.push_back(need[i]); }
             else dd.push_back(d[i]);
         }
-        const double t = kfac_eig_jacobi_seconds((int)dj.size(), dj.data(), sj.data()) + kfac_eig_direct_seconds((int)dd.size(), dd.data());
+        const double t = kfac_eig_jacobi_seconds((int)dj.size(), dj.data(), sj.data()) + kfac_eig_direct_seconds(ctx->coop_wgs, (int)dd.size(), dd.data());
         if (t < least && kfac_eig_jacobi_ws_bytes((int)dj.size(), dj.data()) <= ctx->ws_bytes) {
             least = t;
             best = which;

@@ -136,7 +136,7 @@ size_t kfac_eig_jacobi_ws_bytes(int batch, const int *d);
 double kfac_eig_jacobi_seconds(int batch, const int *d, const int *sweeps);
 int kfac_launch_eig_jacobi(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
                            const kfac_eig_opts *opts, kfac_eig_info *info);
-double kfac_eig_direct_seconds(int batch, const int *d);
+double kfac_eig_direct_seconds(int capacity /* kfac_ctx::coop_wgs */, int batch, const int *d);
 int kfac_launch_eig_direct(kfac_ctx *ctx, int batch, const float *const *F, const int *d, float *const *Q, float *const *lam,
                            double diag_tol, double *stat /* pinned, 4 per factor */, const std::function<bool()> *go_on);
 constexpr int KFAC_EIG_STOPPED = 1;  // its result if go_on() said no

@@ -400,6 +400,23 @@ def test_eig_start_basis_moved_a_little_and_more(ctx, n, moved, sweeps):
     check_eigpairs(F, lam[0].cpu().numpy(), Q[0].cpu().numpy(), "moved")
 
 
+def test_eig_start_basis_where_columns_go_by_the_chain():
+    """Where the chain of launches reduces a factor (a device without cooperative launches, columns past what fits the chip), four sweeps from
+    the eigenvectors of a factor that moved by 5 % are cheaper than a decomposition: 7.6 ms, 11.7."""
+    n = 1153
+    F0, F1 = gram_factor(n, 2 * n, seed=n), gram_factor(n, 2 * n, seed=n + 1)
+    F = (0.95 * F0 + 0.05 * F1).astype(np.float32)
+    for workgroups, sweeps in ((256, 1), (0, 4)):
+        c = Ctx(K.kfac_eig_workspace_bytes([n]) + 4096)
+        K.lib().kfac_limit_chip(c.h, workgroups, 1 << 18)
+        _, Q, _ = c.eig([F0])
+        lam = [torch.empty(n, device="cuda")]
+        info = K.kfac_eig(c.h, [torch.from_numpy(F).cuda()], Q, lam, warm_start=True)
+        c.close()
+        assert info[0][2] and info[0][0] == sweeps, (workgroups, info)
+        check_eigpairs(F, lam[0].cpu().numpy(), Q[0].cpu().numpy(), "by the chain")
+
+
 @pytest.mark.parametrize("n", [577, 1153])
 def test_eig_loose_tolerance_takes_few_sweeps(ctx, n):
     """To 1e-2 a few sweeps are cheaper than a decomposition; a cap on them that is too low for that does not stand in its way."""
