@@ -302,21 +302,22 @@ void plan_item(int n, const kfac_factor_item &it, int shift, int &ntri, int &nsp
 
 // A batch with fewer jobs than this: half the slabs per job, and again, down to a sixteenth.  Two jobs share a compute unit, so 512 run at
 // a time; with few jobs per slot the last round is mostly empty, and whole tiles wait beside edge tiles that are done in a quarter
-// of their time.  But a job's partial sums are 64 KB out and in again, as much as four of its slabs: two halvings for MIN_JOBS (bf16, whose
-// jobs are three times as fast: none), more only for MIN_JOBS_SHORT.  us, at the start of it (256 jobs in all cases), with 1024, 2048, 4096 and
+// of their time.  But a job's partial sums are 64 KB out and in again, as much as four of its slabs: two halvings for MIN_JOBS, more only for
+// MIN_JOBS_SHORT.  Jobs of the bf16 engine (form 4), which are three times as fast and gain nothing beyond MIN_JOBS_SHORT of them,
+// count four times, wherever in the list they stand.  us, at the start of it (256 jobs in all cases), with 1024, 2048, 4096 and
 // with 4096 down to a sixteenth: the ResNet-32 step 5880, 5870, 5330, 5228, 5270; fp32 factors of thirty convolutions 8 to 56 wide 1717, 1378, 1193,
 // 1195, 1150, of eighteen blocks up to 928 1055, 1056, 1053, 887, 934, of one layer 4608 and 512 1075, 930, 930, 929, 1011; bf16 ones of eight
 // blocks 17 to 136 wide 442, 244, 244, 248, 281, of seven blocks 53 to 424 798, 802, 803, 801, 871.
 constexpr int MIN_JOBS = 4096, MIN_JOBS_SHORT = 1024, MAX_SHIFT = 4;
 int plan_shift(int n, const kfac_factor_item *items) {
     for (int shift = 0; shift < MAX_SHIFT && n > 1; ++shift) {
-        int64_t jobs = 0;
+        int64_t jobs = 0, fast = 0;
         for (int i = 0; i < n; ++i) {
             int ntri, nsplit, kchunk;
             plan_item(n, items[i], shift, ntri, nsplit, kchunk);
-            jobs += (int64_t)ntri * nsplit;
+            (form_of(items[i]) == 4 ? fast : jobs) += (int64_t)ntri * nsplit;
         }
-        if (jobs >= (form_of(items[0]) == 4 || shift >= 2 ? MIN_JOBS_SHORT : MIN_JOBS)) return shift;
+        if (jobs + fast * (MIN_JOBS / MIN_JOBS_SHORT) >= MIN_JOBS || (shift >= 2 && jobs + fast >= MIN_JOBS_SHORT)) return shift;
     }
     return n > 1 ? MAX_SHIFT : 0;
 }

@@ -73,3 +73,18 @@ def test_eig_workspace_of_many_small_factors():
         one = K.kfac_eig_workspace_bytes([n])
         assert one <= 16 * (n + 16) ** 2 + 1700 * n + 8192, (n, one)
         assert K.kfac_eig_workspace_bytes([n] * 1000) <= 1000 * one
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_factor_workspace_does_not_depend_on_the_order_of_the_list(bf16):
+    """Nor does the plan: convolutions and a Linear layer as backward hooks deliver them (last layer first) and as the forward pass does, and
+    convolutions of both types in one list."""
+    dtype = K.KFAC_BF16 if bf16 else K.KFAC_F32
+    conv = lambda d, T, t=dtype: dict(X=None, dtype=t, layout=K.KFAC_LAYOUT_NDT, N=32, d=d, T=T, append_ones=1, F=None)
+    fc = dict(X=None, dtype=dtype, layout=K.KFAC_LAYOUT_RD, N=32, d=2048, T=1, append_ones=1, F=None)
+    convs = [conv(64, 3136), conv(576, 3136), conv(256, 3136), conv(1152, 784), conv(512, 784), conv(2304, 196), conv(4608, 49)]
+    for items in (convs + [fc], convs[:2] + [conv(128, 784, K.KFAC_F32), conv(128, 784, K.KFAC_BF16)] + convs[2:] + [fc]):
+        want = K.kfac_update_factors_workspace_bytes(items)
+        for k in range(len(items)):
+            assert K.kfac_update_factors_workspace_bytes(items[k:] + items[:k]) == want
+            assert K.kfac_update_factors_workspace_bytes((items[k:] + items[:k])[::-1]) == want
