@@ -314,11 +314,7 @@ size_t count_tiles(int n, const kfac_precond_item *it, int edge) {
 // twenty up to 280 x 496 (249) 605 and 321, one 2400 x 2401 (361) 1449 and 1213, one 2700 x 2501 (440) 1539 and 1707, seven of 1000 x 1001
 // (448) 660 and 719, three up to 2048 (680) 1900 and 2050.
 constexpr size_t SMALL_MAX = 384;
-int tile_edge(int n, const kfac_precond_item *it) {
-    for (int i = 0; i < n; ++i)
-        if (it[i].split_f16) return BM;
-    return count_tiles(n, it, BM) <= SMALL_MAX ? SMALL_EDGE : BM;
-}
+int tile_edge(int n, const kfac_precond_item *it) { return count_tiles(n, it, BM) <= SMALL_MAX ? SMALL_EDGE : BM; }
 
 size_t layout(int n, const kfac_precond_item *it, int edge, size_t &off_tiles, size_t &off_tv, size_t &ntiles) {
     ntiles = count_tiles(n, it, edge);
@@ -336,14 +332,14 @@ size_t layout(int n, const kfac_precond_item *it, int edge, size_t &off_tiles, s
 }  // namespace
 
 size_t kfac_precond_ws_bytes_impl(int n, const kfac_precond_item *items) {
-    size_t a, b, c;
+    size_t a, b, c;      // (of the fp32 chain's tiles: those of the split chain are never smaller, and the caller need not say yet which it is)
     return layout(n, items, tile_edge(n, items), a, b, c);
 }
 
 int kfac_launch_precondition_batched(kfac_ctx *ctx, int n, const kfac_precond_item *items, bool scaled, float kappa, float lr,
                                      float *nu) {
     size_t off_tiles, off_tv, ntiles;
-    int edge = tile_edge(n, items);
+    int edge = std::any_of(items, items + n, [](const kfac_precond_item &it) { return it.split_f16 != 0; }) ? BM : tile_edge(n, items);
     if (layout(n, items, edge, off_tiles, off_tv, ntiles) > ctx->ws_bytes) {      // (the tables of small tiles are a little longer)
         edge = BM;
         if (layout(n, items, edge, off_tiles, off_tv, ntiles) > ctx->ws_bytes) return KFAC_EWORKSPACE;

@@ -88,3 +88,16 @@ def test_factor_workspace_does_not_depend_on_the_order_of_the_list(bf16):
         for k in range(len(items)):
             assert K.kfac_update_factors_workspace_bytes(items[k:] + items[:k]) == want
             assert K.kfac_update_factors_workspace_bytes((items[k:] + items[:k])[::-1]) == want
+
+
+def test_precondition_workspace_follows_from_the_dimensions():
+    """kfac_precondition_workspace_bytes() reads dA and dG only: whatever stands in the other fields, the answer is the same."""
+    for dims in ([(145, 16)], [(1153, 128), (577, 64)], [(2401, 2400)], [(4609, 512)] * 8):
+        arr = (K.kfac_precond_item * len(dims))()
+        for j, (dA, dG) in enumerate(dims):
+            arr[j].dA, arr[j].dG = dA, dG
+        want = K.kfac_precondition_workspace_bytes(dims)
+        for split, dtype in ((1, 0), (0x55555555, -1)):
+            arr[-1].split_f16 = arr[-1].factored_damping = split
+            arr[-1].grad_dtype = dtype
+            assert K.lib().kfac_precondition_workspace_bytes(len(dims), arr) == want, dims
