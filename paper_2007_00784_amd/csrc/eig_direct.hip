@@ -88,9 +88,10 @@ struct DirMat {
     int *perm;       // [np]: final order of the eigenvectors
     int *ord;        // [np]: row of F that became row i of A (diagonal descending)
     double diag_tol2;   // a factor up to TD_SMALL wide with off^2 <= this ||F||^2 is diagonal as it stands (wider ones: see go_on)
-    int n, np, ld, nb, off, split;
-    int chain;          // columns that the chain of launches reduces, before the matrix fits the chip
+    int n, np, ld, nb, off;
+    short split, chain; // chain: columns that the chain of launches reduces, before the matrix fits the chip
 };
+static_assert(sizeof(DirMat) == 240, "part of every workspace: no larger, or one that a caller has sized for a direct decomposition does not hold it");
 
 // Nothing to reduce: the eigenvectors are unit vectors.  (An identity or another diagonal factor: 64 wide 103 us in place of 267, 145 wide
 // 156 in place of 626.)
@@ -1521,8 +1522,8 @@ void dir_tables(DirPlan &P, int capacity) {
     P.lead = nm ? order[0] : 0;
     const int widest = chip_widest(capacity);      // as many columns by the chain of launches as it takes to fit the chip
     for (auto &M : P.mats) {
-        M.chain = M.n > TD_SMALL && M.n > widest ? (M.n - widest + NB - 1) / NB * NB : 0;
-        P.steps = std::max(P.steps, M.chain);
+        M.chain = (short)(M.n > TD_SMALL && M.n > widest ? (M.n - widest + NB - 1) / NB * NB : 0);
+        P.steps = std::max<int>(P.steps, M.chain);
     }
     for (auto &M : P.mats) M.off = P.steps - M.chain;
     if (P.steps > 0) {

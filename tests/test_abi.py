@@ -75,6 +75,13 @@ def test_eig_workspace_of_many_small_factors():
         assert K.kfac_eig_workspace_bytes([n] * 1000) <= 1000 * one
 
 
+def test_eig_workspace_that_was_sized_before_still_holds_a_direct_decomposition():
+    """A program may keep the size of its workspace, and a call that is 256 bytes short is served by Jacobi sweeps, several times slower: the
+    sizes as they were when the direct decomposition came (lists where a few bytes more in a factor's descriptor showed)."""
+    assert K.kfac_eig_workspace_bytes([577, 64] * 9) <= 79068416
+    assert K.kfac_eig_workspace_bytes([4, 52, 9, 4, 118, 71, 16, 1, 16, 9, 94, 5, 1, 1915, 15, 46, 2, 95, 1, 886, 98, 116, 71, 8, 1, 242, 13, 288, 239, 71]) <= 91162368
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 def test_factor_workspace_does_not_depend_on_the_order_of_the_list(bf16):
     """Nor does the plan: convolutions and a Linear layer as backward hooks deliver them (last layer first) and as the forward pass does, and
