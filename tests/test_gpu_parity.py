@@ -1011,6 +1011,42 @@ def test_precondition_batched_with_gradient_scaling(ctx, bf16, split):
         K.kfac_precondition_batched_scaled(ctx.h, QAs, lAs, QGs, lGs, gamma, gd, 0.0, lr, nu_d)
 
 
+def test_gradient_scaling_of_many_layers_and_tiles():
+    """More layers and tiles than one round of the sum's waves and lanes: nu against the fp64 sum over the unscaled results (own rounding 2^-24, that of
+    the results' storage averages out below it), the same in every call.  The sum must not take long beside the products: one tile
+    after another it took 47 us for the twenty layers here."""
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    R = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    for sizes in ([(1, 1)], [(65 + 9 * i, 40 + 7 * i) for i in range(33)] + [(1100, 1000)], [(496, 280)] * 20, [(2049, 2048)]):
+        args = [R(a, a) / a ** 0.5 for a, _ in sizes], [R(a).abs() for a, _ in sizes], [R(g, g) / g ** 0.5 for _, g in sizes], [R(g).abs() for _, g in sizes], 0.1
+        grads = [R(g, a) for a, g in sizes]
+        c = Ctx(K.kfac_precondition_workspace_bytes(sizes))
+        plain, nu = [g.clone() for g in grads], torch.empty(1, device="cuda")
+        K.kfac_precondition_batched(c.h, *args, plain)
+        total = sum(abs(float((p.double() * g.double()).sum())) for p, g in zip(plain, grads))
+        for _ in range(2):
+            got = [g.clone() for g in grads]
+            K.kfac_precondition_batched_scaled(c.h, *args, got, kappa=1e-4 * total, lr=0.1, nu=nu)
+            assert abs(float(nu) - 0.1) <= 2e-7, (len(sizes), float(nu))
+            assert all(torch.equal(x, p * nu) for x, p in zip(got, plain))
+
+        def us(scaled):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(10):
+                if scaled:
+                    K.kfac_precondition_batched_scaled(c.h, *args, plain, kappa=1e30, lr=0.1, nu=nu)
+                else:
+                    K.kfac_precondition_batched(c.h, *args, plain)
+            e1.record()
+            torch.cuda.synchronize()
+            return e0.elapsed_time(e1) * 100
+        if len(sizes) == 20:
+            with_nu, without = min(us(True) for _ in range(5)), min(us(False) for _ in range(5))
+            assert with_nu <= without + 30, (sizes[0], with_nu, without)
+        c.close()
+
+
 @pytest.mark.parametrize("dA,dG", [(145, 16), (300, 130), (577, 64), (230, 100)])
 def test_explicit_inverse_method_matches_cholesky_oracle(ctx, dA, dG):
     """Sec. II-C, Eq. (kfac-damped): (G + gamma I)^-1 grad (A + gamma I)^-1.  The library forms it in the eigenbasis
