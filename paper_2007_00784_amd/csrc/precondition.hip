@@ -54,7 +54,7 @@ __device__ inline void run_tile(OpA a, OpB b, int i0, int j0, int K, int M, int 
     gemm_tile_small(a, b, i0, j0, K, M, N, sm, epi);
 }
 
-// SMALL: tiles of 64 x 64, whose contraction the four waves share, for calls with few tiles (SMALL_MAX).
+// SMALL: tiles of 64 x 64, whose contraction the four waves share, for calls with few tiles (tile_edge).
 template <int STAGE, bool SMALL>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void precond_stage_kernel(const LayerDev *layers, const TileRef *tiles,
                                                                                                        double *dots) {
@@ -320,12 +320,29 @@ size_t count_tiles(int n, const kfac_precond_item *it, int edge) {
     return t;
 }
 
-// Up to this many tiles of 128 small ones are faster: with one tile or little more for a compute unit its four waves wait for every slab.
-// Whole chains in us, tiles of 128 and small ones: one layer 3025 x 314 (72 tiles) 607 and 220, twelve layers up to 127 x 248 (60) 320 and 137,
-// twenty up to 280 x 496 (249) 605 and 321, one 2400 x 2401 (361) 1449 and 1213, one 2700 x 2501 (440) 1539 and 1707, seven of 1000 x 1001
-// (448) 660 and 719, three up to 2048 (680) 1900 and 2050.
-constexpr size_t SMALL_MAX = 384;
-int tile_edge(int n, const kfac_precond_item *it) { return count_tiles(n, it, BM) <= SMALL_MAX ? SMALL_EDGE : BM; }
+// Calls with few tiles of 128 are faster in small ones: with one tile or little more for a compute unit its four waves wait for every slab,
+// and four times the tiles fill more of the chip.  A call's small tiles take time by their number, those of its longest contraction counted whole
+// (`load`); tiles of 128 take one round of the chip up to 256 and 1.6 times that in the second.  So small ones are taken up to a load of 720 in
+// the first round and to 1500 in the second, less with short contractions, where the second round of large ones costs less.
+// us, tiles of 128 and small ones, equal layers: 6, 12 and 24 of 1153 x 128 257 115, 260 168, 271 344 (load 912); 2 and 3 of 1024 381 217, 384 327
+// (768); 2 of 1280 475 487 (800); 26 of 384 177 213 (936).  Second round: 3 of 1280 765 619 (1200); 5 of 1025 x 1024 634 595 (1360), one of
+// 2400 x 2401 1434 1261 (1444), 19 of 513 x 512 348 368 (1368), 31 of 385 x 384 280 312 (1302), 33 of 384 272 265 (1188), 60 and 75 of 256 139 180,
+// 203 216 (960, 1200).  One layer of 3025 x 314 603 230.  Over 239 calls with up to 384 tiles, equal layers and mixed, this is 1.1 % slower than the
+// better one each time would be (17 % at the worst, 120 layers of 147 x 64), small ones throughout 2.9 % (30 %), tiles of 128 throughout 27 %.
+constexpr int SMALL_LOAD = 720, SMALL_LOAD_SECOND = 1250, SMALL_LOAD_SECOND_LONG = 1500, SMALL_SHORT = 512, SMALL_LONG = 1050;
+constexpr size_t SMALL_MAX = 384, ROUND = 256;
+int tile_edge(int n, const kfac_precond_item *it) {
+    const size_t tiles = count_tiles(n, it, BM);
+    if (tiles > SMALL_MAX) return BM;
+    int longest = 1;
+    double load = 0.0;
+    for (int i = 0; i < n; ++i) {
+        longest = std::max(longest, it[i].dA + it[i].dG);
+        load += (double)count_tiles(1, it + i, SMALL_EDGE) * (it[i].dA + it[i].dG);
+    }
+    const int most = tiles <= ROUND || longest <= SMALL_SHORT ? SMALL_LOAD : longest <= SMALL_LONG ? SMALL_LOAD_SECOND : SMALL_LOAD_SECOND_LONG;
+    return load <= (double)most * longest ? SMALL_EDGE : BM;
+}
 
 size_t layout(int n, const kfac_precond_item *it, int edge, size_t &off_tiles, size_t &off_tv, size_t &ntiles) {
     ntiles = count_tiles(n, it, edge);

@@ -108,3 +108,14 @@ def test_precondition_workspace_follows_from_the_dimensions():
             arr[-1].split_f16 = arr[-1].factored_damping = split
             arr[-1].grad_dtype = dtype
             assert K.lib().kfac_precondition_workspace_bytes(len(dims), arr) == want, dims
+
+
+@pytest.mark.parametrize("n,dA,dG,edge", [(1, 145, 16, 64), (1, 3025, 314, 64), (12, 1153, 128, 64), (24, 1153, 128, 128), (26, 384, 384, 128), (20, 496, 280, 128),
+                                          (2, 1024, 1024, 64), (3, 1280, 1280, 64), (60, 256, 256, 128), (75, 256, 256, 128), (1, 2401, 2400, 64), (440, 100, 100, 128)])
+def test_preconditioning_takes_small_tiles_where_they_are_faster(n, dA, dG, edge):
+    """The tables in the workspace have 32 bytes a tile (up to three roundings to 256 of them); with one layer 1 x 1 in the place of each there is one tile each."""
+    elements = lambda a, g: 8 * n * ((a * g + 63) // 64 * 64)
+    tables = K.kfac_precondition_workspace_bytes([(dA, dG)] * n) - elements(dA, dG)
+    ones = K.kfac_precondition_workspace_bytes([(1, 1)] * n) - elements(1, 1)
+    tiles = n * ((dA + edge - 1) // edge) * ((dG + edge - 1) // edge)
+    assert abs(tables - ones - 32 * (tiles - n)) <= 768, (tables, ones, tiles)
