@@ -64,7 +64,7 @@ typedef struct {
     float tol;               /* stop when off(F)_F <= tol * ||F||_F (<=0: 2e-6).  From 1e-6 on the factors are
                                 decomposed directly (Householder reduction, fp64 tridiagonal eigenproblem), to fp32
                                 rounding, except where a few Jacobi sweeps meet tol sooner (a factor that is diagonal
-                                or nearly so, a loose tol); a smaller tol, or a factor whose direct result misses tol,
+                                or nearly so, a very loose tol); a smaller tol, or a factor whose direct result misses tol,
                                 asks for Jacobi sweeps until the rotated matrix meets it.          */
     int fp32_only;           /* 0 (default): errors bounded normwise (relative to ||F||_F); for d >= 2048 the
                                 orthogonalisation products (and, in Jacobi sweeps, the rank-256 update passes) run as

@@ -6,7 +6,7 @@
 // decomposition takes 30), four and more after a running average moved by 5 % (88 ms).  So with a start basis, that distance is
 // estimated first (probe kernels below: 18 us at 145, 64 at 2100, and a wait), and the sweeps take the factors with which the call is cheaper.  Without one, it
 // is off(F)_F, which the direct route forms anyway: running averages that are still diagonal need no sweep (0.55 ms at 577, 1.4 at
-// 2100, in place of 2.4 and 9.3), and a loose tol needs few.
+// 2100, in place of 2.4 and 9.3), and a very loose tol needs few.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -209,16 +209,11 @@ struct EigPart {
     }
 };
 
-// Without a start basis, a tolerance from LOOSE_TOL up is served by sweeps as long as they take less than LOOSE_WORTH times the direct
-// decomposition: who asks for so little sees in info how few sweeps it took, and 1e-2 at 577 takes 3.6 ms this way (2.4 directly).
-constexpr double LOOSE_TOL = 1e-3;
-constexpr double LOOSE_WORTH = 1.8;
-
 // The factors (wider than KFAC_EIG_SMALL: the others gain nothing from a start) to iterate rather than to decompose directly, given
 // the bases they would start from.  Those that need the fewest sweeps first, as many as make the call
 // cheapest, if that is cheaper than all of them directly by the 5 % that the two estimates are good for: a chain of launches is
 // shared by all factors of its kind.
-std::vector<int> choose_sweeps(kfac_ctx *ctx, int batch, const int *d, const std::vector<StartBasis> &start, double tol, int max_sweeps, double worth = 0.95) {
+std::vector<int> choose_sweeps(kfac_ctx *ctx, int batch, const int *d, const std::vector<StartBasis> &start, double tol, int max_sweeps) {
     std::vector<int> need(batch, INT_MAX), levels, best;
     for (int i = 0; i < batch; ++i) {
         if (d[i] <= KFAC_EIG_SMALL || !(start[i].rel >= 0.0)) continue;
@@ -229,7 +224,7 @@ std::vector<int> choose_sweeps(kfac_ctx *ctx, int batch, const int *d, const std
     }
     std::sort(levels.begin(), levels.end());
     levels.erase(std::unique(levels.begin(), levels.end()), levels.end());
-    double least = worth * kfac_eig_direct_seconds(ctx->coop_wgs, batch, d);
+    double least = 0.95 * kfac_eig_direct_seconds(ctx->coop_wgs, batch, d);
     for (int level : levels) {
         std::vector<int> which, dj, sj, dd;
         for (int i = 0; i < batch; ++i) {
@@ -311,8 +306,7 @@ int kfac_launch_eig(kfac_ctx *ctx, int batch, const float *const *F, const int *
             start[i].rel = f2 > 0.0 && f2 < 1e300 ? std::sqrt(off2 / f2) : (f2 == 0.0 ? 0.0 : -1.0);
             start[i].lost = start[i].rel > 1e-2 ? 1.0 : 0.0;
         }
-        if (tol >= LOOSE_TOL) sweep = choose_sweeps(ctx, batch, d, start, tol, max_sweeps, LOOSE_WORTH);
-        else sweep = choose_sweeps(ctx, batch, d, start, tol, max_sweeps);
+        sweep = choose_sweeps(ctx, batch, d, start, tol, max_sweeps);
         return sweep.empty();
     };
     if (!decided) {
