@@ -140,7 +140,9 @@ int kfac_update_factors(kfac_ctx *ctx, const void *X, int dtype, int layout, int
 /* The same update for a batch of factors in as few launches as there are operand forms (layout x dtype):
  * every factor is cut into jobs of similar length that fill the machine together, so small layers cost
  * no launch of their own.  items: host array; fields as the arguments of kfac_update_factors.  The
- * factors of one call must be distinct.  Workspace: kfac_update_factors_workspace_bytes().  */
+ * factors of one call must be distinct.  Workspace: kfac_update_factors_workspace_bytes(), what the fastest plan takes: 64.5 KB of
+ * partial sums per job, 291 MB for ResNet-32's 62 fp32 factors at batch 128, whose jobs have to be short to fill the machine.  With
+ * less the jobs are longer, as long as it takes (a sixteenth of the jobs at the least; KFAC_EWORKSPACE below that).  */
 typedef struct {
     const void *X;
     int dtype, layout;

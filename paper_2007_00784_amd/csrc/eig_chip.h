@@ -18,10 +18,12 @@
 //    that somebody still looks for).  The s_waitcnt before a publication orders it after what its wave has emptied.  Loads and stores
 //    are relaxed agent-scope atomics of 8 bytes.
 //  - Polling too early costs more than it gains (the line is fetched empty, and the writer has to take it away again): measured between
-//    256 workgroups, 4608 words: 3.0 us a column polling at once, 2.3 after a pause of 1024 cycles; 64 workgroups: 2.3 and 1.5.
+//    256 workgroups, 4608 words: 3.0 us a column polling at once, 2.3 after a pause of 1024 cycles; 64 workgroups: 2.3 and 1.5.  In the
+//    reduction the workgroups have something to do meanwhile; pauses of 0, 2, 6, 12 and 16 times 64 cycles, whole decompositions in ms: one factor
+//    of 577 2.72, 2.68, 2.65, 2.71, 2.77, of 2305 12.4, 12.2, 11.6, 11.9, 12.1, three of 4609 72.7, 72.1, 70.0, 69.5, 70.3.
 //
-// Measured (whole decompositions): one factor 577 wide 5.2 -> 2.6 ms, 2049 19.3 -> 10.1, 4609 57.6 -> 32.1; three of 4609 62.5, twenty of 577
-// 3.4.  A column of a 4609-wide factor takes 4.3 us after a quarter of them (1.4 of it the exchange) and 2.2 at its end, where the chain of
+// Measured (whole decompositions, ms, the chain of launches and this): one factor 577 wide 5.2 and 2.5, 2049 19.3 and 10.1, 4609 57.6 and 31.1;
+// three of 4609 62.5, twenty of 577 3.5.  A column of a 4609-wide factor takes 4.3 us after a quarter of them (1.4 of it the exchange) and 2.2 at its end, where the chain of
 // launches took 13 and 7.  Also measured, and worse: shares of x^T A x among the words, so that nobody has to sum over its waves (a barrier less,
 // but every wave looks at up to 262 words more: 577 2.6 -> 3.0 ms, 4609 32.9 -> 37.0); tags beside the values in place of EMPTY (twice the words);
 // a flag per workgroup and plain loads after it.
@@ -36,14 +38,21 @@
 constexpr int CHIP_SLOTS = 9;
 constexpr int CHIP_WIDE = 512, CHIP_NARROW = 256;         // threads of a workgroup
 constexpr int CHIP_NARROW_SLOTS = 8;                      // nine would not leave the registers for anything else
-constexpr int CHIP_CROWD = 16;                            // rows of a wide workgroup from which narrow ones, two to a compute unit, are the better choice
+// Columns of a factor that count as one workgroup of a crowd: where the factors of a call are one (more of them than compute units), narrow
+// workgroups, two to a compute unit, hide each other's exchange.  ms with 4, 16, 32, and without any narrow ones: thirty factors of 1100 14.0, 14.0, 14.0,
+// 16.0, twenty of 577 3.54, 3.53, 3.52, 3.66, nine 3.01, 3.01, 3.08, 3.10, sixty of ResNet-32's widths 3.73, 3.73, 3.91, 3.82; the price is fifty of 300, 2.44, 2.42, 2.39, 2.16.
+constexpr int CHIP_CROWD = 16;
 constexpr int CHIP_MAX_N = CHIP_WIDE * CHIP_SLOTS + 1;    // the widest factor: its first column is never part of the trailing matrix
 constexpr int CHIP_ROWS = 64;                             // rows of a workgroup, at most: the lanes of the wave that publishes
-constexpr int CHIP_ROWS_MIN = 8;                          // a workgroup with fewer saves less than one more in the exchange costs
+// A workgroup with fewer rows saves less than one more in the exchange costs.  ms with at least 4, 8, 12, 24 rows: one factor of 577 2.66, 2.65, 2.67, 2.84,
+// of 2305 11.6, 11.6, 12.2, 12.9, fifty of 300 2.52, 2.42, 2.55, 2.53.
+constexpr int CHIP_ROWS_MIN = 8;
 constexpr int CHIP_WGS = 256;                             // workgroups of a factor, at most
 constexpr int CHIP_JOBS = 64;                             // factors of a launch, at most: a workgroup finds its own by one ballot
 constexpr int CHIP_PAUSE = 6;                             // of 64 cycles, before the first look at the others' words
-constexpr int CHIP_WHOLE = 640, CHIP_STEPS_MIN = 96;      // up to here a factor goes in one launch; the fewest columns of a launch otherwise
+// Up to CHIP_WHOLE columns a factor goes in one launch; the fewest columns of a launch otherwise.  ms up to 256, 400, 640, 900, 1300: one factor of 577 2.88, 2.71,
+// 2.65, 2.65, 2.65, of 1153 5.78, 5.58, 5.54, 5.32, 5.06, sixty of ResNet-32's widths 4.24, 4.04, 3.73, 3.72, 3.72, thirty of 1100 14.9, 14.7, 14.0, 13.9, 18.9.
+constexpr int CHIP_WHOLE = 640, CHIP_STEPS_MIN = 96;
 constexpr int CHIP_LOOK = 256;                            // polls between two looks at whether the call has been given up
 
 // Rows that a workgroup of S column slots can hold, in groups of four (the rows of a matrix instruction; two rows of the nine-slot kind
@@ -404,7 +413,9 @@ inline void chip_plan(std::vector<ChipFactor> left, int cus, std::vector<ChipJob
         int crowd = 0;
         for (const ChipFactor &f : left) crowd += (size(f) + CHIP_CROWD - 1) / CHIP_CROWD;
         const int threads = crowd > cus && widest <= CHIP_NARROW * CHIP_NARROW_SLOTS ? CHIP_NARROW : CHIP_WIDE;
-        // dealing a matrix out anew costs its bytes and a launch, some 50 us for the widest: a sixth of its columns take 40 times that
+        // dealing a matrix out anew costs its bytes and a launch, some 50 us for the widest; not doing it, workgroups that have run out of rows
+        // and factors that wait for their turn.  ms with a third, a quarter, a sixth, a twelfth of the columns: one factor of 1153 5.18, 5.28, 5.54, 5.73, of 4609 33.3, 33.2, 33.5,
+        // 34.4, thirty of 1100 14.9, 14.4, 14.0, 14.0, three of 4609 71.2, 70.8, 70.0, 69.6
         const int steps = widest <= CHIP_WHOLE ? widest : std::max(CHIP_STEPS_MIN, widest / 6);
         ChipLaunch L{(unsigned)jobs.size(), 0, 0, threads, 0.0, 0.0};
         int free = cus * (CHIP_WIDE / threads);

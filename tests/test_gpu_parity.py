@@ -657,8 +657,8 @@ def test_eig_by_sweeps_mixed_sizes_repeatable_and_beside_nan(ctx):
 
 
 def test_eig_direct_many_large_factors(ctx):
-    """Large and small factors in one call, launches beyond and below the tiles of a fused one: every result as good as
-    a single factor's, and complete when the call returns."""
+    """Large and small factors in one call, more than the chip holds at once, so that some wait until others have shrunk: every result as
+    good as a single factor's, and complete when the call returns."""
     dims = [2900, 1300, 2900, 100, 2900, 20, 2900, 2900, 300, 2900]
     gen = torch.Generator(device="cuda").manual_seed(5)
     F = []
@@ -699,9 +699,12 @@ def decompose_on_device(F):
 
 
 # the reduction on the chip: first and last matrix of every number of column slots (512 k wide, without the first column), the widest one, the
-# narrowest that begins with columns by the chain of launches, more factors than fit at once
+# narrowest that begins with columns by the chain of launches, more factors than fit at once; then the same edges of the narrow workgroups (256 k),
+# in calls that crowd the chip from the first launch on (a factor counts for a sixteenth of its columns; 256 and more are a crowd)
 @pytest.mark.parametrize("dims", [[257, 513], [514, 258], [1025, 1026], [1537, 1538], [2049, 2050], [2561, 2562], [3073, 3074], [3585, 3586], [4097, 4098],
-                                  [4609], [4610, 300], [1025] * 14 + [300] * 60])
+                                  [4609], [4610, 300], [1025] * 14 + [300] * 60,
+                                  [257, 258] * 10, [513, 514] * 5, [769, 770] * 3, [1025, 1026] * 3, [1281, 1282] * 2, [1537, 1538] * 2, [1793, 1794] * 2,
+                                  [2049] * 3 + [1000], [2050, 2049, 2049]])
 def test_eig_reduction_at_the_edges_of_its_column_slots(dims):
     F = gram_on_device(dims, 11)
     Q, lam, info = decompose_on_device(F)
