@@ -358,7 +358,9 @@ def main():
     roofline["kernel"] = dom
     roofline["traffic"] = measured_traffic(dom) if args.workload == "resnet50" else None
     roofline["timing"] = ("hipEvents around every launch of the class, over one instrumented step; the launches of a direct "
-                          "decomposition follow each other on one stream there as in the timed steps")
+                          "decomposition follow each other on one stream there as in the timed steps; a launch of the reduction on "
+                          "the chip does the work of eig_reduce_mv and eig_reduce_update, and its time and bytes are divided "
+                          "between them by their operations, not measured apart")
     roofline = {k: roofline[k] for k in ("kernel", "bound", "achieved", "peak", "unit", "frac", "traffic",
                                          "launches", "avg_ms", "total_ms", "algorithmic_bytes_per_launch", "algorithmic_tflops",
                                          "timing") if k in roofline}
