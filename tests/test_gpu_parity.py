@@ -789,6 +789,26 @@ def test_eig_reduction_on_part_of_the_chip(workgroups):
     decompose_with(gram_on_device([1300, 700] + [1025] * (14 if workgroups > 256 else 1) + [90], 41), workgroups, 1 << 18)
 
 
+def test_eig_columns_by_the_chain_do_not_wait_on_the_chip():
+    """6145 wide, a quarter of the columns go by the chain of launches and the rest on the chip: less than all of them by the chain (72 ms and 99;
+    with the chip's launches already queued behind the chain it was 122)."""
+    F = gram_on_device([6145], 71)
+    Q, lam, c = [torch.empty_like(F[0])], [torch.empty(6145, device="cuda")], Ctx(K.kfac_eig_workspace_bytes([6145]) + 4096)
+    took = []
+    for workgroups in (256, 0):
+        K.lib().kfac_limit_chip(c.h, workgroups, 1 << 18)
+        best = 1e9
+        for _ in range(3):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            info = K.kfac_eig(c.h, F, Q, lam)
+            best = min(best, time.perf_counter() - t)
+            assert info[0][2] and info[0][0] == 1, info
+        took.append(best)
+    c.close()
+    assert took[0] < 0.9 * took[1], took
+
+
 OTHER_PROCESS = """
 import sys
 sys.path[:0] = [{root!r}, {tests!r}]
