@@ -1968,7 +1968,8 @@ size_t kfac_eig_jacobi_ws_bytes(int batch, const int *d) {
 
 // What the sweeps of a call take, in seconds, if factor i (wider than KFAC_EIG_SMALL) needs sweeps[i] of them.  A round is bound by
 // launch latency until its products fill the machine; the groups share four streams and, where they overlap, the machine.  Fitted
-// to 40 calls of 1 to 53 factors from 150 to 4609 wide, 0.4 to 190 ms, with the sweeps they took: within 10 % of most.
+// to 40 calls of 1 to 53 factors from 150 to 4609 wide, 0.4 to 190 ms, with the sweeps they took: within 10 % of most.  (No sweeps: ten factors of
+// 257 0.54 ms, by this 0.56, fifty of 300 1.43, 1.46, sixty-five of 260 1.76, 1.74.)
 double kfac_eig_jacobi_seconds(int batch, const int *d, const int *sweeps) {
     std::vector<int> small;
     std::vector<GroupPlan> groups;
@@ -1984,7 +1985,7 @@ double kfac_eig_jacobi_seconds(int batch, const int *d, const int *sweeps) {
             s = std::max(s, sweeps[b]);
         }
         const double sweep = gp.two_level ? gp.splayers * (172e-6 + 4.0 * n2 * LDI / 160e12) : (gp.players - 1) * (40e-6 + 8.0 * n2 * EB / 70e12);
-        cost.push_back(s * sweep + 8.0 * n3 / 100e12 + 250e-6 + 30e-6 * gp.members.size());
+        cost.push_back(s * sweep + 8.0 * n3 / 100e12 + 250e-6 + 20e-6 * gp.members.size());
         sum += cost.back();
     }
     std::sort(cost.begin(), cost.end(), [](double a, double b) { return a > b; });

@@ -1795,25 +1795,45 @@ size_t kfac_eig_direct_ws_bytes(int batch, const int *d) {
     return need;
 }
 
-// What a call takes, in seconds: the widest factor's columns one after another, the arithmetic of all of them, and what columns by the
-// chain of launches take on top, by their number and the bytes of the trailing matrices.  Measured, and by this: one factor of ReLU features
-// 577 wide 2.50 ms, 2.58, 1153 5.28, 5.03, 2305 11.1, 11.1, 4609 31.1, 33.0, 6145 71.5, 73.6, 8192 156.8, 156.6; seventeen of 1100 8.9, 8.0, six of 2305 21.1,
-// 20.3, three of 4609 62.5, 62.4, ResNet-50's 108 87.1, 86.1; without cooperative launches 1153 11.7, 10.3, 4609 58.5, 59.2, 8192 187.3, 182.9.  Factors
-// whose eigenvectors are corrected take 4 to 12 % more, which only the decomposition shows.
+// What a call takes, in seconds:
+//  - the widest factor's columns one after another, and the arithmetic and the traffic of all factors;
+//  - the columns of the register kernels, which run before the chip, one width after another;
+//  - where the widest goes in one launch, the launches of those that find no place in the first (at most CHIP_JOBS factors, of narrow workgroups);
+//  - what columns by the chain of launches take on top, by their number and the bytes of the trailing matrices.
+// Measured, and by this, in ms: one factor of ReLU features 257 wide 1.18, 1.20, 577 2.50, 2.34, 1153 5.28, 5.09, 2100 9.96, 9.94, 4609 31.1, 31.6, 6145 71.5, 71.9,
+// 8192 156.9, 153.3; fifty of 300 1.89, 1.85, a hundred and thirty 4.61, 4.61, sixty-five of 257 2.39, 2.49, two hundred 5.62, 5.12, eighty of 577 8.16, 8.05,
+// forty of 1100 16.0, 14.7, six of 2305 21.0, 20.6; one of 257 beside twenty of 250 2.04, 1.94; without cooperative launches 1153 11.7, 10.4, 4609 58.5, 59.7.
+// Over 57 calls of 1 to 200 factors 5 % off, 13 at the most.  (Without the last three lines, and with the terms of the first alone, 29 % and 68: crowds of narrow
+// factors passed for cheap, and were decomposed where sweeps take half the time.)  Factors whose eigenvectors are corrected take 4 to 12 % more,
+// which only the decomposition shows.
 double kfac_eig_direct_seconds(int capacity, int batch, const int *d) {
-    const int widest = chip_widest(capacity);
-    int nmax = 0, chain = 0;
-    double n3 = 0.0, chain3 = 0.0;
+    const int widest = chip_widest(capacity), cus = std::min(capacity, CHIP_WGS);
+    int nmax = 0, chain = 0, narrow = 0, small[4] = {0, 0, 0, 0};
+    double n2 = 0.0, n3 = 0.0, chain3 = 0.0, launches = 0.0;
     for (int i = 0; i < batch; ++i) {
         const double cube = (double)d[i] * d[i] * d[i];
         nmax = std::max(nmax, d[i]);
         n3 += cube;
-        if (d[i] <= TD_SMALL || d[i] <= widest) continue;
-        chain = std::max(chain, d[i] - widest);
-        chain3 += cube - (double)widest * widest * widest;
+        if (d[i] <= TD_SMALL) {
+            int &w = small[(d[i] - 1) / 64];
+            w = std::max(w, d[i]);
+            continue;
+        }
+        n2 += (double)d[i] * d[i];
+        if (d[i] > widest) {
+            chain = std::max(chain, d[i] - widest);
+            chain3 += cube - (double)widest * widest * widest;
+        } else if (d[i] - 1 <= CHIP_WHOLE) {
+            narrow = std::max(narrow, d[i]);
+            launches += 1.0 / std::min(CHIP_JOBS, std::max(1, cus * (CHIP_WIDE / CHIP_NARROW) / chip_need(d[i] - 1, CHIP_NARROW)));
+        }
     }
     if (nmax == 0) return 0.0;
-    return (nmax > TD_SMALL ? 300e-6 + 3.9e-6 * nmax : 60e-6 + 4.6e-6 * nmax) + 1.5e-13 * n3 + 4.5e-6 * chain + 5.7e-14 * chain3;
+    if (nmax <= TD_SMALL) return 60e-6 + 4.6e-6 * nmax + 1.5e-13 * n3;
+    double t = 320e-6 + (nmax - 1 <= CHIP_WHOLE ? 3.41e-6 : 3.89e-6) * nmax + 7.7e-11 * n2 + 1.2e-13 * n3 + 4.5e-6 * chain + 7.5e-14 * chain3;
+    for (int w : small) t += 2.8e-6 * w;
+    if (nmax - 1 <= CHIP_WHOLE) t += 3.24e-6 * narrow * std::max(0.0, std::ceil(launches - 1e-9) - 1.0);
+    return t;
 }
 
 // All factors of the call by the direct route; stat (pinned host memory): four doubles per factor, off^2 and diag^2 of F, the

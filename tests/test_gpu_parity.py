@@ -388,6 +388,17 @@ def test_eig_diagonal_beside_dense_factors(ctx):
         check_eigpairs(F, Ld[i].cpu().numpy(), Qd[i].cpu().numpy(), "beside[%d]" % i)
 
 
+@pytest.mark.parametrize("n,count", [(260, 65), (300, 50), (257, 130)])
+def test_eig_crowd_of_diagonal_factors_costs_no_decomposition(n, count):
+    """More narrow factors than the first launch on the chip takes: what a decomposition of all of them costs is more than the widest's columns (65 of 260
+    2.6 ms, by sweeps 1.6), so diagonal ones are left to the sweeps, of which they need none."""
+    F = [torch.diag(torch.rand(n, device="cuda") + 0.5) for _ in range(count)]
+    Q, lam, info = decompose_on_device(F)
+    for f, q, l, i in zip(F, Q, lam, info):
+        assert i[2] and i[0] == 0, i
+        assert torch.equal(l, torch.diagonal(f).sort().values) and torch.equal(f @ q, q * l)
+
+
 @pytest.mark.parametrize("n,moved,sweeps", [(577, 1e-2, 2), (577, 5e-2, 1), (1153, 1e-2, 2), (1153, 5e-2, 1)])
 def test_eig_start_basis_moved_a_little_and_more(ctx, n, moved, sweeps):
     """Two sweeps from the eigenvectors of a factor that moved by 1 % are cheaper than a decomposition (which reports one), four after 5 % are not."""
